@@ -23,8 +23,7 @@ SOURCES = [
     "lasad_forward_mfma.hip",
     "lasad_forward_mfma_ws.hip",
     "lasad_forward_mfma_ws12.hip",
-    "lasad_forward_gated_mfma.hip",
-    "lasad_forward_gated_ws.hip",
+    "lasad_forward_gated_chunk.hip",
     "lasad_decode.hip",
     "lasad_decode_cached.hip",
     "lasad_backward.hip",

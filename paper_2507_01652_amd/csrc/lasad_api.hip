@@ -371,7 +371,7 @@ static int forward_gated_common(const void *q, const void *lam, const void *k, c
     if (n_tokens == 0 && (!state_out || state_out == state_in)) return LASAD_OK;
     hipError_t e;
     if (io_dtype == LASAD_BF16 && d == 64 && n_tokens > 0 && !force_generic())
-        e = lasad::launch_forward_gated_mfma(a, (hipStream_t)hip_stream);
+        e = lasad::launch_forward_gated_chunk(a, (hipStream_t)hip_stream);
     else
         e = lasad::launch_forward_generic(a, (hipStream_t)hip_stream);
     if (e != hipSuccess) return hip_fail("lasad_forward_gated launch", e);

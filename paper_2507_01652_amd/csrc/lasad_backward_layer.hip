@@ -194,7 +194,7 @@ hipError_t launch_backward_layer(const LayerBackwardArgs &a, bool use_mfma, hipS
         f.state_in = nullptr; f.state_out = nullptr;
         f.seg_states = nullptr; f.n_segments = 1; f.seg_chunks = 0;
         f.fused_act = 1; f.norm = 0; f.norm_eps = -1.f; f.norm_w = nullptr;
-        e = (in16 && use_mfma) ? launch_forward_gated_mfma(f, s) : launch_forward_generic(f, s);
+        e = (in16 && use_mfma) ? launch_forward_gated_chunk(f, s) : launch_forward_generic(f, s);
         if (e != hipSuccess) return e;
     }
     {                                                                   // 2. d_o (and the weight-gradient partial sums)

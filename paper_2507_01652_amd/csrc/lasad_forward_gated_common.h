@@ -1,6 +1,5 @@
-// Pieces shared by the vector-decay matrix-core kernels (lasad_forward_gated_mfma.hip and its
-// wave-specialised variant lasad_forward_gated_ws.hip): tile geometry, the running-product scan
-// across lanes, and the in-register preparation of one chunk's operands.
+// Pieces of the twelve-wave vector-decay backward passes (lasad_gated_ws_body.h): tile geometry, the
+// running-product scan across lanes, and the in-register preparation of one chunk's operands.
 #pragma once
 
 #include "lasad_mfma_util.h"
@@ -208,16 +207,6 @@ struct ChunkStage {
         }
     }
 };
-
-// The token-serial redo of one sequence (range fallback of the chunked kernels), as a real call:
-// inlined into a kernel it makes the compiler keep the argument block in scratch memory and
-// reload fields from there inside the chunk loop of the twelve-wave kernel (measured: 18 instead
-// of 11 us at the base shape).  The four-wave kernel is faster with the inlined routine.
-template <int OUT_BF16, int OWNKEY>
-__device__ __noinline__ void redo_sequence(const ForwardArgs *a, int bh, float *lds)
-{
-    scan::scan_sequence<1, OUT_BF16, OWNKEY ? scan::OWNKEY : scan::TIED, 64>(*a, bh, 0, lds);
-}
 
 }  // namespace gated
 }  // namespace lasad

@@ -1,0 +1,183 @@
+// Building blocks of the chunked vector-decay kernels (bf16 storage, head dim 64): tiles of 32 tokens,
+// loader wavefronts that prepare a chunk's operands in LDS one chunk ahead, and compute wavefronts that
+// each own 32 columns of the state for the whole sequence.
+//
+// With A_i[c] = prod_{s<=i} lambda_s[c] over the tokens of a chunk (1 at a row boundary),
+//     Q~ = q_scale q . A,   K~ = k / A,
+//     o_i   = Q~_i^T S_prev + sum_{j<=i} (Q~_i . K~_j) v_j,      S_new = diag(A_end) (S_prev + K~^T V).
+//
+// A compute wavefront needs nothing from the others: it takes the chunk's 32 x 32 scores, masks and splits
+// them in its own accumulators (which are an operand fragment of the next MFMA once the reduction index
+// is enumerated in accumulator order), multiplies them with its 16 value channels, adds Q~ S from its own
+// state accumulators and updates them.  State and scores never pass through LDS, and the only barrier is
+// the one per chunk that hands over the loaders' tiles.  Every compute wavefront forms the scores (18 of
+// its 42 MFMAs of 16 x 16 x 32): cheaper than an exchange and a second barrier.  (Two wavefronts of 32
+// columns on 32 x 32 x 16 tiles: a quarter fewer vector instructions in all, but a longer chain per chunk
+// and a wavefront less per SIMD to hide it: 57 against 49 us on the large fused-layer shape.)
+//
+// Enumeration of the reduction indices.  An operand fragment holds, per lane group g = lane / 16, eight
+// elements of the reduction index; accumulators hold rows 4 g + r of a tile.  Tokens: elements 0..3 are
+// tokens 4 g + e, elements 4..7 tokens 16 + 4 g + e (two score tiles).  Key channels: the rows of the
+// four state tiles are enumerated so that a lane's rows of tiles 2 s and 2 s + 1 are the eight consecutive
+// channels that a 16-byte row read of the other operand gives:
+//     tile 2 s + h, row 4 g + r  <->  channel 32 s + 8 g + 4 h + r.
+#pragma once
+
+#include "lasad_mfma_util.h"
+#include "lasad_internal.h"
+
+namespace lasad {
+namespace gchunk {
+
+constexpr int C = 32;                  // tokens per chunk
+constexpr int D = 64;                  // head dim
+// One token's row of a chunk slot: its prepared operands side by side (bf16 elements), so that everything a lane
+// reads or writes of a row lies within the immediate offsets of the LDS instructions.  A row is 164 words: rows read
+// 16 bytes at a time fall on different banks (164 = 36 mod 64).
+constexpr int kRow = 5 * D + 8;
+constexpr int kColKh = 0, kColKl = D, kColQh = 2 * D, kColQl = 3 * D, kColV = 4 * D;
+constexpr int kSlot = C * kRow;
+constexpr int OS = 68;                 // row stride (floats) of the output tile: 272 B
+constexpr float kMaxInvDecay = 1.2676506e30f;      // 2^100: largest 1 / A of a chunk (see lasad_forward_gated.hip)
+
+__device__ __forceinline__ int state_channel(int t, int g) { return 32 * (t >> 1) + 8 * g + 4 * (t & 1); }    // of row 4 g
+
+// A sequence cut into segments that different workgroups walk (few, long sequences): n_seg segments of seg_tokens tokens
+// (the last one may be shorter).  A segment's incoming state P_g is formed by a state pass and a fold before the walk; in
+// the forward it sits in the segment's own part of the output tensor until the segment's first tile is stored.
+struct SegPlan {
+    int n_seg, seg_tokens;             // n_seg = 1: no segments
+};
+
+// A 64 x 64 fp32 state and a vector of 64 after it, laid out over consecutive token rows of the output tensor: float i is
+// in row i / row_floats (a row: 64 elements of the output type).
+struct RowState {
+    float *base;                       // first row
+    int64_t stride;                    // floats from row to row
+    int shift;                         // log2(row_floats): 5 (bf16 rows) or 6
+    __device__ __forceinline__ float *at(int i) const { return base + (i >> shift) * stride + (i & ((1 << shift) - 1)); }
+};
+constexpr int kRowStateTokens = 130;   // rows it needs with bf16 output (65 with fp32)
+
+// Running products of four values along the 16 lanes of a row: x becomes the inclusive product, e the exclusive
+// one (1 in lane 0).  Lanes without a DPP source keep their value.  The four chains are interleaved, so every DPP
+// source was written four instructions earlier; the s_nop covers what preceded the block.
+#define GCHUNK_SCAN(ctrl)                                                                         \
+    "v_mul_f32_dpp %0, %0, %0 " ctrl "\n v_mul_f32_dpp %1, %1, %1 " ctrl "\n"                     \
+    "v_mul_f32_dpp %2, %2, %2 " ctrl "\n v_mul_f32_dpp %3, %3, %3 " ctrl "\n"
+__device__ __forceinline__ void row_scan_mul4(float (&x)[4], float (&e)[4])
+{
+    e[0] = e[1] = e[2] = e[3] = 1.0f;
+    asm("s_nop 1\n"
+        GCHUNK_SCAN("row_shr:1 row_mask:0xf bank_mask:0xf")
+        GCHUNK_SCAN("row_shr:2 row_mask:0xf bank_mask:0xf")
+        GCHUNK_SCAN("row_shr:4 row_mask:0xf bank_mask:0xf")
+        GCHUNK_SCAN("row_shr:8 row_mask:0xf bank_mask:0xf")
+        "v_mov_b32_dpp %4, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n v_mov_b32_dpp %5, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n"
+        "v_mov_b32_dpp %6, %2 row_shr:1 row_mask:0xf bank_mask:0xf\n v_mov_b32_dpp %7, %3 row_shr:1 row_mask:0xf bank_mask:0xf\n"
+        : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(e[0]), "+v"(e[1]), "+v"(e[2]), "+v"(e[3]));
+}
+
+// sum over the eight lanes of an aligned group, in every lane
+__device__ __forceinline__ float sum8(float x)
+{
+    x += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0xB1, 0xf, 0xf, true));    // lane ^ 1
+    x += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x4E, 0xf, 0xf, true));    // lane ^ 2
+    x += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x141, 0xf, 0xf, true));   // the other quad
+    return x;
+}
+
+__device__ __forceinline__ void unpack4(uint2 w, float (&f)[4])
+{
+    f[0] = __uint_as_float(w.x << 16); f[1] = __uint_as_float(w.x & 0xffff0000u);
+    f[2] = __uint_as_float(w.y << 16); f[3] = __uint_as_float(w.y & 0xffff0000u);
+}
+
+// f as bf16 hi + lo, written to one row piece of two tiles
+__device__ __forceinline__ void put_pair4(uint16_t *hi, uint16_t *lo, const float (&f)[4], const SplitConst &sc)
+{
+    uint2 h, l;
+    split2(f[0], f[1], h.x, l.x, sc);
+    split2(f[2], f[3], h.y, l.y, sc);
+    *(uint2 *)hi = h;
+    *(uint2 *)lo = l;
+}
+
+// Which of a chunk's 32 tokens sit on a row boundary (bit = token), advance_by tokens at a time, on the scalar unit: the
+// boundary positions are every W-th one, so a mask is the pattern of multiples of W shifted to the chunk's first one.
+struct RowBoundaries {
+    uint64_t multiples;                // bits 0, W, 2 W, ...
+    int W, step, first;                // first: chunk-local index of the first boundary token (W: none further on is nearer)
+    __device__ __forceinline__ void init(int start, int grid_w, int mode, int advance_by)
+    {
+        W = grid_w;
+        multiples = 1;
+        for (int k = grid_w; k < 64; k += grid_w) multiples |= 1ull << k;
+        step = advance_by % grid_w;
+        const int col0 = start % grid_w;                     // column of the chunk's first token
+        first = mode == LASAD_RESET_LAST_COL ? grid_w - 1 - col0 : col0 ? grid_w - col0 : 0;
+        if (mode == LASAD_RESET_NONE) { multiples = 0; first = 0; }
+    }
+    __device__ __forceinline__ uint32_t mask() const { return first < C ? (uint32_t)(multiples << first) : 0u; }
+    __device__ __forceinline__ void advance()                // to the next chunk
+    {
+        first -= step;
+        if (first < 0) first += W;
+    }
+};
+
+__device__ __forceinline__ float exp_neg(float x) { return __builtin_amdgcn_exp2f(x * -1.44269504088896340736f); }
+
+// ---- compute wavefronts --------------------------------------------------------------------------
+
+// A lane's places in a slot for its operand reads; everything else is immediate offsets.
+struct SlotPtr {
+    const uint16_t *row, *tok, *st;
+    __device__ __forceinline__ SlotPtr(const uint16_t *slot, int lane)
+    {
+        const int l16 = lane & 15, g = lane >> 4;
+        row = slot + l16 * kRow + 8 * g;
+        tok = slot + (4 * g + (l16 >> 2)) * kRow + 4 * (lane & 3);
+        st = slot + (4 * g + (l16 >> 2)) * kRow + 8 * (lane & 3);
+    }
+    // rows row0 + l16, elements col + 32 s + 8 g ..
+    __device__ __forceinline__ Frag rows(int row0, int col, int s) const
+    {
+        Frag f;
+        f.u = *(const uint4 *)(row + row0 * kRow + col + 32 * s);
+        return f;
+    }
+    // the 32 tokens for 16 columns from col in order / for the rows of state tile t
+    __device__ __forceinline__ Frag tokens(int col) const { return pair(tok + col); }
+    __device__ __forceinline__ Frag state_rows(int col, int t) const { return pair(st + col + 32 * (t >> 1) + 4 * (t & 1)); }
+    __device__ __forceinline__ Frag pair(const uint16_t *p) const
+    {
+        Frag f;
+        f.h[0] = tr_read(p);
+        f.h[1] = tr_read(p + 16 * kRow);
+        return f;
+    }
+};
+
+// two accumulator tiles as one operand fragment over their rows, bf16 hi + lo
+__device__ __forceinline__ void split_tiles(const f32x4v &t0, const f32x4v &t1, Frag &hi, Frag &lo, const SplitConst &sc)
+{
+    uint2 h, l;
+    split2(t0[0], t0[1], h.x, l.x, sc);
+    split2(t0[2], t0[3], h.y, l.y, sc);
+    hi.h[0] = h; lo.h[0] = l;
+    split2(t1[0], t1[1], h.x, l.x, sc);
+    split2(t1[2], t1[3], h.y, l.y, sc);
+    hi.h[1] = h; lo.h[1] = l;
+}
+
+// causal mask of a diagonal score tile P^T (this lane: query lane & 15, keys 4 g + r)
+__device__ __forceinline__ void causal_mask(f32x4v &p, int lane)
+{
+    const int cq = (lane & 15) - 4 * (lane >> 4);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) p[r] = r <= cq ? p[r] : 0.f;
+}
+
+}  // namespace gchunk
+}  // namespace lasad

@@ -184,15 +184,13 @@ hipError_t launch_forward_scan(const ForwardArgs &a, hipStream_t s);
 // bf16 in, d == 64: MFMA chunked kernel.
 hipError_t launch_forward_mfma(const ForwardArgs &a, hipStream_t s);
 // bf16 in, d == 64, vector decay (lam given): MFMA chunked kernel.
-hipError_t launch_forward_gated_mfma(const ForwardArgs &a, hipStream_t s);
+hipError_t launch_forward_gated_chunk(const ForwardArgs &a, hipStream_t s);
 // the same with eight wavefronts per sequence (whole sequences only, no segment plan)
 hipError_t launch_forward_mfma_ws(const ForwardArgs &a, hipStream_t s);
 // twelve wavefronts, doubled LDS buffers, one barrier per chunk: for workgroups that own a compute unit
 hipError_t launch_forward_mfma_ws12(const ForwardArgs &a, hipStream_t s);
 // n_pass whole-sequence passes (same shapes, types, gamma; fp32 or bf16 output alike) in ONE launch
 hipError_t launch_forward_mfma_multi(const ForwardArgs &common, const MultiPass &m, hipStream_t s);
-// the vector-decay kernel with twelve wavefronts per sequence (no fused norm)
-hipError_t launch_forward_gated_ws(const ForwardArgs &a, hipStream_t s);
 // device workspace the MFMA kernel wants for n_seq sequences of n_tokens tokens (0 = none)
 size_t forward_mfma_workspace_bytes(int64_t n_seq, int n_tokens);
 hipError_t launch_decode(const DecodeArgs &a, hipStream_t s);

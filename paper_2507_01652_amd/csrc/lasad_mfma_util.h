@@ -71,6 +71,11 @@ __device__ inline f32x16 mfma(const Frag &a, const Frag &b, f32x16 acc)
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, acc, 0, 0, 0);
 }
 
+__device__ inline f32x4v mfma16(const Frag &a, const Frag &b, f32x4v acc)     // 16 x 16 tile, 32 deep
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, acc, 0, 0, 0);
+}
+
 // Constants of the hi/lo split: the packed bf16 pairs (-1, 0) and (0, -1).  They are kept
 // opaque to the compiler (in VGPRs) because, folded into an inline constant of
 // v_dot2c_f32_bf16, -1.0 is encoded in the fp16 format and the product comes out wrong.

@@ -1,0 +1,75 @@
+"""The chunked vector-decay kernels at the edges of their 32-token tiles: lengths around one, two and three tiles, with
+few sequences (a compute unit each: two loader groups) and with more than there are compute units (one loader group),
+own key, tied key and fused layer, a mid-row start and a carried state; and a chunk beyond the range of the factorised
+form in the first, a middle and the last tile.  Tolerance: the storage type's (helpers.TOL) against the fp64 oracle."""
+import numpy as np
+import pytest
+
+from paper_2507_01652_amd import workloads as wl
+from helpers import TOL, both_outputs, gather_pairs, rel_err, sample_pairs
+
+pytestmark = pytest.mark.gpu
+D, W = 64, 23
+
+
+@pytest.fixture(scope="module")
+def lasad():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2507_01652_amd import binding
+    binding.load()
+    return binding
+
+
+def _check(lasad, oracle, n, B, Hh, form, start, seed, spike=None):
+    import torch
+    rng = np.random.default_rng(seed)
+    draw = lambda scale, shift=0.0: wl.store_round(rng.standard_normal((B, n, Hh, D), dtype=np.float32) * np.float32(scale) + np.float32(shift), "bf16")
+    q, v, k = draw(1.0 if form == "layer" else D ** -0.5), draw(D ** -0.5), draw(D ** -0.5)
+    z = draw(1.0, 2.0)
+    if spike is not None:
+        z[:, spike, :, 5] = -90.0 if form == "layer" else -30.0     # a gate of 0 (as good as) in one channel of one token
+    lam = wl.store_round(oracle.sigmoid(z).astype(np.float32), "bf16")
+    s0 = (rng.standard_normal((B, Hh, D, D)) * 0.3).astype(np.float32)
+    H = (start + n + W - 1) // W
+    dev = lambda x: lasad.to_device(x, "bf16")
+    s1 = torch.empty((B, Hh, D, D), dtype=torch.float32, device="cuda")
+    kw = dict(grid_h=H, grid_w=W, start_pos=start, q_scale=0.7, state_in=torch.from_numpy(s0).cuda(), state_out=s1)
+    if form == "layer":
+        o = both_outputs(lasad.lasad_forward_layer, True, q_pre=dev(q), z=dev(z), v=dev(v), norm_eps=1e-5, **kw)
+    else:
+        o = both_outputs(lasad.lasad_forward_gated, True, q=dev(q), lam=dev(lam), v=dev(v), k=dev(k) if form == "own" else None, **kw)
+    torch.cuda.synchronize()
+    pairs = sample_pairs(B, Hh, 4, seed)
+    at = lambda x: gather_pairs(x, pairs)
+    s0s = np.stack([s0[b, h] for b, h in pairs])[None].astype(np.float64)
+    if form == "layer":
+        ref, s_ref = oracle.gated_layer(at(q), at(z), at(v), W, eps=1e-5, start_pos=start, q_scale=0.7, s0=s0s, want_state=True)
+    else:
+        ref, s_ref = oracle.gated_recurrent(at(q), at(lam), at(v), W, k=at(k) if form == "own" else None, start_pos=start,
+                                            q_scale=0.7, s0=s0s, want_state=True)
+    got_s = s1.cpu().numpy()
+    assert rel_err(at(o.cpu().numpy()), ref) <= TOL["bf16"]
+    assert rel_err(np.stack([got_s[b, h] for b, h in pairs])[None], s_ref) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 97])
+@pytest.mark.parametrize("B,Hh", [(1, 3), (20, 13)], ids=["few", "many"])
+@pytest.mark.parametrize("form", ["own", "tied", "layer"])
+def test_tile_edges(lasad, oracle, n, B, Hh, form):
+    _check(lasad, oracle, n, B, Hh, form, start=17, seed=n + B)
+
+
+@pytest.mark.parametrize("spike", [3, 22, 40, 95])      # (22: the last token of a row, where the decay is off)
+@pytest.mark.parametrize("B,Hh", [(1, 3), (20, 13)], ids=["few", "many"])
+@pytest.mark.parametrize("form", ["tied", "layer"])
+def test_range_exit(lasad, oracle, spike, B, Hh, form):
+    _check(lasad, oracle, 97, B, Hh, form, start=0, seed=spike, spike=spike)
+
+
+@pytest.mark.parametrize("n,B,Hh", [(768, 2, 3), (800, 1, 5), (1023, 1, 2), (1300, 4, 20)])
+@pytest.mark.parametrize("form", ["own", "tied", "layer"])
+@pytest.mark.parametrize("spike", [None, 5, 400])
+def test_segments(lasad, oracle, n, B, Hh, form, spike):
+    """Few, long sequences: segments walked by different workgroups from states formed ahead of the walk."""
+    _check(lasad, oracle, n, B, Hh, form, start=30, seed=n, spike=spike)
