@@ -128,21 +128,37 @@ def _check(status: int):
         raise LasadError(status, load().lasad_last_error().decode())
 
 
+# The small calls (decode steps above all) are bound by the host: every attribute of a tensor costs 0.1 us and more, a
+# stream object 2 us (a decode step of one image: 10.0 us a layer before, 6.9 us now).  Pointers and streams therefore go to ctypes as plain integers, the current stream is asked for by
+# its handle, and the checks read a tensor's attributes once.
+_DTYPE_CODES = {torch.float32: F32, torch.bfloat16: BF16}
+
+
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream) -> int:
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
+
+
+def _same(q: torch.Tensor, others, message: str):
+    """Every tensor of `others` is contiguous and has q's shape and dtype."""
+    shape, dtype = q.shape, q.dtype
+    if not q.is_contiguous():
+        raise ValueError(message)
+    for t in others:
+        if t.shape != shape or t.dtype != dtype or not t.is_contiguous():
+            raise ValueError(message)
 
 
 def _scratch(nbytes: int, device, stream) -> torch.Tensor:
@@ -206,9 +222,9 @@ def lasad_forward_chunked(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, gam
     elif out.shape != q.shape:
         raise ValueError("out has the wrong shape")
     for s in (state_in, state_out):
-        if s is not None and (s.dtype != torch.float32 or not s.is_contiguous() or tuple(s.shape) != (B, Hh, d, d)):
+        if s is not None and (s.dtype != torch.float32 or not s.is_contiguous() or s.shape != (B, Hh, d, d)):
             raise ValueError("states must be contiguous fp32 [B, Hh, d, d]")
-    assert gamma.dtype == torch.float32 and gamma.is_contiguous() and tuple(gamma.shape) == (Hh,)
+    assert gamma.dtype == torch.float32 and gamma.is_contiguous() and gamma.shape == (Hh,)
     lq, lo = _layout(q), _layout(out)
     if workspace is None and use_workspace and n > 0:
         need = lasad_forward_workspace_bytes(B, Hh, n, d, _dtype_code(q))
@@ -242,9 +258,9 @@ def lasad_forward_chunked_static(q: torch.Tensor, k: torch.Tensor, v: torch.Tens
     if out.shape != q.shape:
         raise ValueError("out has the wrong shape")
     for s in (state_in, state_out):
-        if s is not None and (s.dtype != torch.float32 or not s.is_contiguous() or tuple(s.shape) != (B, Hh, d, d)):
+        if s is not None and (s.dtype != torch.float32 or not s.is_contiguous() or s.shape != (B, Hh, d, d)):
             raise ValueError("states must be contiguous fp32 [B, Hh, d, d]")
-    assert gamma.dtype == torch.float32 and gamma.is_contiguous() and tuple(gamma.shape) == (Hh,)
+    assert gamma.dtype == torch.float32 and gamma.is_contiguous() and gamma.shape == (Hh,)
     lq, lo = _layout(q), _layout(out)
     _check(load().lasad_forward_chunked_static(
         _ptr(q), _ptr(k), _ptr(v), _ptr(out), ctypes.byref(lq), ctypes.byref(lo),
@@ -261,16 +277,14 @@ def lasad_decode_step(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, gamma: 
     """One decode step at 0-indexed raster position `pos`.  q, k, v: contiguous [B, Hh, d];
     state: contiguous fp32 [B, Hh, d, d], updated in place.  Returns o [B, Hh, d]."""
     B, Hh, d = q.shape
-    for t in (q, k, v):
-        if t.shape != q.shape or t.dtype != q.dtype or not t.is_contiguous():
-            raise ValueError("q, k, v must be contiguous [B, Hh, d] of one dtype")
-    if state.dtype != torch.float32 or not state.is_contiguous() or tuple(state.shape) != (B, Hh, d, d):
+    _same(q, (k, v), "q, k, v must be contiguous [B, Hh, d] of one dtype")
+    if state.dtype != torch.float32 or not state.is_contiguous() or state.shape != (B, Hh, d, d):
         raise ValueError("state must be contiguous fp32 [B, Hh, d, d]")
     if out is None:
         out = torch.empty_like(q, dtype=out_dtype or q.dtype)
     elif out.shape != q.shape or not out.is_contiguous():
         raise ValueError("out must be contiguous [B, Hh, d]")
-    assert gamma.dtype == torch.float32 and gamma.is_contiguous() and tuple(gamma.shape) == (Hh,)
+    assert gamma.dtype == torch.float32 and gamma.is_contiguous() and gamma.shape == (Hh,)
     _check(load().lasad_decode_step(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _dtype_code(q), _dtype_code(out),
                                     B, Hh, d, grid_h, grid_w, pos, _ptr(gamma), boundary_mode, q_scale,
                                     _ptr(state), _stream(stream)))
@@ -285,9 +299,7 @@ def lasad_decode_step_cached(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, 
     """The decode step at position `pos` from key / value caches (contiguous [B, Hh, T, d] of q's dtype,
     rows 0..pos-1 filled by the earlier steps; this step's k, v are appended as row pos).  Returns o."""
     B, Hh, d = q.shape
-    for t in (q, k, v):
-        if t.shape != q.shape or t.dtype != q.dtype or not t.is_contiguous():
-            raise ValueError("q, k, v must be contiguous [B, Hh, d] of one dtype")
+    _same(q, (k, v), "q, k, v must be contiguous [B, Hh, d] of one dtype")
     for t in (k_cache, v_cache):
         if t.dim() != 4 or tuple(t.shape[:2]) != (B, Hh) or t.shape[3] != d or t.dtype != q.dtype or not t.is_contiguous():
             raise ValueError("caches must be contiguous [B, Hh, T, d] of q's dtype")
@@ -297,7 +309,7 @@ def lasad_decode_step_cached(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, 
         out = torch.empty_like(q, dtype=out_dtype or q.dtype)
     elif out.shape != q.shape or not out.is_contiguous():
         raise ValueError("out must be contiguous [B, Hh, d]")
-    assert gamma.dtype == torch.float32 and gamma.is_contiguous() and tuple(gamma.shape) == (Hh,)
+    assert gamma.dtype == torch.float32 and gamma.is_contiguous() and gamma.shape == (Hh,)
     _check(load().lasad_decode_step_cached(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(k_cache), _ptr(v_cache),
                                            k_cache.shape[2], _dtype_code(q), _dtype_code(out), B, Hh, d,
                                            grid_h, grid_w, pos, _ptr(gamma), boundary_mode, q_scale, _stream(stream)))
@@ -316,9 +328,7 @@ def lasad_decode_step_gated_cached(q: torch.Tensor, lam: torch.Tensor, v: torch.
     B, Hh, d = q.shape
     if (k is None) != (k_cache is None):
         raise ValueError("k and k_cache go together")
-    for t in (q, lam, v) + (() if k is None else (k,)):
-        if t.shape != q.shape or t.dtype != q.dtype or not t.is_contiguous():
-            raise ValueError("q, lam, k, v must be contiguous [B, Hh, d] of one dtype")
+    _same(q, (lam, v) if k is None else (lam, v, k), "q, lam, k, v must be contiguous [B, Hh, d] of one dtype")
     for t in (lam_cache, v_cache) + (() if k_cache is None else (k_cache,)):
         if t.dim() != 4 or tuple(t.shape[:2]) != (B, Hh) or t.shape[3] != d or t.dtype != q.dtype or not t.is_contiguous():
             raise ValueError("caches must be contiguous [B, Hh, T, d] of q's dtype")
@@ -352,7 +362,7 @@ def lasad_forward_gated(q: torch.Tensor, lam: torch.Tensor, v: torch.Tensor, gri
     elif out.shape != q.shape:
         raise ValueError("out has the wrong shape")
     for s in (state_in, state_out):
-        if s is not None and (s.dtype != torch.float32 or not s.is_contiguous() or tuple(s.shape) != (B, Hh, d, d)):
+        if s is not None and (s.dtype != torch.float32 or not s.is_contiguous() or s.shape != (B, Hh, d, d)):
             raise ValueError("states must be contiguous fp32 [B, Hh, d, d]")
     lq, lo = _layout(q), _layout(out)
     _check(load().lasad_forward_gated(
@@ -369,10 +379,8 @@ def lasad_decode_step_gated(q: torch.Tensor, lam: torch.Tensor, v: torch.Tensor,
                             stream=None) -> torch.Tensor:
     """One vector-decay decode step.  q, lam, v (k): contiguous [B, Hh, d]; state fp32 [B, Hh, d, d] in place."""
     B, Hh, d = q.shape
-    for t in (q, lam, v) + (() if k is None else (k,)):
-        if t.shape != q.shape or t.dtype != q.dtype or not t.is_contiguous():
-            raise ValueError("q, lam, k, v must be contiguous [B, Hh, d] of one dtype")
-    if state.dtype != torch.float32 or not state.is_contiguous() or tuple(state.shape) != (B, Hh, d, d):
+    _same(q, (lam, v) if k is None else (lam, v, k), "q, lam, k, v must be contiguous [B, Hh, d] of one dtype")
+    if state.dtype != torch.float32 or not state.is_contiguous() or state.shape != (B, Hh, d, d):
         raise ValueError("state must be contiguous fp32 [B, Hh, d, d]")
     if out is None:
         out = torch.empty_like(q, dtype=out_dtype or q.dtype)
@@ -402,7 +410,7 @@ def lasad_forward_layer(q_pre: torch.Tensor, z: torch.Tensor, v: torch.Tensor, g
     if out is None:
         out = torch.empty_like(q_pre, dtype=out_dtype or q_pre.dtype)
     for s in (state_in, state_out):
-        if s is not None and (s.dtype != torch.float32 or not s.is_contiguous() or tuple(s.shape) != (B, Hh, d, d)):
+        if s is not None and (s.dtype != torch.float32 or not s.is_contiguous() or s.shape != (B, Hh, d, d)):
             raise ValueError("states must be contiguous fp32 [B, Hh, d, d]")
     lq, lo = _layout(q_pre), _layout(out)
     _check(load().lasad_forward_layer(
@@ -419,10 +427,8 @@ def lasad_decode_step_layer(q_pre: torch.Tensor, z: torch.Tensor, v: torch.Tenso
                             stream=None) -> torch.Tensor:
     """One decode step of the fused layer.  q_pre, z, v: contiguous [B, Hh, d]; state fp32 in place."""
     B, Hh, d = q_pre.shape
-    for t in (q_pre, z, v):
-        if t.shape != q_pre.shape or t.dtype != q_pre.dtype or not t.is_contiguous():
-            raise ValueError("q_pre, z, v must be contiguous [B, Hh, d] of one dtype")
-    if state.dtype != torch.float32 or not state.is_contiguous() or tuple(state.shape) != (B, Hh, d, d):
+    _same(q_pre, (z, v), "q_pre, z, v must be contiguous [B, Hh, d] of one dtype")
+    if state.dtype != torch.float32 or not state.is_contiguous() or state.shape != (B, Hh, d, d):
         raise ValueError("state must be contiguous fp32 [B, Hh, d, d]")
     if out is None:
         out = torch.empty_like(q_pre, dtype=out_dtype or q_pre.dtype)
@@ -441,10 +447,8 @@ def lasad_decode_step_rows(q: torch.Tensor, v: torch.Tensor, state: torch.Tensor
     """One decode step with a raster position per batch row (pos_rows: int32 [B] on the device; entries
     outside the grid mark inactive rows).  Scalar decay: give gamma and k; vector decay: give lam (k optional)."""
     B, Hh, d = q.shape
-    for t in (q, v) + tuple(x for x in (k, lam) if x is not None):
-        if t.shape != q.shape or t.dtype != q.dtype or not t.is_contiguous():
-            raise ValueError("q, lam, k, v must be contiguous [B, Hh, d] of one dtype")
-    if state.dtype != torch.float32 or not state.is_contiguous() or tuple(state.shape) != (B, Hh, d, d):
+    _same(q, [x for x in (v, k, lam) if x is not None], "q, lam, k, v must be contiguous [B, Hh, d] of one dtype")
+    if state.dtype != torch.float32 or not state.is_contiguous() or state.shape != (B, Hh, d, d):
         raise ValueError("state must be contiguous fp32 [B, Hh, d, d]")
     if pos_rows.dtype != torch.int32 or pos_rows.numel() != B or not pos_rows.is_contiguous():
         raise ValueError("pos_rows must be contiguous int32 [B]")
