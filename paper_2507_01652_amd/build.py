@@ -20,6 +20,7 @@ SOURCES = [
     "lasad_decay.hip",
     "lasad_forward_generic.hip",
     "lasad_forward_scan.hip",
+    "lasad_forward_f32_chunk.hip",
     "lasad_forward_mfma.hip",
     "lasad_forward_mfma_ws.hip",
     "lasad_forward_mfma_ws12.hip",

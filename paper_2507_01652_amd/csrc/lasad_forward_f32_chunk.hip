@@ -1,0 +1,176 @@
+// Chunked scalar-decay forward for fp32 storage, head dim 64, on the fp32 matrix instruction
+// v_mfma_f32_16x16x4_f32 (fp32 operands and sums: nothing is rounded to a shorter type).
+//
+// Over a chunk of 16 tokens, with e_i the number of decaying steps among its first i + 1 tokens,
+//     o_i   = gamma^e_i q_i^T S_prev + sum_{j<=i} gamma^(e_i - e_j) (q_i . k_j) v_j
+//     S_new = gamma^e_end S_prev     + sum_j      gamma^(e_end - e_j) k_j v_j^T.
+// Every exponent is an integer from 0 to 16 and every power is used as it stands (none is a reciprocal), so any gamma goes
+// this way, zero included; the 17 powers of a head are products in fp64, rounded once.
+//
+// A workgroup of four wavefronts walks a sequence; a wavefront owns 16 value channels, and its accumulators hold those
+// columns of the state for the whole sequence.  Accumulator rows 4 g + r (g = lane / 16) of a tile are at the same time
+// the A operand's reduction index of the next product when that is enumerated as 16 t + 4 g + r, so neither state nor scores
+// pass through LDS; every wavefront forms the scores itself (16 of its 52 matrix instructions a chunk: cheaper than an
+// exchange and a second barrier).  q, k and v go through LDS, 32 tokens a barrier, doubled, the next 32 in flight
+// in registers.
+//
+// Bound by the chain from chunk to chunk on the compute units that have a sequence: 52 matrix instructions of 32 cycles a
+// chunk and SIMD (0.8 us) and the LDS reads, decay and mask between them; 1.7 us a chunk in all.  96 sequences of 256
+// tokens: 27 us a call, 64 with the token-serial kernel (lasad_scan.h), which is left to the vector decay and to
+// bf16 storage; distance from fp64 results the same.
+#include "lasad_gated_chunk.h"
+
+namespace lasad {
+
+namespace {
+
+constexpr int D = 64;
+constexpr int T = 32;                  // tokens per barrier: gchunk::RowBoundaries counts in these
+constexpr int kThreads = 256;
+constexpr int RS = D + 4;              // row stride of the staged tiles: 16-byte reads of 16 rows fall on different banks
+static_assert(T == gchunk::C, "row boundaries are counted 32 tokens at a time");
+
+__device__ __forceinline__ f32x4v mfma_f32(float a, float b, f32x4v acc)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
+}
+
+__global__ void __launch_bounds__(kThreads, 3)
+forward_f32_chunk_kernel(ForwardArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float tiles[2][3][T * RS];      // q, k, v
+    __shared__ float pw[17];                                                // gamma^0 .. gamma^16
+    const int bh = blockIdx.x, b = bh / a.Hh, h = bh - b * a.Hh;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int l16 = lane & 15, g = lane >> 4;
+    const int n = a.n_tokens, n_steps = (n + T - 1) / T;
+
+    if (tid < 17) {
+        const double gm = a.gamma[h];
+        double p = 1.0;
+        for (int i = 0; i < tid; ++i) p *= gm;
+        pw[tid] = (float)p;
+    }
+
+    // staging: thread = token tid / 16 (+ 16), channels 4 (tid % 16) ..
+    const int srow = tid >> 4, scol = (tid & 15) * 4;
+    const int64_t in_base = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + scol;
+    const float *src[3] = {(const float *)a.q + in_base, (const float *)a.k + in_base, (const float *)a.v + in_base};
+    f32x4v stage[3][2];
+    auto fetch = [&](int step) {                   // (rows past the end re-read the last token)
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const int64_t off = (int64_t)min(step * T + srow + 16 * it, n - 1) * a.in.stride_n;
+#pragma unroll
+            for (int x = 0; x < 3; ++x) stage[x][it] = *(const f32x4v *)(src[x] + off);
+        }
+    };
+    auto put = [&](int step) {                     // rows past the end: zero
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const bool live = step * T + srow + 16 * it < n;
+#pragma unroll
+            for (int x = 0; x < 3; ++x)
+                *(f32x4v *)&tiles[step & 1][x][(srow + 16 * it) * RS + scol] = live ? stage[x][it] : f32x4v{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+
+    const int col0 = 16 * wave;
+    const int64_t s_off = (int64_t)bh * D * D + col0 + l16;
+    f32x4v S[4];                                   // S[16 t + 4 g + r][col0 + l16]
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S[t][r] = a.state_in ? a.state_in[s_off + (16 * t + 4 * g + r) * D] : 0.f;
+
+    gchunk::RowBoundaries bounds;
+    bounds.init(a.start_pos, a.grid_w, a.mode, T);
+    float *const o_lane = (float *)a.o + (int64_t)b * a.out.stride_b + (int64_t)h * a.out.stride_h + col0 + 4 * g;
+
+    fetch(0);
+    put(0);
+    if (n_steps > 1) fetch(1);
+    __syncthreads();
+    for (int step = 0; step < n_steps; ++step) {
+        if (step + 1 < n_steps) {
+            put(step + 1);
+            if (step + 2 < n_steps) fetch(step + 2);
+        }
+        // tokens whose step decays (a row past the end does not)
+        uint32_t decays = ~bounds.mask();
+        bounds.advance();
+        const int left = n - step * T;
+        if (left < T) decays &= (1u << left) - 1;
+        if (step == 0 && a.first_decay_off) decays &= ~1u;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (half * 16 >= left) break;
+            const float *tq = &tiles[step & 1][0][16 * half * RS], *tk = &tiles[step & 1][1][16 * half * RS];
+            const float *tv = &tiles[step & 1][2][16 * half * RS + col0];
+            const uint32_t dm = (decays >> (16 * half)) & 0xffffu;
+            const int e_end = __builtin_popcount(dm);
+            const int e_i = __builtin_popcount(dm & ((2u << l16) - 1));
+            int e_j[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) e_j[r] = __builtin_popcount(dm & ((2u << (4 * g + r)) - 1));
+            // ---- scores P^T[j][i] = sum_c K[j][c] Q[i][c], and O^T[n][i] = sum_c S[c][n] Q[i][c]: two chains each ----
+            f32x4v p0 = {0.f, 0.f, 0.f, 0.f}, p1 = p0, o0 = p0, o1 = p0;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const f32x4v q = *(const f32x4v *)&tq[l16 * RS + 16 * t + 4 * g];
+                const f32x4v k = *(const f32x4v *)&tk[l16 * RS + 16 * t + 4 * g];
+                p0 = mfma_f32(k[0], q[0], p0);
+                o0 = mfma_f32(S[t][0], q[0], o0);
+                p1 = mfma_f32(k[1], q[1], p1);
+                o1 = mfma_f32(S[t][1], q[1], o1);
+                p0 = mfma_f32(k[2], q[2], p0);
+                o0 = mfma_f32(S[t][2], q[2], o0);
+                p1 = mfma_f32(k[3], q[3], p1);
+                o1 = mfma_f32(S[t][3], q[3], o1);
+            }
+            float v[4];                            // V[4 g + r][col0 + l16]
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = tv[(4 * g + r) * RS + l16];
+            // ---- decay and causal mask (this lane: query l16, keys 4 g + r) ----
+            const float r_i = pw[e_i];
+            f32x4v o = (o0 + o1) * r_i, p = p0 + p1;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p[r] = 4 * g + r <= l16 ? p[r] * pw[max(e_i - e_j[r], 0)] : 0.f;
+            // ---- O^T[n][i] += sum_j V[j][n] P^T[j][i] ----
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o = mfma_f32(v[r], p[r], o);
+            // ---- S[c][n] <- gamma^e_end S + sum_j K[j][c] gamma^(e_end - e_j) V[j][n] ----
+            const float r_end = pw[e_end];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] *= pw[e_end - e_j[r]];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) S[t] *= r_end;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) S[t] = mfma_f32(tk[(4 * g + r) * RS + 16 * t + l16], v[r], S[t]);
+            const int tok = step * T + 16 * half + l16;
+            if (tok < n) *(f32x4v *)(o_lane + (int64_t)tok * a.out.stride_n) = o * a.q_scale;
+        }
+        __syncthreads();
+    }
+    if (a.state_out) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a.state_out[s_off + (16 * t + 4 * g + r) * D] = S[t][r];
+    }
+}
+
+}  // namespace
+
+hipError_t launch_forward_f32_chunk(const ForwardArgs &a, hipStream_t s)
+{
+    if (a.d != D || a.io_dtype != LASAD_F32 || a.out_dtype != LASAD_F32 || a.n_tokens < 1 || a.lam) return hipErrorInvalidValue;
+    if ((int64_t)a.B * a.Hh > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(forward_f32_chunk_kernel, dim3((unsigned)(a.B * a.Hh)), dim3(kThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace lasad

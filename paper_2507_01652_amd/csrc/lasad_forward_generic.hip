@@ -46,6 +46,9 @@ hipError_t launch_forward_generic(const ForwardArgs &a, hipStream_t s)
     // the fused activations and the norm exist in the scan kernel only: such calls go there whatever the switch says
     const bool fused = a.fused_act || a.norm;
     if (fused && a.d != 64) return hipErrorInvalidValue;
+    // scalar decay in fp32: in chunks on the fp32 matrix instruction, whatever gamma and the sizes are (16 tokens take it
+    // what the token-serial kernel takes for 6 or 7: 96 sequences of 256 tokens 27 us against 64)
+    if (a.d == 64 && scan && !a.lam && a.io_dtype == LASAD_F32 && a.n_tokens > 0) return launch_forward_f32_chunk(a, s);
     if (a.d == 64 && (scan || fused)) return launch_forward_scan(a, s);
     switch (a.d) {
         case 32: return launch_d<32>(a, s);

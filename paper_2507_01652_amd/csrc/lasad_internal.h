@@ -179,6 +179,8 @@ size_t backward_gated_carried_extra_bytes(int64_t n_seq, int d);
 hipError_t launch_decay_factors(const float *gamma, int Hh, int grid_w, int start_pos, int n,
                                 int mode, float *lambda_out, int32_t *cum_out, hipStream_t s);
 hipError_t launch_forward_generic(const ForwardArgs &a, hipStream_t s);
+// fp32 in and out, d == 64, scalar decay: chunks on the fp32 matrix instruction.
+hipError_t launch_forward_f32_chunk(const ForwardArgs &a, hipStream_t s);
 // d == 64, any storage type, scalar or vector decay: token-serial fp32 scan kernel.
 hipError_t launch_forward_scan(const ForwardArgs &a, hipStream_t s);
 // bf16 in, d == 64: MFMA chunked kernel.

@@ -1,0 +1,41 @@
+"""The chunked fp32 scalar-decay forward at the edges of its tiles (16 tokens a chunk, 32 a barrier): lengths around one,
+two and three of them, narrow and wide grids, a mid-row start and a carried state, strided inputs, all three boundary
+rules, and gammas from 0 to 1 (no power of which is ever a reciprocal).  Tolerance: fp32 (helpers.TOL) against the fp64 oracle."""
+import numpy as np
+import pytest
+
+from helpers import TOL, rel_err
+
+pytestmark = pytest.mark.gpu
+D = 64
+GAMMA = np.array([0.0, 1e-30, 0.01, 0.5, 0.93, 0.9999, 1.0], dtype=np.float32)
+
+
+@pytest.fixture(scope="module")
+def lasad():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2507_01652_amd import binding
+    binding.load()
+    return binding
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65, 97])
+@pytest.mark.parametrize("W,mode,start", [(1, 0, 0), (5, 1, 7), (16, 0, 0), (23, 0, 17), (23, 2, 3), (70, 1, 40)])
+def test_tile_edges(lasad, oracle, n, W, mode, start):
+    import torch
+    rng = np.random.default_rng(n + W)
+    B, Hh = 2, len(GAMMA)
+    x = rng.standard_normal((3, B, n + 2, Hh, D), dtype=np.float32) / 8
+    s0 = (rng.standard_normal((B, Hh, D, D)) * 0.3).astype(np.float32)
+    dev = torch.from_numpy(x).cuda()[:, :, 1:n + 1]                 # token rows of a larger buffer
+    q, k, v = (np.ascontiguousarray(t[:, 1:n + 1]) for t in x)
+    H = (start + n + W - 1) // W
+    s1 = torch.empty((B, Hh, D, D), dtype=torch.float32, device="cuda")
+    o = lasad.lasad_forward_chunked(dev[0], dev[1], dev[2], torch.from_numpy(GAMMA).cuda(), H, W, start_pos=start,
+                                    boundary_mode=mode, q_scale=0.7, state_in=torch.from_numpy(s0).cuda(), state_out=s1)
+    torch.cuda.synchronize()
+    lam, _ = oracle.decay_factors(GAMMA, H, W, start, n, mode)
+    ref, s_ref = oracle.forward_fullmask(q, k, v, lam, q_scale=0.7, s0=s0.astype(np.float64), want_state=True)
+    assert rel_err(o.cpu().numpy(), ref) <= TOL["f32"]
+    assert rel_err(s1.cpu().numpy(), s_ref) <= TOL["f32"]
