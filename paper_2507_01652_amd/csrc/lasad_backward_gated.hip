@@ -42,6 +42,7 @@
 namespace lasad {
 
 hipError_t launch_backward_gated_passes(const ForwardArgs *a, const scan::ScanRoles *roles, bool tied, hipStream_t s);
+bool backward_gated_passes_fit(int64_t stride_n);
 
 namespace {
 
@@ -482,7 +483,7 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
 #undef LASAD_GEN_WALK
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-    } else if (in16 && !force_walk) {
+    } else if (in16 && !force_walk && backward_gated_passes_fit(b.in.stride_n)) {
         // matrix-core passes: the pass's operands in the forward's fields
         ForwardArgs p[3] = {f, f, f};
         p[0].q = b.d_o; p[0].lam = b.lam; p[0].k = b.k; p[0].v = b.v; p[0].o = dq32;                  // dq

@@ -377,7 +377,7 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
     bool fine = true;
     for (int chunk = 0; fine && chunk < n_chunks; ++chunk) {
         const int4 f = *(const int4 *)sTrip[chunk & 1];
-        const SlotPtr sp(slots + (chunk & 1) * kSlot, lane);
+        const SlotPtr<> sp(slots + (chunk & 1) * kSlot, lane);
         f32x4v p00 = zero4, p01 = zero4, p11 = zero4;              // scores P^T[j][i]: (key tile, query tile)
         f32x4v o0 = zero4, o1 = zero4;                             // O^T[n][i] of the two query tiles
 #pragma unroll

@@ -1,6 +1,6 @@
 // Building blocks of the chunked vector-decay kernels (bf16 storage, head dim 64): tiles of 32 tokens,
 // loader wavefronts that prepare a chunk's operands in LDS one chunk ahead, and compute wavefronts that
-// each own 32 columns of the state for the whole sequence.
+// each own 16 columns of the state for the whole sequence.
 //
 // With A_i[c] = prod_{s<=i} lambda_s[c] over the tokens of a chunk (1 at a row boundary),
 //     Q~ = q_scale q . A,   K~ = k / A,
@@ -38,7 +38,7 @@ constexpr int kRow = 5 * D + 8;
 constexpr int kColKh = 0, kColKl = D, kColQh = 2 * D, kColQl = 3 * D, kColV = 4 * D;
 constexpr int kSlot = C * kRow;
 constexpr int OS = 68;                 // row stride (floats) of the output tile: 272 B
-constexpr float kMaxInvDecay = 1.2676506e30f;      // 2^100: largest 1 / A of a chunk (see lasad_forward_gated.hip)
+constexpr float kMaxInvDecay = 1.2676506e30f;      // 2^100: largest 1 / A of a chunk (see lasad_forward_gated_chunk.hip)
 
 __device__ __forceinline__ int state_channel(int t, int g) { return 32 * (t >> 1) + 8 * g + 4 * (t & 1); }    // of row 4 g
 
@@ -131,20 +131,21 @@ __device__ __forceinline__ float exp_neg(float x) { return __builtin_amdgcn_exp2
 // ---- compute wavefronts --------------------------------------------------------------------------
 
 // A lane's places in a slot for its operand reads; everything else is immediate offsets.
+template <int ROW = kRow>
 struct SlotPtr {
     const uint16_t *row, *tok, *st;
     __device__ __forceinline__ SlotPtr(const uint16_t *slot, int lane)
     {
         const int l16 = lane & 15, g = lane >> 4;
-        row = slot + l16 * kRow + 8 * g;
-        tok = slot + (4 * g + (l16 >> 2)) * kRow + 4 * (lane & 3);
-        st = slot + (4 * g + (l16 >> 2)) * kRow + 8 * (lane & 3);
+        row = slot + l16 * ROW + 8 * g;
+        tok = slot + (4 * g + (l16 >> 2)) * ROW + 4 * (lane & 3);
+        st = slot + (4 * g + (l16 >> 2)) * ROW + 8 * (lane & 3);
     }
     // rows row0 + l16, elements col + 32 s + 8 g ..
     __device__ __forceinline__ Frag rows(int row0, int col, int s) const
     {
         Frag f;
-        f.u = *(const uint4 *)(row + row0 * kRow + col + 32 * s);
+        f.u = *(const uint4 *)(row + row0 * ROW + col + 32 * s);
         return f;
     }
     // the 32 tokens for 16 columns from col in order / for the rows of state tile t
@@ -154,7 +155,7 @@ struct SlotPtr {
     {
         Frag f;
         f.h[0] = tr_read(p);
-        f.h[1] = tr_read(p + 16 * kRow);
+        f.h[1] = tr_read(p + 16 * ROW);
         return f;
     }
 };

@@ -1,0 +1,60 @@
+"""The chunked vector-decay backward passes at the edges of their 32-token tiles and of the pairs of tiles they are walked
+in: lengths around one to four tiles, own and tied key, a mid-row start and carried states, and a chunk beyond the range
+of the factorised form in the first, a middle and the last tile.  Tolerance: the storage type's (helpers.TOL) against
+the fp64 oracle; where a gate is next to zero the decay gradient, a quotient by it, is left out."""
+import numpy as np
+import pytest
+
+from paper_2507_01652_amd import workloads as wl
+from helpers import TOL, both_outputs, rel_err
+
+pytestmark = pytest.mark.gpu
+D, W = 64, 23
+
+
+@pytest.fixture(scope="module")
+def lasad():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2507_01652_amd import binding
+    binding.load()
+    return binding
+
+
+def _check(lasad, oracle, n, own_key, start, seed, spike=None):
+    import torch
+    rng = np.random.default_rng(seed)
+    B, Hh = 2, 3
+    draw = lambda: wl.store_round(rng.standard_normal((B, n, Hh, D), dtype=np.float32) / np.float32(8), "bf16")
+    q, v, g = draw(), draw(), draw()
+    k = draw() if own_key else None
+    lam = wl.gate_inputs((B, n, Hh, D), "bf16", seed + 1)
+    if spike is not None:
+        lam[:, spike, :, 5] = 2.0 ** -120
+    s0, ds = ((rng.standard_normal((B, Hh, D, D)) * 0.3).astype(np.float32) for _ in range(2))
+    H = (start + n + W - 1) // W
+    dev = lambda x: None if x is None else lasad.to_device(x, "bf16")
+    up = lambda x: torch.from_numpy(x).cuda()
+    res = both_outputs(lasad.lasad_backward_gated, True, dtype_kw="grad_dtype", q=dev(q), lam=dev(lam), v=dev(v), d_o=dev(g),
+                       grid_h=H, grid_w=W, k=dev(k), start_pos=start, q_scale=0.7)
+    ref = oracle.gated_backward(q, lam, v, g, W, k=k, start_pos=start, q_scale=0.7)
+    car = lasad.lasad_backward_gated_carried(dev(q), dev(lam), dev(v), dev(g), H, W, k=dev(k), start_pos=start, q_scale=0.7,
+                                             state_in=up(s0), d_state_out=up(ds), grad_dtype=torch.float32)
+    rc = oracle.gated_backward_carried(q, lam, v, g, W, k=k, start_pos=start, q_scale=0.7, s0=s0, d_state=ds)
+    torch.cuda.synchronize()
+    for got, want in ((res, ref), (car, rc)):
+        for i, (a, r) in enumerate(zip(got, want)):
+            if a is not None and not (spike is not None and i == 1):
+                assert rel_err(a.cpu().numpy(), r) <= TOL["bf16"], (i, rel_err(a.cpu().numpy(), r))
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 64, 65, 96, 97, 128])
+@pytest.mark.parametrize("own_key", [False, True], ids=["tied", "own"])
+def test_tile_edges(lasad, oracle, n, own_key):
+    _check(lasad, oracle, n, own_key, start=17, seed=n)
+
+
+@pytest.mark.parametrize("spike", [3, 40, 70, 96])
+@pytest.mark.parametrize("own_key", [False, True], ids=["tied", "own"])
+def test_range_exit(lasad, oracle, spike, own_key):
+    _check(lasad, oracle, 97, own_key, start=0, seed=spike, spike=spike)
