@@ -138,8 +138,21 @@ forward_f32_chunk_kernel(ForwardArgs a)
 #pragma unroll
             for (int r = 0; r < 4; ++r) p[r] = 4 * g + r <= l16 ? p[r] * pw[max(e_i - e_j[r], 0)] : 0.f;
             // ---- O^T[n][i] += sum_j V[j][n] P^T[j][i] ----
+            uint32_t top = 0;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o = mfma_f32(v[r], p[r], o);
+            for (int r = 0; r < 4; ++r) top = max(top, __float_as_uint(v[r]) & 0x7fffffffu);
+            if (__builtin_expect(__any(top >= 0x7f800000u), 0)) {
+                // an infinity or NaN among the values: its zero score would still make NaN of the queries before it
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const float pj = __shfl(p[j & 3], 16 * (j >> 2) + l16);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[r] = j <= l16 ? fmaf(tv[j * RS + 4 * g + r], pj, o[r]) : o[r];
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o = mfma_f32(v[r], p[r], o);
+            }
             // ---- S[c][n] <- gamma^e_end S + sum_j K[j][c] gamma^(e_end - e_j) V[j][n] ----
             const float r_end = pw[e_end];
 #pragma unroll

@@ -39,3 +39,22 @@ def test_tile_edges(lasad, oracle, n, W, mode, start):
     ref, s_ref = oracle.forward_fullmask(q, k, v, lam, q_scale=0.7, s0=s0.astype(np.float64), want_state=True)
     assert rel_err(o.cpu().numpy(), ref) <= TOL["f32"]
     assert rel_err(s1.cpu().numpy(), s_ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("t", [0, 1, 13, 15, 16, 30, 47])
+def test_non_finite_value_stays_causal(lasad, oracle, t, bad):
+    """A value that is no number reaches its own and later tokens of its channel only."""
+    import torch
+    rng = np.random.default_rng(t)
+    n, W, Hh, c = 48, 70, 2, 21
+    q, k, v = (rng.standard_normal((1, n, Hh, D), dtype=np.float32) / 8 for _ in range(3))
+    gamma = np.array([0.9, 0.5], dtype=np.float32)
+    lam, _ = oracle.decay_factors(gamma, 1, W, 0, n, 0)
+    ref = oracle.forward_fullmask(q, k, v, lam)
+    v[0, t, :, c] = bad
+    up = lambda x: torch.from_numpy(x).cuda()
+    o = lasad.lasad_forward_chunked(up(q), up(k), up(v), up(gamma), 1, W).cpu().numpy()
+    assert not np.isfinite(o[0, t:, :, c]).any()
+    o[0, t:, :, c] = ref[0, t:, :, c]
+    assert rel_err(o, ref) <= TOL["f32"]
