@@ -174,6 +174,17 @@ backward_gated_generic_walk_kernel(WalkArgs w)
 
 constexpr int kFinBlock = 64;          // tokens per step of the finishing kernel
 
+// States at the bounds between segments, [sequence][bound][key channel][value channel], and after them one flag per
+// sequence: 0 where the token-serial walk took the pass over and kept none.  Either pointer NULL: not kept.
+struct BoundStates {
+    const float *s, *g;                // S before the bound's token; G at it, without q_scale and the token's own decay
+    int64_t flags;                     // floats up to the flags
+    __device__ __forceinline__ bool kept(int bh) const
+    {
+        return s && ((const int *)(s + flags))[bh] && ((const int *)(g + flags))[bh];
+    }
+};
+
 // One workgroup per sequence walks it in blocks of 64 tokens from the last block to the first,
 // every thread holding four channels of one token (16-byte loads; the next block's loads are in
 // flight while this one is worked on).  Per block: r = q dq - k dk into LDS, suffix sums down the
@@ -182,6 +193,11 @@ constexpr int kFinBlock = 64;          // tokens per step of the finishing kerne
 // Few long sequences are cut into n_seg segments of seg_blocks blocks with a workgroup each
 // (blockIdx.y): a first launch (TOTALS) only adds up r over each segment, the second starts every
 // segment from the totals of the segments after it.  seg_totals: [sequence][segment][d] fp32.
+// Where the matrix-core passes kept their states at the segment bounds (bs), the first launch reads those instead of q, k,
+// dq and dk: the suffix sum at the first token t of the next segment is sum_n (l_t G_t)[c][n] S_{t-1}[c][n] itself (with
+// what the final state's gradient adds), 32 KB a bound for 200 KB and more, and no sum over the tokens after it.
+// Forward and backward with an own key, 4 x 24 sequences of 4096 tokens: 602 -> 555 us; dlam against fp64 (2-norm): 1.8e-4
+// -> 5.5e-5 with an own key, 6.8e-5 -> 2.0e-5 with the tied one.
 // The channels are independent: with few workgroups a sequence's channels are further divided between
 // 64 / CH workgroups (blockIdx.z) of 16 CH threads, which shortens nothing of the chain of blocks but
 // puts more of them in flight.
@@ -189,7 +205,7 @@ constexpr int kFinBlock = 64;          // tokens per step of the finishing kerne
 template <int IN_BF16, int OUT_BF16, int TOTALS, int CH>
 __global__ void __launch_bounds__(16 * CH)
 backward_gated_finish_kernel(GatedBackwardArgs a, const float *dq32, const float *dk32,
-                             float *seg_totals, int n_seg, int seg_blocks, const float *sink)
+                             float *seg_totals, int n_seg, int seg_blocks, const float *sink, BoundStates bs)
 {
     // sink [sequence][d] (or NULL): per key channel, sum_n H[c][n] s_n[c][n] for H = dL/d(final state): the products of
     // decays that end in the final state pass through EVERY step of the call, so every suffix sum starts from it
@@ -251,6 +267,24 @@ backward_gated_finish_kernel(GatedBackwardArgs a, const float *dq32, const float
     const int seg = blockIdx.y;
     const int blk_lo = seg * seg_blocks, blk_hi = min(blk_lo + seg_blocks, nblk) - 1;     // this workgroup's blocks
     float *totals = seg_totals + ((int64_t)bh * n_seg) * a.d + ch0;
+    const bool direct = n_seg > 1 && bs.kept(bh);              // totals: the suffix sums after each segment
+    if (TOTALS && direct) {
+        if (seg == n_seg - 1) return;
+        const int c = ch0 + (tid >> 4), t = blk_lo * kFinBlock + seg_blocks * kFinBlock;      // 16 threads a channel
+        const int64_t i = (((int64_t)bh * (n_seg - 1) + seg) * kD + c) * kD + 4 * (tid & 15);
+        const f4 x = *(const f4 *)(bs.s + i), y = *(const f4 *)(bs.g + i);
+        float acc = (x[0] * y[0] + x[1] * y[1]) + (x[2] * y[2] + x[3] * y[3]);
+#pragma unroll
+        for (int m = 8; m > 0; m >>= 1) acc += __shfl_xor(acc, m);
+        float l = 1.0f;
+        if (!is_boundary(a.start_pos + t + 1, a.grid_w, a.mode)) {
+            const int64_t e = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + (int64_t)t * a.in.stride_n + c;
+            l = IN_BF16 ? bf16_bits_to_float(((const uint16_t *)a.lam)[e]) : ((const float *)a.lam)[e];
+            if (a.fused_act) l = sigmoid_f32(l);
+        }
+        if ((tid & 15) == 0) totals[seg * a.d + (tid >> 4)] = acc * a.q_scale * l;
+        return;
+    }
     if (TOTALS) {
         f4 sum = f4{0.f, 0.f, 0.f, 0.f};
         for (int blk = blk_hi; blk >= blk_lo; --blk) {
@@ -269,7 +303,8 @@ backward_gated_finish_kernel(GatedBackwardArgs a, const float *dq32, const float
     }
     if (tid < CH) {
         float carry = sink ? sink[(int64_t)bh * a.d + ch0 + tid] : 0.f;
-        for (int s2 = n_seg - 1; s2 > seg; --s2) carry += totals[s2 * a.d + tid];
+        if (direct && seg < n_seg - 1) carry = totals[seg * a.d + tid];
+        else for (int s2 = n_seg - 1; s2 > seg; --s2) carry += totals[s2 * a.d + tid];
         sCarry[tid] = carry;
     }
     Item cur;
@@ -387,6 +422,30 @@ void launch_walks(const WalkArgs &w, int64_t n_seq, hipStream_t s)
         hipLaunchKernelGGL((backward_gated_walk_kernel<IN_BF16, OUT_BF16, 64>), dim3((unsigned)n_seq, 3), dim3(kThreads), 0, s, w);
 }
 
+// Segments of the finishing kernel: several per sequence when there are few long ones.
+void finish_segments(int64_t n_seq, int n, int *n_seg, int *seg_blocks)
+{
+    const int nblk = (n + kFinBlock - 1) / kFinBlock;
+    int g = 1;
+    if (n_seq < 256 && nblk >= 8) {
+        g = (int)(512 / n_seq);
+        if (g > 8) g = 8;
+        if (g > nblk / 4) g = nblk / 4;
+        if (g < 1) g = 1;
+    }
+    *seg_blocks = (nblk + g - 1) / g;
+    *n_seg = (nblk + *seg_blocks - 1) / *seg_blocks;
+}
+
+// Floats of one pass's bound states and flags; 0: not kept.  The reversed pass walks chunks of 32 tokens from the last
+// token on, so its chunks end on the segment bounds only where the length is a multiple of 32; other lengths add up r.
+size_t bound_states_floats(int64_t n_seq, int n, int d)
+{
+    int n_seg = 1, seg_blocks = 0;
+    if (d == kD && n % 32 == 0 && n > 0) finish_segments(n_seq, n, &n_seg, &seg_blocks);
+    return n_seg > 1 ? (size_t)n_seq * (n_seg - 1) * kD * kD + (size_t)(n_seq + 63) / 64 * 64 : 0;
+}
+
 }  // namespace
 
 size_t backward_gated_carried_extra_bytes(int64_t n_seq, int d)
@@ -397,8 +456,9 @@ size_t backward_gated_carried_extra_bytes(int64_t n_seq, int d)
 
 size_t backward_gated_workspace_bytes(int64_t n_seq, int n_tokens, int d)
 {
-    // dq and dk in fp32, then the finishing kernel's segment totals (at most 8 segments per sequence)
-    return 2 * (size_t)n_seq * n_tokens * d * sizeof(float) + (size_t)n_seq * 8 * d * sizeof(float);
+    // dq and dk in fp32, then the finishing kernel's segment totals (at most 8 segments per sequence) and bound states
+    return 2 * (size_t)n_seq * n_tokens * d * sizeof(float) + (size_t)n_seq * 8 * d * sizeof(float) +
+           2 * bound_states_floats(n_seq, n_tokens, d) * sizeof(float);
 }
 
 hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
@@ -427,7 +487,9 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
     // step: the shifted decay of step 0 is neutral); the dv pass ends with g_1 / q_scale
     const bool carried = b.state_in || b.d_state_out || b.d_state_in;
     const size_t mat = (size_t)n_seq * b.d * b.d;
-    float *cw = dk32 + (size_t)n_seq * n * b.d + (size_t)n_seq * 8 * b.d;      // after the gradients and the segment totals
+    const size_t bound_floats = bound_states_floats(n_seq, n, b.d);
+    float *bounds = dk32 + (size_t)n_seq * n * b.d + (size_t)n_seq * 8 * b.d;  // after the gradients and the segment totals
+    float *cw = bounds + 2 * bound_floats;
     float *hS = cw, *sn = cw + mat, *g1 = cw + 2 * mat, *sink_buf = cw + 3 * mat;
     const float *sink = (carried && b.d_state_out) ? sink_buf : nullptr;
     if (carried && b.d_state_out) {
@@ -470,6 +532,9 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
     const bool in16 = b.io_dtype == LASAD_BF16, out16 = b.grad_dtype == LASAD_BF16;
     static const bool force_walk = [] { const char *e = getenv("LASAD_GATED_BWD"); return e && !strcmp(e, "walk"); }();
     hipError_t e;
+    int n_seg, seg_blocks;
+    finish_segments(n_seq, n, &n_seg, &seg_blocks);
+    BoundStates bs{nullptr, nullptr, 0};
     if (b.d != kD) {
         // other head dims: the plain fp32 recurrence with the tensors in their roles, one workgroup per sequence and pass
         const dim3 grid((unsigned)n_seq, 3), block(kRecThreads);
@@ -496,6 +561,14 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
         p[2].q = v_l; p[2].o = w.o[2]; p[2].out = wl_rev; p[2].out_dtype = LASAD_F32;                  // dk
         p[2].v_lo = gl_l;
         for (int y = 0; y < 3; ++y) { p[y].state_in = st_in[y]; p[y].state_out = st_out[y]; }
+        if (bound_floats) {
+            for (int y = 0; y < 3; y += 2) {
+                p[y].seg_states = y ? bounds + bound_floats : bounds;
+                p[y].n_segments = n_seg; p[y].seg_chunks = seg_blocks * (kFinBlock / 32);
+            }
+            bs.s = bounds; bs.g = bounds + bound_floats;
+            bs.flags = (int64_t)n_seq * (n_seg - 1) * kD * kD;
+        }
         e = launch_backward_gated_passes(p, w.roles, b.k == nullptr, s);
         if (e != hipSuccess) return e;
     } else {
@@ -516,27 +589,16 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    // finishing kernel: one workgroup per sequence, or several segments per sequence when there are
-    // few long ones (then a first launch for the segment totals)
-    const int nblk = (n + kFinBlock - 1) / kFinBlock;
-    int n_seg = 1;
-    if (n_seq < 256 && nblk >= 8) {
-        n_seg = (int)(512 / n_seq);
-        if (n_seg > 8) n_seg = 8;
-        if (n_seg > nblk / 4) n_seg = nblk / 4;
-        if (n_seg < 1) n_seg = 1;
-    }
-    const int seg_blocks = (nblk + n_seg - 1) / n_seg;
-    n_seg = (nblk + seg_blocks - 1) / seg_blocks;
+    // finishing kernel: one workgroup per sequence, or a first launch for the segments' totals and one per segment
     float *seg_totals = dk32 + (size_t)n_seq * n * b.d;          // after the two gradient tensors
     // few workgroups: 16 channels per workgroup (four workgroups of 256 threads per sequence and segment)
     const bool narrow = b.d == kD && n_seq * n_seg < 256;      // (at 480 workgroups the narrow rows already cost more than they gain)
     // head dim 32: one workgroup of 32 channels; 128: two of 64; 64: one of 64 or four of 16
     const dim3 grid((unsigned)n_seq, (unsigned)n_seg, narrow ? 4 : b.d == 128 ? 2 : 1), block(narrow ? 256 : b.d == 32 ? 512 : 1024);
 #define LASAD_FIN_LAUNCH(I, O, T) do { \
-        if (b.d == 32) hipLaunchKernelGGL((backward_gated_finish_kernel<I, O, T, 32>), grid, block, 0, s, b, dq32, dk32, seg_totals, n_seg, seg_blocks, sink); \
-        else if (narrow) hipLaunchKernelGGL((backward_gated_finish_kernel<I, O, T, 16>), grid, block, 0, s, b, dq32, dk32, seg_totals, n_seg, seg_blocks, sink); \
-        else hipLaunchKernelGGL((backward_gated_finish_kernel<I, O, T, 64>), grid, block, 0, s, b, dq32, dk32, seg_totals, n_seg, seg_blocks, sink); \
+        if (b.d == 32) hipLaunchKernelGGL((backward_gated_finish_kernel<I, O, T, 32>), grid, block, 0, s, b, dq32, dk32, seg_totals, n_seg, seg_blocks, sink, bs); \
+        else if (narrow) hipLaunchKernelGGL((backward_gated_finish_kernel<I, O, T, 16>), grid, block, 0, s, b, dq32, dk32, seg_totals, n_seg, seg_blocks, sink, bs); \
+        else hipLaunchKernelGGL((backward_gated_finish_kernel<I, O, T, 64>), grid, block, 0, s, b, dq32, dk32, seg_totals, n_seg, seg_blocks, sink, bs); \
     } while (0)
     if (n_seg > 1) {
         if (in16) LASAD_FIN_LAUNCH(1, 0, 1); else LASAD_FIN_LAUNCH(0, 0, 1);

@@ -322,6 +322,12 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
             for (int r = 0; r < 4; ++r) accS[t][r] = a.state_in[s_off + (state_channel(t, g) + r) * (COL ? 1 : D)];
     }
 
+    // COL: the states at the segment bounds of the finishing kernel (seg_chunks chunks a segment, counted from the first
+    // token; the reversed walk comes to them from the other end)
+    const int n_bounds = COL && a.seg_states ? a.n_segments - 1 : 0;
+    int bound = REV ? n_bounds - 1 : 0;                        // the next one
+    int bound_at = REV ? (n + C - 1) / C - a.seg_chunks * n_bounds : a.seg_chunks;
+
     __syncthreads();
     bool fine = true;
     for (int chunk = 0; (fine || (chunk & 1)) && chunk < 2 * n_pairs; ++chunk) {
@@ -407,6 +413,13 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
             const float end = sTot[chunk & 1][col0 + l16];
 #pragma unroll
             for (int t = 0; t < 4; ++t) accS[t] *= end;
+            if (chunk + 1 == bound_at && (unsigned)bound < (unsigned)n_bounds) {
+                float *p = a.seg_states + (((int64_t)bh * n_bounds + bound) * D + col0 + l16) * D;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) *(f32x4v *)(p + state_channel(t, g)) = accS[t];
+                bound += REV ? -1 : 1;
+                bound_at += a.seg_chunks;
+            }
             // O^T row 4 g + r is key channel col0 + 4 g + r of token l16 / 16 + l16: times its A
             const float *dec = decays + (chunk & 1) * C * OS + l16 * OS + col0 + 4 * g;
             const float4 d0 = *(const float4 *)dec, d1 = *(const float4 *)(dec + 16 * OS);
@@ -443,6 +456,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
         fine = fine && (f.x | f.y | f.z | f.w) == 0;
         __syncthreads();
     }
+    if (n_bounds && tid == 0) ((int *)(a.seg_states + (int64_t)a.B * a.Hh * n_bounds * D * D))[bh] = fine;
     if (!fine) {
         redo();
         return;

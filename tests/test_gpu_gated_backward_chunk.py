@@ -1,7 +1,9 @@
 """The chunked vector-decay backward passes at the edges of their 32-token tiles and of the pairs of tiles they are walked
 in: lengths around one to four tiles, own and tied key, a mid-row start and carried states, and a chunk beyond the range
 of the factorised form in the first, a middle and the last tile.  Tolerance: the storage type's (helpers.TOL) against
-the fp64 oracle; where a gate is next to zero the decay gradient, a quotient by it, is left out."""
+the fp64 oracle; where a gate is next to zero the decay gradient, a quotient by it, is left out.
+
+Few long sequences: the finishing kernel's segments start from the states that the passes kept at the bounds."""
 import numpy as np
 import pytest
 
@@ -21,7 +23,7 @@ def lasad():
     return binding
 
 
-def _check(lasad, oracle, n, own_key, start, seed, spike=None):
+def _check(lasad, oracle, n, own_key, start, seed, spike=None, W=W):
     import torch
     rng = np.random.default_rng(seed)
     B, Hh = 2, 3
@@ -58,3 +60,30 @@ def test_tile_edges(lasad, oracle, n, own_key):
 @pytest.mark.parametrize("own_key", [False, True], ids=["tied", "own"])
 def test_range_exit(lasad, oracle, spike, own_key):
     _check(lasad, oracle, 97, own_key, start=0, seed=spike, spike=spike)
+
+
+# bounds on and off row ends; a shorter last segment; a length that is no multiple of 32 (no states kept)
+@pytest.mark.parametrize("n", [512, 544, 1024, 1040, 1056])
+@pytest.mark.parametrize("start", [0, 15, 17])
+@pytest.mark.parametrize("own_key", [False, True], ids=["tied", "own"])
+def test_segment_bounds(lasad, oracle, n, start, own_key):
+    _check(lasad, oracle, n, own_key, start, seed=n + start, W=16)
+
+
+@pytest.mark.parametrize("spike", [3, 300, 1020])
+def test_segment_bounds_beside_a_range_exit(lasad, oracle, spike):
+    """One sequence goes to the token-serial walk and keeps no states; the channel of its tiny gate is left out."""
+    import torch
+    n, W, c = 1024, 16, 5
+    rng = np.random.default_rng(spike)
+    q, v, g, k = (wl.store_round(rng.standard_normal((1, n, 2, D), dtype=np.float32) / np.float32(8), "bf16") for _ in range(4))
+    lam = wl.gate_inputs((1, n, 2, D), "bf16", spike + 1)
+    lam[:, spike, 1, c] = 2.0 ** -120
+    dev = lambda x: lasad.to_device(x, "bf16")
+    got = lasad.lasad_backward_gated(dev(q), dev(lam), dev(v), dev(g), n // W, W, k=dev(k), grad_dtype=torch.float32)
+    ref = oracle.gated_backward(q, lam, v, g, W, k=k)
+    for i, (a, r) in enumerate(zip(got, ref)):
+        a, r = a.cpu().numpy(), np.array(r)
+        if i == 1:
+            a[:, :, 1, c] = r[:, :, 1, c] = 0
+        assert rel_err(a, r) <= TOL["bf16"], i
