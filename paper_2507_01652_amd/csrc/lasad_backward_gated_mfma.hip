@@ -60,7 +60,7 @@ __device__ __noinline__ void redo_roles(const ForwardArgs *a, const scan::ScanRo
 // tensors, and one 16-byte piece of a row of x, y and the low-order part of d_o.  Uniform bases, advanced chunk by chunk
 // on the scalar unit, plus 32-bit byte offsets; the reversed passes (negative token stride) keep their bases at the
 // chunk's last token, the lowest address.  Rows past the end re-read the last token.
-template <int PASS, int OWNKEY, int LO>
+template <int PASS, int OWNKEY, int LO, int NG>
 struct PassStage {
     static constexpr bool REV = PASS != DQ, COL = PASS != DV, ZLOAD = PASS != DQ || OWNKEY;
     const char *l, *z, *q, *x, *y, *lo;
@@ -72,10 +72,12 @@ struct PassStage {
         u32x4 rx, ry, rlo;
     };
 
-    __device__ __forceinline__ void init(const ForwardArgs &a, int64_t base, int n)
+    // from the walk's token `first` on, n tokens
+    __device__ __forceinline__ void init(const ForwardArgs &a, int64_t base, int first, int n)
     {
         left = n;
-        start = true;
+        start = first == 0;
+        base += first * a.in.stride_n;
         const int64_t s = a.in.stride_n;
         row = (uint32_t)(REV ? -s : s) * 2;
         const int64_t b = base + (REV ? (min(C, n) - 1) * s : 0);
@@ -105,13 +107,13 @@ struct PassStage {
         f.ry = *(const u32x4 *)(y + ov);
         if (LO) f.rlo = *(const u32x4 *)(lo + ov);
     }
-    // on to the next chunk; past the end the last one is read again
+    // on to the group's next chunk; past the end the last one is read again
     __device__ __forceinline__ void next(int64_t stride_n)
     {
-        if (left <= C) return;
-        left -= C;
+        if (left <= NG * C) return;
+        left -= NG * C;
         start = false;
-        const int64_t adv = (REV ? min(C, left) : C) * stride_n * 2;
+        const int64_t adv = ((NG - 1) * C + (REV ? min(C, left) : C)) * stride_n * 2;
         l += adv; y += adv;
         if (ZLOAD) z += adv;
         if (!COL) q += adv;
@@ -120,9 +122,9 @@ struct PassStage {
     }
 };
 
-// One pass of sequence bh by the calling workgroup of eight wavefronts; ka, kr: its arguments and operand roles in the
+// One pass of sequence bh by the calling workgroup of four compute wavefronts and NG groups of four loaders; ka, kr: its arguments and operand roles in the
 // kernel-argument segment (for the redo).
-template <int PASS, int OUT_BF16, int OWNKEY, int FUSED, int LO>
+template <int PASS, int OUT_BF16, int OWNKEY, int FUSED, int LO, int NG>
 __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArgs *ka, const scan::ScanRoles *kr, int bh,
                                           unsigned char *smem, float (*sTot)[D], int (*sTrip)[4])
 {
@@ -135,7 +137,8 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = a.n_tokens;
-    const int n_pairs = (n + 2 * C - 1) / (2 * C);             // the walk goes two chunks at a time; the second may be empty
+    // (one loader group: the walk goes two chunks at a time; the second may be empty)
+    const int n_chunks = NG == 1 ? (n + 2 * C - 1) / (2 * C) * 2 : (n + C - 1) / C;
     SplitConst sc;
     sc.init();
     auto redo = [&]() {
@@ -144,16 +147,18 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
 
     if (wave >= 4) {
         // ===================================== loader wavefronts =====================================
-        const int lw = wave & 3, st = tid & 255;
+        const int grp = NG == 2 ? (wave >> 2) - 1 : 0, lw = wave & 3, st = tid & 255;
+        const int first = grp * C < n ? grp * C : 0;           // (a group without a chunk reads the first one, for nobody)
         const int pr = lane & 15, pcol = 16 * lw + 4 * (lane >> 4);
-        PassStage<PASS, OWNKEY, LO> sg;
-        sg.init(a, (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h, n);
+        using Stage = PassStage<PASS, OWNKEY, LO, NG>;
+        Stage sg;
+        sg.init(a, (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h, first, n - first);
         RowBoundaries bounds;
-        bounds.init(a.start_pos, a.grid_w, a.mode, C);
-        int left = n;                              // tokens from the next chunk to be prepared on
+        bounds.init(a.start_pos + grp * C, a.grid_w, a.mode, NG * C);
+        int left = n - grp * C;                    // tokens from the next chunk to be prepared on
         const int orow = st >> 3, ocol = (st & 7) * 8;
         const int64_t o_lane = orow * a.out.stride_n + ocol;
-        int64_t o_chunk = (int64_t)b * a.out.stride_b + (int64_t)h * a.out.stride_h;
+        int64_t o_chunk = (int64_t)b * a.out.stride_b + (int64_t)h * a.out.stride_h + (NG == 2 && grp == 0 ? C : 0) * a.out.stride_n;
         auto store_tile = [&](int chunk) {
             const float *tile = outs + (chunk & 1) * C * OS + orow * OS + ocol;
             float4 u = *(const float4 *)tile, w = *(const float4 *)(tile + 4);
@@ -168,30 +173,46 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
                     gstore16<false>((float *)a.o + i + 4, w.x, w.y, w.z, w.w);
                 }
             }
-            o_chunk += C * a.out.stride_n;
+            o_chunk += NG * C * a.out.stride_n;                // (of two groups, each stores every other tile)
         };
 
-        // a chunk into slot p; done: the finished chunk to be stored meanwhile, or -1.  (Past the end the last chunk's data
-        // go once more into a slot that nobody reads.)
-        auto prepare = [&](typename PassStage<PASS, OWNKEY, LO>::Regs &f, int p, int done, bool first) {
+        // between the phases of a chunk's preparation
+        uint2 pq[2];
+        u32x4 px, py, plo;
+        bool row_live;
+        float z[2][4], x[2][4], tot[4], exc[4];
+
+        // the plain rows into slot p (a row past the end is a query that nobody stores, and zero as y)
+        auto put_rows = [&](int p) {
+            uint16_t *const piece = slots + p * SL::kHalfs + (st >> 3) * SL::ROW + (st & 7) * 8;
+            if (COL) *(u32x4 *)&piece[SL::X] = px;
+            *(u32x4 *)&piece[SL::Y] = row_live ? py : u32x4{0u, 0u, 0u, 0u};
+            if (LO) *(u32x4 *)&piece[SL::Lo] = row_live ? plo : u32x4{0u, 0u, 0u, 0u};
+        };
+        // Phase A: everything that needs no slot; done: the finished chunk to be stored meanwhile, or -1.  One loader group
+        // runs both phases in one period and puts the plain rows into slot p at once.  (Past the end the last chunk's data go
+        // once more into a slot that nobody reads.)
+        auto phase_a = [&](typename Stage::Regs &f, int p, int done, bool walk_start) {
             uint32_t bmask = bounds.mask();
             bounds.advance();
-            if (REV && first) bmask |= 1u;         // (the walk's first step: no decay)
-            uint2 pq[2];
-            float z[2][4], x[2][4], tot[4], exc[4];
+            if (REV && walk_start) bmask |= 1u;    // (the walk's first step: no decay)
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
                 unpack4(f.rl[it], x[it]);
                 if (sg.ZLOAD) unpack4(f.rz[it], z[it]);
                 if (!COL) pq[it] = f.rq[it];
             }
-            // the plain rows straight into the slot (a row past the end is a query that nobody stores, and zero as y)
-            uint16_t *const slot = slots + p * SL::kHalfs;
-            uint16_t *const piece = slot + (st >> 3) * SL::ROW + (st & 7) * 8;
-            const bool row_live = (st >> 3) < left;
-            if (COL) *(u32x4 *)&piece[SL::X] = f.rx;
-            *(u32x4 *)&piece[SL::Y] = row_live ? f.ry : u32x4{0u, 0u, 0u, 0u};
-            if (LO) *(u32x4 *)&piece[SL::Lo] = row_live ? f.rlo : u32x4{0u, 0u, 0u, 0u};
+            row_live = (st >> 3) < left;
+            if (COL) px = f.rx;
+            py = f.ry;
+            if (LO) plo = f.rlo;
+            if (NG == 1) {
+                put_rows(p);
+            } else {
+                if (COL) asm volatile("" : "+v"(px));
+                asm volatile("" : "+v"(py));
+                if (LO) asm volatile("" : "+v"(plo));
+            }
             // (the fetched registers are free from here on, and the compiler must see it so: lasad_forward_gated_chunk.hip)
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
@@ -240,10 +261,14 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
                     }
                 }
             }
-            left -= C;
+            left -= NG * C;
 #pragma unroll
             for (int e = 0; e < 4; ++e) tot[e] = x[0][e] * x[1][e];
             row_scan_mul4(tot, exc);               // (FUSED: of the reciprocals throughout)
+        };
+        // Phase B: the chunk into slot p, and its range flag for the barrier that ends this period.
+        auto phase_b = [&](int p) {
+            if (NG == 2) put_rows(p);
             bool trip;
             if (FUSED) trip = !(fmaxf(fmaxf(tot[0], tot[1]), fmaxf(tot[2], tot[3])) <= kMaxInvDecay);
             else trip = !(fminf(fminf(tot[0], tot[1]), fminf(tot[2], tot[3])) >= 1.0f / kMaxInvDecay);
@@ -253,7 +278,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
                                                   : make_float4(tot[0], tot[1], tot[2], tot[3]);
             const bool any = __any(trip);
             if (lane == 0) sTrip[p][lw] = any ? 1 : 0;
-            uint16_t *rows = slot + 2 * pr * SL::ROW + pcol;
+            uint16_t *rows = slots + p * SL::kHalfs + 2 * pr * SL::ROW + pcol;
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
                 float zt[4], dec[4];               // Z~ and A of this token
@@ -282,26 +307,58 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
                 }
             }
         };
-        // Two chunks of loads in flight, in two sets of registers.  (A pair of chunks is always done as a whole, range flags
-        // tested at its end: with a way out between its halves the compiler waits for both sets at the loop's top.)
-        typename PassStage<PASS, OWNKEY, LO>::Regs r0, r1;
-        sg.fetch(r0, pr, pcol, st);
-        sg.next(a.in.stride_n);
-        sg.fetch(r1, pr, pcol, st);
-        prepare(r0, 0, -1, true);
-        __syncthreads();
         bool fine = true;
-        for (int pair = 0; fine && pair < n_pairs; ++pair) {
-            const int4 t0 = *(const int4 *)sTrip[0];
-            prepare(r1, 1, 2 * pair - 1, false);
+        if constexpr (NG == 1) {
+            // Two chunks of loads in flight, in two sets of registers.  (A pair of chunks is always done as a whole, range
+            // flags tested at its end: with a way out between its halves the compiler waits for both sets at the loop's top.)
+            typename Stage::Regs r0, r1;
+            auto prepare = [&](typename Stage::Regs &f, int p, int done, bool walk_start) {
+                phase_a(f, p, done, walk_start);
+                phase_b(p);
+            };
+            sg.fetch(r0, pr, pcol, st);
+            sg.next(a.in.stride_n);
+            sg.fetch(r1, pr, pcol, st);
+            prepare(r0, 0, -1, true);
             __syncthreads();
-            const int4 t1 = *(const int4 *)sTrip[1];
-            prepare(r0, 0, 2 * pair, false);
-            fine = (t0.x | t0.y | t0.z | t0.w | t1.x | t1.y | t1.z | t1.w) == 0;
+            for (int chunk = 0; fine && chunk < n_chunks; chunk += 2) {
+                const int4 t0 = *(const int4 *)sTrip[0];
+                prepare(r1, 1, chunk - 1, false);
+                __syncthreads();
+                const int4 t1 = *(const int4 *)sTrip[1];
+                prepare(r0, 0, chunk, false);
+                fine = (t0.x | t0.y | t0.z | t0.w | t1.x | t1.y | t1.z | t1.w) == 0;
+                __syncthreads();
+            }
+        } else {
+            // the groups take the chunks in turn, a period for each phase
+            typename Stage::Regs r;
+            sg.fetch(r, pr, pcol, st);
+            phase_a(r, 0, -1, grp == 0);
+            if (grp == 0) phase_b(0);
             __syncthreads();
+            int4 f;                                // a chunk's range flags, read at the start of its period and tested at the end
+            auto end_period = [&]() {
+                fine = (f.x | f.y | f.z | f.w) == 0;
+                __syncthreads();
+            };
+            if (grp == 1) {                        // period 0
+                f = *(const int4 *)sTrip[0];
+                phase_b(1);
+                end_period();
+            }
+            for (int chunk = grp; fine && chunk < n_chunks; chunk += 2) {
+                f = *(const int4 *)sTrip[chunk & 1];
+                phase_a(r, 0, chunk - 1, false);
+                end_period();
+                if (!fine || chunk + 1 == n_chunks) break;
+                f = *(const int4 *)sTrip[(chunk + 1) & 1];
+                phase_b(chunk & 1);
+                end_period();
+            }
         }
         if (!fine) redo();
-        else store_tile(2 * n_pairs - 1);
+        else if (NG == 1 || grp == (n_chunks & 1)) store_tile(n_chunks - 1);
         return;
     }
 
@@ -330,7 +387,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
 
     __syncthreads();
     bool fine = true;
-    for (int chunk = 0; (fine || (chunk & 1)) && chunk < 2 * n_pairs; ++chunk) {
+    for (int chunk = 0; (fine || (NG == 1 && (chunk & 1))) && chunk < n_chunks; ++chunk) {
         const int4 f = *(const int4 *)sTrip[chunk & 1];
         const SlotPtr<SL::ROW> sp(slots + (chunk & 1) * SL::kHalfs, lane);
         f32x4v p00 = zero4, p01 = zero4, p11 = zero4;              // scores P^T[j][i]: (key tile, query tile)
@@ -484,8 +541,10 @@ struct PassSet {
 // orthogonal to the recurrence output, which makes dq and dk small differences of larger terms
 // early in a sequence; a single bf16 there costs up to 0.15 of the RMS in single elements, and in dv, which for
 // the last tokens of a sequence is a multiple of a single d_o row, up to 0.02.
-template <int OUT_BF16, int TIED, int FUSED = 0>
-__global__ void __launch_bounds__(2 * kThreads, 4)
+// NG = 2: a second loader group, for workgroups that have a compute unit to themselves (a lone workgroup is bound by what
+// its loaders issue, as in the forward).
+template <int OUT_BF16, int TIED, int FUSED, int NG>
+__global__ void __launch_bounds__((1 + NG) * kThreads, NG == 1 ? 4 : 3)
 backward_gated_passes_kernel(PassSet ps)
 {
     constexpr int kScanFloats = scan::lds_floats<scan::ROLES_ROW>();
@@ -497,9 +556,9 @@ backward_gated_passes_kernel(PassSet ps)
     const int pass = r >> 3, bh = grp * 8 + (r & 7);
     if (bh >= ps.a[0].B * ps.a[0].Hh) return;                  // (the last group may be partly empty)
     const PassSet *kp = (const PassSet *)__builtin_amdgcn_kernarg_segment_ptr();
-    if (pass == DQ) pass_body<DQ, 0, !TIED, FUSED, FUSED>(ps.a[0], &kp->a[0], &kp->roles[0], bh, smem, sTot, sTrip);
-    else if (pass == DV) pass_body<DV, OUT_BF16, !TIED, FUSED, FUSED>(ps.a[1], &kp->a[1], &kp->roles[1], bh, smem, sTot, sTrip);
-    else pass_body<DK, 0, !TIED, FUSED, FUSED>(ps.a[2], &kp->a[2], &kp->roles[2], bh, smem, sTot, sTrip);
+    if (pass == DQ) pass_body<DQ, 0, !TIED, FUSED, FUSED, NG>(ps.a[0], &kp->a[0], &kp->roles[0], bh, smem, sTot, sTrip);
+    else if (pass == DV) pass_body<DV, OUT_BF16, !TIED, FUSED, FUSED, NG>(ps.a[1], &kp->a[1], &kp->roles[1], bh, smem, sTot, sTrip);
+    else pass_body<DK, 0, !TIED, FUSED, FUSED, NG>(ps.a[2], &kp->a[2], &kp->roles[2], bh, smem, sTot, sTrip);
 }
 
 }  // namespace
@@ -516,19 +575,22 @@ hipError_t launch_backward_gated_passes(const ForwardArgs *a, const scan::ScanRo
     if ((n_seq + 7) / 8 * 24 > 0x7fffffff) return hipErrorInvalidValue;
     PassSet ps;
     for (int i = 0; i < 3; ++i) { ps.a[i] = a[i]; ps.roles[i] = roles[i]; }
-    const dim3 grid((unsigned)((n_seq + 7) / 8 * 24)), block(2 * kThreads);
+// A compute unit for every workgroup: an XCD gets three workgroups of every eighth sequence and has 32 units, so up to
+    // 80 sequences.  One -> two loader groups, us a call: 12 sequences of 4096 tokens 182 -> 180, fused layer 265 -> 222; 24 of
+    // 1024 59 -> 57, 106 -> 96; 80 of 576 47 -> 46.5, 88 -> 82; but 84 of 256 30.9 -> 32.5, 54.9 -> 57.0.
+    const int ng = n_seq <= 80 ? 2 : 1;
+    const dim3 grid((unsigned)((n_seq + 7) / 8 * 24)), block((1 + ng) * kThreads);
     const bool out16 = a[1].out_dtype == LASAD_BF16;
-    if (a[0].fused_act) {
-        if (!tied || !a[0].q_lo || !a[1].v_lo || !a[2].v_lo) return hipErrorInvalidValue;
-        if (out16) hipLaunchKernelGGL((backward_gated_passes_kernel<1, 1, 1>), grid, block, 0, s, ps);
-        else hipLaunchKernelGGL((backward_gated_passes_kernel<0, 1, 1>), grid, block, 0, s, ps);
-    } else if (tied) {
-        if (out16) hipLaunchKernelGGL((backward_gated_passes_kernel<1, 1>), grid, block, 0, s, ps);
-        else hipLaunchKernelGGL((backward_gated_passes_kernel<0, 1>), grid, block, 0, s, ps);
-    } else {
-        if (out16) hipLaunchKernelGGL((backward_gated_passes_kernel<1, 0>), grid, block, 0, s, ps);
-        else hipLaunchKernelGGL((backward_gated_passes_kernel<0, 0>), grid, block, 0, s, ps);
-    }
+    if (a[0].fused_act && (!tied || !a[0].q_lo || !a[1].v_lo || !a[2].v_lo)) return hipErrorInvalidValue;
+#define LASAD_LAUNCH1(O, T, F) do { \
+        if (ng == 2) hipLaunchKernelGGL((backward_gated_passes_kernel<O, T, F, 2>), grid, block, 0, s, ps); \
+        else hipLaunchKernelGGL((backward_gated_passes_kernel<O, T, F, 1>), grid, block, 0, s, ps); } while (0)
+#define LASAD_LAUNCH(T, F) do { if (out16) LASAD_LAUNCH1(1, T, F); else LASAD_LAUNCH1(0, T, F); } while (0)
+    if (a[0].fused_act) LASAD_LAUNCH(1, 1);
+    else if (tied) LASAD_LAUNCH(1, 0);
+    else LASAD_LAUNCH(0, 0);
+#undef LASAD_LAUNCH
+#undef LASAD_LAUNCH1
     return hipGetLastError();
 }
 

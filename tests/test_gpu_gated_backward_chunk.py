@@ -87,3 +87,17 @@ def test_segment_bounds_beside_a_range_exit(lasad, oracle, spike):
         if i == 1:
             a[:, :, 1, c] = r[:, :, 1, c] = 0
         assert rel_err(a, r) <= TOL["bf16"], i
+
+
+@pytest.mark.parametrize("n", [1, 32, 33, 64, 96, 97, 129])
+@pytest.mark.parametrize("Hh", [80, 81], ids=["two_loader_groups", "one"])
+def test_loader_groups(lasad, oracle, n, Hh):
+    """Both sides of the rule that gives a workgroup a second loader group (a compute unit for every workgroup)."""
+    import torch
+    rng = np.random.default_rng(n)
+    q, v, g = (wl.store_round(rng.standard_normal((1, n, Hh, D), dtype=np.float32) / np.float32(8), "bf16") for _ in range(3))
+    lam = wl.gate_inputs((1, n, Hh, D), "bf16", n)
+    dev = lambda x: lasad.to_device(x, "bf16")
+    got = lasad.lasad_backward_gated(dev(q), dev(lam), dev(v), dev(g), (n + W - 1) // W, W, grad_dtype=torch.float32)
+    for i, (a, r) in enumerate(zip(got, oracle.gated_backward(q, lam, v, g, W))):
+        assert rel_err(a.cpu().numpy(), r) <= TOL["bf16"], i
