@@ -604,17 +604,18 @@ gated_segment_fold_kernel(ForwardArgs a, SegPlan plan)
 }
 
 // Few, long sequences are cut into segments that fill the chip (512 workgroups, two per compute unit).  The state pass
-// and the fold have to pay: at least 8 chunks (256 tokens) a segment and three segments, and at least four where the
-// sequences alone give more than a workgroup to every second compute unit.  Measured (tied key, us, one workgroup per
-// sequence -> segments): 96 x 4096 tokens 144 -> 91 (5 segments); 12 x 4096 141 -> 41 (8); 32 x 1024 37.8 -> 26.8 (4),
-// 31.8 (3), 40.5 (2); 128 x 2304 83 -> 74 (4); 192 x 4096 145 -> 196 (2), 181 (3), not taken.
+// and the fold have to pay: at least 8 chunks (256 tokens) a segment and three segments; where three segments would put
+// two workgroups on a compute unit (more than 85 sequences), four.  Measured (tied key, us, one
+// workgroup per sequence -> segments): 96 x 4096 tokens 144 -> 91 (5 segments); 12 x 4096 141 -> 41 (8); 32 x 1024 37.8 ->
+// 26.8 (4), 31.8 (3), 40.5 (2); 128 x 2304 83 -> 74 (4), 96 x 1444 53 -> 44 (5), 96 x 1024 38 -> 38 (4); not taken: 96 x 900 34.9 -> 39.6 (3), 192 x 4096 145 -> 196 (2),
+// 181 (3).
 SegPlan segment_plan(int64_t n_seq, int n_tokens)
 {
     const int n_chunks = (n_tokens + C - 1) / C;
     int g = (int)(512 / n_seq);
     if (g > kMaxSegments) g = kMaxSegments;
     if (g > n_chunks / 8) g = n_chunks / 8;
-    if (g < (n_seq > 128 ? 4 : 3)) return SegPlan{1, n_tokens};
+    if (g < (n_seq > 85 ? 4 : 3)) return SegPlan{1, n_tokens};
     const int seg_chunks = (n_chunks + g - 1) / g;
     g = (n_chunks + seg_chunks - 1) / seg_chunks;
     static_assert(8 * C >= kRowStateTokens, "a segment's rows hold its incoming state");
