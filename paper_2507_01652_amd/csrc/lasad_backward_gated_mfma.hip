@@ -244,7 +244,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             // (the tied key keeps its own lambda, see the forward)
-                            if (PASS == DQ && FUSED) z[it][e] = z[it][e] < 1e30f ? z[it][e] * __builtin_amdgcn_rcpf(x[it][e]) : 1.0f;
+                            if (PASS == DQ && FUSED) z[it][e] = z[it][e] >= 1e30f ? 1.0f : z[it][e] * __builtin_amdgcn_rcpf(x[it][e]);
                             x[it][e] = 1.0f;
                         }
                     }

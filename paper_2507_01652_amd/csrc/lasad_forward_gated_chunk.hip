@@ -249,8 +249,8 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             // FUSED: k = 1 - lambda = exp(-z) lambda, and K~ = k / A = exp(-z) / (A of the token before); at a
-                            // boundary A does not change, and the key needs its own lambda
-                            if (FUSED) key[it][e] = key[it][e] < 1e30f ? key[it][e] * __builtin_amdgcn_rcpf(x[it][e]) : 1.0f;
+                            // boundary A does not change, and the key needs its own lambda (exp(-z) up to infinity: 1; NaN stays)
+                            if (FUSED) key[it][e] = key[it][e] >= 1e30f ? 1.0f : key[it][e] * __builtin_amdgcn_rcpf(x[it][e]);
                             x[it][e] = 1.0f;
                         }
                     }

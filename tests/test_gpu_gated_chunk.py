@@ -73,3 +73,29 @@ def test_range_exit(lasad, oracle, spike, B, Hh, form):
 def test_segments(lasad, oracle, n, B, Hh, form, spike):
     """Few, long sequences: segments walked by different workgroups from states formed ahead of the walk."""
     _check(lasad, oracle, n, B, Hh, form, start=30, seed=n, spike=spike)
+
+
+@pytest.mark.parametrize("n,B,Hh", [(97, 1, 3), (97, 20, 13), (1023, 1, 2)], ids=["few", "many", "segments"])
+@pytest.mark.parametrize("row", [0, 1, -1])
+def test_nan_gate_at_a_row_end(lasad, oracle, n, B, Hh, row):
+    """Where the decay is off the gate still makes the key: a NaN logit there reaches its own and all later tokens.  (The
+    kernels split operands in pairs of channels, so the state's row beside the channel's own may be NaN as well.)"""
+    import torch
+    rng = np.random.default_rng(n)
+    q, z, v = (wl.store_round(rng.standard_normal((B, n, Hh, D), dtype=np.float32), "bf16") for _ in range(3))
+    t, c = (row % (n // W)) * W + W - 1, 9
+    pairs = sample_pairs(B, Hh, 2, n)
+    at = lambda x: gather_pairs(x, pairs)
+    ref = oracle.gated_layer(at(q), at(z), at(v), W, eps=1e-5)
+    z[:, t, :, c] = np.nan
+    dev = lambda x: lasad.to_device(x, "bf16")
+    s1 = torch.empty((B, Hh, D, D), dtype=torch.float32, device="cuda")
+    o = lasad.lasad_forward_layer(dev(q), dev(z), dev(v), -(-n // W), W, norm_eps=1e-5, state_out=s1, out_dtype=torch.float32)
+    o, s1 = o.cpu().numpy(), s1.cpu().numpy()
+    assert np.isnan(o[:, t:]).all() and np.isfinite(o[:, :t]).all()
+    assert np.isnan(s1[:, :, c]).all() and np.isfinite(np.delete(s1, (c, c ^ 1), axis=2)).all()
+    assert rel_err(at(o)[:, :t], ref[:, :t]) <= TOL["bf16"]
+    # without the norm nothing but the state carries it into the gradient of the query
+    g = lasad.lasad_backward_layer(dev(q), dev(z), dev(v), dev(v), -(-n // W), W, norm_eps=-1.0, grad_dtype=torch.float32)
+    dq = g[0].cpu().numpy()
+    assert np.isnan(dq[:, t:, :, c]).all() and np.isfinite(np.delete(dq, (c, c ^ 1), axis=3)[:, :t]).all()
