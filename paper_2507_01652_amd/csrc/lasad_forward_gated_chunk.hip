@@ -139,9 +139,9 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
     const int b = bh / a.Hh, h = bh - b * a.Hh;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int seg_t0 = seg * plan.seg_tokens;
-    const int n = min(plan.seg_tokens, a.n_tokens - seg_t0);               // tokens of this workgroup
+    const int seg_t0 = plan.start(seg);
     const bool last_seg = seg == plan.n_seg - 1;
+    const int n = (last_seg ? a.n_tokens : plan.start(seg + 1)) - seg_t0;  // tokens of this workgroup
     const int n_chunks = (n + C - 1) / C;
     SplitConst sc;
     sc.init();
@@ -466,7 +466,7 @@ gated_segment_state_kernel(ForwardArgs a, SegPlan plan)
     const int st = threadIdx.x, lane = st & 63;
     const int wave = __builtin_amdgcn_readfirstlane(st >> 6);
     const int pr = lane & 15, l16 = lane & 15, g = lane >> 4, pcol = 16 * wave + 4 * g;
-    const int seg_t0 = seg * plan.seg_tokens, n_chunks = plan.seg_tokens / C;      // (whole chunks)
+    const int seg_t0 = plan.start(seg), next_t0 = plan.start(seg + 1), n_chunks = (next_t0 - seg_t0) / C;
     const int64_t base = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + seg_t0 * a.in.stride_n;
     SplitConst sc;
     sc.init();
@@ -563,7 +563,7 @@ gated_segment_state_kernel(ForwardArgs a, SegPlan plan)
         }
         __syncthreads();
     }
-    const RowState us = segment_state(a, b, h, seg_t0 + plan.seg_tokens);
+    const RowState us = segment_state(a, b, h, next_t0);
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -588,7 +588,7 @@ gated_segment_fold_kernel(ForwardArgs a, SegPlan plan)
     float dec[kMaxSegments];
 #pragma unroll
     for (int s = 1; s < kMaxSegments; ++s) {
-        const RowState rs = segment_state(a, b, h, min(s, plan.n_seg - 1) * plan.seg_tokens);
+        const RowState rs = segment_state(a, b, h, plan.start(min(s, plan.n_seg - 1)));
         u[s] = *(const float4 *)rs.at(i);
         dec[s] = *rs.at(D * D + i / D);
     }
@@ -598,30 +598,27 @@ gated_segment_fold_kernel(ForwardArgs a, SegPlan plan)
     for (int s = 1; s < kMaxSegments; ++s) {
         if (s < plan.n_seg) {
             p = make_float4(fmaf(dec[s], p.x, u[s].x), fmaf(dec[s], p.y, u[s].y), fmaf(dec[s], p.z, u[s].z), fmaf(dec[s], p.w, u[s].w));
-            *(float4 *)segment_state(a, b, h, s * plan.seg_tokens).at(i) = p;
+            *(float4 *)segment_state(a, b, h, plan.start(s)).at(i) = p;
         }
     }
 }
 
 // Few, long sequences are cut into segments that fill the chip (512 workgroups, two per compute unit).  The state pass
 // and the fold have to pay: at least 8 chunks (256 tokens) a segment and three segments; where three segments would put
-// two workgroups on a compute unit (more than 85 sequences), four.  Measured (tied key, us, one
-// workgroup per sequence -> segments): 96 x 4096 tokens 144 -> 91 (5 segments); 12 x 4096 141 -> 41 (8); 32 x 1024 37.8 ->
-// 26.8 (4), 31.8 (3), 40.5 (2); 128 x 2304 83 -> 74 (4), 96 x 1444 53 -> 44 (5), 96 x 1024 38 -> 38 (4); not taken: 96 x 900 34.9 -> 39.6 (3), 192 x 4096 145 -> 196 (2),
-// 181 (3).
+// two workgroups on a compute unit (more than 85 sequences), four.  The chunks are dealt out evenly, so every length
+// finds a plan.  Measured (tied key, us, one workgroup per sequence -> segments): 12 x 4096 tokens 141 -> 29 (16
+// segments), 12 x 3844 133 -> 30 (15), 24 x 2116 76 -> 30 (8), 48 x 1849 66 -> 39 (7), 96 x 4096 144 -> 91 (5), 32 x
+// 1024 37.8 -> 26.8 (4), 31.8 (3), 40.5 (2); 128 x 2304 83 -> 74 (4), 96 x 1444 53 -> 43 (5), 96 x 1024 38 -> 38 (4);
+// not taken: 96 x 900 34.9 -> 39.6 (3), 192 x 4096 145 -> 196 (2), 181 (3).
 SegPlan segment_plan(int64_t n_seq, int n_tokens)
 {
     const int n_chunks = (n_tokens + C - 1) / C;
     int g = (int)(512 / n_seq);
     if (g > kMaxSegments) g = kMaxSegments;
     if (g > n_chunks / 8) g = n_chunks / 8;
-    if (g < (n_seq > 85 ? 4 : 3)) return SegPlan{1, n_tokens};
-    const int seg_chunks = (n_chunks + g - 1) / g;
-    g = (n_chunks + seg_chunks - 1) / seg_chunks;
-    static_assert(8 * C >= kRowStateTokens, "a segment's rows hold its incoming state");
-    // (the last segment may be short of kRowStateTokens rows: then the plan would not fit)
-    if (n_tokens - (g - 1) * seg_chunks * C < kRowStateTokens) return SegPlan{1, n_tokens};
-    return SegPlan{g, seg_chunks * C};
+    if (g < (n_seq > 85 ? 4 : 3)) return SegPlan{1, n_chunks, 0};
+    static_assert(7 * C + 1 >= kRowStateTokens, "the rows of a segment of 8 chunks hold its incoming state");
+    return SegPlan{g, n_chunks / g, n_chunks % g};
 }
 
 }  // namespace

@@ -42,11 +42,13 @@ constexpr float kMaxInvDecay = 1.2676506e30f;      // 2^100: largest 1 / A of a 
 
 __device__ __forceinline__ int state_channel(int t, int g) { return 32 * (t >> 1) + 8 * g + 4 * (t & 1); }    // of row 4 g
 
-// A sequence cut into segments that different workgroups walk (few, long sequences): n_seg segments of seg_tokens tokens
-// (the last one may be shorter).  A segment's incoming state P_g is formed by a state pass and a fold before the walk; in
-// the forward it sits in the segment's own part of the output tensor until the segment's first tile is stored.
+// A sequence cut into segments that different workgroups walk (few, long sequences), whole chunks each, the first
+// `longer` of them one chunk longer than the rest (the last chunk may be short of tokens).  A segment's incoming state
+// P_g is formed by a state pass and a fold before the walk; in the forward it sits in the segment's own part of the
+// output tensor until the segment's first tile is stored.
 struct SegPlan {
-    int n_seg, seg_tokens;             // n_seg = 1: no segments
+    int n_seg, chunks, longer;         // n_seg = 1: no segments
+    __host__ __device__ __forceinline__ int start(int seg) const { return (seg * chunks + (seg < longer ? seg : longer)) * C; }
 };
 
 // A 64 x 64 fp32 state and a vector of 64 after it, laid out over consecutive token rows of the output tensor: float i is

@@ -75,6 +75,58 @@ def test_segments(lasad, oracle, n, B, Hh, form, spike):
     _check(lasad, oracle, n, B, Hh, form, start=30, seed=n, spike=spike)
 
 
+def _out_view(layout, B, n, Hh, dtype):
+    import torch
+    if layout == "head_major":
+        return torch.full((B, Hh, n, D), 7.0, dtype=dtype, device="cuda").transpose(1, 2), None
+    if layout == "padded":                             # rows of a wider buffer, which keeps what stands beside them
+        buf = torch.full((B, n, Hh + 1, D + 8), 7.0, dtype=dtype, device="cuda")
+        return buf[:, :, :Hh, :D], buf
+    return torch.empty((B, n, Hh, D), dtype=dtype, device="cuda"), None
+
+
+# Lengths that no number of equally long segments fits (1281, 1537: one token in the last chunk), from 4 to 16 segments;
+# the incoming states pass through the output's rows, whatever its strides are
+@pytest.mark.parametrize("n,Hh", [(1281, 12), (1537, 90), (2116, 24), (3844, 3)])
+@pytest.mark.parametrize("layout,dtype", [("dense", "bf16"), ("head_major", "bf16"), ("padded", "bf16"), ("padded", "f32")])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_segment_forms(lasad, oracle, n, Hh, layout, dtype, mode):
+    import torch
+    rng = np.random.default_rng(n + mode)
+    form = ["own", "tied", "layer"][(mode + n) % 3]
+    q, k, v, z = (wl.store_round(rng.standard_normal((1, n, Hh, D), dtype=np.float32) * np.float32(s), "bf16")
+                  for s in (1.0 if form == "layer" else 0.125, 0.125, 0.125, 1.0))
+    lam = wl.store_round(oracle.sigmoid(z + 2.0).astype(np.float32), "bf16")
+    s0 = (rng.standard_normal((1, Hh, D, D)) * 0.3).astype(np.float32)
+    H, start = (30 + n + W - 1) // W, 30
+    dev = lambda x: lasad.to_device(x, "bf16")
+    def call(out):                                     # the final state replaces the incoming one
+        state = torch.from_numpy(s0).cuda()
+        kw = dict(start_pos=start, boundary_mode=mode, q_scale=0.7, state_in=state, state_out=state, out=out)
+        if form == "layer":
+            lasad.lasad_forward_layer(dev(q), dev(z), dev(v), H, W, norm_eps=1e-5, **kw)
+        else:
+            lasad.lasad_forward_gated(dev(q), dev(lam), dev(v), H, W, k=dev(k) if form == "own" else None, **kw)
+        return out, state
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    view, buf = _out_view(layout, 1, n, Hh, t)
+    out, state = call(view)
+    out32, state32 = call(torch.empty((1, n, Hh, D), dtype=torch.float32, device="cuda"))
+    assert torch.equal(out, out32.to(t)) and torch.equal(state, state32)
+    pairs = sample_pairs(1, Hh, 3, n)
+    at = lambda x: gather_pairs(x, pairs)
+    rk = dict(start_pos=start, mode=mode, q_scale=0.7, s0=np.stack([s0[b, h] for b, h in pairs])[None].astype(np.float64), want_state=True)
+    if form == "layer":
+        ref, s_ref = oracle.gated_layer(at(q), at(z), at(v), W, eps=1e-5, **rk)
+    else:
+        ref, s_ref = oracle.gated_recurrent(at(q), at(lam), at(v), W, k=at(k) if form == "own" else None, **rk)
+    assert rel_err(at(out32.cpu().numpy()), ref) <= TOL["bf16"]
+    got = state.cpu().numpy()
+    assert rel_err(np.stack([got[b, h] for b, h in pairs])[None], s_ref) <= TOL["bf16"]
+    if buf is not None:
+        assert (buf[:, :, Hh] == 7).all() and (buf[..., D:] == 7).all()
+
+
 @pytest.mark.parametrize("n,B,Hh", [(97, 1, 3), (97, 20, 13), (1023, 1, 2)], ids=["few", "many", "segments"])
 @pytest.mark.parametrize("row", [0, 1, -1])
 def test_nan_gate_at_a_row_end(lasad, oracle, n, B, Hh, row):
