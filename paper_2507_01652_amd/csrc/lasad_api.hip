@@ -499,7 +499,8 @@ int lasad_backward_chunked_carried(const void *q, const void *k, const void *v, 
 size_t lasad_backward_gated_workspace_bytes(int B, int n_heads, int n_tokens, int d)
 {
     if (B < 1 || n_heads < 1 || n_tokens < 1 || d < 1) return 0;
-    return lasad::backward_gated_workspace_bytes((int64_t)B * n_heads, n_tokens, d);
+    return lasad::backward_gated_workspace_bytes((int64_t)B * n_heads, n_tokens, d) +
+           lasad::backward_gated_bounds_bytes((int64_t)B * n_heads, n_tokens, d);
 }
 
 size_t lasad_backward_gated_carried_workspace_bytes(int B, int n_heads, int n_tokens, int d)
@@ -564,8 +565,11 @@ static int backward_gated_impl(const void *q, const void *lam, const void *k, co
         }
         return LASAD_OK;
     }
-    const size_t need = carried ? lasad_backward_gated_carried_workspace_bytes(B, n_heads, n_tokens, d)
-                                : lasad_backward_gated_workspace_bytes(B, n_heads, n_tokens, d);
+    // the states at segment bounds come last and may be left out: their part is 0 for some lengths, and a workspace that
+    // was sized for such a longer call serves a shorter one
+    const int64_t n_seq = (int64_t)B * n_heads;
+    const size_t need = lasad::backward_gated_workspace_bytes(n_seq, n_tokens, d) +
+                        (carried ? lasad::backward_gated_carried_extra_bytes(n_seq, d) : 0);
     if (!workspace || workspace_bytes < need)
         return fail(LASAD_ERR_WORKSPACE, "workspace of %zu bytes given, %zu needed", workspace ? workspace_bytes : (size_t)0, need);
 
@@ -578,6 +582,8 @@ static int backward_gated_impl(const void *q, const void *lam, const void *k, co
     a.start_pos = start_pos; a.n_tokens = n_tokens;
     a.mode = boundary_mode; a.q_scale = q_scale;
     a.workspace = workspace;
+    const bool bounds_fit = workspace_bytes - need >= lasad::backward_gated_bounds_bytes(n_seq, n_tokens, d);
+    a.bounds = bounds_fit ? (float *)((char *)workspace + need) : nullptr;
     a.fused_act = 0; a.d_o_lo = nullptr;
     a.state_in = state_in; a.d_state_out = d_state_out; a.d_state_in = d_state_in;
     hipError_t e = lasad::launch_backward_gated(a, (hipStream_t)hip_stream);

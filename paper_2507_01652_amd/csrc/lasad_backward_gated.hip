@@ -437,7 +437,7 @@ void finish_segments(int64_t n_seq, int n, int *n_seg, int *seg_blocks)
     *n_seg = (nblk + *seg_blocks - 1) / *seg_blocks;
 }
 
-// Floats of one pass's bound states and flags; 0: not kept.  The reversed pass walks chunks of 32 tokens from the last
+// Floats of one pass's bound states and flags; 0: none.  The reversed pass walks chunks of 32 tokens from the last
 // token on, so its chunks end on the segment bounds only where the length is a multiple of 32; other lengths add up r.
 size_t bound_states_floats(int64_t n_seq, int n, int d)
 {
@@ -456,9 +456,13 @@ size_t backward_gated_carried_extra_bytes(int64_t n_seq, int d)
 
 size_t backward_gated_workspace_bytes(int64_t n_seq, int n_tokens, int d)
 {
-    // dq and dk in fp32, then the finishing kernel's segment totals (at most 8 segments per sequence) and bound states
-    return 2 * (size_t)n_seq * n_tokens * d * sizeof(float) + (size_t)n_seq * 8 * d * sizeof(float) +
-           2 * bound_states_floats(n_seq, n_tokens, d) * sizeof(float);
+    // dq and dk in fp32, then the finishing kernel's segment totals (at most 8 segments per sequence)
+    return 2 * (size_t)n_seq * n_tokens * d * sizeof(float) + (size_t)n_seq * 8 * d * sizeof(float);
+}
+
+size_t backward_gated_bounds_bytes(int64_t n_seq, int n_tokens, int d)
+{
+    return 2 * bound_states_floats(n_seq, n_tokens, d) * sizeof(float);
 }
 
 hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
@@ -487,9 +491,8 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
     // step: the shifted decay of step 0 is neutral); the dv pass ends with g_1 / q_scale
     const bool carried = b.state_in || b.d_state_out || b.d_state_in;
     const size_t mat = (size_t)n_seq * b.d * b.d;
-    const size_t bound_floats = bound_states_floats(n_seq, n, b.d);
-    float *bounds = dk32 + (size_t)n_seq * n * b.d + (size_t)n_seq * 8 * b.d;  // after the gradients and the segment totals
-    float *cw = bounds + 2 * bound_floats;
+    const size_t bound_floats = b.bounds ? bound_states_floats(n_seq, n, b.d) : 0;
+    float *cw = dk32 + (size_t)n_seq * n * b.d + (size_t)n_seq * 8 * b.d;      // after the gradients and the segment totals
     float *hS = cw, *sn = cw + mat, *g1 = cw + 2 * mat, *sink_buf = cw + 3 * mat;
     const float *sink = (carried && b.d_state_out) ? sink_buf : nullptr;
     if (carried && b.d_state_out) {
@@ -563,10 +566,10 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
         for (int y = 0; y < 3; ++y) { p[y].state_in = st_in[y]; p[y].state_out = st_out[y]; }
         if (bound_floats) {
             for (int y = 0; y < 3; y += 2) {
-                p[y].seg_states = y ? bounds + bound_floats : bounds;
+                p[y].seg_states = y ? b.bounds + bound_floats : b.bounds;
                 p[y].n_segments = n_seg; p[y].seg_chunks = seg_blocks * (kFinBlock / 32);
             }
-            bs.s = bounds; bs.g = bounds + bound_floats;
+            bs.s = b.bounds; bs.g = b.bounds + bound_floats;
             bs.flags = (int64_t)n_seq * (n_seg - 1) * kD * kD;
         }
         e = launch_backward_gated_passes(p, w.roles, b.k == nullptr, s);

@@ -222,6 +222,7 @@ hipError_t launch_backward_layer(const LayerBackwardArgs &a, bool use_mfma, hipS
     g.start_pos = a.start_pos; g.n_tokens = n;
     g.mode = a.mode; g.q_scale = a.q_scale;
     g.workspace = ws + r.core;
+    g.bounds = o32;                                                     // (free by now; 32 KB a bound, 64 KB and more of o a segment)
     g.fused_act = 1; g.d_o_lo = d_o_lo;
     e = launch_backward_gated(g, s);
     if (e != hipSuccess) return e;

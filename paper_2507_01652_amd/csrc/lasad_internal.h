@@ -141,6 +141,8 @@ struct GatedBackwardArgs {
     int mode;
     float q_scale;
     void *workspace;
+    float *bounds;                       // backward_gated_bounds_bytes of scratch for the states at segment bounds; NULL: sums
+                                         //   of dq and dk take their place (slower, and a third of the accuracy of dlam)
     const void *d_o_lo;                  // fused_act with bf16 inputs: low-order bf16 part of d_o (d_o is hi + lo), else NULL
     int fused_act;                       // 1: q and lam hold Algorithm 1's pre-activation query and gate logits
                                          // (tied key only); dq and dlam are then the gradients of THOSE tensors
@@ -172,7 +174,8 @@ struct LayerBackwardArgs {
 };
 hipError_t launch_backward_layer(const LayerBackwardArgs &a, bool use_mfma, hipStream_t s);
 size_t backward_layer_workspace_bytes(int B, int Hh, int n_tokens, int d, int io_dtype, const lasad_layout_t &in);
-size_t backward_gated_workspace_bytes(int64_t n_seq, int n_tokens, int d);
+size_t backward_gated_workspace_bytes(int64_t n_seq, int n_tokens, int d);       // without the next two
+size_t backward_gated_bounds_bytes(int64_t n_seq, int n_tokens, int d);
 // extra workspace of lasad_backward_gated with carried states
 size_t backward_gated_carried_extra_bytes(int64_t n_seq, int d);
 

@@ -101,3 +101,32 @@ def test_loader_groups(lasad, oracle, n, Hh):
     got = lasad.lasad_backward_gated(dev(q), dev(lam), dev(v), dev(g), (n + W - 1) // W, W, grad_dtype=torch.float32)
     for i, (a, r) in enumerate(zip(got, oracle.gated_backward(q, lam, v, g, W))):
         assert rel_err(a.cpu().numpy(), r) <= TOL["bf16"], i
+
+
+@pytest.mark.parametrize("carried", [False, True])
+@pytest.mark.parametrize("n,longer", [(1024, 1040), (1024, 1025), (544, 545)])
+def test_workspace_of_a_longer_call(lasad, oracle, n, longer, carried):
+    """The states at segment bounds need scratch of their own, and lengths that keep none ask for less: a workspace sized
+    for such a longer call serves the shorter one; a byte less than it cannot do without is refused."""
+    import torch
+    rng = np.random.default_rng(n)
+    Hh = 5
+    q, v, g = (wl.store_round(rng.standard_normal((1, n, Hh, D), dtype=np.float32) / np.float32(8), "bf16") for _ in range(3))
+    lam = wl.gate_inputs((1, n, Hh, D), "bf16", n)
+    size, call, ref = lasad.lasad_backward_gated_workspace_bytes, lasad.lasad_backward_gated, oracle.gated_backward
+    if carried:
+        size, call = lasad.lasad_backward_gated_carried_workspace_bytes, lasad.lasad_backward_gated_carried
+    given = size(1, Hh, longer, D)
+    assert given < size(1, Hh, n, D)
+    dev = lambda x: lasad.to_device(x, "bf16")
+    ws = torch.empty(given, dtype=torch.uint8, device="cuda")
+    args = dev(q), dev(lam), dev(v), dev(g), (n + W - 1) // W, W
+    got = call(*args, grad_dtype=torch.float32, workspace=ws)
+    for i, (a, r) in enumerate(zip(got, ref(q, lam, v, g, W))):
+        assert rel_err(a.cpu().numpy(), r) <= TOL["bf16"], i
+    least = given - (longer - n) * Hh * D * 8
+    call(*args, workspace=ws[:least])
+    with pytest.raises(lasad.LasadError):
+        call(*args, workspace=ws[:least - 1])
+    layer = [lasad.lasad_backward_layer_workspace_bytes(torch.empty((1, m, Hh, D), dtype=torch.bfloat16)) for m in (n, longer)]
+    assert layer[0] < layer[1]
