@@ -30,17 +30,18 @@ constexpr int64_t kMaxStride = 1 << 25;        // 32 rows of it, two bytes an el
 enum { DQ = 0, DV = 1, DK = 2 };
 
 // A token's row of a chunk slot (bf16 elements): Z~ hi, lo, then COL: x, y, the low-order part of one of them;
-// ROW: Q~ hi, lo, V, low-order part of V.  328 and 392 elements are 36 and 4 words (mod 64).
+// ROW: Q~ hi, lo, V, low-order part of V.
 template <int PASS>
 struct Slot {
     static constexpr bool COL = PASS != DV;
-    static constexpr int ROW = (COL ? 5 : 6) * D + 8;
+    static constexpr int ROW = (COL ? 5 : 6) * D + 16;
     static constexpr int Zh = 0, Zl = D;
     static constexpr int X = 2 * D;                            // COL
     static constexpr int Qh = 2 * D, Ql = 3 * D;               // ROW
     static constexpr int Y = COL ? 3 * D : 4 * D;              // y; ROW: V
     static constexpr int Lo = COL ? 4 * D : 5 * D;             // low-order part of d_o: x (dq), y (dk), V (dv)
-    static constexpr int kHalfs = C * ROW;
+    using Map = SlotMap<ROW>;
+    static constexpr int kHalfs = Map::kHalfs;
     // two slots, the output tiles, COL: the tiles of A
     static constexpr int kBytes = 2 * kHalfs * 2 + 2 * C * OS * 4 + (COL ? 2 * C * OS * 4 : 0);
 };
@@ -156,6 +157,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
         RowBoundaries bounds;
         bounds.init(a.start_pos + grp * C, a.grid_w, a.mode, NG * C);
         int left = n - grp * C;                    // tokens from the next chunk to be prepared on
+        const int put = SL::Map::at(2 * pr, pcol), put_piece = SL::Map::at(st >> 3, (st & 7) * 8);
         const int orow = st >> 3, ocol = (st & 7) * 8;
         const int64_t o_lane = orow * a.out.stride_n + ocol;
         int64_t o_chunk = (int64_t)b * a.out.stride_b + (int64_t)h * a.out.stride_h + (NG == 2 && grp == 0 ? C : 0) * a.out.stride_n;
@@ -184,7 +186,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
 
         // the plain rows into slot p (a row past the end is a query that nobody stores, and zero as y)
         auto put_rows = [&](int p) {
-            uint16_t *const piece = slots + p * SL::kHalfs + (st >> 3) * SL::ROW + (st & 7) * 8;
+            uint16_t *const piece = slots + p * SL::kHalfs + put_piece;
             if (COL) *(u32x4 *)&piece[SL::X] = px;
             *(u32x4 *)&piece[SL::Y] = row_live ? py : u32x4{0u, 0u, 0u, 0u};
             if (LO) *(u32x4 *)&piece[SL::Lo] = row_live ? plo : u32x4{0u, 0u, 0u, 0u};
@@ -278,7 +280,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
                                                   : make_float4(tot[0], tot[1], tot[2], tot[3]);
             const bool any = __any(trip);
             if (lane == 0) sTrip[p][lw] = any ? 1 : 0;
-            uint16_t *rows = slots + p * SL::kHalfs + 2 * pr * SL::ROW + pcol;
+            uint16_t *rows = slots + p * SL::kHalfs + put;
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
                 float zt[4], dec[4];               // Z~ and A of this token

@@ -165,6 +165,7 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
         RowBoundaries bounds;
         bounds.init(a.start_pos + seg_t0 + grp * C, a.grid_w, a.mode, NG * C);
         int left = n - grp * C;                    // tokens from the next chunk to be prepared on
+        const int put = SlotMap<kRow>::at(2 * pr, pcol), put_v = SlotMap<kRow>::at(st >> 3, (st & 7) * 8) + kColV;
         // the output tile of a finished chunk: thread = token st / 8, channels 8 (st & 7) .., times q_scale (NORM: and
         // the norm's factors: (q_scale o) / sqrt(mean((q_scale o)^2) + eps))
         const int orow = st >> 3, ocol = (st & 7) * 8;
@@ -276,7 +277,7 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
         };
         // the chunk's operands into slot p; leaves the range flag for the barrier that ends this period
         auto phase_b = [&](int p) {
-            *(uint4 *)&slots[p * kSlot + (st >> 3) * kRow + kColV + (st & 7) * 8] =
+            *(uint4 *)&slots[p * kSlot + put_v] =
                 make_uint4(v_live ? pv.x : 0u, v_live ? pv.y : 0u, v_live ? pv.z : 0u, v_live ? pv.w : 0u);
             bool trip;
             if (FUSED) trip = !(fmaxf(fmaxf(tot[0], tot[1]), fmaxf(tot[2], tot[3])) <= kMaxInvDecay);
@@ -287,7 +288,7 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
                                                   : make_float4(tot[0], tot[1], tot[2], tot[3]);
             const bool any = __any(trip);
             if (lane == 0) sTrip[p][lw] = any ? 1 : 0;
-            uint16_t *rows = slots + p * kSlot + 2 * pr * kRow + pcol;
+            uint16_t *rows = slots + p * kSlot + put;
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
                 float q[4], kt[4], qt[4];
@@ -454,12 +455,13 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
 // The decays to the END of a chunk are running products from its last token backwards (<= 1: nothing to divide, no range
 // to leave), so the tokens are dealt to the lanes in reverse.  One workgroup of four wavefronts: each prepares 16 key
 // channels of the next chunk and updates 16 value channels of the state.
-constexpr int kStateRow = 3 * D + 8;           // K^ hi, lo, V; 100 words (36 mod 64)
+constexpr int kStateRow = 3 * D + 16;          // K^ hi, lo, V
 template <int OWNKEY, int FUSED>
 __global__ void __launch_bounds__(256)
 gated_segment_state_kernel(ForwardArgs a, SegPlan plan)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[2 * C * kStateRow];
+    using Map = SlotMap<kStateRow>;
+    __shared__ __attribute__((aligned(16))) uint16_t smem[2 * Map::kHalfs];
     __shared__ __attribute__((aligned(16))) float sTot[2][D];
     const int bh = blockIdx.x / (plan.n_seg - 1), seg = blockIdx.x - bh * (plan.n_seg - 1);
     const int b = bh / a.Hh, h = bh - b * a.Hh;
@@ -486,8 +488,9 @@ gated_segment_state_kernel(ForwardArgs a, SegPlan plan)
     RowBoundaries bounds;
     bounds.init(a.start_pos + seg_t0, a.grid_w, a.mode, C);
 
+    const int put = Map::at(C - 1 - 2 * pr, pcol), put_v = Map::at(st >> 3, (st & 7) * 8) + 2 * D;
     auto prepare = [&](int chunk) {                // chunk -> its slot
-        uint16_t *slot = smem + (chunk & 1) * C * kStateRow;
+        uint16_t *slot = smem + (chunk & 1) * Map::kHalfs;
         const uint32_t bmask = bounds.mask();
         bounds.advance();
         float x[2][4], key[2][4];
@@ -496,7 +499,7 @@ gated_segment_state_kernel(ForwardArgs a, SegPlan plan)
             unpack4(rl[it], x[it]);
             if (OWNKEY) unpack4(rk[it], key[it]);
         }
-        *(uint4 *)&slot[(st >> 3) * kStateRow + 2 * D + (st & 7) * 8] = rv;
+        *(uint4 *)&slot[put_v] = rv;
 #pragma unroll
         for (int it = 0; it < 2; ++it) {           // (the registers are free, see the walk's loaders)
             asm volatile("" : "+v"(x[it][0]), "+v"(x[it][1]), "+v"(x[it][2]), "+v"(x[it][3]));
@@ -520,7 +523,7 @@ gated_segment_state_kernel(ForwardArgs a, SegPlan plan)
         for (int e = 0; e < 4; ++e) tot[e] = x[0][e] * x[1][e];
         row_scan_mul4(tot, exc);
         if (pr == 15) *(float4 *)&sTot[chunk & 1][pcol] = make_float4(tot[0], tot[1], tot[2], tot[3]);
-        uint16_t *p = &slot[(C - 1 - 2 * pr) * kStateRow + pcol];
+        uint16_t *p = &slot[put];
         float kt[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) kt[e] = key[0][e] * exc[e];
@@ -542,24 +545,15 @@ gated_segment_state_kernel(ForwardArgs a, SegPlan plan)
     __syncthreads();
     for (int chunk = 0; chunk < n_chunks; ++chunk) {
         prepare(chunk + 1);                        // (past the end: into a slot that nobody reads)
-        const uint16_t *slot = smem + (chunk & 1) * C * kStateRow;
-        const uint16_t *tok = slot + (4 * g + (l16 >> 2)) * kStateRow + 2 * D + 16 * wave + 4 * (lane & 3);
-        const uint16_t *stp = slot + (4 * g + (l16 >> 2)) * kStateRow + 8 * (lane & 3);
-        Frag fv, fk;
-        fv.h[0] = tr_read(tok);
-        fv.h[1] = tr_read(tok + 16 * kStateRow);
+        const SlotPtr<kStateRow> sp(smem + (chunk & 1) * Map::kHalfs, lane);
+        const Frag fv = sp.tokens(2 * D + 16 * wave);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const float4 t4 = *(const float4 *)&sTot[chunk & 1][state_channel(t, g)];
             accS[t][0] *= t4.x; accS[t][1] *= t4.y; accS[t][2] *= t4.z; accS[t][3] *= t4.w;
             run[t][0] *= t4.x; run[t][1] *= t4.y; run[t][2] *= t4.z; run[t][3] *= t4.w;
 #pragma unroll
-            for (int part = 0; part < 2; ++part) {
-                const uint16_t *q = stp + part * D + 32 * (t >> 1) + 4 * (t & 1);
-                fk.h[0] = tr_read(q);
-                fk.h[1] = tr_read(q + 16 * kStateRow);
-                accS[t] = mfma16(fk, fv, accS[t]);
-            }
+            for (int part = 0; part < 2; ++part) accS[t] = mfma16(sp.state_rows(part * D, t), fv, accS[t]);
         }
         __syncthreads();
     }

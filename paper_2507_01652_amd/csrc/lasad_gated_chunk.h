@@ -32,11 +32,29 @@ namespace gchunk {
 constexpr int C = 32;                  // tokens per chunk
 constexpr int D = 64;                  // head dim
 // One token's row of a chunk slot: its prepared operands side by side (bf16 elements), so that everything a lane
-// reads or writes of a row lies within the immediate offsets of the LDS instructions.  A row is 164 words: rows read
-// 16 bytes at a time fall on different banks (164 = 36 mod 64).
-constexpr int kRow = 5 * D + 8;
+// reads or writes of a row lies within the immediate offsets of the LDS instructions.
+//
+// Where a row stands.  Sixteen lanes are served together: of a 16-byte read lanes 0-3, 12-15 (rows) and 20-27 (rows 4-11,
+// the next 16 bytes), of an 8-byte write sixteen rows two apart.  Conflict-free are both with rows of 16 mod 32 elements
+// (an even number of 16-byte pieces, twice an odd one), rows 8-15 (mod 16) half a bank turn on and with their 16-byte
+// pieces swapped in pairs, and rows from 16 on two pieces on.  Cycles an instruction (eight wavefronts, one compute
+// unit): 16-byte reads 4.4, transposing reads 2.7 and 4.2, 8-byte writes 8.2; plain rows of 164 words 8.1, 4.2, 6.1 and
+// 16.1.  With those the conflicts were 960 of a lone workgroup's 1780 LDS cycles a chunk of 2500, now 290 of 1110.
+// 24 sequences of 24 x 24 tokens, us: tied key 23.9 -> 21.3, own key 25.4 -> 22.1, backward 39.2 -> 34.6.
+constexpr int kRow = 5 * D + 16;
 constexpr int kColKh = 0, kColKl = D, kColQh = 2 * D, kColQl = 3 * D, kColV = 4 * D;
-constexpr int kSlot = C * kRow;
+template <int ROW>
+struct SlotMap {
+    static_assert(ROW % 32 == 16, "see above");
+    static constexpr int kHalf = 16 * ROW + 144;       // from a row to the one 16 on
+    static constexpr int kHalfs = 32 * ROW + 208;      // the whole slot
+    static __device__ __forceinline__ int row(int r) { return (r & 15) * ROW + 64 * ((r >> 3) & 1) + kHalf * (r >> 4); }
+    // 16-byte piece of row r, from the row's start on
+    static __device__ __forceinline__ int piece(int r, int i) { return 8 * (i ^ ((r >> 3) & 1)); }
+    // four elements from column c on (a multiple of 4) of row r, from the slot's start on
+    static __device__ __forceinline__ int at(int r, int c) { return row(r) + piece(r, c >> 3) + (c & 4); }
+};
+constexpr int kSlot = SlotMap<kRow>::kHalfs;
 constexpr int OS = 68;                 // row stride (floats) of the output tile: 272 B
 constexpr float kMaxInvDecay = 1.2676506e30f;      // 2^100: largest 1 / A of a chunk (see lasad_forward_gated_chunk.hip)
 
@@ -135,19 +153,21 @@ __device__ __forceinline__ float exp_neg(float x) { return __builtin_amdgcn_exp2
 // A lane's places in a slot for its operand reads; everything else is immediate offsets.
 template <int ROW = kRow>
 struct SlotPtr {
+    using Map = SlotMap<ROW>;
     const uint16_t *row, *tok, *st;
     __device__ __forceinline__ SlotPtr(const uint16_t *slot, int lane)
     {
         const int l16 = lane & 15, g = lane >> 4;
-        row = slot + l16 * ROW + 8 * g;
-        tok = slot + (4 * g + (l16 >> 2)) * ROW + 4 * (lane & 3);
-        st = slot + (4 * g + (l16 >> 2)) * ROW + 8 * (lane & 3);
+        const int r = 4 * g + (l16 >> 2);
+        row = slot + Map::at(l16, 8 * g);
+        tok = slot + Map::at(r, 4 * (lane & 3));
+        st = slot + Map::at(r, 8 * (lane & 3));
     }
-    // rows row0 + l16, elements col + 32 s + 8 g ..
+    // rows row0 + l16 (row0: 0 or 16), elements col + 32 s + 8 g ..
     __device__ __forceinline__ Frag rows(int row0, int col, int s) const
     {
         Frag f;
-        f.u = *(const uint4 *)(row + row0 * ROW + col + 32 * s);
+        f.u = *(const uint4 *)(row + (row0 ? Map::kHalf : 0) + col + 32 * s);
         return f;
     }
     // the 32 tokens for 16 columns from col in order / for the rows of state tile t
@@ -157,7 +177,7 @@ struct SlotPtr {
     {
         Frag f;
         f.h[0] = tr_read(p);
-        f.h[1] = tr_read(p + 16 * ROW);
+        f.h[1] = tr_read(p + Map::kHalf);
         return f;
     }
 };
