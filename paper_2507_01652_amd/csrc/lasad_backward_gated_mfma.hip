@@ -154,6 +154,13 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
         using Stage = PassStage<PASS, OWNKEY, LO, NG>;
         Stage sg;
         sg.init(a, (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h, first, n - first);
+        typename Stage::Regs r0, r1;               // (one loader group: two chunks of loads in flight)
+        sg.fetch(r0, pr, pcol, st);                // ahead of everything that does not need it
+        if (NG == 1) {
+            sg.next(a.in.stride_n);
+            sg.fetch(r1, pr, pcol, st);
+        }
+        __builtin_amdgcn_sched_barrier(0);
         RowBoundaries bounds;
         bounds.init(a.start_pos + grp * C, a.grid_w, a.mode, NG * C);
         int left = n - grp * C;                    // tokens from the next chunk to be prepared on
@@ -313,14 +320,10 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
         if constexpr (NG == 1) {
             // Two chunks of loads in flight, in two sets of registers.  (A pair of chunks is always done as a whole, range
             // flags tested at its end: with a way out between its halves the compiler waits for both sets at the loop's top.)
-            typename Stage::Regs r0, r1;
             auto prepare = [&](typename Stage::Regs &f, int p, int done, bool walk_start) {
                 phase_a(f, p, done, walk_start);
                 phase_b(p);
             };
-            sg.fetch(r0, pr, pcol, st);
-            sg.next(a.in.stride_n);
-            sg.fetch(r1, pr, pcol, st);
             prepare(r0, 0, -1, true);
             __syncthreads();
             for (int chunk = 0; fine && chunk < n_chunks; chunk += 2) {
@@ -334,16 +337,14 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
             }
         } else {
             // the groups take the chunks in turn, a period for each phase
-            typename Stage::Regs r;
-            sg.fetch(r, pr, pcol, st);
-            phase_a(r, 0, -1, grp == 0);
-            if (grp == 0) phase_b(0);
-            __syncthreads();
             int4 f;                                // a chunk's range flags, read at the start of its period and tested at the end
             auto end_period = [&]() {
                 fine = (f.x | f.y | f.z | f.w) == 0;
                 __syncthreads();
             };
+            phase_a(r0, 0, -1, grp == 0);
+            if (grp == 0) phase_b(0);
+            __syncthreads();
             if (grp == 1) {                        // period 0
                 f = *(const int4 *)sTrip[0];
                 phase_b(1);
@@ -351,7 +352,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
             }
             for (int chunk = grp; fine && chunk < n_chunks; chunk += 2) {
                 f = *(const int4 *)sTrip[chunk & 1];
-                phase_a(r, 0, chunk - 1, false);
+                phase_a(r0, 0, chunk - 1, false);
                 end_period();
                 if (!fine || chunk + 1 == n_chunks) break;
                 f = *(const int4 *)sTrip[(chunk + 1) & 1];
