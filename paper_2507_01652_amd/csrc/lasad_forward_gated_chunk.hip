@@ -608,20 +608,27 @@ gated_segment_fold_kernel(ForwardArgs a, SegPlan plan)
     }
 }
 
-// Few, long sequences are cut into segments that fill the chip (512 workgroups, two per compute unit).  The state pass
-// and the fold have to pay: at least 8 chunks (256 tokens) a segment and three segments; where three segments would put
-// two workgroups on a compute unit (more than 85 sequences), four.  The chunks are dealt out evenly, so every length
-// finds a plan.  Measured (tied key, us, one workgroup per sequence -> segments): 12 x 4096 tokens 141 -> 29 (16
-// segments), 12 x 3844 133 -> 30 (15), 24 x 2116 76 -> 30 (8), 48 x 1849 66 -> 39 (7), 96 x 4096 144 -> 91 (5), 32 x
-// 1024 37.8 -> 26.8 (4), 31.8 (3), 40.5 (2); 128 x 2304 83 -> 74 (4), 96 x 1444 53 -> 43 (5), 96 x 1024 38 -> 38 (4);
-// not taken: 96 x 900 34.9 -> 39.6 (3), 192 x 4096 145 -> 196 (2), 181 (3).
+// Few, long sequences are cut into segments of at least 8 chunks, the chunks dealt out evenly: one workgroup per compute
+// unit (256 in all), or two where that at least doubles the number of segments (a chunk then takes 1.6 times as long).
+// State pass and fold have to pay: 16 chunks off the walk's length, 24 with more than 128 workgroups, 30 with two per unit.
+// Measured (us, one workgroup per sequence -> segments, tied key unless noted): 12 x 4096 tokens 120 -> 30 (16 segments),
+// 12 x 3844 113 -> 30 (15), 24 x 2116 65 -> 31 (8), 40 x 2116 66 -> 37 (6; 8 of them: 41), 60 x 1024 35 -> 29 (4), 60 x 4096
+// 122 -> 62 (8; 4: 72), 96 x 4096 123 -> 95 (5), 96 x 1444 49 -> 46 (5), 110 x 2116 70 -> 64 (4), fused layer 12 x 768 29 -> 27
+// (3); not taken: 60 x 768 27 -> 28 (3), 80 x 1024 33 -> 34 (3), own key 34 -> 38, 128 x 1024 37 -> 42 (4), 128 x 1444
+// 50 -> 52 (4), 192 x 2116 74 -> 91 (5).
 SegPlan segment_plan(int64_t n_seq, int n_tokens)
 {
     const int n_chunks = (n_tokens + C - 1) / C;
-    int g = (int)(512 / n_seq);
-    if (g > kMaxSegments) g = kMaxSegments;
-    if (g > n_chunks / 8) g = n_chunks / 8;
-    if (g < (n_seq > 85 ? 4 : 3)) return SegPlan{1, n_chunks, 0};
+    auto segments = [&](int n_wg) {
+        const int most = n_chunks / 8 < kMaxSegments ? n_chunks / 8 : kMaxSegments;
+        return n_wg / n_seq < most ? (int)(n_wg / n_seq) : most;
+    };
+    const int g1 = segments(256), g2 = segments(512);
+    const bool two = g2 >= 2 * g1;
+    const int g = two ? g2 : g1;
+    if (g < 3) return SegPlan{1, n_chunks, 0};
+    const int saved = two ? n_chunks - 8 * n_chunks / (5 * g) : n_chunks - n_chunks / g;
+    if (saved < (two ? 30 : n_seq * g > 128 ? 24 : 16)) return SegPlan{1, n_chunks, 0};
     static_assert(7 * C + 1 >= kRowStateTokens, "the rows of a segment of 8 chunks hold its incoming state");
     return SegPlan{g, n_chunks / g, n_chunks % g};
 }

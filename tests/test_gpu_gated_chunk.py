@@ -67,7 +67,7 @@ def test_range_exit(lasad, oracle, spike, B, Hh, form):
     _check(lasad, oracle, 97, B, Hh, form, start=0, seed=spike, spike=spike)
 
 
-@pytest.mark.parametrize("n,B,Hh", [(768, 2, 3), (800, 1, 5), (1023, 1, 2), (1300, 4, 20)])
+@pytest.mark.parametrize("n,B,Hh", [(768, 2, 3), (800, 1, 5), (929, 3, 4), (1023, 1, 2), (1300, 4, 20)])
 @pytest.mark.parametrize("form", ["own", "tied", "layer"])
 @pytest.mark.parametrize("spike", [None, 5, 400])
 def test_segments(lasad, oracle, n, B, Hh, form, spike):
