@@ -37,7 +37,7 @@
  *   LASAD_SPLIT=1|2        twelve-wave kernel: whole sequences | two workgroups per sequence
  *   LASAD_WS_MULTI=8|12    merged backward launch: eight- or twelve-wave workgroups
  *   LASAD_GATED_BWD=walk   vector-decay backward: fp32 token-serial walks instead of the chunked passes
- *   LASAD_SCAN=0           fp32 head dim 64: the generic recurrence kernel instead of the scan kernel
+ *   LASAD_SCAN=0           fp32 head dim 64: the generic recurrence kernel instead of the chunked (scalar decay) and scan kernels
  *   LASAD_FORCE_GENERIC=1  bf16 head dim 64: the fp32 kernels instead of the matrix-core kernels
  */
 #ifndef LASAD_H

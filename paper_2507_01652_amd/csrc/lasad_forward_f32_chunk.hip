@@ -16,8 +16,8 @@
 //
 // Bound by the chain from chunk to chunk on the compute units that have a sequence: 52 matrix instructions of 32 cycles a
 // chunk and SIMD (0.8 us) and the LDS reads, decay and mask between them; 1.7 us a chunk in all.  96 sequences of 256
-// tokens: 27 us a call, 64 with the token-serial kernel (lasad_scan.h), which is left to the vector decay and to
-// bf16 storage; distance from fp64 results the same.
+// tokens: 27 us a call, 64 with the token-serial kernel (lasad_scan.h), which is left to the vector decay, to bf16
+// storage and to up to four tokens of few sequences; distance from fp64 results the same.
 #include "lasad_gated_chunk.h"
 
 namespace lasad {

@@ -4,7 +4,8 @@
 // kernel does not take, and for the vector (data-dependent) decay of Section 3.4.
 // One workgroup walks one (batch, head) sequence with the recurrence of
 // Section 3.4 (see lasad_recurrence.h).  Head dim 64 goes to the faster scan kernel
-// (lasad_forward_scan.hip) unless the environment sets LASAD_SCAN=0.
+// (lasad_forward_scan.hip) or, scalar decay in fp32, to the chunked one
+// (lasad_forward_f32_chunk.hip), unless the environment sets LASAD_SCAN=0.
 #include <stdlib.h>
 
 #include "lasad_recurrence.h"
@@ -46,9 +47,11 @@ hipError_t launch_forward_generic(const ForwardArgs &a, hipStream_t s)
     // the fused activations and the norm exist in the scan kernel only: such calls go there whatever the switch says
     const bool fused = a.fused_act || a.norm;
     if (fused && a.d != 64) return hipErrorInvalidValue;
-    // scalar decay in fp32: in chunks on the fp32 matrix instruction, whatever gamma and the sizes are (16 tokens take it
-    // what the token-serial kernel takes for 6 or 7: 96 sequences of 256 tokens 27 us against 64)
-    if (a.d == 64 && scan && !a.lam && a.io_dtype == LASAD_F32 && a.n_tokens > 0) return launch_forward_f32_chunk(a, s);
+    // scalar decay in fp32: in chunks on the fp32 matrix instruction, whatever gamma is (96 sequences of 256 tokens 27 us,
+    // 64 with the token-serial kernel).  Up to four tokens of few sequences stay with the latter, two workgroups a
+    // sequence: 12 x 1 4.0 us against 4.5, 96 x 4 4.5 against 4.6; but 96 x 5 4.7 against 4.6, 192 x 1 4.7 against 4.6
+    const bool few = a.n_tokens <= 4 && (int64_t)a.B * a.Hh <= 128;
+    if (a.d == 64 && scan && !a.lam && a.io_dtype == LASAD_F32 && !few && a.n_tokens > 0) return launch_forward_f32_chunk(a, s);
     if (a.d == 64 && (scan || fused)) return launch_forward_scan(a, s);
     switch (a.d) {
         case 32: return launch_d<32>(a, s);

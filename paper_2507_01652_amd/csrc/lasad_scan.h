@@ -2,7 +2,8 @@
 //     S <- diag(lambda_t) S + k_t v_t^T,   o_t = q_scale * S^T q_t,
 // with lambda_t either the per-head scalar gamma (1 at a row boundary) or the per-token
 // decay vector of Algorithm 1 (key tied to it, k_t = 1 - lambda_t, unless a key is given).
-// It is the path for the vector decay and for fp32 inputs; arithmetic is fp32 throughout.
+// It is the path for the vector decay with fp32 inputs, for the first few tokens of the scalar one, and the range
+// fallback of the chunked vector-decay kernels; arithmetic is fp32 throughout.
 //
 // Work split.  One 256-thread workgroup owns NJ value channels (columns of S) of one
 // (batch, head) sequence: NJ = 64 (whole head) or 32 (two workgroups per head, chosen when

@@ -41,6 +41,23 @@ def test_tile_edges(lasad, oracle, n, W, mode, start):
     assert rel_err(s1.cpu().numpy(), s_ref) <= TOL["f32"]
 
 
+@pytest.mark.parametrize("n", [1, 4, 5])
+@pytest.mark.parametrize("Hh", [64, 65], ids=["128_sequences", "130"])
+def test_few_tokens(lasad, oracle, n, Hh):
+    """Both sides of the rule that leaves up to four tokens of few sequences to the token-serial kernel."""
+    import torch
+    rng = np.random.default_rng(n)
+    q, k, v = (rng.standard_normal((2, n, Hh, D), dtype=np.float32) / 8 for _ in range(3))
+    s0 = (rng.standard_normal((2, Hh, D, D)) * 0.3).astype(np.float32)
+    gamma = rng.uniform(0.5, 1.0, Hh).astype(np.float32)
+    up = lambda x: torch.from_numpy(x).cuda()
+    s1 = torch.empty((2, Hh, D, D), dtype=torch.float32, device="cuda")
+    o = lasad.lasad_forward_chunked(up(q), up(k), up(v), up(gamma), 3, 3, start_pos=1, state_in=up(s0), state_out=s1)
+    lam, _ = oracle.decay_factors(gamma, 3, 3, 1, n, 0)
+    ref, s_ref = oracle.forward_fullmask(q, k, v, lam, s0=s0.astype(np.float64), want_state=True)
+    assert rel_err(o.cpu().numpy(), ref) <= TOL["f32"] and rel_err(s1.cpu().numpy(), s_ref) <= TOL["f32"]
+
+
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
 @pytest.mark.parametrize("t", [0, 1, 13, 15, 16, 30, 47])
 def test_non_finite_value_stays_causal(lasad, oracle, t, bad):
