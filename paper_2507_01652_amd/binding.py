@@ -129,8 +129,9 @@ def _check(status: int):
 
 
 # The small calls (decode steps above all) are bound by the host: every attribute of a tensor costs 0.1 us and more, a
-# stream object 2 us (a decode step of one image: 10.0 us a layer before, 6.9 us now).  Pointers and streams therefore go to ctypes as plain integers, the current stream is asked for by
-# its handle, and the checks read a tensor's attributes once.
+# stream object 2 us (a decode step of one image: 10.0 us a layer before, 6.9 us now).  Pointers and streams therefore
+# go to ctypes as plain integers, the current stream is asked for by its handle, and the checks read a tensor's
+# attributes once.
 _DTYPE_CODES = {torch.float32: F32, torch.bfloat16: BF16}
 
 
