@@ -123,8 +123,8 @@ struct PassStage {
     }
 };
 
-// One pass of sequence bh by the calling workgroup of four compute wavefronts and NG groups of four loaders; ka, kr: its arguments and operand roles in the
-// kernel-argument segment (for the redo).
+// One pass of sequence bh by the calling workgroup of four compute wavefronts and NG groups of four loaders; ka, kr: its
+// arguments and operand roles in the kernel-argument segment (for the redo).
 template <int PASS, int OUT_BF16, int OWNKEY, int FUSED, int LO, int NG>
 __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArgs *ka, const scan::ScanRoles *kr, int bh,
                                           unsigned char *smem, float (*sTot)[D], int (*sTrip)[4])
@@ -578,10 +578,12 @@ hipError_t launch_backward_gated_passes(const ForwardArgs *a, const scan::ScanRo
     if ((n_seq + 7) / 8 * 24 > 0x7fffffff) return hipErrorInvalidValue;
     PassSet ps;
     for (int i = 0; i < 3; ++i) { ps.a[i] = a[i]; ps.roles[i] = roles[i]; }
-// A compute unit for every workgroup: an XCD gets three workgroups of every eighth sequence and has 32 units, so up to
-    // 80 sequences.  One -> two loader groups, us a call: 12 sequences of 4096 tokens 182 -> 180, fused layer 265 -> 222; 24 of
-    // 1024 59 -> 57, 106 -> 96; 80 of 576 47 -> 46.5, 88 -> 82; but 84 of 256 30.9 -> 32.5, 54.9 -> 57.0.
-    const int ng = n_seq <= 80 ? 2 : 1;
+    // A compute unit for every workgroup: an XCD gets three workgroups of every eighth sequence and has 32 units, so up to
+    // 80 sequences.  One -> two loader groups, us a call: 12 sequences of 4096 tokens 162 -> 142, fused layer 247 -> 213; 24
+    // of 1024 54 -> 49, 103 -> 94; 80 of 576 44.1 -> 42.8, 88 -> 80; but 84 of 256 29.5 -> 32.7, of 576 49 -> 54.  Two chunks
+    // (one pair of one group) are bound by their first loads: 24 of 64 10.0 -> 10.4, of 96 13.4 -> 12.6.
+    const bool pair = a[0].n_tokens > C && a[0].n_tokens <= 2 * C;
+    const int ng = n_seq <= 80 && !pair ? 2 : 1;
     const dim3 grid((unsigned)((n_seq + 7) / 8 * 24)), block((1 + ng) * kThreads);
     const bool out16 = a[1].out_dtype == LASAD_BF16;
     if (a[0].fused_act && (!tied || !a[0].q_lo || !a[1].v_lo || !a[2].v_lo)) return hipErrorInvalidValue;

@@ -653,9 +653,13 @@ hipError_t launch_forward_gated_chunk(const ForwardArgs &a, hipStream_t s)
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    // one workgroup per compute unit: two loader groups (see above); more of them: one, and two workgroups per unit
+    // One workgroup per compute unit: two loader groups (see above); more of them: one, and two workgroups per unit.  us, one
+    // group -> two: tied key 96 x 256 tokens 13.0 -> 12.0, 192 x 1444 58 -> 52, 256 x 576 28.5 -> 26.3, 300 x 576 37.7 -> 42.5;
+    // fused layer 200 x 576 30.5 -> 26.4.  A call of a few chunks is bound by its first loads, and a second group only adds
+    // to them: own key 24 x 32 5.1 -> 6.0, x 64 6.4 -> 7.0, x 96 7.6 -> 8.0, x 160 10.0 -> 9.6; fused layer x 32 5.3 -> 5.7, x 96
+    // 8.1 -> 7.9.
     const int64_t n_wg = n_seq * plan.n_seg;
-    const int ng = n_wg <= 256 ? 2 : 1;
+    const int ng = n_wg <= 256 && a.n_tokens > (a.k ? 96 : 32) ? 2 : 1;
     const dim3 grid((unsigned)n_wg), block((1 + ng) * kThreads);
 #define LASAD_LAUNCH1(O, K, F, N) do { \
         if (ng == 2) hipLaunchKernelGGL((forward_gated_chunk_kernel<O, K, F, N, 2>), grid, block, 0, s, a, plan); \
