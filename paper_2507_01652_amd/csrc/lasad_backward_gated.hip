@@ -437,12 +437,11 @@ void finish_segments(int64_t n_seq, int n, int *n_seg, int *seg_blocks)
     *n_seg = (nblk + *seg_blocks - 1) / *seg_blocks;
 }
 
-// Floats of one pass's bound states and flags; 0: none.  The reversed pass walks chunks of 32 tokens from the last
-// token on, so its chunks end on the segment bounds only where the length is a multiple of 32; other lengths add up r.
+// Floats of one pass's bound states and flags; 0: none.
 size_t bound_states_floats(int64_t n_seq, int n, int d)
 {
     int n_seg = 1, seg_blocks = 0;
-    if (d == kD && n % 32 == 0 && n > 0) finish_segments(n_seq, n, &n_seg, &seg_blocks);
+    if (d == kD && n > 0) finish_segments(n_seq, n, &n_seg, &seg_blocks);
     return n_seg > 1 ? (size_t)n_seq * (n_seg - 1) * kD * kD + (size_t)(n_seq + 63) / 64 * 64 : 0;
 }
 

@@ -61,27 +61,30 @@ __device__ __noinline__ void redo_roles(const ForwardArgs *a, const scan::ScanRo
 // tensors, and one 16-byte piece of a row of x, y and the low-order part of d_o.  Uniform bases, advanced chunk by chunk
 // on the scalar unit, plus 32-bit byte offsets; the reversed passes (negative token stride) keep their bases at the
 // chunk's last token, the lowest address.  Rows past the end re-read the last token.
+// A reversed pass starts with the chunk that the forward one ends with: its first `lead` rows are no tokens (they re-read
+// the first one), so that both have their chunks' ends at the same tokens, where the finishing kernel wants their states.
 template <int PASS, int OWNKEY, int LO, int NG>
 struct PassStage {
     static constexpr bool REV = PASS != DQ, COL = PASS != DV, ZLOAD = PASS != DQ || OWNKEY;
     const char *l, *z, *q, *x, *y, *lo;
     uint32_t row;                      // bytes from token to token
-    int left;                          // tokens from the chunk's first one on, > 0
-    bool start;                        // the walk's first chunk: its first step has no decay to read
+    int left;                          // rows from the chunk's first one on, > 0
+    int lead;                          // REV: rows of the chunk before the walk's first token
+    bool start;                        // REV: the walk's first chunk: its first step has no decay to read
     struct Regs {
         uint2 rl[2], rz[2], rq[2];
         u32x4 rx, ry, rlo;
     };
 
-    // from the walk's token `first` on, n tokens
-    __device__ __forceinline__ void init(const ForwardArgs &a, int64_t base, int first, int n)
+    // from the walk's row `first` on, n rows; its first `pad` rows (REV) are no tokens
+    __device__ __forceinline__ void init(const ForwardArgs &a, int64_t base, int first, int n, int pad)
     {
         left = n;
         start = first == 0;
-        base += first * a.in.stride_n;
+        lead = start ? pad : 0;
         const int64_t s = a.in.stride_n;
         row = (uint32_t)(REV ? -s : s) * 2;
-        const int64_t b = base + (REV ? (min(C, n) - 1) * s : 0);
+        const int64_t b = base + (first + (REV ? C - 1 - pad : 0)) * s;
         l = (const char *)((const uint16_t *)a.lam + b);
         z = ZLOAD ? (const char *)((const uint16_t *)a.k + b) : nullptr;
         q = COL ? nullptr : (const char *)((const uint16_t *)a.q + b);
@@ -91,13 +94,14 @@ struct PassStage {
     }
     __device__ __forceinline__ void fetch(Regs &f, int pr, int pcol, int st) const
     {
-        const int last = min(C, left) - 1;
-        const int m0 = min(2 * pr, last), m1 = min(2 * pr + 1, last), mv = min(st >> 3, last);
+        const int last = REV ? C - 1 : min(C, left) - 1;
+        const int m0 = REV ? max(2 * pr, lead) : min(2 * pr, last), m1 = REV ? max(2 * pr + 1, lead) : min(2 * pr + 1, last);
+        const int mv = REV ? max(st >> 3, lead) : min(st >> 3, last);
         const uint32_t o0 = (REV ? last - m0 : m0) * row + pcol * 2, o1 = (REV ? last - m1 : m1) * row + pcol * 2;
         const uint32_t ov = (REV ? last - mv : mv) * row + (st & 7) * 16;
         if (REV) {                     // step m applies the decay of the token walked before it
-            f.rl[0] = *(const uint2 *)(l + (start && m0 == 0 ? o0 : o0 + row));
-            f.rl[1] = *(const uint2 *)(l + (start && m1 == 0 ? o1 : o1 + row));
+            f.rl[0] = *(const uint2 *)(l + (start && m0 == lead ? o0 : o0 + row));
+            f.rl[1] = *(const uint2 *)(l + (start && m1 == lead ? o1 : o1 + row));
         } else {
             f.rl[0] = *(const uint2 *)(l + o0);
             f.rl[1] = *(const uint2 *)(l + o1);
@@ -113,8 +117,9 @@ struct PassStage {
     {
         if (left <= NG * C) return;
         left -= NG * C;
+        lead = 0;
         start = false;
-        const int64_t adv = ((NG - 1) * C + (REV ? min(C, left) : C)) * stride_n * 2;
+        const int64_t adv = NG * C * stride_n * 2;
         l += adv; y += adv;
         if (ZLOAD) z += adv;
         if (!COL) q += adv;
@@ -137,7 +142,8 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
     const int b = bh / a.Hh, h = bh - b * a.Hh;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int n = a.n_tokens;
+    const int pad = REV ? (C - 1) - (a.n_tokens - 1) % C : 0;      // rows before the walk's first token
+    const int n = a.n_tokens + pad;                        // rows
     // (one loader group: the walk goes two chunks at a time; the second may be empty)
     const int n_chunks = NG == 1 ? (n + 2 * C - 1) / (2 * C) * 2 : (n + C - 1) / C;
     SplitConst sc;
@@ -153,7 +159,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
         const int pr = lane & 15, pcol = 16 * lw + 4 * (lane >> 4);
         using Stage = PassStage<PASS, OWNKEY, LO, NG>;
         Stage sg;
-        sg.init(a, (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h, first, n - first);
+        sg.init(a, (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h, first, n - first, pad);
         typename Stage::Regs r0, r1;               // (one loader group: two chunks of loads in flight)
         sg.fetch(r0, pr, pcol, st);                // ahead of everything that does not need it
         if (NG == 1) {
@@ -162,18 +168,24 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
         }
         __builtin_amdgcn_sched_barrier(0);
         RowBoundaries bounds;
-        bounds.init(a.start_pos + grp * C, a.grid_w, a.mode, NG * C);
-        int left = n - grp * C;                    // tokens from the next chunk to be prepared on
+        int col = a.start_pos;                     // of the walk's first row
+        if (REV) {
+            col = col % a.grid_w - pad % a.grid_w;
+            if (col < 0) col += a.grid_w;
+        }
+        bounds.init(col + grp * C, a.grid_w, a.mode, NG * C);
+        int left = n - grp * C;                    // rows from the next chunk to be prepared on
         const int put = SL::Map::at(2 * pr, pcol), put_piece = SL::Map::at(st >> 3, (st & 7) * 8);
         const int orow = st >> 3, ocol = (st & 7) * 8;
         const int64_t o_lane = orow * a.out.stride_n + ocol;
-        int64_t o_chunk = (int64_t)b * a.out.stride_b + (int64_t)h * a.out.stride_h + (NG == 2 && grp == 0 ? C : 0) * a.out.stride_n;
+        int64_t o_chunk = (int64_t)b * a.out.stride_b + (int64_t)h * a.out.stride_h +
+                          ((NG == 2 && grp == 0 ? C : 0) - pad) * a.out.stride_n;
         auto store_tile = [&](int chunk) {
             const float *tile = outs + (chunk & 1) * C * OS + orow * OS + ocol;
             float4 u = *(const float4 *)tile, w = *(const float4 *)(tile + 4);
             u = make_float4(u.x * a.q_scale, u.y * a.q_scale, u.z * a.q_scale, u.w * a.q_scale);
             w = make_float4(w.x * a.q_scale, w.y * a.q_scale, w.z * a.q_scale, w.w * a.q_scale);
-            if (chunk * C + orow < n) {
+            if (chunk * C + orow >= pad && chunk * C + orow < n) {
                 const int64_t i = o_chunk + o_lane;
                 if (OUT_BF16) {
                     gstore16<true>((uint16_t *)a.o + i, make_uint4(pack2(u.x, u.y), pack2(u.z, u.w), pack2(w.x, w.y), pack2(w.z, w.w)));
@@ -191,7 +203,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
         bool row_live;
         float z[2][4], x[2][4], tot[4], exc[4];
 
-        // the plain rows into slot p (a row past the end is a query that nobody stores, and zero as y)
+        // the plain rows into slot p (a row that is no token is a query that nobody stores, and zero as y)
         auto put_rows = [&](int p) {
             uint16_t *const piece = slots + p * SL::kHalfs + put_piece;
             if (COL) *(u32x4 *)&piece[SL::X] = px;
@@ -204,14 +216,15 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
         auto phase_a = [&](typename Stage::Regs &f, int p, int done, bool walk_start) {
             uint32_t bmask = bounds.mask();
             bounds.advance();
-            if (REV && walk_start) bmask |= 1u;    // (the walk's first step: no decay)
+            const int lead = REV && walk_start ? pad : 0;
+            if (REV && walk_start) bmask |= 1u << lead;        // (the walk's first step: no decay)
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
                 unpack4(f.rl[it], x[it]);
                 if (sg.ZLOAD) unpack4(f.rz[it], z[it]);
                 if (!COL) pq[it] = f.rq[it];
             }
-            row_live = (st >> 3) < left;
+            row_live = (st >> 3) >= lead && (st >> 3) < left;
             if (COL) px = f.rx;
             py = f.ry;
             if (LO) plo = f.rlo;
@@ -259,10 +272,10 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
                     }
                 }
             }
-            if (left < C) {                        // tail chunk: rows past the end get lambda 1, z = 0
+            if (left < C || (REV && lead > 0)) {   // rows that are no tokens get lambda 1, z = 0
 #pragma unroll
                 for (int it = 0; it < 2; ++it) {
-                    const bool live = 2 * pr + it < left;
+                    const bool live = 2 * pr + it >= lead && 2 * pr + it < left;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         x[it][e] = live ? x[it][e] : 1.0f;
@@ -383,7 +396,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
     }
 
     // COL: the states at the segment bounds of the finishing kernel (seg_chunks chunks a segment, counted from the first
-    // token; the reversed walk comes to them from the other end)
+    // token; the reversed walk comes to them from the other end, its chunks' ends at the same tokens)
     const int n_bounds = COL && a.seg_states ? a.n_segments - 1 : 0;
     int bound = REV ? n_bounds - 1 : 0;                        // the next one
     int bound_at = REV ? (n + C - 1) / C - a.seg_chunks * n_bounds : a.seg_chunks;

@@ -62,8 +62,8 @@ def test_range_exit(lasad, oracle, spike, own_key):
     _check(lasad, oracle, 97, own_key, start=0, seed=spike, spike=spike)
 
 
-# bounds on and off row ends; a shorter last segment; a length that is no multiple of 32 (no states kept)
-@pytest.mark.parametrize("n", [512, 544, 1024, 1040, 1056])
+# bounds on and off row ends; a shorter last segment; lengths that fill no chunk
+@pytest.mark.parametrize("n", [512, 513, 543, 544, 1024, 1040, 1056])
 @pytest.mark.parametrize("start", [0, 15, 17])
 @pytest.mark.parametrize("own_key", [False, True], ids=["tied", "own"])
 def test_segment_bounds(lasad, oracle, n, start, own_key):
@@ -104,10 +104,10 @@ def test_loader_groups(lasad, oracle, n, Hh):
 
 
 @pytest.mark.parametrize("carried", [False, True])
-@pytest.mark.parametrize("n,longer", [(1024, 1040), (1024, 1025), (544, 545)])
+@pytest.mark.parametrize("n,longer", [(1536, 1537), (1536, 1552), (1792, 1793)])
 def test_workspace_of_a_longer_call(lasad, oracle, n, longer, carried):
-    """The states at segment bounds need scratch of their own, and lengths that keep none ask for less: a workspace sized
-    for such a longer call serves the shorter one; a byte less than it cannot do without is refused."""
+    """The states at segment bounds need scratch of their own, and some longer calls have fewer bounds and ask for less: a
+    workspace sized for such a call serves the shorter one; a byte less than it cannot do without is refused."""
     import torch
     rng = np.random.default_rng(n)
     Hh = 5
@@ -124,7 +124,7 @@ def test_workspace_of_a_longer_call(lasad, oracle, n, longer, carried):
     got = call(*args, grad_dtype=torch.float32, workspace=ws)
     for i, (a, r) in enumerate(zip(got, ref(q, lam, v, g, W))):
         assert rel_err(a.cpu().numpy(), r) <= TOL["bf16"], i
-    least = given - (longer - n) * Hh * D * 8
+    least = 2 * n * Hh * D * 4 + Hh * 8 * D * 4 + (3 * Hh * D * D * 4 + Hh * D * 4 if carried else 0)
     call(*args, workspace=ws[:least])
     with pytest.raises(lasad.LasadError):
         call(*args, workspace=ws[:least - 1])
