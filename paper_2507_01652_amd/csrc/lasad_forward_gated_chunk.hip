@@ -385,11 +385,12 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
             for (int r = 0; r < 4; ++r) accS[t][r] = a.state_in[s_off + (state_channel(t, g) + r) * D];
     }
 
+    const SlotPtr<> sp0(slots, lane);
     __syncthreads();
     bool fine = true;
     for (int chunk = 0; fine && chunk < n_chunks; ++chunk) {
         const int4 f = *(const int4 *)sTrip[chunk & 1];
-        const SlotPtr<> sp(slots + (chunk & 1) * kSlot, lane);
+        const SlotPtr<> sp(sp0, (chunk & 1) * kSlot);
         f32x4v p00 = zero4, p01 = zero4, p11 = zero4;              // scores P^T[j][i]: (key tile, query tile)
         f32x4v o0 = zero4, o1 = zero4;                             // O^T[n][i] of the two query tiles
 #pragma unroll
@@ -553,10 +554,11 @@ gated_segment_state_kernel(ForwardArgs a, SegPlan plan)
     }
     fetch();
     prepare(0);
+    const SlotPtr<kStateRow> sp0(smem, lane);
     __syncthreads();
     for (int chunk = 0; chunk < n_chunks; ++chunk) {
         prepare(chunk + 1);                        // (past the end: into a slot that nobody reads)
-        const SlotPtr<kStateRow> sp(smem + (chunk & 1) * Map::kHalfs, lane);
+        const SlotPtr<kStateRow> sp(sp0, (chunk & 1) * Map::kHalfs);
         const Frag fv = sp.tokens(2 * D + 16 * wave);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
