@@ -359,8 +359,8 @@ int lasad_backward_chunked_carried(const void *q, const void *k, const void *v, 
  *   workspace           device memory of at least lasad_backward_gated_workspace_bytes(...) bytes,
  *                       256-byte aligned, owned by the caller (LASAD_ERR_WORKSPACE if too small).  For few long
  *                       sequences the query includes scratch that the call can do without (states kept at
- *                       segment bounds; some lengths have none): a workspace that the query gave for a longer
- *                       call serves every shorter one, which is then a little slower and less accurate in dlam.
+ *                       segment bounds; some longer calls have fewer): a workspace that the query gave for a longer
+ *                       call serves every shorter one, which may then be a little slower and less accurate in dlam.
  * Asynchronous on hip_stream; no allocation, no synchronisation; deterministic.
  */
 size_t lasad_backward_gated_workspace_bytes(int B, int n_heads, int n_tokens, int d);

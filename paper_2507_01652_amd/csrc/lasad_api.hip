@@ -565,8 +565,8 @@ static int backward_gated_impl(const void *q, const void *lam, const void *k, co
         }
         return LASAD_OK;
     }
-    // the states at segment bounds come last and may be left out: their part is 0 for some lengths, and a workspace that
-    // was sized for such a longer call serves a shorter one
+    // the states at segment bounds come last and may be left out: some longer calls have fewer, and a workspace that was
+    // sized for one of them serves a shorter one
     const int64_t n_seq = (int64_t)B * n_heads;
     const size_t need = lasad::backward_gated_workspace_bytes(n_seq, n_tokens, d) +
                         (carried ? lasad::backward_gated_carried_extra_bytes(n_seq, d) : 0);

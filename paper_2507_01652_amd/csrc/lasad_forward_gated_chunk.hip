@@ -18,9 +18,10 @@
 //
 // Bound by vector-instruction issue (about 1700 wave instructions per chunk, matrix instructions included, in
 // 4000 cycles of four SIMDs at two workgroups per unit).  Measured against the kernels this one replaced (four wavefronts
-// of 64-token chunks, or twelve with a workgroup per compute unit), bf16, us per call: fused layer 32 x 16 sequences of
-// 24 x 24 tokens 58.2 -> 50.5, 12 x 24 of 16 x 16 26.4 -> 21.5; tied key 32 x 16 of 24 x 24 54.1 -> 47.4, own key 73 ->
-// 61.8; 4 x 24 of 64 x 64 132 -> 90 (segments); one workgroup per unit 8 x 24 of 64 x 64 138 -> 144.
+// of 64-token chunks, or twelve with a workgroup per compute unit), bf16, us per call (graph replay): 512 sequences of
+// 24 x 24 tokens, fused layer 54.6 -> 47.4, tied key 53.7 -> 42, own key 60.4 -> 44; 288 of 16 x 16 fused layer 26.4 -> 21.5;
+// 96 of 64 x 64 132 -> 84 (segments); one workgroup per unit, 192 of 64 x 64 137 -> 125, own key 155 -> 151, 96 of 16 x 16
+// 11.5 -> 11.0, own key 11.9 -> 12.0.  Slower: two chunks where the other had one, 24 x 64 tokens 5.1 -> 5.4, own key 5.3 -> 5.7.
 //
 // Precision: Q~, K~, P and S are computed operands and are each split into bf16 hi + lo (three MFMAs for
 // a product of two split operands, two when one side is exact); v is exact bf16.

@@ -130,3 +130,20 @@ def test_workspace_of_a_longer_call(lasad, oracle, n, longer, carried):
         call(*args, workspace=ws[:least - 1])
     layer = [lasad.lasad_backward_layer_workspace_bytes(torch.empty((1, m, Hh, D), dtype=torch.bfloat16)) for m in (n, longer)]
     assert layer[0] < layer[1]
+
+
+@pytest.mark.parametrize("W,start", [(1, 0), (3, 2), (5, 31), (23, 17), (70, 69)])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("n,Hh", [(33, 3), (63, 85), (77, 3), (513, 3)])
+def test_reversed_start(lasad, oracle, W, start, mode, n, Hh):
+    """The reversed passes start with a chunk of n % 32 tokens: every row rule on grids narrower and wider than what is
+    missing from it, with two loader groups (few sequences) and with one."""
+    import torch
+    rng = np.random.default_rng(n + W)
+    q, v, g = (wl.store_round(rng.standard_normal((1, n, Hh, D), dtype=np.float32) / np.float32(8), "bf16") for _ in range(3))
+    lam = wl.gate_inputs((1, n, Hh, D), "bf16", n)
+    dev = lambda x: lasad.to_device(x, "bf16")
+    got = lasad.lasad_backward_gated(dev(q), dev(lam), dev(v), dev(g), (start + n + W - 1) // W, W, start_pos=start,
+                                     boundary_mode=mode, q_scale=0.7, grad_dtype=torch.float32)
+    for i, (a, r) in enumerate(zip(got, oracle.gated_backward(q, lam, v, g, W, start_pos=start, mode=mode, q_scale=0.7))):
+        assert rel_err(a.cpu().numpy(), r) <= TOL["bf16"], i
