@@ -30,6 +30,7 @@ SOURCES = [
     "lasad_backward.hip",
     "lasad_backward_gated.hip",
     "lasad_backward_gated_mfma.hip",
+    "lasad_backward_gated_chunk.hip",
     "lasad_backward_layer.hip",
 ]
 

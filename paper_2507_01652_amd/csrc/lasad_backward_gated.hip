@@ -19,8 +19,9 @@
 // decay of step m is the lambda of the token one step EARLIER in walking order (l_{t+1}), read with a
 // token shift of -1, and the row-boundary pattern is the forward one mirrored and shifted, i.e. that
 // of another start column (as in the scalar-decay backward).  The three walks run in one launch.
-// With bf16 inputs the three passes run on the matrix cores instead, chunk by chunk
-// (lasad_backward_gated_mfma.hip, again one launch); the walks remain the path for fp32 inputs
+// With bf16 inputs they run on the matrix cores instead, chunk by chunk: two walks, the second of which also does what
+// follows below (lasad_backward_gated_chunk.hip), or for few short sequences the three passes in one launch
+// (lasad_backward_gated_mfma.hip); the token-serial walks remain the path for fp32 inputs
 // and the range fallback of those kernels (LASAD_GATED_BWD=walk forces them).
 //
 // Decay gradient.  L depends on l only through the products prod_{s=j+1..i} l_s[c] between a key
@@ -29,13 +30,16 @@
 //   l_t[c] * dL/dl_t[c] = sum_{i >= t} r_i[c]            (every pair with j < t <= i, once)
 //
 // and dlam_t = (t a boundary or the first token ? 0 : that suffix sum / lambda_t) - (tied key: dk_t).
-// The suffix sums cancel heavily, so dq and dk go through the workspace in fp32; the finishing kernel
+// The suffix sums cancel heavily, so dq and dk stay fp32 until then and, but for the second walk, go through the workspace; the
+// finishing kernel
 // (one workgroup per sequence, blocks of 64 tokens from the last to the first) forms them in a fixed
 // order and stores dq, dk, dlam in the caller's type.  lambda must be > 0 where it is applied, and the result loses precision like
 // 1 / lambda for very small decays (the quotient of a rounded sum).
 #include <stdlib.h>
 #include <string.h>
 
+#include "lasad_gated_backward.h"
+#include "lasad_gated_finish.h"
 #include "lasad_recurrence.h"
 #include "lasad_scan.h"
 
@@ -172,8 +176,6 @@ backward_gated_generic_walk_kernel(WalkArgs w)
     else recurrence_roles<D, IN_BF16, 0, 1>(a, w.roles[pass], blockIdx.x, lds);     // fp32 into the workspace
 }
 
-constexpr int kFinBlock = 64;          // tokens per step of the finishing kernel
-
 // States at the bounds between segments, [sequence][bound][key channel][value channel], and after them one flag per
 // sequence: 0 where the token-serial walk took the pass over and kept none.  Either pointer NULL: not kept.
 struct BoundStates {
@@ -185,23 +187,17 @@ struct BoundStates {
     }
 };
 
-// One workgroup per sequence walks it in blocks of 64 tokens from the last block to the first,
-// every thread holding four channels of one token (16-byte loads; the next block's loads are in
-// flight while this one is worked on).  Per block: r = q dq - k dk into LDS, suffix sums down the
-// block's tokens per channel (four 16-token quarters side by side, then their totals), outputs,
-// and the block's total joins the carry.  Every input is read once; the order of all sums is fixed.
+// The finishing step of the three passes (FinishWalk: one workgroup per sequence, blocks of 64 tokens from the last one on).
 // Few long sequences are cut into n_seg segments of seg_blocks blocks with a workgroup each
 // (blockIdx.y): a first launch (TOTALS) only adds up r over each segment, the second starts every
 // segment from the totals of the segments after it.  seg_totals: [sequence][segment][d] fp32.
 // Where the matrix-core passes kept their states at the segment bounds (bs), the first launch reads those instead of q, k,
 // dq and dk: the suffix sum at the first token t of the next segment is sum_n (l_t G_t)[c][n] S_{t-1}[c][n] itself (with
-// what the final state's gradient adds), 32 KB a bound for 200 KB and more, and no sum over the tokens after it.
-// Forward and backward with an own key, 4 x 24 sequences of 4096 tokens: 602 -> 555 us; dlam against fp64 (2-norm): 1.8e-4
-// -> 5.5e-5 with an own key, 6.8e-5 -> 2.0e-5 with the tied one.
+// what the final state's gradient adds), 32 KB a bound for 200 KB and more, and no sum over the tokens after it: dlam
+// against fp64 (2-norm, 4096 tokens) 1.8e-4 -> 5.5e-5 with an own key, 6.8e-5 -> 2.0e-5 with the tied one.
 // The channels are independent: with few workgroups a sequence's channels are further divided between
 // 64 / CH workgroups (blockIdx.z) of 16 CH threads, which shortens nothing of the chain of blocks but
 // puts more of them in flight.
-// (fp64 sums were tried: no gain in accuracy, the error left is that of the fp32 dq and dk.)
 template <int IN_BF16, int OUT_BF16, int TOTALS, int CH>
 __global__ void __launch_bounds__(16 * CH)
 backward_gated_finish_kernel(GatedBackwardArgs a, const float *dq32, const float *dk32,
@@ -209,68 +205,18 @@ backward_gated_finish_kernel(GatedBackwardArgs a, const float *dq32, const float
 {
     // sink [sequence][d] (or NULL): per key channel, sum_n H[c][n] s_n[c][n] for H = dL/d(final state): the products of
     // decays that end in the final state pass through EVERY step of the call, so every suffix sum starts from it
-    constexpr int LPR = CH / 4;            // threads per token
-    __shared__ __attribute__((aligned(16))) float sR[kFinBlock][CH + 4];
-    __shared__ __attribute__((aligned(16))) float sQtr[4][CH];
-    __shared__ __attribute__((aligned(16))) float sCarry[CH];
+    __shared__ __attribute__((aligned(16))) float lds[finish_lds_floats<CH>()];
     const int bh = blockIdx.x, b = bh / a.Hh, h = bh - b * a.Hh;
     const int tid = threadIdx.x;
     const int ch0 = blockIdx.z * CH;       // this workgroup's first channel
-    const int row = tid / LPR, c4l = (tid % LPR) * 4, c4 = ch0 + c4l;
-    const int n = a.n_tokens;
-    const int nblk = (n + kFinBlock - 1) / kFinBlock;
-    const int64_t in_base = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + c4;
-    const int64_t g_base = (int64_t)b * a.grad.stride_b + (int64_t)h * a.grad.stride_h + c4;
-    const int64_t w_base = ((int64_t)b * n * a.Hh + h) * a.d + c4;       // workspace: [B][n][Hh][d] fp32
-    const int64_t w_stride_n = (int64_t)a.Hh * a.d;
-
-    struct Item { f4 q, k, lam, dq, dk, dact; };     // dact: d(activation)/d(input) of q, fused activations only
-    auto in4 = [&](const void *p, int t) {
-        const int64_t i = in_base + (int64_t)t * a.in.stride_n;
-        if (IN_BF16) {
-            const uint2 w = *(const uint2 *)((const uint16_t *)p + i);
-            return f4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u),
-                      __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u)};
-        }
-        return *(const f4 *)((const float *)p + i);
-    };
-    auto load = [&](int blk, Item &it) {
-        const int t = min(blk * kFinBlock + row, n - 1);
-        it.q = in4(a.q, t);
-        it.lam = in4(a.lam, t);
-        if (a.fused_act) {                 // q = SiLU(x), SiLU'(x) = s (1 + x (1 - s)) with s = sigmoid(x); lambda = sigmoid(z)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float x = it.q[e], sg = sigmoid_f32(x);
-                it.q[e] = x * sg;
-                it.dact[e] = sg * (1.0f + x * (1.0f - sg));
-                it.lam[e] = sigmoid_f32(it.lam[e]);
-            }
-        }
-        if (a.k) it.k = in4(a.k, t);
-        else it.k = f4{1.0f, 1.0f, 1.0f, 1.0f} - it.lam;
-        it.dq = *(const f4 *)(dq32 + w_base + t * w_stride_n);
-        it.dk = *(const f4 *)(dk32 + w_base + t * w_stride_n);
-    };
-    auto put4 = [&](void *p, int t, f4 x) {
-        const int64_t i = g_base + (int64_t)t * a.grad.stride_n;
-        if (OUT_BF16) {
-            uint2 w;
-            w.x = (uint32_t)float_to_bf16_bits(x[0]) | ((uint32_t)float_to_bf16_bits(x[1]) << 16);
-            w.y = (uint32_t)float_to_bf16_bits(x[2]) | ((uint32_t)float_to_bf16_bits(x[3]) << 16);
-            *(uint2 *)((uint16_t *)p + i) = w;
-        } else {
-            *(f4 *)((float *)p + i) = x;
-        }
-    };
-
     const int seg = blockIdx.y;
-    const int blk_lo = seg * seg_blocks, blk_hi = min(blk_lo + seg_blocks, nblk) - 1;     // this workgroup's blocks
+    const int t_lo = seg * seg_blocks * kFinBlock, t_hi = min(t_lo + seg_blocks * kFinBlock, a.n_tokens);
     float *totals = seg_totals + ((int64_t)bh * n_seg) * a.d + ch0;
     const bool direct = n_seg > 1 && bs.kept(bh);              // totals: the suffix sums after each segment
+    const FinishWalk<IN_BF16, OUT_BF16, CH> f(a, dq32, dk32, bh, ch0);
     if (TOTALS && direct) {
         if (seg == n_seg - 1) return;
-        const int c = ch0 + (tid >> 4), t = blk_lo * kFinBlock + seg_blocks * kFinBlock;      // 16 threads a channel
+        const int c = ch0 + (tid >> 4), t = t_lo + seg_blocks * kFinBlock;                    // 16 threads a channel
         const int64_t i = (((int64_t)bh * (n_seg - 1) + seg) * kD + c) * kD + 4 * (tid & 15);
         const f4 x = *(const f4 *)(bs.s + i), y = *(const f4 *)(bs.g + i);
         float acc = (x[0] * y[0] + x[1] * y[1]) + (x[2] * y[2] + x[3] * y[3]);
@@ -286,72 +232,16 @@ backward_gated_finish_kernel(GatedBackwardArgs a, const float *dq32, const float
         return;
     }
     if (TOTALS) {
-        f4 sum = f4{0.f, 0.f, 0.f, 0.f};
-        for (int blk = blk_hi; blk >= blk_lo; --blk) {
-            Item it;
-            load(blk, it);
-            if (blk * kFinBlock + row < n) sum += it.q * it.dq - it.k * it.dk;
-        }
-        *(f4 *)&sR[row][c4l] = sum;
-        __syncthreads();
-        if (tid < CH) {
-            float acc = 0.f;
-            for (int r2 = kFinBlock - 1; r2 >= 0; --r2) acc += sR[r2][tid];
-            totals[seg * a.d + tid] = acc;
-        }
+        f.totals(t_lo, t_hi, totals + seg * a.d, lds);
         return;
     }
+    float carry = 0.f;
     if (tid < CH) {
-        float carry = sink ? sink[(int64_t)bh * a.d + ch0 + tid] : 0.f;
+        if (sink) carry = sink[(int64_t)bh * a.d + ch0 + tid];
         if (direct && seg < n_seg - 1) carry = totals[seg * a.d + tid];
         else for (int s2 = n_seg - 1; s2 > seg; --s2) carry += totals[s2 * a.d + tid];
-        sCarry[tid] = carry;
     }
-    Item cur;
-    load(blk_hi, cur);
-    for (int blk = blk_hi; blk >= blk_lo; --blk) {
-        Item nxt = cur;
-        if (blk > blk_lo) load(blk - 1, nxt);
-        const int t = blk * kFinBlock + row;
-        const bool live = t < n;
-        f4 r = cur.q * cur.dq - cur.k * cur.dk;
-        if (!live) r = f4{0.f, 0.f, 0.f, 0.f};
-        *(f4 *)&sR[row][c4l] = r;
-        __syncthreads();
-        if (tid < 4 * CH) {                // suffix sums inside a quarter of the block, top down
-            const int c = tid % CH, qtr = tid / CH;
-            float acc = 0.f;
-#pragma unroll
-            for (int tt = 15; tt >= 0; --tt) {
-                acc += sR[16 * qtr + tt][c];
-                sR[16 * qtr + tt][c] = acc;
-            }
-            sQtr[qtr][c] = acc;
-        }
-        __syncthreads();
-        {
-            f4 suffix = *(const f4 *)&sR[row][c4l] + *(const f4 *)&sCarry[c4l];
-            for (int q2 = 3; q2 > (row >> 4); --q2) suffix += *(const f4 *)&sQtr[q2][c4l];
-            // (from a zero state the first token's decay multiplies nothing)
-            const bool no_decay = (t == 0 && !a.state_in) || is_boundary(a.start_pos + t + 1, a.grid_w, a.mode);
-            f4 dl = suffix / cur.lam;
-            if (no_decay) dl = f4{0.f, 0.f, 0.f, 0.f};
-            if (!a.k) dl -= cur.dk;
-            f4 dqo = cur.dq;
-            if (a.fused_act) {             // chain rule to the pre-activation inputs; sigmoid' = lambda (1 - lambda)
-                dl = dl * cur.lam * (f4{1.0f, 1.0f, 1.0f, 1.0f} - cur.lam);
-                dqo = dqo * cur.dact;
-            }
-            if (live) {
-                put4(a.dlam, t, dl);
-                put4(a.dq, t, dqo);
-                if (a.k) put4(a.dk, t, cur.dk);
-            }
-        }
-        __syncthreads();
-        if (tid < CH) sCarry[tid] += (sQtr[3][tid] + sQtr[2][tid]) + (sQtr[1][tid] + sQtr[0][tid]);
-        cur = nxt;
-    }
+    f.walk(t_lo, t_hi, carry, lds);
 }
 
 // hS = H / q_scale for the reversed passes (the kernels multiply their outputs by q_scale; the state gradient carries it
@@ -437,12 +327,46 @@ void finish_segments(int64_t n_seq, int n, int *n_seg, int *seg_blocks)
     *n_seg = (nblk + *seg_blocks - 1) / *seg_blocks;
 }
 
-// Floats of one pass's bound states and flags; 0: none.
-size_t bound_states_floats(int64_t n_seq, int n, int d)
+// How a call with bf16 inputs and head dim 64 runs.
+// PASSES: three independent passes side by side and a finishing kernel (lasad_backward_gated_mfma.hip), for calls whose
+//   passes all get a compute unit of their own (80 sequences) and that are too short to be cut.
+// WALKS: dq, then the reversed walk with everything else (lasad_backward_gated_chunk.hip).  Few long sequences are cut into
+//   segments, one workgroup a compute unit (two a unit: 96 sequences of 4096 tokens, own key, 259 -> 264 us, but 48 of 4096
+//   126 -> 143).  For the accuracy of dlam they keep the states at the bounds of as many parts as the passes had segments.
+// us a call, passes -> walks uncut -> cut (own key): 12 x 400 tokens 31.5 -> 41 -> 35; 12 x 576 35 -> 54 -> 39; 12 x 784 44 -> 71
+// -> 38; 48 x 576 41 -> 57 -> 44; 48 x 784 49 -> 76 -> 47; 80 x 784 57 -> 81 -> 61; 80 x 1024 75 -> 107 -> 74; 96 x 256 33.3 -> 33.1 ->
+// 36.6; 96 x 400 48.4 -> 46.0 -> 46.0; 96 x 576 58 -> 59 -> 53; 128 x 576 63 -> 60 -> 56; 96 x 4096 410 -> 378 -> 264; uncut only: 160
+// x 1024 126 -> 109, 240 x 4096 752 -> 470, 512 x 576 234 -> 167.
+struct ChunkPlan { bool passes; int n_seg, n_part; };          // parts: of a segment
+ChunkPlan chunk_plan(int64_t n_seq, int n)
 {
-    int n_seg = 1, seg_blocks = 0;
-    if (d == kD && n > 0) finish_segments(n_seq, n, &n_seg, &seg_blocks);
-    return n_seg > 1 ? (size_t)n_seq * (n_seg - 1) * kD * kD + (size_t)(n_seq + 63) / 64 * 64 : 0;
+    const int nblk = (n + kFinBlock - 1) / kFinBlock;
+    int parts, part_blocks;
+    finish_segments(n_seq, n, &parts, &part_blocks);
+    if (n_seq <= 80 && nblk <= (n_seq <= 48 ? 10 : 14)) return ChunkPlan{true, parts, 1};
+    if (n_seq > 128 || nblk < 8) return ChunkPlan{false, 1, parts};
+    int g = (int)(256 / n_seq);
+    if (g > kMaxSegments) g = kMaxSegments;
+    if (g > nblk / 2) g = nblk / 2;
+    const int blocks = (nblk + g - 1) / g;
+    g = (nblk + blocks - 1) / blocks;
+    return ChunkPlan{false, g, (parts + g - 1) / g};
+}
+
+// Floats of scratch for it: the states at the bounds and a flag per sequence and side or segment; of the walks also what the
+// suffix sums start from.  0: none.
+struct BoundsLayout { size_t s, g, parts, sinks, flags, total; };
+BoundsLayout bounds_layout(const ChunkPlan &p, int64_t n_seq)
+{
+    const size_t states = (size_t)n_seq * (p.n_seg - 1) * kD * kD, flags = (size_t)(n_seq + 63) / 64 * 64;
+    BoundsLayout l{0, 0, 0, 0, 0, 0};
+    if (p.n_seg * p.n_part == 1) return l;
+    l.g = states + (p.passes ? flags : 0);
+    l.parts = l.g + states;
+    l.sinks = l.parts + (size_t)n_seq * p.n_seg * (p.n_part - 1) * kD * kD;
+    l.flags = l.sinks + (p.passes ? 0 : (size_t)n_seq * kMaxSegments * kD);
+    l.total = l.flags + (p.passes ? 1 : p.n_seg) * flags;
+    return l;
 }
 
 }  // namespace
@@ -461,7 +385,7 @@ size_t backward_gated_workspace_bytes(int64_t n_seq, int n_tokens, int d)
 
 size_t backward_gated_bounds_bytes(int64_t n_seq, int n_tokens, int d)
 {
-    return 2 * bound_states_floats(n_seq, n_tokens, d) * sizeof(float);
+    return d == kD && n_tokens > 0 ? bounds_layout(chunk_plan(n_seq, n_tokens), n_seq).total * sizeof(float) : 0;
 }
 
 hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
@@ -490,7 +414,7 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
     // step: the shifted decay of step 0 is neutral); the dv pass ends with g_1 / q_scale
     const bool carried = b.state_in || b.d_state_out || b.d_state_in;
     const size_t mat = (size_t)n_seq * b.d * b.d;
-    const size_t bound_floats = b.bounds ? bound_states_floats(n_seq, n, b.d) : 0;
+    const ChunkPlan plan = chunk_plan(n_seq, n);
     float *cw = dk32 + (size_t)n_seq * n * b.d + (size_t)n_seq * 8 * b.d;      // after the gradients and the segment totals
     float *hS = cw, *sn = cw + mat, *g1 = cw + 2 * mat, *sink_buf = cw + 3 * mat;
     const float *sink = (carried && b.d_state_out) ? sink_buf : nullptr;
@@ -550,6 +474,48 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
 #undef LASAD_GEN_WALK
         e = hipGetLastError();
         if (e != hipSuccess) return e;
+    } else if (in16 && !force_walk && !plan.passes && backward_gated_chunk_fits(b)) {
+        // matrix-core walks: dq in forward order, then the others with everything that follows from dq, dk and their sums
+        GatedChunkArgs p;
+        p.b = b;
+        p.dq32 = dq32; p.dk32 = dk32;
+        p.g_in = st_in[1]; p.s_out = st_out[0]; p.g_out = st_out[1]; p.sink = sink;
+        const int n_chunks = (n + gchunk::C - 1) / gchunk::C;
+        const bool bounds = b.bounds && plan.n_seg * plan.n_part > 1;
+        p.cut = gchunk::SegPlan{1, n_chunks, 0};
+        p.n_part = 1;
+        p.bounds_s = p.bounds_g = p.parts_s = p.sinks = nullptr;
+        p.kept = nullptr;
+        if (bounds) {
+            const BoundsLayout l = bounds_layout(plan, n_seq);
+            p.cut = gchunk::SegPlan{plan.n_seg, n_chunks / plan.n_seg, n_chunks % plan.n_seg};
+            p.n_part = plan.n_part;
+            p.bounds_s = b.bounds + l.s; p.bounds_g = b.bounds + l.g; p.parts_s = b.bounds + l.parts;
+            p.sinks = b.bounds + l.sinks;
+            p.kept = (int *)(b.bounds + l.flags);
+        }
+        for (int y = 0; y < 3; ++y) {
+            p.serial[y] = f;
+            p.serial[y].o = w.o[y]; p.serial[y].in = w.in[y]; p.serial[y].out = w.out[y]; p.serial[y].start_pos = w.start_pos[y];
+            p.roles[y] = w.roles[y];
+        }
+        if (p.cut.n_seg > 1) {
+            e = launch_backward_gated_chunk_states(p, s);
+            if (e != hipSuccess) return e;
+        }
+        e = launch_backward_gated_chunk_dq(p, s);
+        if (e != hipSuccess) return e;
+        if (sink) {
+            GatedBackwardArgs only_sink = b;
+            only_sink.d_state_in = nullptr;
+            hipLaunchKernelGGL((gated_carried_finish_kernel<1>), dim3((unsigned)n_seq), dim3(256), 0, s, only_sink, g1, sn, (float *)sink);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        e = launch_backward_gated_chunk_reversed(p, s);
+        if (e != hipSuccess) return e;
+        if (b.d_state_in) hipLaunchKernelGGL((gated_carried_finish_kernel<1>), dim3((unsigned)n_seq), dim3(256), 0, s, b, g1, sn, (float *)nullptr);
+        return hipGetLastError();
     } else if (in16 && !force_walk && backward_gated_passes_fit(b.in.stride_n)) {
         // matrix-core passes: the pass's operands in the forward's fields
         ForwardArgs p[3] = {f, f, f};
@@ -563,12 +529,13 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
         p[2].q = v_l; p[2].o = w.o[2]; p[2].out = wl_rev; p[2].out_dtype = LASAD_F32;                  // dk
         p[2].v_lo = gl_l;
         for (int y = 0; y < 3; ++y) { p[y].state_in = st_in[y]; p[y].state_out = st_out[y]; }
-        if (bound_floats) {
+        if (b.bounds && plan.passes && n_seg > 1) {
+            float *const side[3] = {b.bounds, nullptr, b.bounds + bounds_layout(plan, n_seq).g};
             for (int y = 0; y < 3; y += 2) {
-                p[y].seg_states = y ? b.bounds + bound_floats : b.bounds;
+                p[y].seg_states = side[y];
                 p[y].n_segments = n_seg; p[y].seg_chunks = seg_blocks * (kFinBlock / 32);
             }
-            bs.s = b.bounds; bs.g = b.bounds + bound_floats;
+            bs.s = side[0]; bs.g = side[2];
             bs.flags = (int64_t)n_seq * (n_seg - 1) * kD * kD;
         }
         e = launch_backward_gated_passes(p, w.roles, b.k == nullptr, s);

@@ -113,6 +113,27 @@ __device__ __forceinline__ void unpack4(uint2 w, float (&f)[4])
     f[2] = __uint_as_float(w.y << 16); f[3] = __uint_as_float(w.y & 0xffff0000u);
 }
 
+// How a loader wavefront comes by its share of a tensor's 32 rows, tokens 2 pr, 2 pr + 1 and four channels a lane (pr = lane &
+// 15) of the wavefront's sixteen: read as 16 bytes a lane, two lanes a row, and turned in LDS, in rows of its own that nobody
+// else touches meanwhile (no barrier).  Read like that straight from memory, 8 bytes a lane in sixteen rows, a tile takes
+// a compute unit 230 ns: the address unit spends about four cycles on every row that an instruction touches.  16 bytes in 32
+// rows: 123 ns.  (Whole rows, 49 ns, would have to cross wavefronts.)
+template <int ROW>
+struct Turn {
+    using Map = SlotMap<ROW>;
+    int put, get;                      // elements from the tile's slot on, without the tensor's column
+    __device__ __forceinline__ Turn(int lw, int lane)
+    {
+        const int m = lane >> 1;
+        put = Map::row(m) + Map::piece(m, 2 * lw + (lane & 1));
+        get = Map::at(2 * (lane & 15), 16 * lw + 4 * (lane >> 4));
+    }
+    __device__ __forceinline__ void write(uint16_t *slot, int col, u32x4 x) const { *(u32x4 *)(slot + put + col) = x; }
+    __device__ __forceinline__ uint2 read(const uint16_t *slot, int col, int it) const { return *(const uint2 *)(slot + get + col + it * ROW); }
+    static __device__ __forceinline__ int row(int lane) { return lane >> 1; }                       // what the lane reads from memory:
+    static __device__ __forceinline__ int byte(int lw, int lane) { return 32 * lw + 16 * (lane & 1); }     // row, and where in it
+};
+
 // f as bf16 hi + lo, written to one row piece of two tiles
 __device__ __forceinline__ void put_pair4(uint16_t *hi, uint16_t *lo, const float (&f)[4], const SplitConst &sc)
 {
@@ -143,6 +164,11 @@ struct RowBoundaries {
     {
         first -= step;
         if (first < 0) first += W;
+    }
+    __device__ __forceinline__ void retreat()                // to the chunk before
+    {
+        first += step;
+        if (first >= W) first -= W;
     }
 };
 

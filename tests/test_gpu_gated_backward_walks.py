@@ -1,0 +1,96 @@
+"""The two walks of the vector-decay backward (dq, then dv, dk and the decay gradient in reversed order) on both sides of
+the rules that choose them: 81 sequences and more (fewer take three passes when they are short), segments with a workgroup
+each up to 128 sequences of 449 tokens and more, parts of a sequence beyond that.  Lengths around the 32-token tiles, row ends
+on and off the bounds, carried states, all three key forms, bf16 and fp32 gradients, and a gate beyond the range of the
+factorised form (the token-serial walk of that part, and no states kept by it).  A few sequences of each call against the
+fp64 oracle at the storage type's tolerance (helpers.TOL)."""
+import numpy as np
+import pytest
+
+from paper_2507_01652_amd import workloads as wl
+from helpers import TOL, both_outputs, rel_err
+
+pytestmark = pytest.mark.gpu
+D = 64
+
+
+@pytest.fixture(scope="module")
+def lasad():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2507_01652_amd import binding
+    binding.load()
+    return binding
+
+
+def _inputs(n, Hh, seed):
+    rng = np.random.default_rng(seed)
+    q, v, g, k = (wl.store_round(rng.standard_normal((1, n, Hh, D), dtype=np.float32) / np.float32(8), "bf16") for _ in range(4))
+    return rng, q, v, g, k, wl.gate_inputs((1, n, Hh, D), "bf16", seed + 1)
+
+
+def _check(lasad, oracle, n, Hh, own, W, start=0, spike=None, carried=False):
+    import torch
+    rng, q, v, g, k, lam = _inputs(n, Hh, 7 * n + Hh)
+    pick, c = [0, Hh // 2, Hh - 1], 5
+    if spike is not None:
+        lam[:, spike, Hh // 2, c] = 2.0 ** -120
+    if not own:
+        k = None
+    s0, ds = ((rng.standard_normal((1, Hh, D, D)) * 0.3).astype(np.float32) for _ in range(2))
+    dev = lambda x: None if x is None else lasad.to_device(x, "bf16")
+    sub = lambda x: None if x is None else np.ascontiguousarray(x[:, :, pick])
+    H = (start + n + W - 1) // W
+    kw = dict(q=dev(q), lam=dev(lam), v=dev(v), d_o=dev(g), grid_h=H, grid_w=W, k=dev(k), start_pos=start, q_scale=0.7)
+    if carried:
+        up = lambda x: torch.from_numpy(x).cuda()
+        got = lasad.lasad_backward_gated_carried(state_in=up(s0), d_state_out=up(ds), grad_dtype=torch.float32, **kw)
+        ref = oracle.gated_backward_carried(sub(q), sub(lam), sub(v), sub(g), W, k=sub(k), start_pos=start, q_scale=0.7,
+                                            s0=s0[:, pick], d_state=ds[:, pick])
+    else:
+        got = both_outputs(lasad.lasad_backward_gated, True, dtype_kw="grad_dtype", **kw)      # (bf16: the fp32 ones rounded)
+        ref = oracle.gated_backward(sub(q), sub(lam), sub(v), sub(g), W, k=sub(k), start_pos=start, q_scale=0.7)
+    state = len(got) - 1 if carried else -1
+    for i, (a, r) in enumerate(zip(got, [x for x in ref if x is not None])):
+        a = a.float().cpu().numpy()
+        a, r = (a[:, pick] if i == state else a[:, :, pick]), np.array(r)
+        if i == 1 and spike is not None:                     # a quotient by the tiny gate, and what it hides of the steps before
+            a[:, :, 1, c] = r[:, :, 1, c] = 0
+        assert rel_err(a, r) <= TOL["bf16"], (i, rel_err(a, r))
+
+
+@pytest.mark.parametrize("n,Hh", [(1, 81), (31, 81), (33, 81), (64, 81), (97, 81), (449, 81), (513, 100), (545, 129), (600, 129), (640, 257)])
+@pytest.mark.parametrize("own", [False, True], ids=["tied", "own"])
+def test_walks(lasad, oracle, n, Hh, own):
+    _check(lasad, oracle, n, Hh, own, W=16, start=n % 16)
+
+
+@pytest.mark.parametrize("n,Hh", [(40, 81), (520, 100), (1000, 12), (577, 129)])
+@pytest.mark.parametrize("own", [False, True], ids=["tied", "own"])
+def test_carried(lasad, oracle, n, Hh, own):
+    _check(lasad, oracle, n, Hh, own, W=23, start=5, carried=True)
+
+
+@pytest.mark.parametrize("n,Hh,spike", [(97, 81, 40), (520, 100, 3), (520, 100, 300), (520, 100, 519), (577, 129, 100), (577, 129, 570)])
+@pytest.mark.parametrize("carried", [False, True])
+def test_range_exit(lasad, oracle, n, Hh, spike, carried):
+    _check(lasad, oracle, n, Hh, True, W=23, spike=spike, carried=carried)
+
+
+@pytest.mark.parametrize("n,Hh,mode", [(33, 81, 0), (100, 81, 1), (513, 96, 0), (580, 129, 2), (1000, 12, 1)])
+def test_layer(lasad, oracle, n, Hh, mode):
+    import torch
+    W = 16
+    rng, q, v, g, z, _ = _inputs(n, Hh, n + Hh)
+    q, z = wl.store_round(q * 8, "bf16"), wl.store_round(z * 8 + 2, "bf16")
+    w = (1 + 0.1 * rng.standard_normal((Hh, D))).astype(np.float32)
+    pick = [0, Hh // 2, Hh - 1]
+    sub = lambda x: np.ascontiguousarray(x[:, :, pick])
+    dev = lambda x: lasad.to_device(x, "bf16")
+    got = both_outputs(lasad.lasad_backward_layer, True, dtype_kw="grad_dtype", q_pre=dev(q), z=dev(z), v=dev(v), d_out=dev(g),
+                       grid_h=(n + W - 1) // W, grid_w=W, norm_weight=torch.from_numpy(w).cuda(), boundary_mode=mode)
+    ref = oracle.gated_layer_backward(sub(q), sub(z), sub(v), sub(g), W, mode=mode, norm_weight=w[pick])
+    for i in range(3):
+        a = got[i].float().cpu().numpy()[:, :, pick]
+        assert rel_err(a, ref[i]) <= TOL["bf16"], (i, rel_err(a, ref[i]))
+    assert rel_err(got[3].cpu().numpy()[pick], ref[3]) <= TOL["bf16"]
