@@ -33,6 +33,7 @@
 // channel is below that (or zero) cannot be factored this way; the loaders see it one chunk ahead, and the
 // workgroup redoes its whole sequence with the token-serial fp32 routine (lasad_scan.h).
 #include "lasad_gated_chunk.h"
+#include "lasad_gated_state.h"
 #include "lasad_scan.h"
 
 namespace lasad {
@@ -462,126 +463,20 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
     }
 }
 
-// State pass of the segment plan: what segment `seg` (all but the last) adds to the state, and its total decay per key
-// channel, into the rows of the segment after it:
-//     U = sum_j (k_j A_end / A_j) v_j^T  chunk by chunk,   U <- diag(A_end) U + ...
-// The decays to the END of a chunk are running products from its last token backwards (<= 1: nothing to divide, no range
-// to leave), so the tokens are dealt to the lanes in reverse.  One workgroup of four wavefronts: each prepares 16 key
-// channels of the next chunk and updates 16 value channels of the state.
-constexpr int kStateRow = 3 * D + 16;          // K^ hi, lo, V
+// State pass of the segment plan: what a segment (all but the last) adds to the state, and its total decay per key
+// channel, into the rows of the segment after it (lasad_gated_state.h).
 template <int OWNKEY, int FUSED>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 2)
 gated_segment_state_kernel(ForwardArgs a, SegPlan plan)
 {
-    using Map = SlotMap<kStateRow>;
-    __shared__ __attribute__((aligned(16))) uint16_t smem[2 * Map::kHalfs];
-    __shared__ __attribute__((aligned(16))) float sTot[2][D];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kStateLdsBytes];
     const int bh = blockIdx.x / (plan.n_seg - 1), seg = blockIdx.x - bh * (plan.n_seg - 1);
     const int b = bh / a.Hh, h = bh - b * a.Hh;
-    const int st = threadIdx.x, lane = st & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(st >> 6);
-    const int pr = lane & 15, l16 = lane & 15, g = lane >> 4, pcol = 16 * wave + 4 * g;
-    const int seg_t0 = plan.start(seg), next_t0 = plan.start(seg + 1), n_chunks = (next_t0 - seg_t0) / C;
-    const int64_t base = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + seg_t0 * a.in.stride_n;
-    SplitConst sc;
-    sc.init();
-
-    const char *gl = (const char *)((const uint16_t *)a.lam + base), *gv = (const char *)((const uint16_t *)a.v + base);
-    const char *gk = OWNKEY ? (const char *)((const uint16_t *)a.k + base) : nullptr;
-    const uint32_t row = (uint32_t)a.in.stride_n * 2;
-    const uint32_t off0 = (C - 1 - 2 * pr) * row + pcol * 2, off1 = off0 - row, voff = (st >> 3) * row + (st & 7) * 16;
-    const int64_t adv = C * a.in.stride_n * 2;
-    uint2 rl[2], rk[2];
-    uint4 rv;
-    auto fetch = [&]() {
-        rl[0] = *(const uint2 *)(gl + off0); rl[1] = *(const uint2 *)(gl + off1);
-        if (OWNKEY) { rk[0] = *(const uint2 *)(gk + off0); rk[1] = *(const uint2 *)(gk + off1); }
-        rv = *(const uint4 *)(gv + voff);
-    };
-    RowBoundaries bounds;
-    bounds.init(a.start_pos + seg_t0, a.grid_w, a.mode, C);
-
-    const int put = Map::at(C - 1 - 2 * pr, pcol), put_v = Map::at(st >> 3, (st & 7) * 8) + 2 * D;
-    auto prepare = [&](int chunk) {                // chunk -> its slot
-        uint16_t *slot = smem + (chunk & 1) * Map::kHalfs;
-        const uint32_t bmask = bounds.mask();
-        bounds.advance();
-        float x[2][4], key[2][4];
-#pragma unroll
-        for (int it = 0; it < 2; ++it) {
-            unpack4(rl[it], x[it]);
-            if (OWNKEY) unpack4(rk[it], key[it]);
-        }
-        *(uint4 *)&slot[put_v] = rv;
-#pragma unroll
-        for (int it = 0; it < 2; ++it) {           // (the registers are free, see the walk's loaders)
-            asm volatile("" : "+v"(x[it][0]), "+v"(x[it][1]), "+v"(x[it][2]), "+v"(x[it][3]));
-            if (OWNKEY) asm volatile("" : "+v"(key[it][0]), "+v"(key[it][1]), "+v"(key[it][2]), "+v"(key[it][3]));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (chunk + 1 < n_chunks) { gl += adv; gv += adv; if (OWNKEY) gk += adv; }
-        fetch();
-        float tot[4], exc[4];
-#pragma unroll
-        for (int it = 0; it < 2; ++it) {
-            const bool bnd = (bmask >> (C - 1 - 2 * pr - it)) & 1u;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (FUSED) x[it][e] = __builtin_amdgcn_rcpf(1.0f + exp_neg(x[it][e]));
-                if (!OWNKEY) key[it][e] = 1.0f - x[it][e];
-                x[it][e] = bnd ? 1.0f : x[it][e];
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) tot[e] = x[0][e] * x[1][e];
-        row_scan_mul4(tot, exc);
-        if (pr == 15) *(float4 *)&sTot[chunk & 1][pcol] = make_float4(tot[0], tot[1], tot[2], tot[3]);
-        uint16_t *p = &slot[put];
-        float kt[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) kt[e] = key[0][e] * exc[e];
-        put_pair4(p, p + D, kt, sc);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) kt[e] = key[1][e] * (exc[e] * x[0][e]);
-        put_pair4(p - kStateRow, p - kStateRow + D, kt, sc);
-    };
-
-    f32x4v accS[4];
-    float run[4][4];                               // total decay of the lane's state rows
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        accS[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
-        run[t][0] = run[t][1] = run[t][2] = run[t][3] = 1.0f;
-    }
-    fetch();
-    prepare(0);
-    const SlotPtr<kStateRow> sp0(smem, lane);
-    __syncthreads();
-    for (int chunk = 0; chunk < n_chunks; ++chunk) {
-        prepare(chunk + 1);                        // (past the end: into a slot that nobody reads)
-        const SlotPtr<kStateRow> sp(sp0, (chunk & 1) * Map::kHalfs);
-        const Frag fv = sp.tokens(2 * D + 16 * wave);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const float4 t4 = *(const float4 *)&sTot[chunk & 1][state_channel(t, g)];
-            accS[t][0] *= t4.x; accS[t][1] *= t4.y; accS[t][2] *= t4.z; accS[t][3] *= t4.w;
-            run[t][0] *= t4.x; run[t][1] *= t4.y; run[t][2] *= t4.z; run[t][3] *= t4.w;
-#pragma unroll
-            for (int part = 0; part < 2; ++part) accS[t] = mfma16(sp.state_rows(part * D, t), fv, accS[t]);
-        }
-        __syncthreads();
-    }
-    const RowState us = segment_state(a, b, h, next_t0);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) *us.at((state_channel(t, g) + r) * D + 16 * wave + l16) = accS[t][r];
-    if (wave == 0 && l16 == 0) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) *us.at(D * D + state_channel(t, g) + r) = run[t][r];
-    }
+    const StatePass p{a.lam, OWNKEY ? a.k : nullptr, a.v, nullptr, a.in, a.Hh, a.grid_w, a.start_pos, a.n_tokens, a.mode, plan};
+    const RowState out = segment_state(a, b, h, plan.start(seg + 1));
+    RowState decay = out;                          // after the state: from row 4096 / (floats a row) on
+    decay.base = out.at(D * D);
+    state_pass<0, OWNKEY, FUSED, 0>(p, bh, seg, lds, out, decay);
 }
 
 // Fold: every segment's incoming state, P_0 = state_in, P_{g+1} = diag(A_g) P_g + U_g, in place (each element by one

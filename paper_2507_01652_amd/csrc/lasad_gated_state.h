@@ -45,8 +45,6 @@ __device__ __forceinline__ void state_pass(const StatePass &a, int bh, int seg, 
     // this wavefront's run of chunks, walked towards the segment's start (REV: end)
     const int c_lo = first + n_chunks * wave / 4, c_hi = first + n_chunks * (wave + 1) / 4;
     uint16_t *const slot = (uint16_t *)lds + wave * kStateSlot;
-    SplitConst sc;
-    sc.init();
 
     const int64_t base = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h;
     const uint32_t row = (uint32_t)a.in.stride_n * 2;
@@ -77,12 +75,15 @@ __device__ __forceinline__ void state_pass(const StatePass &a, int bh, int seg, 
 #pragma unroll
         for (int e = 0; e < 8; ++e) R[s][e] = 1.0f;
 
+    if (c_lo < c_hi) fetch(REV ? c_lo : c_hi - 1);             // ahead of everything that does not need it
+    __builtin_amdgcn_sched_barrier(0);
+    SplitConst sc;
+    sc.init();
     RowBoundaries bounds;
     bounds.init(a.start_pos + (REV ? c_lo : c_hi - 1) * C, a.grid_w, a.mode, C);
     const SlotPtr<kStateRow> sp(slot, lane);
     // the token of this lane's step 0 / 1 (in walking order of the running products)
     const int m0 = REV ? 2 * pr : C - 1 - 2 * pr, m1 = REV ? m0 + 1 : m0 - 1;
-    if (c_lo < c_hi) fetch(REV ? c_lo : c_hi - 1);
     for (int i = 0; i < c_hi - c_lo; ++i) {
         const int chunk = REV ? c_lo + i : c_hi - 1 - i;
         const int left = end_tok - chunk * C;
