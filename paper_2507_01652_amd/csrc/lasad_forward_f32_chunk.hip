@@ -15,9 +15,11 @@
 // in registers.
 //
 // Bound by the chain from chunk to chunk on the compute units that have a sequence: 52 matrix instructions of 32 cycles a
-// chunk and SIMD (0.8 us) and the LDS reads, decay and mask between them; 1.7 us a chunk in all.  96 sequences of 256
-// tokens: 27 us a call, 64 with the token-serial kernel (lasad_scan.h), which is left to the vector decay, to bf16
-// storage and to up to four tokens of few sequences; distance from fp64 results the same.
+// chunk and SIMD (0.8 us) and the LDS reads, decay and mask between them; 1.7 us a chunk in all, 0.5 of a chunk that is only
+// taken into the state.  So few sequences are dealt to several workgroups each (Parts).  96 sequences of 256
+// tokens: 22 us a call (27 with one workgroup each), 64 with the token-serial kernel (lasad_scan.h), which is left to the vector
+// decay, to bf16 storage and to up to four tokens of few sequences; distance from fp64 results the same.  (The scores in
+// wavefronts of their own beside those with the state: 31 in the place of 27; a test in the loop for steps without output: 36.)
 #include "lasad_gated_chunk.h"
 
 namespace lasad {
@@ -35,16 +37,24 @@ __device__ __forceinline__ f32x4v mfma_f32(float a, float b, f32x4v acc)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
 }
 
-__global__ void __launch_bounds__(kThreads, 3)
-forward_f32_chunk_kernel(ForwardArgs a)
+// A sequence dealt to several workgroups: part p outputs steps first[p] .. first[p + 1] - 1 (of T tokens) and has to form the
+// state before them by itself, from the steps before, in the same order and with the same operations as the part that outputs those.
+constexpr int kMaxParts = 4;
+struct Parts { int n, first[kMaxParts + 1]; };
+
+template <int PARTS>
+__global__ void __launch_bounds__(kThreads, PARTS ? 1 : 3)
+forward_f32_chunk_kernel(ForwardArgs a, Parts parts)
 {
     __shared__ __attribute__((aligned(16))) float tiles[2][3][T * RS];      // q, k, v
     __shared__ float pw[17];                                                // gamma^0 .. gamma^16
-    const int bh = blockIdx.x, b = bh / a.Hh, h = bh - b * a.Hh;
+    const int bh = PARTS ? blockIdx.x / parts.n : blockIdx.x, part = PARTS ? blockIdx.x - bh * parts.n : 0;
+    const int b = bh / a.Hh, h = bh - b * a.Hh;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l16 = lane & 15, g = lane >> 4;
-    const int n = a.n_tokens, n_steps = (n + T - 1) / T;
+    const int n = a.n_tokens;
+    const int first = PARTS ? parts.first[part] : 0, n_steps = PARTS ? parts.first[part + 1] : (n + T - 1) / T;      // its steps
 
     if (tid < 17) {
         const double gm = a.gamma[h];
@@ -88,21 +98,78 @@ forward_f32_chunk_kernel(ForwardArgs a)
     bounds.init(a.start_pos, a.grid_w, a.mode, T);
     float *const o_lane = (float *)a.o + (int64_t)b * a.out.stride_b + (int64_t)h * a.out.stride_h + col0 + 4 * g;
 
-    fetch(0);
-    put(0);
-    if (n_steps > 1) fetch(1);
+    // tokens of a step that decay (a row past the end does not)
+    auto decaying = [&](int step) {
+        uint32_t decays = ~bounds.mask();
+        bounds.advance();
+        if (n - step * T < T) decays &= (1u << (n - step * T)) - 1;
+        if (step == 0 && a.first_decay_off) decays &= ~1u;
+        return decays;
+    };
+    // S[c][n] <- gamma^e_end S + sum_j K[j][c] gamma^(e_end - e_j) V[j][n] over a chunk
+    auto update = [&](const float *tk, float (&v)[4], int e_end, const int (&e_j)[4]) {
+        const float r_end = pw[e_end];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] *= pw[e_end - e_j[r]];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) S[t] *= r_end;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) S[t] = mfma_f32(tk[(4 * g + r) * RS + 16 * t + l16], v[r], S[t]);
+    };
+
+    fetch(first);
+    if (PARTS && first > 0) {                      // the state before the part: k and v only (full steps)
+        f32x4v before[2][2];
+        auto fetch_kv = [&](int step) {
+#pragma unroll
+            for (int it = 0; it < 2; ++it)
+#pragma unroll
+                for (int x = 0; x < 2; ++x) before[x][it] = *(const f32x4v *)(src[1 + x] + (int64_t)(step * T + srow + 16 * it) * a.in.stride_n);
+        };
+        auto put_kv = [&](int step) {
+#pragma unroll
+            for (int it = 0; it < 2; ++it)
+#pragma unroll
+                for (int x = 0; x < 2; ++x) *(f32x4v *)&tiles[step & 1][1 + x][(srow + 16 * it) * RS + scol] = before[x][it];
+        };
+        fetch_kv(0);
+        put_kv(0);
+        fetch_kv(min(1, first - 1));
+        __syncthreads();
+        for (int step = 0; step < first; ++step) {
+            if (step + 1 < first) {
+                put_kv(step + 1);
+                fetch_kv(min(step + 2, first - 1));
+            }
+            const uint32_t decays = decaying(step);
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const float *tk = &tiles[step & 1][1][16 * half * RS], *tv = &tiles[step & 1][2][16 * half * RS + col0];
+                const uint32_t dm = (decays >> (16 * half)) & 0xffffu;
+                int e_j[4];
+                float v[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    e_j[r] = __builtin_popcount(dm & ((2u << (4 * g + r)) - 1));
+                    v[r] = tv[(4 * g + r) * RS + l16];
+                }
+                update(tk, v, __builtin_popcount(dm), e_j);
+            }
+            __syncthreads();
+        }
+    }
+    put(first);
+    if (first + 1 < n_steps) fetch(first + 1);
     __syncthreads();
-    for (int step = 0; step < n_steps; ++step) {
+    for (int step = first; step < n_steps; ++step) {
         if (step + 1 < n_steps) {
             put(step + 1);
             if (step + 2 < n_steps) fetch(step + 2);
         }
-        // tokens whose step decays (a row past the end does not)
-        uint32_t decays = ~bounds.mask();
-        bounds.advance();
         const int left = n - step * T;
-        if (left < T) decays &= (1u << left) - 1;
-        if (step == 0 && a.first_decay_off) decays &= ~1u;
+        const uint32_t decays = decaying(step);
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             if (half * 16 >= left) break;
@@ -153,22 +220,13 @@ forward_f32_chunk_kernel(ForwardArgs a)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) o = mfma_f32(v[r], p[r], o);
             }
-            // ---- S[c][n] <- gamma^e_end S + sum_j K[j][c] gamma^(e_end - e_j) V[j][n] ----
-            const float r_end = pw[e_end];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] *= pw[e_end - e_j[r]];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) S[t] *= r_end;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) S[t] = mfma_f32(tk[(4 * g + r) * RS + 16 * t + l16], v[r], S[t]);
+            update(tk, v, e_end, e_j);
             const int tok = step * T + 16 * half + l16;
             if (tok < n) *(f32x4v *)(o_lane + (int64_t)tok * a.out.stride_n) = o * a.q_scale;
         }
         __syncthreads();
     }
-    if (a.state_out) {
+    if (a.state_out && (!PARTS || part == parts.n - 1)) {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -176,13 +234,42 @@ forward_f32_chunk_kernel(ForwardArgs a)
     }
 }
 
+// As many parts as leave every workgroup a compute unit, dealt so that they end together.  us a call, one part -> parts: 12
+// sequences of 256 tokens 27.2 -> 16.6 (four), of 1024 97 -> 52; 60 of 256 27.5 -> 18.3, of 1024 98 -> 57; 96 and 128 (two)
+// of 256 28.5 -> 22.2 and 24.1, of 1024 98 -> 77.  Two parts in the place of four: 12 of 256 20.1, of 1024 70.
+Parts deal(int64_t n_seq, int n_steps)
+{
+    constexpr float ratio = 0.35f;                 // of a step without output to one with it (0.2 and 0.5: up to 3 and 15 % slower)
+    int g = (int)(256 / n_seq);
+    if (g > kMaxParts) g = kMaxParts;
+    if (g > n_steps / 2) g = n_steps / 2;
+    if (g < 2) return Parts{1, {0, n_steps}};
+    Parts p{g, {0}};
+    for (float time = (float)n_steps / g;; time += 0.25f) {
+        for (int i = 0; i < g; ++i) {
+            const int more = (int)(time - ratio * p.first[i]);
+            p.first[i + 1] = p.first[i] + (more > 0 ? more : 0);
+            if (p.first[i + 1] > n_steps) p.first[i + 1] = n_steps;
+        }
+        if (p.first[g] == n_steps) break;
+    }
+    while (p.n > 1 && p.first[p.n - 1] == n_steps) --p.n;
+    return p;
+}
+
 }  // namespace
 
 hipError_t launch_forward_f32_chunk(const ForwardArgs &a, hipStream_t s)
 {
     if (a.d != D || a.io_dtype != LASAD_F32 || a.out_dtype != LASAD_F32 || a.n_tokens < 1 || a.lam) return hipErrorInvalidValue;
-    if ((int64_t)a.B * a.Hh > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(forward_f32_chunk_kernel, dim3((unsigned)(a.B * a.Hh)), dim3(kThreads), 0, s, a);
+    const int64_t n_seq = (int64_t)a.B * a.Hh;
+    if (n_seq > 0x7fffffff) return hipErrorInvalidValue;
+    // (a part reads the incoming state when another may have written the final one: not into the same memory)
+    const float *in = a.state_in, *out = a.state_out;
+    const bool in_place = in && out && in < out + n_seq * D * D && out < in + n_seq * D * D;
+    const Parts parts = in_place ? Parts{1, {0}} : deal(n_seq, (a.n_tokens + T - 1) / T);
+    if (parts.n > 1) hipLaunchKernelGGL(forward_f32_chunk_kernel<1>, dim3((unsigned)(n_seq * parts.n)), dim3(kThreads), 0, s, a, parts);
+    else hipLaunchKernelGGL(forward_f32_chunk_kernel<0>, dim3((unsigned)n_seq), dim3(kThreads), 0, s, a, parts);
     return hipGetLastError();
 }
 

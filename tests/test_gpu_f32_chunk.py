@@ -75,3 +75,32 @@ def test_non_finite_value_stays_causal(lasad, oracle, t, bad):
     assert not np.isfinite(o[0, t:, :, c]).any()
     o[0, t:, :, c] = ref[0, t:, :, c]
     assert rel_err(o, ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("n", [127, 128, 129, 160, 257, 1000])
+@pytest.mark.parametrize("Hh", [2, 60, 70, 100, 128])
+def test_dealt_to_several_workgroups(lasad, n, Hh):
+    """Few sequences are dealt to two to four workgroups each, which form the state before their steps with the same
+    operations: the same bits as in a call of so many sequences that each has one workgroup, an infinite value included, and
+    with the final state written over the incoming one."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    many, W, start = 260, 19, 7
+    x = torch.randn((3, 1, n, many, D), generator=gen, device="cuda") / 8
+    x[2, 0, n // 2, 1, 3] = float("inf")
+    s0 = torch.randn((1, many, D, D), generator=gen, device="cuda") * 0.3
+    gamma = torch.rand(many, generator=gen, device="cuda")
+
+    def call(h, in_place):
+        a = x[:, :, :, :h].contiguous()
+        si = s0[:, :h].contiguous()
+        so = si if in_place else torch.empty_like(si)
+        o = lasad.lasad_forward_chunked(a[0], a[1], a[2], gamma[:h].contiguous(), (start + n + W - 1) // W, W, start_pos=start,
+                                        q_scale=0.7, state_in=si, state_out=so)
+        torch.cuda.synchronize()
+        return o, so
+    o, s = call(many, False)
+    for in_place in (False, True):
+        got, st = call(Hh, in_place)
+        assert torch.equal(got.view(torch.int32), o[:, :, :Hh].contiguous().view(torch.int32))
+        assert torch.equal(st.view(torch.int32), s[:, :Hh].contiguous().view(torch.int32))
