@@ -50,7 +50,14 @@ forward_mfma_ws_kernel(ForwardArgs a, MultiPass m)
     // q, k, v and o rows are touched once by a forward call: non-temporal.  The passes of a backward launch read
     // each tensor two or three times and share it through the L2: ordinary loads there.
     constexpr bool NT = !DOT;
-    constexpr int kLdsHalfs = C * RS + 3 * C * VS + 2 * D * RS + C * RS;
+    // How Q comes to the output waves.  A forward call: straight from memory in operand layout, one chunk ahead.  The passes of a
+    // backward launch: whole rows through LDS (QLDS), because there the address unit is the busier one: it spends about four
+    // cycles on every row that an instruction touches, and the operand's pieces of 32 rows are 16 instructions a chunk
+    // where whole rows are 8 of 8 rows.  us a call: backward of 512 sequences of 24 x 24 tokens 129 -> 121, 96 of 64 x 64
+    // 228 -> 206, 1000 of 256 115 -> 106; in the forward the read after the barrier costs more than it saves, 34.0 -> 37.0.
+    // (The fourth tensor of DOT in 16-byte pieces, halves swapped between the lanes: 102 -> 105 in a trace.)
+    constexpr bool QLDS = DOT;
+    constexpr int kLdsHalfs = C * RS + 3 * C * VS + 2 * D * RS + (QLDS ? 2 : 1) * C * RS;
     __shared__ __attribute__((aligned(16))) uint16_t smem[kLdsHalfs];
     __shared__ __attribute__((aligned(16))) float tabC[C];
     static_assert(kLdsHalfs * 2 >= recurrence_lds_floats<D>() * 4, "fallback needs the LDS block");
@@ -61,6 +68,7 @@ forward_mfma_ws_kernel(ForwardArgs a, MultiPass m)
     uint16_t *sSh = sKl + C * VS;      // S^T [dv][dk], bf16 hi / lo
     uint16_t *sSl = sSh + D * RS;
     uint16_t *sO = sSl + D * RS;       // bf16 output tile [token][dv]
+    uint16_t *sQ = sO + C * RS;        // Q as loaded (16-byte row reads)
 
     const int G = a.n_segments;
     const int bh = wg / G, seg = wg - bh * G;
@@ -95,8 +103,14 @@ forward_mfma_ws_kernel(ForwardArgs a, MultiPass m)
 
     if (state_wave) {
         // ===================================== state waves =====================================
-        uint4 rk[2], rv[2];
+        uint4 rk[2], rv[2], rq[2];
+        auto load_q = [&](int t0) {
+#pragma unroll
+            for (int it = 0; it < 2; ++it)
+                rq[it] = gload16<NT>(gq + (int64_t)min(t0 + (st >> 3) + 32 * it, n - 1) * a.in.stride_n + (st & 7) * 8);
+        };
         load_kv<NT>(rk, rv, gk, gv, 0, n, a.in.stride_n, st);
+        if (QLDS) load_q(0);
 
         f32x16 accS;                   // S[dk = wa*32 + 8*(r/4) + 4*g + r%4][dv = wc*32 + l32]
         if (a.state_in) {
@@ -144,8 +158,18 @@ forward_mfma_ws_kernel(ForwardArgs a, MultiPass m)
             const int t0 = chunk * C;
             const int nt = min(C, n - t0);
             write_tiles<true>(sK, sV, sKh, sKl, tabC, rk, rv, sk, st);
+            if (QLDS) {
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {          // (tail rows: queries that nobody stores)
+                    const int row = (st >> 3) + 32 * it;
+                    *(uint4 *)&sQ[row * RS + (st & 7) * 8] = row < nt ? rq[it] : make_uint4(0, 0, 0, 0);
+                }
+            }
             __syncthreads();                              // (A) tiles, c_j table and S^T visible
-            if (chunk + 1 < n_chunks) load_kv<NT>(rk, rv, gk, gv, t0 + C, n, a.in.stride_n, st);
+            if (chunk + 1 < n_chunks) {
+                load_kv<NT>(rk, rv, gk, gv, t0 + C, n, a.in.stride_n, st);
+                if (QLDS) load_q(t0 + C);
+            }
             Frag fv[4];
             load_v_frags(fv, sV, wc, lane);
             state_update(accS, sKh, sKl, fv, wa, lane);
@@ -181,7 +205,7 @@ forward_mfma_ws_kernel(ForwardArgs a, MultiPass m)
 #pragma unroll
         for (int s = 0; s < 4; ++s) fq[s].u = live ? fqn[s].u : make_uint4(0, 0, 0, 0);
     };
-    prefetch_q(0);
+    if (!QLDS) prefetch_q(0);
     GradDot gd;
     if (DOT) gd.init(a, m, pass, in_base);
 
@@ -192,10 +216,16 @@ forward_mfma_ws_kernel(ForwardArgs a, MultiPass m)
         const int t0 = chunk * C;
         const int nt = min(C, n - t0);
         const int qa = wa ^ (chunk & 1);                  // query half of this wave in this chunk
-        take_q(chunk);
+        if (!QLDS) take_q(chunk);
         __syncthreads();                                  // (A)
-        if (chunk + 1 < n_chunks) prefetch_q(chunk + 1);
         const int i_row = qa * 32 + l32;
+        if (DOT) gd.fetch(min(t0 + i_row, n - 1), wc * 32 + 4 * g);
+        if (QLDS) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) fq[s].u = *(const uint4 *)&sQ[i_row * RS + 16 * s + 8 * g];
+        } else if (chunk + 1 < n_chunks) {
+            prefetch_q(chunk + 1);
+        }
 
         const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         f32x16 acc0 = zero16, acc1 = zero16, accO = zero16;
@@ -224,7 +254,6 @@ forward_mfma_ws_kernel(ForwardArgs a, MultiPass m)
                 acc1 = mfma(fk, fq[s], acc1);
             }
         }
-        if (DOT) gd.fetch(min(t0 + i_row, n - 1), wc * 32 + 4 * g);     // (here the Q fragments' registers are free)
         Frag fv[4];
         load_v_frags(fv, sV, wc, lane);
 
