@@ -80,11 +80,13 @@ struct DqSlot {
 // on the scalar unit, plus 32-bit byte offsets.  Rows past the end re-read the last token.
 template <int OWNKEY, int LO, int NG>
 struct DqStage {
+    static constexpr bool TURN = NG == 1 && OWNKEY;        // decay and key: 16 bytes of one row, turned in the slot (as in the forward)
     const char *l, *z, *x, *y, *lo;
     uint32_t row;                      // bytes from token to token
     int left;                          // rows from the chunk's first one on, > 0
     struct Regs {
         uint2 rl[2], rz[2];
+        u32x4 tl, tz;                  // (TURN)
         u32x4 rx, ry, rlo;
     };
     __device__ __forceinline__ void init(const GatedBackwardArgs &a, int64_t base, int n)
@@ -102,9 +104,15 @@ struct DqStage {
         const int last = min(C, left) - 1;
         const uint32_t o0 = min(2 * pr, last) * row + pcol * 2, o1 = min(2 * pr + 1, last) * row + pcol * 2;
         const uint32_t ov = min(st >> 3, last) * row + (st & 7) * 16;
-        f.rl[0] = *(const uint2 *)(l + o0);
-        f.rl[1] = *(const uint2 *)(l + o1);
-        if (OWNKEY) { f.rz[0] = *(const uint2 *)(z + o0); f.rz[1] = *(const uint2 *)(z + o1); }
+        if (TURN) {
+            const uint32_t o = min(Turn<DqSlot::ROW>::row(st & 63), last) * row + Turn<DqSlot::ROW>::byte(st >> 6, st & 63);
+            f.tl = *(const u32x4 *)(l + o);
+            if (OWNKEY) f.tz = *(const u32x4 *)(z + o);
+        } else {
+            f.rl[0] = *(const uint2 *)(l + o0);
+            f.rl[1] = *(const uint2 *)(l + o1);
+            if (OWNKEY) { f.rz[0] = *(const uint2 *)(z + o0); f.rz[1] = *(const uint2 *)(z + o1); }
+        }
         f.rx = *(const u32x4 *)(x + ov);
         f.ry = *(const u32x4 *)(y + ov);
         if (LO) f.rlo = *(const u32x4 *)(lo + ov);
@@ -165,6 +173,7 @@ backward_gated_dq_kernel(GatedChunkArgs p)
         const int first = grp * C < n ? grp * C : 0;           // (a group without a chunk reads the first one, for nobody)
         const int pr = lane & 15, pcol = 16 * lw + 4 * (lane >> 4);
         using Stage = DqStage<OWNKEY, LO, NG>;
+        const Turn<SL::ROW> turn(lw, lane);
         Stage sg;
         sg.init(a, (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + (t0 + first) * a.in.stride_n, n - first);
         typename Stage::Regs r0, r1;               // (one loader group: two chunks of loads in flight)
@@ -210,10 +219,15 @@ backward_gated_dq_kernel(GatedChunkArgs p)
         auto phase_a = [&](typename Stage::Regs &f, int q, int done) {
             const uint32_t bmask = bounds.mask();
             bounds.advance();
+            if (Stage::TURN) {
+                turn.write(slots + q * SL::kHalfs, SL::Zh, f.tl);
+                if (OWNKEY) turn.write(slots + q * SL::kHalfs, SL::Zl, f.tz);
+            } else {
 #pragma unroll
-            for (int it = 0; it < 2; ++it) {
-                unpack4(f.rl[it], x[it]);
-                if (OWNKEY) unpack4(f.rz[it], z[it]);
+                for (int it = 0; it < 2; ++it) {
+                    unpack4(f.rl[it], x[it]);
+                    if (OWNKEY) unpack4(f.rz[it], z[it]);
+                }
             }
             row_live = (st >> 3) < left;
             px = f.rx;
@@ -229,6 +243,7 @@ backward_gated_dq_kernel(GatedChunkArgs p)
             // (the fetched registers are free from here on, and the compiler must see it so: lasad_forward_gated_chunk.hip)
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
+                if (Stage::TURN) break;
                 asm volatile("" : "+v"(x[it][0]), "+v"(x[it][1]), "+v"(x[it][2]), "+v"(x[it][3]));
                 if (OWNKEY) asm volatile("" : "+v"(z[it][0]), "+v"(z[it][1]), "+v"(z[it][2]), "+v"(z[it][3]));
             }
@@ -236,6 +251,13 @@ backward_gated_dq_kernel(GatedChunkArgs p)
             __builtin_amdgcn_sched_barrier(0);
             sg.next(a.in.stride_n);
             sg.fetch(f, pr, pcol, st);
+            if (Stage::TURN) {
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    unpack4(turn.read(slots + q * SL::kHalfs, SL::Zh, it), x[it]);
+                    if (OWNKEY) unpack4(turn.read(slots + q * SL::kHalfs, SL::Zl, it), z[it]);
+                }
+            }
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
 #pragma unroll

@@ -48,12 +48,17 @@ constexpr int64_t kMaxStride = 1 << 25;        // 32 rows of it, two bytes an el
 // This thread's share of a chunk: tokens 2 pr, 2 pr + 1 (pr = lane & 15) and channels 16 lw + 4 (lane >> 4) .. + 3 of
 // q, gate and key, and one 16-byte piece of a V row.  The addresses are a uniform base per tensor, advanced chunk by
 // chunk on the scalar unit, plus 32-bit byte offsets of the lane; rows past the end re-read the last token.
-template <int OWNKEY>
+// TURN (one loader group, own key): of q, gate and key 16 bytes of one row, turned to that share in the chunk's slot
+// (gchunk::Turn).  us a call on rotating buffers: 512 sequences of 24 x 24 tokens 60.5 -> 51.5, 96 of 64 x 64 114 -> 110, 1000 of
+// 16 x 16 59.6 -> 52.8.  With two tensors to turn in the place of three the address unit is not what the loaders wait for:
+// tied key 512 of 24 x 24 46.6 -> 50, fused layer 48.2 -> 48.8.
+template <int OWNKEY, int TURN>
 struct Stage {
     const char *q, *l, *k, *v;
     uint32_t off, voff, row;           // bytes; row: one token on
     int left;                          // tokens from the base on, > 0
     uint2 rq[2], rl[2], rk[2];
+    u32x4 tq, tl, tk;
     uint4 rv;
 
     __device__ __forceinline__ void init(const ForwardArgs &a, int64_t base, int n, int pr, int pcol, int st)
@@ -64,13 +69,22 @@ struct Stage {
         v = (const char *)((const uint16_t *)a.v + base);
         left = n;
         row = (uint32_t)a.in.stride_n * 2;
-        off = 2 * pr * row + pcol * 2;
+        off = TURN ? 0 : 2 * pr * row + pcol * 2;
         voff = (st >> 3) * row + (st & 7) * 16;
     }
     // the chunk at the base.  (Always the same loads: a load under a condition would make the compiler wait for everything
     // outstanding wherever the paths meet.)
     __device__ __forceinline__ void fetch(int pr, int pcol, int st)
     {
+        if (TURN) {
+            const int last = min(left, C) - 1, lane = st & 63;
+            const uint32_t o = min(Turn<kRow>::row(lane), last) * row + Turn<kRow>::byte(st >> 6, lane);
+            tl = *(const u32x4 *)(l + o);
+            tq = *(const u32x4 *)(q + o);
+            if (OWNKEY) tk = *(const u32x4 *)(k + o);
+            rv = *(const uint4 *)(v + (left < C ? min(st >> 3, last) * row + (st & 7) * 16 : voff));
+            return;
+        }
         uint32_t o0 = off, o1 = off + row, ov = voff;
         if (left < C) {
             o0 = min(2 * pr, left - 1) * row + pcol * 2;
@@ -162,7 +176,9 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
         const int first = grp * C < n ? grp * C : 0;           // (a group without a chunk reads the first one, for nobody)
         const int pr = lane & 15, pcol = 16 * lw + 4 * (lane >> 4);
         const int64_t in_base = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + seg_t0 * a.in.stride_n;
-        Stage<OWNKEY> sg;
+        constexpr bool TURN = NG == 1 && OWNKEY;
+        const Turn<kRow> turn(lw, lane);
+        Stage<OWNKEY, TURN> sg;
         sg.init(a, in_base + first * a.in.stride_n, n - first, pr, pcol, st);
         sg.fetch(pr, pcol, st);                    // ahead of everything that does not need it (0.3 us a call)
         __builtin_amdgcn_sched_barrier(0);
@@ -211,14 +227,22 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
 
         // done: the finished chunk to be stored meanwhile, or -1.  Past the end of the sequence (the last periods) the last
         // chunk's data go once more into a slot that nobody reads.
-        auto phase_a = [&](int done) {
+        auto phase_a = [&](int done, int p) {      // (p: the slot to come, TURN)
             const uint32_t bmask = bounds.mask();
             bounds.advance();
+            if (TURN) {                            // where the operands that come of them will be
+                uint16_t *const slot = slots + p * kSlot;
+                turn.write(slot, kColKh, sg.tl);
+                turn.write(slot, kColQh, sg.tq);
+                if (OWNKEY) turn.write(slot, kColKl, sg.tk);
+            }
+            if (!TURN) {
 #pragma unroll
-            for (int it = 0; it < 2; ++it) {
-                pq[it] = sg.rq[it];
-                unpack4(sg.rl[it], x[it]);
-                if (OWNKEY) unpack4(sg.rk[it], key[it]);
+                for (int it = 0; it < 2; ++it) {
+                    pq[it] = sg.rq[it];
+                    unpack4(sg.rl[it], x[it]);
+                    if (OWNKEY) unpack4(sg.rk[it], key[it]);
+                }
             }
             pv = sg.rv;
             v_live = (st >> 3) < left;
@@ -228,6 +252,7 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
             // this one.
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
+                if (TURN) break;
                 asm volatile("" : "+v"(pq[it].x), "+v"(pq[it].y));
                 asm volatile("" : "+v"(x[it][0]), "+v"(x[it][1]), "+v"(x[it][2]), "+v"(x[it][3]));
                 if (OWNKEY) asm volatile("" : "+v"(key[it][0]), "+v"(key[it][1]), "+v"(key[it][2]), "+v"(key[it][3]));
@@ -237,6 +262,15 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
             __builtin_amdgcn_sched_barrier(0);
             sg.next(NG * C, a.in.stride_n);
             sg.fetch(pr, pcol, st);
+            if (TURN) {
+                const uint16_t *const slot = slots + p * kSlot;
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    pq[it] = turn.read(slot, kColQh, it);
+                    unpack4(turn.read(slot, kColKh, it), x[it]);
+                    if (OWNKEY) unpack4(turn.read(slot, kColKl, it), key[it]);
+                }
+            }
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
 #pragma unroll
@@ -325,7 +359,7 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
             // of a call the code itself comes from memory (24 x 64 tokens 5.8 -> 5.5 us).  (The fused layer is 2 % slower so.)
             for (int chunk = -1;; ++chunk) {
                 f = chunk < 0 ? make_int4(0, 0, 0, 0) : *(const int4 *)sTrip[chunk & 1];
-                phase_a(chunk - 1);
+                phase_a(chunk - 1, 0);
                 if (grp == 1 || chunk >= 0) {      // (the first group runs both phases for chunk 0 at once)
                     end_period();
                     if (!fine || ++chunk == n_chunks) break;
@@ -336,7 +370,7 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
                 if (!fine || chunk + 1 == n_chunks) break;
             }
         } else {
-            phase_a(-1);
+            phase_a(-1, 0);
             if (grp == 0) phase_b(0);
             __syncthreads();
             if (NG == 2 && grp == 1) {             // period 0
@@ -346,7 +380,7 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
             }
             for (int chunk = grp; fine && chunk < n_chunks; chunk += NG) {
                 f = *(const int4 *)sTrip[chunk & 1];
-                phase_a(chunk - 1);
+                phase_a(chunk - 1, (chunk + NG) & 1);
                 if (NG == 2) {
                     end_period();
                     if (!fine || chunk + 1 == n_chunks) break;
