@@ -1,16 +1,18 @@
 // Backward pass of the fused layer (Algorithm 1 between its two Linear maps, zero initial state):
 //     q = SiLU(q_pre),  lambda = sigmoid(z),  k = 1 - lambda,  o = recurrence(q, lambda, k, v),
 //     y = o * rstd * w,  rstd = (mean_c(o^2) + eps)^(-1/2)        (per token and head)
-// given d_out = dL/dy.  Composition of existing pieces around two small kernels of this file:
+// given d_out = dL/dy.  Composition of the recurrence's kernels and two small ones of this file:
 //
-//   1. o is recomputed by the forward kernels (activations on load, no norm), fp32, into the workspace;
-//   2. norm_backward_kernel: with gw = d_out * w,
+//   1. o is recomputed by the forward kernels (activations on load, no norm), fp32;
+//   2. the normalisation's backward: with gw = d_out * w,
 //          d_o = rstd gw - o rstd^3 mean_c(gw o),      dw[h][c] += d_out o rstd
 //      d_o goes to the workspace in the inputs' type and with the inputs' strides (the recurrence
-//      kernels read all their operands with one layout); the weight gradient is first summed over
-//      the 64 tokens of a workgroup, in a fixed order;
+//      kernels read all their operands with one layout); the weight gradient is first summed over a
+//      workgroup's tokens, in a fixed order.  bf16: the epilogue of the forward's tiles
+//      (lasad_forward_gated_chunk.hip, NORM 2), o itself reaches no memory; else (fp32, strides the
+//      chunked forward refuses) o goes through the workspace to norm_backward_kernel of this file;
 //   3. the vector-decay backward (lasad_backward_gated.hip) with activations on load and the chain
-//      rule to q_pre and z in its finishing kernel;
+//      rule to q_pre and z where it stores the gradients;
 //   4. weight_grad_kernel adds the per-workgroup sums of step 2, again in a fixed order.
 //
 // Without a normalisation (norm_eps < 0) step 1 is skipped and step 2 only copies d_out.
@@ -181,6 +183,8 @@ hipError_t launch_backward_layer(const LayerBackwardArgs &a, bool use_mfma, hipS
     const bool norm = a.norm_eps >= 0.f;
     const bool in16 = a.io_dtype == LASAD_BF16;
     hipError_t e;
+    bool fused = false;
+    int w_items = nblk;                                                 // parts of the weight gradient's sums per sequence
 
     if (norm) {                                                         // 1. o, fp32, [B][n][Hh][d]
         ForwardArgs f;
@@ -194,10 +198,16 @@ hipError_t launch_backward_layer(const LayerBackwardArgs &a, bool use_mfma, hipS
         f.state_in = nullptr; f.state_out = nullptr;
         f.seg_states = nullptr; f.n_segments = 1; f.seg_chunks = 0;
         f.fused_act = 1; f.norm = 0; f.norm_eps = -1.f; f.norm_w = nullptr;
-        e = (in16 && use_mfma) ? launch_forward_gated_chunk(f, s) : launch_forward_generic(f, s);
+        if (in16 && use_mfma && forward_gated_chunk_fits(f)) {              // ... and 2. in one
+            const NormBackwardArgs nb{a.d_out, a.dout, a.norm_w, a.norm_eps, d_o, d_o_lo, a.d_o_f32, dl, wpart};
+            e = launch_forward_gated_norm_backward(f, nb, &w_items, s);
+            fused = true;
+        } else {
+            e = launch_forward_generic(f, s);
+        }
         if (e != hipSuccess) return e;
     }
-    {                                                                   // 2. d_o (and the weight-gradient partial sums)
+    if (!fused) {                                                       // 2. d_o (and the weight-gradient partial sums)
         const dim3 grid((unsigned)(n_seq * nblk)), block(kNbThreads);
         if (in16 && norm) hipLaunchKernelGGL((norm_backward_kernel<1, 1>), grid, block, 0, s, a, o32, d_o, d_o_lo, dl, wpart, nblk);
         else if (in16) hipLaunchKernelGGL((norm_backward_kernel<1, 0>), grid, block, 0, s, a, o32, d_o, d_o_lo, dl, wpart, nblk);
@@ -208,7 +218,7 @@ hipError_t launch_backward_layer(const LayerBackwardArgs &a, bool use_mfma, hipS
     }
     if (a.d_o_out) {                                                    // the normalisation's part only
         if (a.dweight) {
-            if (norm) hipLaunchKernelGGL(weight_grad_kernel, dim3((unsigned)a.Hh * 4), dim3(1024), 0, s, wpart, a.dweight, a.B, a.Hh, nblk);
+            if (norm) hipLaunchKernelGGL(weight_grad_kernel, dim3((unsigned)a.Hh * 4), dim3(1024), 0, s, wpart, a.dweight, a.B, a.Hh, w_items);
             else return launch_zero_f32(a.dweight, a.Hh * a.d, s);
         }
         return hipGetLastError();
@@ -228,7 +238,7 @@ hipError_t launch_backward_layer(const LayerBackwardArgs &a, bool use_mfma, hipS
     if (e != hipSuccess) return e;
     if (a.dweight) {                                                    // 4. weight gradient (zero without a norm)
         if (norm) {
-            hipLaunchKernelGGL(weight_grad_kernel, dim3((unsigned)a.Hh * 4), dim3(1024), 0, s, wpart, a.dweight, a.B, a.Hh, nblk);
+            hipLaunchKernelGGL(weight_grad_kernel, dim3((unsigned)a.Hh * 4), dim3(1024), 0, s, wpart, a.dweight, a.B, a.Hh, w_items);
             e = hipGetLastError();
         } else {
             e = launch_zero_f32(a.dweight, a.Hh * a.d, s);

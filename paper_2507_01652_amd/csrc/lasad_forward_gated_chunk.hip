@@ -134,10 +134,93 @@ __device__ __noinline__ void redo_sequence(const ForwardArgs *args, int bh, int 
     scan::scan_sequence<1, OUT_BF16, OWNKEY ? scan::OWNKEY : scan::TIED, 64>(a, bh, 0, lds);
 }
 
+// What the normalisation's backward makes of an output row and the gradient of its normalised form, for a lane's eight of the
+// row's channels (the row is eight lanes): d_o = rstd gw - o rstd^3 mean(gw o) with gw = d_out w, and d_out o rstd.
+__device__ __forceinline__ void norm_backward8(const float (&o)[8], uint4 dout, const float (&w)[8], float eps, float (&res)[8], float (&dw)[8])
+{
+    float g[8];
+    const uint32_t words[4] = {dout.x, dout.y, dout.z, dout.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        g[2 * e] = __uint_as_float(words[e] << 16);
+        g[2 * e + 1] = __uint_as_float(words[e] & 0xffff0000u);
+    }
+    float ss = 0.f, go = 0.f, gw[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        gw[e] = g[e] * w[e];
+        ss = fmaf(o[e], o[e], ss);
+        go = fmaf(gw[e], o[e], go);
+    }
+    const float rstd = 1.0f / sqrtf(sum8(ss) * (1.0f / D) + eps);
+    const float back = rstd * rstd * rstd * sum8(go) * (1.0f / D);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        res[e] = gw[e] * rstd - o[e] * back;
+        dw[e] = g[e] * o[e] * rstd;
+    }
+}
+// ... to memory
+__device__ __forceinline__ void store_grad8(const NormBackwardArgs &nb, int64_t i, const float (&res)[8], const SplitConst &sc)
+{
+    if (nb.d_o_f32) {
+        *(float4 *)((float *)nb.d_o + i) = make_float4(res[0], res[1], res[2], res[3]);
+        *(float4 *)((float *)nb.d_o + i + 4) = make_float4(res[4], res[5], res[6], res[7]);
+        return;
+    }
+    uint4 hi, lo;
+    split2(res[0], res[1], hi.x, lo.x, sc);
+    split2(res[2], res[3], hi.y, lo.y, sc);
+    split2(res[4], res[5], hi.z, lo.z, sc);
+    split2(res[6], res[7], hi.w, lo.w, sc);
+    *(uint4 *)((uint16_t *)nb.d_o + i) = hi;
+    if (nb.d_o_lo) *(uint4 *)((uint16_t *)nb.d_o_lo + i) = lo;
+}
+// The same from the fp32 rows that a token-serial walk of tokens t0 .. t0 + n - 1 has left in o, by its 256 threads, and their
+// part of the weight's gradient.
+__device__ __noinline__ void redo_norm_backward(const ForwardArgs *a, const NormBackwardArgs *nb, int bh, int t0, int n, float *wpart, float *lds)
+{
+    const int b = bh / a->Hh, h = bh - b * a->Hh;
+    const int row = threadIdx.x >> 3, col = (threadIdx.x & 7) * 8;
+    SplitConst sc;
+    sc.init();
+    float w[8], sum[8];
+    for (int e = 0; e < 8; ++e) {
+        w[e] = nb->norm_w ? nb->norm_w[h * D + col + e] : 1.0f;
+        sum[e] = 0.f;
+    }
+    __syncthreads();                               // (o is this workgroup's own)
+    for (int t = t0; t < t0 + n; t += 32) {
+        const int tok = min(t + row, t0 + n - 1);  // (all eight lanes of a row take part in its sums)
+        const float *o_row = (const float *)a->o + (int64_t)b * a->out.stride_b + (int64_t)tok * a->out.stride_n + (int64_t)h * a->out.stride_h + col;
+        float o[8], res[8], dw[8];
+        for (int e = 0; e < 8; ++e) o[e] = o_row[e];
+        const uint4 g = *(const uint4 *)((const uint16_t *)nb->d_out + (int64_t)b * nb->dout.stride_b + (int64_t)tok * nb->dout.stride_n +
+                                         (int64_t)h * nb->dout.stride_h + col);
+        norm_backward8(o, g, w, nb->norm_eps, res, dw);
+        if (t + row < t0 + n) {
+            store_grad8(*nb, (int64_t)b * nb->dl.stride_b + (int64_t)tok * nb->dl.stride_n + (int64_t)h * nb->dl.stride_h + col, res, sc);
+            for (int e = 0; e < 8; ++e) sum[e] += dw[e];
+        }
+    }
+    for (int e = 0; e < 8; ++e) lds[row * D + col + e] = sum[e];
+    __syncthreads();
+    if (threadIdx.x < D) {
+        float acc = 0.f;
+        for (int r = 0; r < 32; ++r) acc += lds[r * D + threadIdx.x];
+        wpart[threadIdx.x] = acc;
+    }
+}
+
+// NORM: 1 the normalised output; 2 the output is not stored, but what the normalisation's backward makes of it, from the
+// gradient's row that the loaders hold one tile ahead.  In a pass of its own that was another fp32 tensor written and read, bound
+// by memory: 288 sequences of 16 x 16 tokens 23 + 16 us -> 29, a whole layer backward on rotating buffers 98 -> 90, 512 of 24 x 24
+// 256 -> 222, 96 of 64 x 64 436 -> 388, 300 of 8 x 8 42 -> 38, 12 of 16 x 16 41.7 -> 41.1.
 template <int OUT_BF16, int OWNKEY, int FUSED, int NORM, int NG>
 __global__ void __launch_bounds__((1 + NG) * kThreads, NG == 1 ? 4 : 3)
-forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
+forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan, NormBackwardArgs nb)
 {
+    struct KernelArgs { ForwardArgs a; SegPlan plan; NormBackwardArgs nb; };       // as the launch lays them out
     // tiles, then the segment's incoming state (kept for a redo, which reads it before its own buffers reach that far)
     constexpr int kTileBytes = 2 * kSlot * 2 + 2 * C * OS * 4;
     constexpr int kScanBytes = scan::lds_floats<OWNKEY ? scan::OWNKEY : scan::TIED>() * 4;
@@ -146,7 +229,8 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
     __shared__ __attribute__((aligned(16))) unsigned char smem[kLdsBytes];
     __shared__ __attribute__((aligned(16))) float sTot[2][D];              // A_end per key channel, by chunk parity
     __shared__ __attribute__((aligned(16))) int sTrip[2][4];               // range flag of each loader wavefront, by barrier parity
-    __shared__ __attribute__((aligned(16))) float sW[NORM ? D : 1];        // norm weight times q_scale
+    __shared__ __attribute__((aligned(16))) float sW[NORM ? D : 1];        // norm weight (times q_scale)
+    __shared__ __attribute__((aligned(16))) float sDw[NORM == 2 ? 4 * NG : 1][D];      // each loader wavefront's sums for the weight
     uint16_t *const slots = (uint16_t *)smem;
     float *const outs = (float *)(slots + 2 * kSlot);
 
@@ -165,9 +249,11 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
     // token-serial redo of the sequence by the first four wavefronts, out of line (inlined it would keep the argument
     // block in scratch memory); it reads the arguments where the launch put them
     auto redo = [&]() {
-        if (tid < scan::kThreads)
-            redo_sequence<OUT_BF16, OWNKEY>((const ForwardArgs *)__builtin_amdgcn_kernarg_segment_ptr(), bh, seg_t0, n,
-                                            plan.n_seg > 1 ? seg_state : nullptr, (float *)smem);
+        if (tid >= scan::kThreads) return;
+        const KernelArgs *ka = (const KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        redo_sequence<OUT_BF16, OWNKEY>(&ka->a, bh, seg_t0, n, plan.n_seg > 1 ? seg_state : nullptr, (float *)smem);
+        if (NORM == 2)
+            redo_norm_backward(&ka->a, &ka->nb, bh, seg_t0, n, ka->nb.wpart + ((int64_t)bh * plan.n_seg + seg) * D, (float *)smem);
     };
 
     if (wave >= 4) {
@@ -193,9 +279,38 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
         const int64_t o_lane = orow * a.out.stride_n + ocol;
         int64_t o_chunk = (int64_t)b * a.out.stride_b + (int64_t)h * a.out.stride_h +
                           (seg_t0 + (NG == 2 && grp == 0 ? C : 0)) * a.out.stride_n;
+        // NORM 2: the gradient's row of the next tile to be stored, one period ahead
+        uint4 rg = make_uint4(0u, 0u, 0u, 0u);
+        float dw[8];
+        int g_tok = NG == 2 && grp == 0 ? C : 0;               // that tile's first token (of two groups the second stores chunk 0)
+        auto fetch_dout = [&]() {
+            const int64_t tok = seg_t0 + min(g_tok + orow, n - 1);
+            rg = *(const uint4 *)((const uint16_t *)nb.d_out + (int64_t)b * nb.dout.stride_b + (int64_t)h * nb.dout.stride_h +
+                                  tok * nb.dout.stride_n + ocol);
+            g_tok += NG * C;
+        };
+        if (NORM == 2) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dw[e] = 0.f;
+            fetch_dout();
+        }
         auto store_tile = [&](int chunk) {
             const float *tile = outs + (chunk & 1) * C * OS + orow * OS + ocol;
             float4 u = *(const float4 *)tile, w = *(const float4 *)(tile + 4);
+            if (NORM == 2) {
+                const float4 w0 = *(const float4 *)&sW[ocol], w1 = *(const float4 *)&sW[ocol + 4];
+                const float o[8] = {u.x * a.q_scale, u.y * a.q_scale, u.z * a.q_scale, u.w * a.q_scale,
+                                    w.x * a.q_scale, w.y * a.q_scale, w.z * a.q_scale, w.w * a.q_scale};
+                const float nw[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+                float res[8], dws[8];
+                norm_backward8(o, rg, nw, nb.norm_eps, res, dws);
+                if (chunk * C + orow < n) {
+                    store_grad8(nb, (int64_t)b * nb.dl.stride_b + (int64_t)h * nb.dl.stride_h + (int64_t)(seg_t0 + chunk * C + orow) * nb.dl.stride_n + ocol, res, sc);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) dw[e] += dws[e];
+                }
+                return;
+            }
             if (NORM) {
                 const float ss = (u.x * u.x + u.y * u.y) + (u.z * u.z + u.w * u.w) + ((w.x * w.x + w.y * w.y) + (w.z * w.z + w.w * w.w));
                 const float rstd = __builtin_amdgcn_rsqf(sum8(ss) * ms_scale + a.norm_eps);
@@ -260,6 +375,7 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
             // (the store between the waits for these loads and the issue of the next ones: no wait ever includes a new store)
             if (done >= 0) store_tile(done);
             __builtin_amdgcn_sched_barrier(0);
+            if (NORM == 2 && done >= 0) fetch_dout();
             sg.next(NG * C, a.in.stride_n);
             sg.fetch(pr, pcol, st);
             if (TURN) {
@@ -347,7 +463,8 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
                 put_pair4(rows + it * kRow + kColQh, rows + it * kRow + kColQl, qt, sc);
             }
         };
-        if (NORM && grp == 0 && st < D) sW[st] = a.q_scale * (a.norm_w ? a.norm_w[h * D + st] : 1.0f);
+        if (NORM == 1 && grp == 0 && st < D) sW[st] = a.q_scale * (a.norm_w ? a.norm_w[h * D + st] : 1.0f);
+        if (NORM == 2 && grp == 0 && st < D) sW[st] = nb.norm_w ? nb.norm_w[h * D + st] : 1.0f;
         bool fine = true;
         int4 f;                                    // a chunk's range flags, read at the start of its period and tested at the end
         auto end_period = [&]() {
@@ -392,6 +509,23 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan)
         }
         if (!fine) redo();
         else if (NG == 1 || grp == (n_chunks & 1)) store_tile(n_chunks - 1);
+        if (NORM == 2 && fine) {                   // the weight's gradient: eight rows a wavefront, then the wavefronts
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int m = 8; m <= 32; m <<= 1) dw[e] += __shfl_xor(dw[e], m);
+            if (lane < 8) {
+                *(float4 *)&sDw[wave - 4][8 * lane] = make_float4(dw[0], dw[1], dw[2], dw[3]);
+                *(float4 *)&sDw[wave - 4][8 * lane + 4] = make_float4(dw[4], dw[5], dw[6], dw[7]);
+            }
+            __syncthreads();                       // (the compute wavefronts have left)
+            if (grp == 0 && st < D) {
+                float acc = 0.f;
+#pragma unroll
+                for (int w = 0; w < 4 * NG; ++w) acc += sDw[w][st];
+                nb.wpart[((int64_t)bh * plan.n_seg + seg) * D + st] = acc;
+            }
+        }
         return;
     }
 
@@ -567,15 +701,19 @@ SegPlan segment_plan(int64_t n_seq, int n_tokens)
 
 }  // namespace
 
-hipError_t launch_forward_gated_chunk(const ForwardArgs &a, hipStream_t s)
+bool forward_gated_chunk_fits(const ForwardArgs &a) { return a.in.stride_n <= kMaxStride; }
+
+static hipError_t launch(const ForwardArgs &a, const NormBackwardArgs *nb, int *n_seg, hipStream_t s)
 {
     if (a.d != D || a.io_dtype != LASAD_BF16 || a.n_tokens < 1 || !a.lam) return hipErrorInvalidValue;
     if ((a.fused_act && a.k) || (a.norm && !a.fused_act)) return hipErrorInvalidValue;      // the layer of Algorithm 1 ties the key to the gate
     const int64_t n_seq = (int64_t)a.B * a.Hh;
     if (n_seq > 0x7fffffff) return hipErrorInvalidValue;
-    if (a.in.stride_n > kMaxStride) return launch_forward_generic(a, s);      // (a lane's offsets in a chunk are 32 bits)
+    if (!forward_gated_chunk_fits(a)) return nb ? hipErrorInvalidValue : launch_forward_generic(a, s);      // (a lane's offsets in a chunk are 32 bits)
     const bool out16 = a.out_dtype == LASAD_BF16;
     const SegPlan plan = segment_plan(n_seq, a.n_tokens);
+    if (n_seg) *n_seg = plan.n_seg;
+    const NormBackwardArgs none{};
     if (plan.n_seg > 1) {
         const dim3 sgrid((unsigned)(n_seq * (plan.n_seg - 1)));
         if (a.fused_act) hipLaunchKernelGGL((gated_segment_state_kernel<0, 1>), sgrid, dim3(256), 0, s, a, plan);
@@ -594,16 +732,25 @@ hipError_t launch_forward_gated_chunk(const ForwardArgs &a, hipStream_t s)
     const int ng = n_wg <= 256 && a.n_tokens > (a.k ? 96 : 32) ? 2 : 1;
     const dim3 grid((unsigned)n_wg), block((1 + ng) * kThreads);
 #define LASAD_LAUNCH1(O, K, F, N) do { \
-        if (ng == 2) hipLaunchKernelGGL((forward_gated_chunk_kernel<O, K, F, N, 2>), grid, block, 0, s, a, plan); \
-        else hipLaunchKernelGGL((forward_gated_chunk_kernel<O, K, F, N, 1>), grid, block, 0, s, a, plan); } while (0)
+        if (ng == 2) hipLaunchKernelGGL((forward_gated_chunk_kernel<O, K, F, N, 2>), grid, block, 0, s, a, plan, nb ? *nb : none); \
+        else hipLaunchKernelGGL((forward_gated_chunk_kernel<O, K, F, N, 1>), grid, block, 0, s, a, plan, nb ? *nb : none); } while (0)
 #define LASAD_LAUNCH(K, F, N) do { if (out16) LASAD_LAUNCH1(1, K, F, N); else LASAD_LAUNCH1(0, K, F, N); } while (0)
-    if (a.norm) LASAD_LAUNCH(0, 1, 1);
+    if (nb) LASAD_LAUNCH1(0, 0, 1, 2);
+    else if (a.norm) LASAD_LAUNCH(0, 1, 1);
     else if (a.fused_act) LASAD_LAUNCH(0, 1, 0);
     else if (a.k) LASAD_LAUNCH(1, 0, 0);
     else LASAD_LAUNCH(0, 0, 0);
 #undef LASAD_LAUNCH
 #undef LASAD_LAUNCH1
     return hipGetLastError();
+}
+
+hipError_t launch_forward_gated_chunk(const ForwardArgs &a, hipStream_t s) { return launch(a, nullptr, nullptr, s); }
+
+hipError_t launch_forward_gated_norm_backward(const ForwardArgs &a, const NormBackwardArgs &nb, int *n_seg, hipStream_t s)
+{
+    if (!a.fused_act || a.norm || a.out_dtype != LASAD_F32) return hipErrorInvalidValue;
+    return launch(a, &nb, n_seg, s);
 }
 
 }  // namespace lasad

@@ -71,6 +71,19 @@ struct MultiPass {
     int first_decay_off[3] = {0, 0, 0};
 };
 
+// The normalisation's backward as the epilogue of a vector-decay forward whose own output nobody else wants (bf16; the
+// ForwardArgs are a fused layer's without a norm, o an fp32 scratch of [B, n, Hh, d]).
+struct NormBackwardArgs {
+    const void *d_out;             // dL/d(normalised output)
+    lasad_layout_t dout;
+    const float *norm_w;           // [Hh, d] or NULL (ones)
+    float norm_eps;
+    void *d_o, *d_o_lo;            // dL/d(recurrence output), layout dl: a bf16 pair hi + lo, or (d_o_lo NULL) one tensor,
+    int d_o_f32;                   //   bf16 or fp32
+    lasad_layout_t dl;
+    float *wpart;                  // [sequence][segment][d]: sums of d_out o rstd
+};
+
 struct DecodeArgs {
     const void *q, *k, *v;
     const void *lam;             // vector decay [B, Hh, d], or NULL: per-head gamma (k NULL: key = 1 - lam)
@@ -190,6 +203,9 @@ hipError_t launch_forward_scan(const ForwardArgs &a, hipStream_t s);
 hipError_t launch_forward_mfma(const ForwardArgs &a, hipStream_t s);
 // bf16 in, d == 64, vector decay (lam given): MFMA chunked kernel.
 hipError_t launch_forward_gated_chunk(const ForwardArgs &a, hipStream_t s);
+// with the normalisation's backward; n_seg: segments a sequence (of wpart)
+bool forward_gated_chunk_fits(const ForwardArgs &a);
+hipError_t launch_forward_gated_norm_backward(const ForwardArgs &a, const NormBackwardArgs &nb, int *n_seg, hipStream_t s);
 // the same with eight wavefronts per sequence (whole sequences only, no segment plan)
 hipError_t launch_forward_mfma_ws(const ForwardArgs &a, hipStream_t s);
 // twelve wavefronts, doubled LDS buffers, one barrier per chunk: for workgroups that own a compute unit
@@ -200,7 +216,7 @@ hipError_t launch_forward_mfma_multi(const ForwardArgs &common, const MultiPass 
 size_t forward_mfma_workspace_bytes(int64_t n_seq, int n_tokens);
 hipError_t launch_decode(const DecodeArgs &a, hipStream_t s);
 // Backward of the scalar-decay forward: three runs of the forward kernels (MFMA kernel if
-// use_mfma, else the generic / scan kernels) plus two small finishing kernels.
+// use_mfma, else the generic / scan kernels) plus two small kernels.
 hipError_t launch_backward(const BackwardArgs &a, bool use_mfma, hipStream_t s);
 hipError_t launch_zero_f32(float *p, int n, hipStream_t s);
 hipError_t launch_copy_state(const float *src, float *dst, int64_t n, hipStream_t s);   // dst = src (zeros if src is NULL)

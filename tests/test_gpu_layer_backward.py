@@ -251,3 +251,21 @@ def test_backward_layer_head_major_inputs(lasad, oracle):
     dev_in = tuple(to_hm(x) for x in (q, z, v, g))
     assert dev_in[0].stride(1) == 64 and dev_in[0].stride(2) == H * W * 64
     _check_parts(lasad, oracle, dev_in, q, z, v, g, H, W, w, 1e-5)
+
+
+@pytest.mark.parametrize("B,Hh,H,W,gate", [
+    (1, 1, 1, 32, None), (2, 2, 1, 33, None), (2, 2, 5, 13, None),     # two loader groups: one, two and three chunks
+    (130, 2, 5, 13, None), (130, 2, 1, 32, None),                      # one loader group
+    (1, 2, 31, 67, None),                                              # segments, the last one short
+    (1, 2, 31, 67, 1500),                                              # ... one of them left to the token-serial walk
+    (130, 2, 5, 13, 40), (1, 2, 6, 11, 40),                            # a range left in a later chunk
+])
+def test_backward_layer_norm_in_the_recomputed_forward(lasad, oracle, B, Hh, H, W, gate):
+    """The normalisation's backward is the recomputed forward's epilogue: every tile edge of both loader arrangements, a
+    sequence cut into segments, and the token-serial walk (gate: strong gates from this token on, for 40 tokens)."""
+    q, z, v, g = _inputs(B, H * W, Hh, 64, "bf16", 900 + B + H * W)
+    if gate is not None:
+        z[:, gate:gate + 40] = wl.store_round(z[:, gate:gate + 40] - np.float32(3.5), "bf16")
+    w = _weight(Hh, 64)
+    dev_in = tuple(lasad.to_device(x, "bf16") for x in (q, z, v, g))
+    _check_parts(lasad, oracle, dev_in, q, z, v, g, H, W, w, 1e-5, q_scale=0.125)
