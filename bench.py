@@ -433,9 +433,9 @@ def bench_gated(args, timer, torch, lasad, wl):
         b_s = b_ms * 1e-3
         bwd = {"workload": w.name + " (q, gate, v, d_o; k = 1 - gate)", "value": w.B * w.N / b_s, "unit": "tokens/s",
                "ms_per_step": b_ms, "steps_timed": bsteps,
-               "launches_per_step": "one launch of the chunked matrix-core kernel over the 3 passes (dq, dv, dk) + 1 finishing kernel "
-                                    "(suffix sums for dlam)",
-               "roofline": hbm_roofline("lasad_backward_gated (both launches of one call)", bytes_bwd, b_s,
+               "launches_per_step": "dq walk + reversed walk (dv, dk, dlam; few long sequences: + state passes and folds; up to 80 "
+                                    "short sequences: 3 passes in one launch + 1 finishing kernel)",
+               "roofline": hbm_roofline("lasad_backward_gated (all launches of one call)", bytes_bwd, b_s,
                                         measured_traffic("gated_backward", w.name))}
         del grads, ws_b, td
     # the same launch with Algorithm 1's elementwise steps fused in (SiLU, sigmoid, RMS norm): the gate buffers
@@ -452,8 +452,8 @@ def bench_gated(args, timer, torch, lasad, wl):
             lasad.lasad_forward_layer(a, b, c, w.grid_h, w.grid_w, out=o)
 
     layer_ms, _, _ = timer.steps(run_layer, steps, warm)
-    # backward of the fused layer: forward recomputation, norm backward, the three passes with the
-    # activations on load, finishing kernel with the chain rule, weight-gradient sum
+    # backward of the fused layer: forward recomputation with the norm backward, the two walks with the
+    # activations on load and the chain rule, weight-gradient sum
     layer_bwd = None
     if not args.no_backward:
         td = lasad.to_device(wl.store_round(np.random.default_rng(w.seed + 101).standard_normal(q.shape, dtype=np.float32)
@@ -474,7 +474,8 @@ def bench_gated(args, timer, torch, lasad, wl):
         lb_s = lb_ms * 1e-3
         layer_bwd = {"workload": w.name + " (q_pre, z, v, d_out; SiLU, sigmoid gate, tied key, RMS norm)",
                      "value": w.B * w.N / lb_s, "unit": "tokens/s", "ms_per_step": lb_ms, "steps_timed": lsteps,
-                     "launches_per_step": "forward recomputation + norm backward + 3-pass kernel + finishing kernel + weight-gradient sum",
+                     "launches_per_step": "forward recomputation with the norm backward + the launches of the vector-decay backward "
+                                          "+ weight-gradient sum",
                      "roofline": hbm_roofline("lasad_backward_layer (all launches of one call)", bytes_bwd, lb_s,
                                               measured_traffic("layer_backward", w.name))}
         del grads, ws_l, td, dwt
