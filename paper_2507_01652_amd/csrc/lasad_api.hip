@@ -565,8 +565,8 @@ static int backward_gated_impl(const void *q, const void *lam, const void *k, co
         }
         return LASAD_OK;
     }
-    // the states at segment bounds come last and may be left out: some longer calls have fewer, and a workspace that was
-    // sized for one of them serves a shorter one
+    // the states at segment bounds come last, as many as there is room for: some longer calls have fewer, and a workspace that
+    // was sized for one of them serves a shorter one
     const int64_t n_seq = (int64_t)B * n_heads;
     const size_t need = lasad::backward_gated_workspace_bytes(n_seq, n_tokens, d) +
                         (carried ? lasad::backward_gated_carried_extra_bytes(n_seq, d) : 0);
@@ -582,8 +582,8 @@ static int backward_gated_impl(const void *q, const void *lam, const void *k, co
     a.start_pos = start_pos; a.n_tokens = n_tokens;
     a.mode = boundary_mode; a.q_scale = q_scale;
     a.workspace = workspace;
-    const bool bounds_fit = workspace_bytes - need >= lasad::backward_gated_bounds_bytes(n_seq, n_tokens, d);
-    a.bounds = bounds_fit ? (float *)((char *)workspace + need) : nullptr;
+    a.bounds = (float *)((char *)workspace + need);
+    a.bounds_bytes = workspace_bytes - need;
     a.fused_act = 0; a.d_o_lo = nullptr;
     a.state_in = state_in; a.d_state_out = d_state_out; a.d_state_in = d_state_in;
     hipError_t e = lasad::launch_backward_gated(a, (hipStream_t)hip_stream);

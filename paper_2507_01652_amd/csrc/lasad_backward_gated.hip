@@ -338,21 +338,6 @@ void finish_segments(int64_t n_seq, int n, int *n_seg, int *seg_blocks)
 // 36.6; 96 x 400 48.4 -> 46.0 -> 46.0; 96 x 576 58 -> 59 -> 53; 128 x 576 63 -> 60 -> 56; 96 x 4096 410 -> 378 -> 264; uncut only: 160
 // x 1024 126 -> 109, 240 x 4096 752 -> 470, 512 x 576 234 -> 167.
 struct ChunkPlan { bool passes; int n_seg, n_part; };          // parts: of a segment
-ChunkPlan chunk_plan(int64_t n_seq, int n)
-{
-    const int nblk = (n + kFinBlock - 1) / kFinBlock;
-    int parts, part_blocks;
-    finish_segments(n_seq, n, &parts, &part_blocks);
-    if (n_seq <= 80 && nblk <= (n_seq <= 48 ? 10 : 14)) return ChunkPlan{true, parts, 1};
-    if (n_seq > 128 || nblk < 8) return ChunkPlan{false, 1, parts};
-    int g = (int)(256 / n_seq);
-    if (g > kMaxSegments) g = kMaxSegments;
-    if (g > nblk / 2) g = nblk / 2;
-    const int blocks = (nblk + g - 1) / g;
-    g = (nblk + blocks - 1) / blocks;
-    return ChunkPlan{false, g, (parts + g - 1) / g};
-}
-
 // Floats of scratch for it: the states at the bounds and a flag per sequence and side or segment; of the walks also what the
 // suffix sums start from.  0: none.
 struct BoundsLayout { size_t s, g, parts, sinks, flags, total; };
@@ -367,6 +352,32 @@ BoundsLayout bounds_layout(const ChunkPlan &p, int64_t n_seq)
     l.flags = l.sinks + (p.passes ? 0 : (size_t)n_seq * kMaxSegments * kD);
     l.total = l.flags + (p.passes ? 1 : p.n_seg) * flags;
     return l;
+}
+
+// The plan that suits the sizes, where `room` floats of scratch hold what it keeps at the bounds (a workspace sized for another
+// call may have less); else fewer segments, and without room for those what is fastest without them: us, own key, three passes
+// against uncut walks: 12 x 1024 tokens 48 | 84, 48 x 4096 214 | 325, 80 x 1024 76 | 88, but 96 x 4096 410 | 378.  Three segments
+// are worth the walks there, and two where the passes have no compute unit to spare.
+ChunkPlan chunk_plan(int64_t n_seq, int n, size_t room)
+{
+    const int nblk = (n + kFinBlock - 1) / kFinBlock;
+    auto fits = [&](const ChunkPlan &p) { return bounds_layout(p, n_seq).total <= room; };
+    int parts, part_blocks;
+    finish_segments(n_seq, n, &parts, &part_blocks);
+    const bool few = n_seq <= 80;
+    if (!(few && nblk <= (n_seq <= 48 ? 10 : 14)) && n_seq <= 128 && nblk >= 8) {
+        int most = (int)(256 / n_seq);
+        if (most > kMaxSegments) most = kMaxSegments;
+        if (most > nblk / 2) most = nblk / 2;
+        for (int g = most; g >= (n_seq <= 48 ? 3 : 2); --g) {
+            const int blocks = (nblk + g - 1) / g;
+            g = (nblk + blocks - 1) / blocks;
+            const ChunkPlan p{false, g, (parts + g - 1) / g};
+            if (fits(p)) return p;
+        }
+    }
+    const ChunkPlan whole{few, few ? parts : 1, few ? 1 : parts};
+    return fits(whole) ? whole : ChunkPlan{few, 1, 1};
 }
 
 }  // namespace
@@ -385,7 +396,7 @@ size_t backward_gated_workspace_bytes(int64_t n_seq, int n_tokens, int d)
 
 size_t backward_gated_bounds_bytes(int64_t n_seq, int n_tokens, int d)
 {
-    return d == kD && n_tokens > 0 ? bounds_layout(chunk_plan(n_seq, n_tokens), n_seq).total * sizeof(float) : 0;
+    return d == kD && n_tokens > 0 ? bounds_layout(chunk_plan(n_seq, n_tokens, SIZE_MAX), n_seq).total * sizeof(float) : 0;
 }
 
 hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
@@ -414,7 +425,7 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
     // step: the shifted decay of step 0 is neutral); the dv pass ends with g_1 / q_scale
     const bool carried = b.state_in || b.d_state_out || b.d_state_in;
     const size_t mat = (size_t)n_seq * b.d * b.d;
-    const ChunkPlan plan = chunk_plan(n_seq, n);
+    const ChunkPlan plan = chunk_plan(n_seq, n, b.bounds ? b.bounds_bytes / sizeof(float) : 0);
     float *cw = dk32 + (size_t)n_seq * n * b.d + (size_t)n_seq * 8 * b.d;      // after the gradients and the segment totals
     float *hS = cw, *sn = cw + mat, *g1 = cw + 2 * mat, *sink_buf = cw + 3 * mat;
     const float *sink = (carried && b.d_state_out) ? sink_buf : nullptr;
@@ -481,7 +492,7 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
         p.dq32 = dq32; p.dk32 = dk32;
         p.g_in = st_in[1]; p.s_out = st_out[0]; p.g_out = st_out[1]; p.sink = sink;
         const int n_chunks = (n + gchunk::C - 1) / gchunk::C;
-        const bool bounds = b.bounds && plan.n_seg * plan.n_part > 1;
+        const bool bounds = plan.n_seg * plan.n_part > 1;
         p.cut = gchunk::SegPlan{1, n_chunks, 0};
         p.n_part = 1;
         p.bounds_s = p.bounds_g = p.parts_s = p.sinks = nullptr;
@@ -529,7 +540,7 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
         p[2].q = v_l; p[2].o = w.o[2]; p[2].out = wl_rev; p[2].out_dtype = LASAD_F32;                  // dk
         p[2].v_lo = gl_l;
         for (int y = 0; y < 3; ++y) { p[y].state_in = st_in[y]; p[y].state_out = st_out[y]; }
-        if (b.bounds && plan.passes && n_seg > 1) {
+        if (plan.passes && plan.n_seg > 1) {
             float *const side[3] = {b.bounds, nullptr, b.bounds + bounds_layout(plan, n_seq).g};
             for (int y = 0; y < 3; y += 2) {
                 p[y].seg_states = side[y];

@@ -233,6 +233,7 @@ hipError_t launch_backward_layer(const LayerBackwardArgs &a, bool use_mfma, hipS
     g.mode = a.mode; g.q_scale = a.q_scale;
     g.workspace = ws + r.core;
     g.bounds = o32;                                                     // (free by now; 32 KB a bound, 64 KB and more of o a segment)
+    g.bounds_bytes = r.d_o - r.o32;
     g.fused_act = 1; g.d_o_lo = d_o_lo;
     e = launch_backward_gated(g, s);
     if (e != hipSuccess) return e;

@@ -154,8 +154,9 @@ struct GatedBackwardArgs {
     int mode;
     float q_scale;
     void *workspace;
-    float *bounds;                       // backward_gated_bounds_bytes of scratch for the states at segment bounds; NULL: sums
-                                         //   of dq and dk take their place (slower, and a third of the accuracy of dlam)
+    float *bounds;                       // scratch for the states at segment bounds, best backward_gated_bounds_bytes: with less
+    size_t bounds_bytes;                 //   of it there are fewer bounds, or sums of dq and dk take their place (slower, and a
+                                         //   third of the accuracy of dlam)
     const void *d_o_lo;                  // fused_act with bf16 inputs: low-order bf16 part of d_o (d_o is hi + lo), else NULL
     int fused_act;                       // 1: q and lam hold Algorithm 1's pre-activation query and gate logits
                                          // (tied key only); dq and dlam are then the gradients of THOSE tensors
