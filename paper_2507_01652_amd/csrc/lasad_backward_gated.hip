@@ -338,19 +338,18 @@ void finish_segments(int64_t n_seq, int n, int *n_seg, int *seg_blocks)
 // 36.6; 96 x 400 48.4 -> 46.0 -> 46.0; 96 x 576 58 -> 59 -> 53; 128 x 576 63 -> 60 -> 56; 96 x 4096 410 -> 378 -> 264; uncut only: 160
 // x 1024 126 -> 109, 240 x 4096 752 -> 470, 512 x 576 234 -> 167.
 struct ChunkPlan { bool passes; int n_seg, n_part; };          // parts: of a segment
-// Floats of scratch for it: the states at the bounds and a flag per sequence and side or segment; of the walks also what the
+// Floats of scratch for it: the states at the bounds, of the passes also a flag per sequence and side, of the walks what the
 // suffix sums start from.  0: none.
-struct BoundsLayout { size_t s, g, parts, sinks, flags, total; };
+struct BoundsLayout { size_t s, g, parts, sinks, total; };
 BoundsLayout bounds_layout(const ChunkPlan &p, int64_t n_seq)
 {
-    const size_t states = (size_t)n_seq * (p.n_seg - 1) * kD * kD, flags = (size_t)(n_seq + 63) / 64 * 64;
-    BoundsLayout l{0, 0, 0, 0, 0, 0};
+    const size_t side = (size_t)n_seq * (p.n_seg - 1) * kD * kD + (p.passes ? (size_t)(n_seq + 63) / 64 * 64 : 0);
+    BoundsLayout l{0, 0, 0, 0, 0};
     if (p.n_seg * p.n_part == 1) return l;
-    l.g = states + (p.passes ? flags : 0);
-    l.parts = l.g + states;
+    l.g = side;
+    l.parts = l.g + side;
     l.sinks = l.parts + (size_t)n_seq * p.n_seg * (p.n_part - 1) * kD * kD;
-    l.flags = l.sinks + (p.passes ? 0 : (size_t)n_seq * kMaxSegments * kD);
-    l.total = l.flags + (p.passes ? 1 : p.n_seg) * flags;
+    l.total = l.sinks + (p.passes ? 0 : (size_t)n_seq * kMaxSegments * kD);
     return l;
 }
 
@@ -390,7 +389,7 @@ size_t backward_gated_carried_extra_bytes(int64_t n_seq, int d)
 
 size_t backward_gated_workspace_bytes(int64_t n_seq, int n_tokens, int d)
 {
-    // dq and dk in fp32, then the finishing kernel's segment totals (at most 8 segments per sequence)
+    // dq and dk in fp32, then the finishing kernel's segment totals (at most 8 segments per sequence) or the walks' flags
     return 2 * (size_t)n_seq * n_tokens * d * sizeof(float) + (size_t)n_seq * 8 * d * sizeof(float);
 }
 
@@ -496,14 +495,14 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
         p.cut = gchunk::SegPlan{1, n_chunks, 0};
         p.n_part = 1;
         p.bounds_s = p.bounds_g = p.parts_s = p.sinks = nullptr;
-        p.kept = nullptr;
+        static_assert(kMaxSegments <= 8 * kD, "the flags take the place of the finishing kernel's segment totals");
+        p.kept = (int *)(dk32 + (size_t)n_seq * n * b.d);
         if (bounds) {
             const BoundsLayout l = bounds_layout(plan, n_seq);
             p.cut = gchunk::SegPlan{plan.n_seg, n_chunks / plan.n_seg, n_chunks % plan.n_seg};
             p.n_part = plan.n_part;
             p.bounds_s = b.bounds + l.s; p.bounds_g = b.bounds + l.g; p.parts_s = b.bounds + l.parts;
             p.sinks = b.bounds + l.sinks;
-            p.kept = (int *)(b.bounds + l.flags);
         }
         for (int y = 0; y < 3; ++y) {
             p.serial[y] = f;

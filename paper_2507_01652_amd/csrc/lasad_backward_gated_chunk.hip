@@ -23,8 +23,11 @@
 // us).  Its address unit is as busy as its vector units, which is why rows are read and written as whole lines wherever LDS can
 // turn them: finished rows stored straight from the lanes that make them took 400 us in the place of 314 (uncut).
 //
-// A chunk that leaves the range of the factorisation sends the workgroup to the token-serial walk
-// of the same passes (lasad_scan.h with operand roles).
+// A chunk that leaves the range of the factorisation sends the sequence (segment) to the token-serial walks of the same passes
+// (lasad_scan.h with operand roles).  The dq walk only says so and ends; the reversed kernel's workgroup then has a compute unit
+// and sixteen wavefronts for all three, side by side, and the finishing step.  us a call whose gates all leave the range (own
+// key), one after the other -> side by side: 96 x 256 tokens 288 -> 139, 96 x 1024 in segments 591 -> 284, 240 x 1024 1187 -> 528,
+// 512 x 576 1206 -> 624.  (Three passes with a compute unit or half of one each: 119, 433, 764, 756.)
 #include "lasad_gated_chunk.h"
 #include "lasad_gated_finish.h"
 #include "lasad_gated_backward.h"
@@ -42,11 +45,12 @@ constexpr int64_t kMaxStride = (1 << 25) - 1;  // 32 rows of it, four bytes an e
 
 __device__ __forceinline__ const float *state_of(const float *states, int bh) { return states ? states + (int64_t)bh * D * D : nullptr; }
 
-// Token-serial walk `w` (0 dq, 1 dv, 2 dk) of walking steps m0 .. m0 + n - 1 of sequence bh, from the state s_in (64 x 64, or NULL).
+// Token-serial walk `w` (0 dq, 1 dv, 2 dk) of walking steps m0 .. m0 + n - 1 of sequence bh, from the state s_in (64 x 64, or NULL),
+// by four wavefronts of the workgroup.
 // Out of line, and handed the arguments where the launch put them (the kernel-argument segment): references to the
 // kernel's by-value parameter, or copies, would make every thread of every launch write them to its stack first.
 template <int OUT_BF16, int COL>
-__device__ __noinline__ void redo_walk(const GatedChunkArgs *p, int w, int bh, int m0, int n, const float *s_in, float *s_out, float *lds)
+__device__ __noinline__ void redo_walk(const GatedChunkArgs *p, int w, int bh, int m0, int n, const float *s_in, float *s_out, LdsFloat *lds)
 {
     ForwardArgs a = p->serial[w];
     scan::ScanRoles r = p->roles[w];
@@ -59,8 +63,8 @@ __device__ __noinline__ void redo_walk(const GatedChunkArgs *p, int w, int bh, i
     a.n_tokens = n;
     a.state_in = s_in ? s_in - (int64_t)bh * D * D : nullptr;
     a.state_out = s_out;
-    if (COL) scan::scan_sequence<1, 0, scan::ROLES_COL, 64>(a, bh, 0, lds, &r);
-    else scan::scan_sequence<1, OUT_BF16, scan::ROLES_ROW, 64>(a, bh, 0, lds, &r);
+    if (COL) scan::scan_sequence<1, 0, scan::ROLES_COL, 64, 1>(a, bh, 0, (float *)lds, &r);
+    else scan::scan_sequence<1, OUT_BF16, scan::ROLES_ROW, 64, 1>(a, bh, 0, (float *)lds, &r);
 }
 
 // ============================================ dq, forward order ============================================
@@ -141,7 +145,6 @@ backward_gated_dq_kernel(GatedChunkArgs p)
 {
     using SL = DqSlot;
     constexpr int LO = FUSED;
-    static_assert(SL::kBytes >= scan::lds_floats<scan::ROLES_ROW>() * 4, "the redo needs the LDS block");
     __shared__ __attribute__((aligned(16))) unsigned char smem[SL::kBytes];
     __shared__ __attribute__((aligned(16))) float sTot[2][D];  // A_end per key channel, by chunk parity
     __shared__ __attribute__((aligned(16))) int sTrip[2][4];   // range flag of each loader wavefront, by barrier parity
@@ -160,12 +163,6 @@ backward_gated_dq_kernel(GatedChunkArgs p)
     const int n_chunks = NG == 1 ? (n + 2 * C - 1) / (2 * C) * 2 : (n + C - 1) / C;
     SplitConst sc;
     sc.init();
-    auto redo = [&]() {
-        if (tid >= scan::kThreads) return;
-        const GatedChunkArgs *kp = (const GatedChunkArgs *)__builtin_amdgcn_kernarg_segment_ptr();
-        redo_walk<0, 1>(kp, 0, bh, t0, n, seg ? kp->bound_s(bh, seg - 1) : state_of(kp->b.state_in, bh),
-                        last_seg ? kp->s_out : nullptr, (float *)smem);
-    };
 
     if (wave >= 4) {
         // ===================================== loader wavefronts =====================================
@@ -369,8 +366,7 @@ backward_gated_dq_kernel(GatedChunkArgs p)
                 end_period();
             }
         }
-        if (!fine) redo();
-        else if (NG == 1 || grp == (n_chunks & 1)) store_tile(n_chunks - 1);
+        if (fine && (NG == 1 || grp == (n_chunks & 1))) store_tile(n_chunks - 1);
         return;
     }
 
@@ -464,11 +460,8 @@ backward_gated_dq_kernel(GatedChunkArgs p)
         fine = fine && (f.x | f.y | f.z | f.w) == 0;
         __syncthreads();
     }
-    if (p.n_part > 1 && tid == 0) p.kept[bh * p.cut.n_seg + seg] = fine;
-    if (!fine) {
-        redo();
-        return;
-    }
+    if (tid == 0) p.kept[bh * p.cut.n_seg + seg] = fine;
+    if (!fine) return;
     if (p.s_out && last_seg) {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -548,27 +541,43 @@ __device__ __forceinline__ void put_grad4(uint16_t *p, float a, float b, float c
     else *(float4 *)p = make_float4(a, b, c, d);
 }
 
-// The token-serial walks of a segment of the reversed order, and the finishing step on what they leave.
+// The token-serial walks of a segment, by four wavefronts each, and the finishing step on what they leave, by all of them.
+// dq only where its own walk did not hold: else it is there, and so is the sink.
+constexpr int kRedoFloats = scan::lds_floats<scan::ROLES_ROW, 1>();
 template <int OUT_BF16>
-__device__ __noinline__ void redo_reversed(const GatedChunkArgs *p, int bh, int seg, float *lds)
+__device__ __noinline__ void redo_reversed(const GatedChunkArgs *p, int bh, int seg, LdsFloat *lds)
 {
     const int t_lo = p->cut.start(seg);
     const bool last_seg = seg == p->cut.n_seg - 1;
     const int t_hi = last_seg ? p->b.n_tokens : p->cut.start(seg + 1);
     const float *sink = p->sink_of(bh, seg);
-    const float *s_in = last_seg ? state_of(p->g_in, bh) : p->bound_g(bh, seg);
+    const float *g_in = last_seg ? state_of(p->g_in, bh) : p->bound_g(bh, seg);
     const int m0 = p->b.n_tokens - t_hi, n = t_hi - t_lo;
-    redo_walk<OUT_BF16, 0>(p, 1, bh, m0, n, s_in, seg == 0 ? p->g_out : nullptr, lds);
-    __syncthreads();
-    redo_walk<OUT_BF16, 1>(p, 2, bh, m0, n, s_in, nullptr, lds);
-    __syncthreads();                               // (dk32 is this workgroup's own)
-    for (int ch0 = 0; ch0 < D; ch0 += 16) {
-        const FinishWalk<1, OUT_BF16, 16> f(p->b, p->dq32, p->dk32, bh, ch0);
-        f.walk(t_lo, t_hi, sink && threadIdx.x < 16 ? sink[ch0 + threadIdx.x] : 0.f, lds);
-        __syncthreads();
+    const bool no_dq = !p->kept[bh * p->cut.n_seg + seg];
+    const int walk = __builtin_amdgcn_readfirstlane(threadIdx.x / scan::kThreads);
+    LdsFloat *const mine = lds + walk * kRedoFloats;
+    if (walk == 0 && no_dq) redo_walk<0, 1>(p, 0, bh, t_lo, n, seg ? p->bound_s(bh, seg - 1) : state_of(p->b.state_in, bh), last_seg ? p->s_out : nullptr, mine);
+    else if (walk == 1) redo_walk<OUT_BF16, 0>(p, 1, bh, m0, n, g_in, seg == 0 ? p->g_out : nullptr, mine);
+    else if (walk == 2) redo_walk<OUT_BF16, 1>(p, 2, bh, m0, n, g_in, nullptr, mine);
+    else scan::barriers_only<1>(n);
+    __syncthreads();                               // (dq32, dk32 and s_out of this sequence are this workgroup's own)
+    const int c = threadIdx.x;
+    float carry = 0.f;
+    if (sink && c < D) {
+        if (last_seg && no_dq) {                   // sum_n H[c][n] S_n[c][n], as gated_carried_finish_kernel adds it up
+            float part[4] = {0.f, 0.f, 0.f, 0.f};
+            const int64_t row = (int64_t)bh * D * D + c * D;
+            for (int i = 0; i < D; ++i) part[i >> 4] = fmaf(p->b.d_state_out[row + i], p->s_out[row + i], part[i >> 4]);
+            carry = (part[0] + part[1]) + (part[2] + part[3]);
+        } else {
+            carry = sink[c];
+        }
     }
+    const FinishWalk<1, OUT_BF16, D> f(p->b, p->dq32, p->dk32, bh, 0);
+    f.walk(t_lo, t_hi, carry, (float *)lds);
 }
 
+// (The redo is called in one place, which all roles come to: three calls took 0.7 us of every launch, 81 sequences of 64 tokens.)
 // One workgroup per sequence or segment, one barrier per chunk: in the period of chunk c four compute wavefronts take its dv
 // and four its dk, four loaders prepare chunk c + 1, and four finishing wavefronts turn chunk c - 1 into dq, dk, dlam and dv.
 template <int OUT_BF16, int OWNKEY, int FUSED>
@@ -577,8 +586,9 @@ backward_gated_reversed_kernel(GatedChunkArgs p)
 {
     constexpr int LO = FUSED;
     using SL = RevSlot<OUT_BF16, OWNKEY, LO>;
-    static_assert(SL::kBytes >= scan::lds_floats<scan::ROLES_ROW>() * 4, "the redo needs the LDS block");
-    __shared__ __attribute__((aligned(16))) unsigned char smem[SL::kBytes];
+    constexpr int kRedoBytes = 3 * kRedoFloats * 4;
+    static_assert(kRedoBytes >= finish_lds_floats<D>() * 4, "the finishing step needs the LDS block");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SL::kBytes > kRedoBytes ? SL::kBytes : kRedoBytes];
     __shared__ __attribute__((aligned(16))) float sTot[2][D];      // A_end per key channel, by chunk parity
     __shared__ __attribute__((aligned(16))) float sSync[D];        // <G, S> at a part's bound
     __shared__ __attribute__((aligned(16))) int sTrip[2][4];       // range flag of each loader wavefront, by barrier parity
@@ -598,13 +608,10 @@ backward_gated_reversed_kernel(GatedChunkArgs p)
     const int n_chunks = (t_hi - t_lo + pad) / C;
     SplitConst sc;
     sc.init();
-    auto redo = [&]() {
-        if (tid >= scan::kThreads) return;
-        const GatedChunkArgs *kp = (const GatedChunkArgs *)__builtin_amdgcn_kernarg_segment_ptr();
-        redo_reversed<OUT_BF16>(kp, bh, seg, (float *)smem);
-    };
+    const int lost = !p.kept[bh * p.cut.n_seg + seg];      // (tested with the first chunk's flags)
+    bool fine = true;
     // the next bound between parts, from the segment's end on, and the chunks walked when it is reached
-    int part = p.n_part > 1 && p.kept[bh * p.cut.n_seg + seg] ? p.n_part - 1 : 0;
+    int part = p.n_part - 1;
     auto part_chunks = [&]() { return part > 0 ? n_chunks - part * n_chunks / p.n_part : 0; };
     int part_at = part_chunks();
 
@@ -759,17 +766,13 @@ backward_gated_reversed_kernel(GatedChunkArgs p)
         };
         prepare(0, pad);
         __syncthreads();
-        bool fine = true;
         for (int chunk = 0; fine && chunk < n_chunks; ++chunk) {
             const int4 f = *(const int4 *)sTrip[chunk & 1];
             prepare((chunk + 1) & 1, -1);          // (past the end the last one goes once more into a slot that nobody reads)
-            fine = (f.x | f.y | f.z | f.w) == 0;
+            fine = (f.x | f.y | f.z | f.w | lost) == 0;
             __syncthreads();
         }
-        if (!fine) redo();
-        return;
-    }
-    if (wave >= 12) {
+    } else if (wave >= 12) {
         // ===================================== finishing wavefronts =====================================
         const uint16_t *l = (const uint16_t *)a.lam + in_base, *z = (const uint16_t *)a.q + in_base;
         const uint16_t *k = OWNKEY ? (const uint16_t *)a.k + in_base : nullptr;
@@ -968,189 +971,185 @@ backward_gated_reversed_kernel(GatedChunkArgs p)
             at -= C * a.grad.stride_n;
         };
         __syncthreads();
-        bool fine = true;
         for (int chunk = 0; fine && chunk < n_chunks; ++chunk) {
             const int4 f = *(const int4 *)sTrip[chunk & 1];
             if (chunk > 0) finish(chunk - 1);
             take(chunk);
-            fine = (f.x | f.y | f.z | f.w) == 0;
+            fine = (f.x | f.y | f.z | f.w | lost) == 0;
             __syncthreads();
         }
-        if (!fine) return;                         // (the first four wavefronts redo it all)
-        finish(n_chunks - 1);
-        __syncthreads();                           // (the other wavefronts have left)
-        Leaving rest;
-        read_done(rest, n_chunks - 1);
-        store(rest, n_chunks - 1, at + C * a.grad.stride_n);
-        return;
-    }
-
-    // ===================================== compute wavefronts =====================================
-    __builtin_amdgcn_s_setprio(2);                 // the chain from chunk to chunk; the loaders fill the gaps
-    const int l16 = lane & 15, g = lane >> 4;
-    const bool is_dk = wave >= 4;
-    const int col0 = 16 * (wave & 3);              // value channels (dv) / key channels (dk) of this wavefront
-    // element (t, r) of the accumulators: dv: G[state_channel(t, g) + r][col0 + l16]; dk: the same of G^T
-    const int s_lane = is_dk ? (col0 + l16) * D : col0 + l16, s_step = is_dk ? 1 : D;
-    f32x4v accS[4];
-    const f32x4v zero4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < 4; ++t) accS[t] = zero4;
-    if (const float *g_in = last_seg ? state_of(p.g_in, bh) : p.bound_g(bh, seg)) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) accS[t][r] = g_in[s_lane + (state_channel(t, g) + r) * s_step];
-    }
-    __syncthreads();
-    bool fine = true;
-    if (!is_dk) {
-        for (int chunk = 0; fine && chunk < n_chunks; ++chunk) {
-            const int4 f = *(const int4 *)sTrip[chunk & 1];
-            const SlotPtr<SL::ROW> sp(slots + (chunk & 1) * SL::kHalfs, lane);
-            f32x4v p00 = zero4, p01 = zero4, p11 = zero4;          // scores P^T[j][i]: (Q~ tile, K^ tile)
-            f32x4v o0 = zero4, o1 = zero4;                         // O^T[n][i] of the two row tiles
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                if (s) __builtin_amdgcn_sched_barrier(0);
-                const Frag q0h = sp.rows(0, SL::Qh, s), q1h = sp.rows(16, SL::Qh, s);
-                const Frag q0l = sp.rows(0, SL::Ql, s), q1l = sp.rows(16, SL::Ql, s);
-                const Frag k0h = sp.rows(0, SL::Zh, s), k0l = sp.rows(0, SL::Zl, s);
-                const Frag k1h = sp.rows(16, SL::Zh, s), k1l = sp.rows(16, SL::Zl, s);
-                Frag sh, sl;
-                split_tiles(accS[2 * s], accS[2 * s + 1], sh, sl, sc);
-                p00 = mfma16(k0h, q0h, p00);
-                p01 = mfma16(k0h, q1h, p01);
-                p11 = mfma16(k1h, q1h, p11);
-                o0 = mfma16(sh, q0h, o0);
-                o1 = mfma16(sh, q1h, o1);
-                p00 = mfma16(k0l, q0h, p00);
-                p01 = mfma16(k0l, q1h, p01);
-                p11 = mfma16(k1l, q1h, p11);
-                o0 = mfma16(sl, q0h, o0);
-                o1 = mfma16(sl, q1h, o1);
-                p00 = mfma16(k0h, q0l, p00);
-                p01 = mfma16(k0h, q1l, p01);
-                p11 = mfma16(k1h, q1l, p11);
-                o0 = mfma16(sh, q0l, o0);
-                o1 = mfma16(sh, q1l, o1);
-            }
-            causal_mask(p00, lane);
-            causal_mask(p11, lane);
-            Frag ph, pl;
-            const Frag fv = sp.tokens(SL::Y + col0);
-            Frag fl;
-            if (LO) fl = sp.tokens(SL::Lo + col0);
-            // ---- G[c][n] += sum_j Q~[j][c] g[j][n], O^T[n][i] += sum_j g[j][n] P^T[j][i] ----
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const Frag zh = sp.state_rows(SL::Zh, t);
-                accS[t] = mfma16(zh, fv, accS[t]);
-                accS[t] = mfma16(sp.state_rows(SL::Zl, t), fv, accS[t]);
-                if (LO) accS[t] = mfma16(zh, fl, accS[t]);
-            }
-            split_tiles(p00, zero4, ph, pl, sc);
-            o0 = mfma16(fv, ph, o0);
-            o0 = mfma16(fv, pl, o0);
-            if (LO) o0 = mfma16(fl, ph, o0);
-            split_tiles(p01, p11, ph, pl, sc);
-            o1 = mfma16(fv, ph, o1);
-            o1 = mfma16(fv, pl, o1);
-            if (LO) o1 = mfma16(fl, ph, o1);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float4 t4 = *(const float4 *)&sTot[chunk & 1][state_channel(t, g)];
-                accS[t][0] *= t4.x; accS[t][1] *= t4.y; accS[t][2] *= t4.z; accS[t][3] *= t4.w;
-            }
-            float *tile = outs + (chunk & 1) * C * OS + l16 * OS + col0 + 4 * g;
-            *(float4 *)tile = make_float4(o0[0], o0[1], o0[2], o0[3]);
-            *(float4 *)(tile + 16 * OS) = make_float4(o1[0], o1[1], o1[2], o1[3]);
-            fine = (f.x | f.y | f.z | f.w) == 0;
-            __syncthreads();
+        if (fine) {
+            finish(n_chunks - 1);
+            __syncthreads();                       // (the other wavefronts have left)
+            Leaving rest;
+            read_done(rest, n_chunks - 1);
+            store(rest, n_chunks - 1, at + C * a.grad.stride_n);
         }
     } else {
-        for (int chunk = 0; fine && chunk < n_chunks; ++chunk) {
-            const int4 f = *(const int4 *)sTrip[chunk & 1];
-            const SlotPtr<SL::ROW> sp(slots + (chunk & 1) * SL::kHalfs, lane);
-            f32x4v p00 = zero4, p01 = zero4, p11 = zero4;          // scores P^T[j][i]: (g tile, v tile)
-            f32x4v o0 = zero4, o1 = zero4;                         // O^T[c][i] / A of the two row tiles
+        // ===================================== compute wavefronts =====================================
+        __builtin_amdgcn_s_setprio(2);                 // the chain from chunk to chunk; the loaders fill the gaps
+        const int l16 = lane & 15, g = lane >> 4;
+        const bool is_dk = wave >= 4;
+        const int col0 = 16 * (wave & 3);              // value channels (dv) / key channels (dk) of this wavefront
+        // element (t, r) of the accumulators: dv: G[state_channel(t, g) + r][col0 + l16]; dk: the same of G^T
+        const int s_lane = is_dk ? (col0 + l16) * D : col0 + l16, s_step = is_dk ? 1 : D;
+        f32x4v accS[4];
+        const f32x4v zero4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const Frag x0 = sp.rows(0, SL::X, s), x1 = sp.rows(16, SL::X, s);
-                const Frag y0 = sp.rows(0, SL::Y, s), y1 = sp.rows(16, SL::Y, s);
-                Frag l0, l1;
-                if (LO) { l0 = sp.rows(0, SL::Lo, s); l1 = sp.rows(16, SL::Lo, s); }
-                Frag sh, sl;
-                split_tiles(accS[2 * s], accS[2 * s + 1], sh, sl, sc);
-                p00 = mfma16(y0, x0, p00);
-                p01 = mfma16(y0, x1, p01);
-                p11 = mfma16(y1, x1, p11);
-                o0 = mfma16(sh, x0, o0);
-                o1 = mfma16(sh, x1, o1);
-                if (LO) {
-                    p00 = mfma16(l0, x0, p00);
-                    p01 = mfma16(l0, x1, p01);
-                    p11 = mfma16(l1, x1, p11);
+        for (int t = 0; t < 4; ++t) accS[t] = zero4;
+        if (const float *g_in = last_seg ? state_of(p.g_in, bh) : p.bound_g(bh, seg)) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) accS[t][r] = g_in[s_lane + (state_channel(t, g) + r) * s_step];
+        }
+        __syncthreads();
+        if (!is_dk) {
+            for (int chunk = 0; fine && chunk < n_chunks; ++chunk) {
+                const int4 f = *(const int4 *)sTrip[chunk & 1];
+                const SlotPtr<SL::ROW> sp(slots + (chunk & 1) * SL::kHalfs, lane);
+                f32x4v p00 = zero4, p01 = zero4, p11 = zero4;          // scores P^T[j][i]: (Q~ tile, K^ tile)
+                f32x4v o0 = zero4, o1 = zero4;                         // O^T[n][i] of the two row tiles
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    if (s) __builtin_amdgcn_sched_barrier(0);
+                    const Frag q0h = sp.rows(0, SL::Qh, s), q1h = sp.rows(16, SL::Qh, s);
+                    const Frag q0l = sp.rows(0, SL::Ql, s), q1l = sp.rows(16, SL::Ql, s);
+                    const Frag k0h = sp.rows(0, SL::Zh, s), k0l = sp.rows(0, SL::Zl, s);
+                    const Frag k1h = sp.rows(16, SL::Zh, s), k1l = sp.rows(16, SL::Zl, s);
+                    Frag sh, sl;
+                    split_tiles(accS[2 * s], accS[2 * s + 1], sh, sl, sc);
+                    p00 = mfma16(k0h, q0h, p00);
+                    p01 = mfma16(k0h, q1h, p01);
+                    p11 = mfma16(k1h, q1h, p11);
+                    o0 = mfma16(sh, q0h, o0);
+                    o1 = mfma16(sh, q1h, o1);
+                    p00 = mfma16(k0l, q0h, p00);
+                    p01 = mfma16(k0l, q1h, p01);
+                    p11 = mfma16(k1l, q1h, p11);
+                    o0 = mfma16(sl, q0h, o0);
+                    o1 = mfma16(sl, q1h, o1);
+                    p00 = mfma16(k0h, q0l, p00);
+                    p01 = mfma16(k0h, q1l, p01);
+                    p11 = mfma16(k1h, q1l, p11);
+                    o0 = mfma16(sh, q0l, o0);
+                    o1 = mfma16(sh, q1l, o1);
                 }
-                o0 = mfma16(sl, x0, o0);
-                o1 = mfma16(sl, x1, o1);
-            }
-            causal_mask(p00, lane);
-            causal_mask(p11, lane);
-            Frag ph, pl;
-            const Frag zh = sp.tokens(SL::Zh + col0), zl = sp.tokens(SL::Zl + col0);
-            // ---- G^T[e][c] += sum_j g[j][e] Q~[j][c], O^T[c][i] += sum_j Q~[j][c] P^T[j][i] ----
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const Frag fy = sp.state_rows(SL::Y, t);
-                accS[t] = mfma16(fy, zh, accS[t]);
-                accS[t] = mfma16(fy, zl, accS[t]);
-                if (LO) accS[t] = mfma16(sp.state_rows(SL::Lo, t), zh, accS[t]);
-            }
-            split_tiles(p00, zero4, ph, pl, sc);
-            o0 = mfma16(zh, ph, o0);
-            o0 = mfma16(zl, ph, o0);
-            o0 = mfma16(zh, pl, o0);
-            split_tiles(p01, p11, ph, pl, sc);
-            o1 = mfma16(zh, ph, o1);
-            o1 = mfma16(zl, ph, o1);
-            o1 = mfma16(zh, pl, o1);
-            const float end = sTot[chunk & 1][col0 + l16];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) accS[t] *= end;
-            if (chunk + 1 == part_at) {
-                // sum over the value channels of G (at the chunk's last row) times S before it
-                const float *s = p.part_s(bh, seg, part - 1) + s_lane;
-                float acc = 0.f;
+                causal_mask(p00, lane);
+                causal_mask(p11, lane);
+                Frag ph, pl;
+                const Frag fv = sp.tokens(SL::Y + col0);
+                Frag fl;
+                if (LO) fl = sp.tokens(SL::Lo + col0);
+                // ---- G[c][n] += sum_j Q~[j][c] g[j][n], O^T[n][i] += sum_j g[j][n] P^T[j][i] ----
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    const f32x4v s4 = *(const f32x4v *)(s + state_channel(t, g));
-                    acc += (s4[0] * accS[t][0] + s4[1] * accS[t][1]) + (s4[2] * accS[t][2] + s4[3] * accS[t][3]);
+                    const Frag zh = sp.state_rows(SL::Zh, t);
+                    accS[t] = mfma16(zh, fv, accS[t]);
+                    accS[t] = mfma16(sp.state_rows(SL::Zl, t), fv, accS[t]);
+                    if (LO) accS[t] = mfma16(zh, fl, accS[t]);
                 }
-                acc += __shfl_xor(acc, 16);
-                acc += __shfl_xor(acc, 32);
-                if (g == 0) sSync[col0 + l16] = acc;
-                --part;
-                part_at = part_chunks();
+                split_tiles(p00, zero4, ph, pl, sc);
+                o0 = mfma16(fv, ph, o0);
+                o0 = mfma16(fv, pl, o0);
+                if (LO) o0 = mfma16(fl, ph, o0);
+                split_tiles(p01, p11, ph, pl, sc);
+                o1 = mfma16(fv, ph, o1);
+                o1 = mfma16(fv, pl, o1);
+                if (LO) o1 = mfma16(fl, ph, o1);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float4 t4 = *(const float4 *)&sTot[chunk & 1][state_channel(t, g)];
+                    accS[t][0] *= t4.x; accS[t][1] *= t4.y; accS[t][2] *= t4.z; accS[t][3] *= t4.w;
+                }
+                float *tile = outs + (chunk & 1) * C * OS + l16 * OS + col0 + 4 * g;
+                *(float4 *)tile = make_float4(o0[0], o0[1], o0[2], o0[3]);
+                *(float4 *)(tile + 16 * OS) = make_float4(o1[0], o1[1], o1[2], o1[3]);
+                fine = (f.x | f.y | f.z | f.w | lost) == 0;
+                __syncthreads();
             }
-            // O^T row 4 g + r is key channel col0 + 4 g + r of token l16 / 16 + l16 (its A: with the end of the chunk)
-            float *tile = outs + (2 + (chunk & 1)) * C * OS + l16 * OS + col0 + 4 * g;
-            *(float4 *)tile = make_float4(o0[0], o0[1], o0[2], o0[3]);
-            *(float4 *)(tile + 16 * OS) = make_float4(o1[0], o1[1], o1[2], o1[3]);
-            fine = (f.x | f.y | f.z | f.w) == 0;
-            __syncthreads();
+        } else {
+            for (int chunk = 0; fine && chunk < n_chunks; ++chunk) {
+                const int4 f = *(const int4 *)sTrip[chunk & 1];
+                const SlotPtr<SL::ROW> sp(slots + (chunk & 1) * SL::kHalfs, lane);
+                f32x4v p00 = zero4, p01 = zero4, p11 = zero4;          // scores P^T[j][i]: (g tile, v tile)
+                f32x4v o0 = zero4, o1 = zero4;                         // O^T[c][i] / A of the two row tiles
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const Frag x0 = sp.rows(0, SL::X, s), x1 = sp.rows(16, SL::X, s);
+                    const Frag y0 = sp.rows(0, SL::Y, s), y1 = sp.rows(16, SL::Y, s);
+                    Frag l0, l1;
+                    if (LO) { l0 = sp.rows(0, SL::Lo, s); l1 = sp.rows(16, SL::Lo, s); }
+                    Frag sh, sl;
+                    split_tiles(accS[2 * s], accS[2 * s + 1], sh, sl, sc);
+                    p00 = mfma16(y0, x0, p00);
+                    p01 = mfma16(y0, x1, p01);
+                    p11 = mfma16(y1, x1, p11);
+                    o0 = mfma16(sh, x0, o0);
+                    o1 = mfma16(sh, x1, o1);
+                    if (LO) {
+                        p00 = mfma16(l0, x0, p00);
+                        p01 = mfma16(l0, x1, p01);
+                        p11 = mfma16(l1, x1, p11);
+                    }
+                    o0 = mfma16(sl, x0, o0);
+                    o1 = mfma16(sl, x1, o1);
+                }
+                causal_mask(p00, lane);
+                causal_mask(p11, lane);
+                Frag ph, pl;
+                const Frag zh = sp.tokens(SL::Zh + col0), zl = sp.tokens(SL::Zl + col0);
+                // ---- G^T[e][c] += sum_j g[j][e] Q~[j][c], O^T[c][i] += sum_j Q~[j][c] P^T[j][i] ----
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const Frag fy = sp.state_rows(SL::Y, t);
+                    accS[t] = mfma16(fy, zh, accS[t]);
+                    accS[t] = mfma16(fy, zl, accS[t]);
+                    if (LO) accS[t] = mfma16(sp.state_rows(SL::Lo, t), zh, accS[t]);
+                }
+                split_tiles(p00, zero4, ph, pl, sc);
+                o0 = mfma16(zh, ph, o0);
+                o0 = mfma16(zl, ph, o0);
+                o0 = mfma16(zh, pl, o0);
+                split_tiles(p01, p11, ph, pl, sc);
+                o1 = mfma16(zh, ph, o1);
+                o1 = mfma16(zl, ph, o1);
+                o1 = mfma16(zh, pl, o1);
+                const float end = sTot[chunk & 1][col0 + l16];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) accS[t] *= end;
+                if (chunk + 1 == part_at) {
+                    // sum over the value channels of G (at the chunk's last row) times S before it
+                    const float *s = p.part_s(bh, seg, part - 1) + s_lane;
+                    float acc = 0.f;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const f32x4v s4 = *(const f32x4v *)(s + state_channel(t, g));
+                        acc += (s4[0] * accS[t][0] + s4[1] * accS[t][1]) + (s4[2] * accS[t][2] + s4[3] * accS[t][3]);
+                    }
+                    acc += __shfl_xor(acc, 16);
+                    acc += __shfl_xor(acc, 32);
+                    if (g == 0) sSync[col0 + l16] = acc;
+                    --part;
+                    part_at = part_chunks();
+                }
+                // O^T row 4 g + r is key channel col0 + 4 g + r of token l16 / 16 + l16 (its A: with the end of the chunk)
+                float *tile = outs + (2 + (chunk & 1)) * C * OS + l16 * OS + col0 + 4 * g;
+                *(float4 *)tile = make_float4(o0[0], o0[1], o0[2], o0[3]);
+                *(float4 *)(tile + 16 * OS) = make_float4(o1[0], o1[1], o1[2], o1[3]);
+                fine = (f.x | f.y | f.z | f.w | lost) == 0;
+                __syncthreads();
+            }
+        }
+        if (fine && p.g_out && seg == 0 && !is_dk) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) p.g_out[(int64_t)bh * D * D + s_lane + (state_channel(t, g) + r) * s_step] = accS[t][r];
         }
     }
-    if (!fine) {
-        redo();
-        return;
-    }
-    if (p.g_out && seg == 0 && !is_dk) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) p.g_out[(int64_t)bh * D * D + s_lane + (state_channel(t, g) + r) * s_step] = accS[t][r];
-    }
+    if (!fine)                                     // (every wavefront, after the barrier of the period that found a chunk out of range)
+        redo_reversed<OUT_BF16>((const GatedChunkArgs *)__builtin_amdgcn_kernarg_segment_ptr(), bh, seg, (LdsFloat *)smem);
 }
 
 // ============================================ segments ============================================

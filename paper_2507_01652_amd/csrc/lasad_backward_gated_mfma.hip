@@ -52,10 +52,10 @@ constexpr int kLdsBytes = Slot<DQ>::kBytes > Slot<DV>::kBytes ? Slot<DQ>::kBytes
 // them (the kernel-argument segment): references to the kernel's by-value parameter, or copies,
 // would make every thread of every launch write them to its stack first.
 template <int OUT_BF16, int COL>
-__device__ __noinline__ void redo_roles(const ForwardArgs *a, const scan::ScanRoles *r, int bh, float *lds)
+__device__ __noinline__ void redo_roles(const ForwardArgs *a, const scan::ScanRoles *r, int bh, LdsFloat *lds)
 {
-    if (COL) scan::scan_sequence<1, 0, scan::ROLES_COL, 64>(*a, bh, 0, lds, r);
-    else scan::scan_sequence<1, OUT_BF16, scan::ROLES_ROW, 64>(*a, bh, 0, lds, r);
+    if (COL) scan::scan_sequence<1, 0, scan::ROLES_COL, 64>(*a, bh, 0, (float *)lds, r);
+    else scan::scan_sequence<1, OUT_BF16, scan::ROLES_ROW, 64>(*a, bh, 0, (float *)lds, r);
 }
 
 // A loader thread's share of a chunk: tokens 2 pr, 2 pr + 1 and channels pcol .. + 3 of the decay, z and (ROW) query
@@ -150,7 +150,7 @@ __device__ __forceinline__ void pass_body(const ForwardArgs &a, const ForwardArg
     SplitConst sc;
     sc.init();
     auto redo = [&]() {
-        if (tid < scan::kThreads) redo_roles<OUT_BF16, COL>(ka, kr, bh, (float *)smem);
+        if (tid < scan::kThreads) redo_roles<OUT_BF16, COL>(ka, kr, bh, (LdsFloat *)smem);
     };
 
     if (wave >= 4) {

@@ -119,7 +119,7 @@ __device__ __forceinline__ RowState segment_state(const ForwardArgs &a, int b, i
 
 // The token-serial walk of tokens t0 .. t0 + n - 1 of a sequence, from the state s_in (or the call's state_in).
 template <int OUT_BF16, int OWNKEY>
-__device__ __noinline__ void redo_sequence(const ForwardArgs *args, int bh, int t0, int n, const float *s_in, float *lds)
+__device__ __noinline__ void redo_sequence(const ForwardArgs *args, int bh, int t0, int n, const float *s_in, LdsFloat *lds)
 {
     ForwardArgs a = *args;
     a.q = (const uint16_t *)a.q + t0 * a.in.stride_n;
@@ -131,7 +131,7 @@ __device__ __noinline__ void redo_sequence(const ForwardArgs *args, int bh, int 
     if (t0 + n < a.n_tokens) a.state_out = nullptr;
     a.n_tokens = n;
     if (s_in) a.state_in = s_in - (int64_t)bh * D * D;
-    scan::scan_sequence<1, OUT_BF16, OWNKEY ? scan::OWNKEY : scan::TIED, 64>(a, bh, 0, lds);
+    scan::scan_sequence<1, OUT_BF16, OWNKEY ? scan::OWNKEY : scan::TIED, 64>(a, bh, 0, (float *)lds);
 }
 
 // What the normalisation's backward makes of an output row and the gradient of its normalised form, for a lane's eight of the
@@ -251,7 +251,7 @@ forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan, NormBackwardArgs nb)
     auto redo = [&]() {
         if (tid >= scan::kThreads) return;
         const KernelArgs *ka = (const KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
-        redo_sequence<OUT_BF16, OWNKEY>(&ka->a, bh, seg_t0, n, plan.n_seg > 1 ? seg_state : nullptr, (float *)smem);
+        redo_sequence<OUT_BF16, OWNKEY>(&ka->a, bh, seg_t0, n, plan.n_seg > 1 ? seg_state : nullptr, (LdsFloat *)smem);
         if (NORM == 2)
             redo_norm_backward(&ka->a, &ka->nb, bh, seg_t0, n, ka->nb.wpart + ((int64_t)bh * plan.n_seg + seg) * D, (float *)smem);
     };

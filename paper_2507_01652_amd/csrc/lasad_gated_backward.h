@@ -15,7 +15,8 @@ struct GatedChunkArgs {
     // incoming and final states of the walks ([B, Hh, d, d], [key channel][value channel]), or NULL
     const float *g_in;                 // dL/d(final state) / q_scale
     float *s_out, *g_out;              // S_n; the adjoint state at the first token / q_scale, without that token's decay
-    const float *sink;                 // [sequence][d]: what every suffix sum of r starts from (cut: of the last segment), or NULL
+    const float *sink;                 // [sequence][d]: what every suffix sum of r starts from (cut: of the last segment), or NULL;
+                                       //   of sequences whose dq walk did not hold the reversed walk forms it again
     gchunk::SegPlan cut;               // segments with a workgroup each
     // Parts of a segment at whose bounds the reversed walk takes the suffix sum from the states (bound j: the segment's chunks
     // j * count / n_part).
@@ -24,7 +25,7 @@ struct GatedChunkArgs {
     // / q_scale
     float *bounds_s, *bounds_g;
     float *parts_s;                    // [sequence][segment][part - 1]: the states before the parts, from the dq walk
-    int *kept;                         // [sequence][segment]: whether it kept them
+    int *kept;                         // [sequence][segment]: whether the dq walk stayed in its range (else nothing of it holds)
     float *sinks;                      // cut: [sequence][kMaxSegments][d], what the suffix sums of a segment but the last start from
     // the same walks for the token-serial routine: dq, dv, dk
     ForwardArgs serial[3];

@@ -249,6 +249,10 @@ inline const void *last_token(const void *p, const lasad_layout_t &l, int n, int
 
 // ---- device helpers -----------------------------------------------------------
 
+// A pointer to LDS as the argument of a function that is not inlined: through a plain one every access would be a flat one, which
+// costs the address unit and the wait of a load from memory.
+typedef __attribute__((address_space(3))) float LdsFloat;
+
 // Is 1-indexed raster position t one where the decay is switched off
 // (Section 3.4 second equation / Algorithm 1 boundary branch)?
 __host__ __device__ inline bool is_boundary(int t, int grid_w, int mode)

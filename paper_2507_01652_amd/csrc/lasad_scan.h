@@ -35,6 +35,9 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
+// of the 256 that walk a sequence (a larger workgroup may run several walks, four wavefronts each)
+__device__ __forceinline__ int thread() { return threadIdx.x & (kThreads - 1); }
+
 // decay kind: per-head scalar; vector with k = 1 - lambda; vector with own key; and the two walks of the
 // vector-decay BACKWARD passes, which are the same recurrence with the tensors in other roles
 // (ScanRoles): decay per key channel (row of S) as in the forward, or per column of S
@@ -110,16 +113,20 @@ struct Loader {
     static constexpr int VEC = IN_BF16 ? 8 : 4;                 // elements per 16-byte load
     static constexpr int NA = KIND >= OWNKEY ? 4 : 3;           // tensors read from memory
     static constexpr bool ROLES = KIND >= ROLES_ROW;
-    const ScanRoles *roles = nullptr;                           // ROLES kinds only
     static constexpr int PER_ARRAY = kT * kD / VEC;             // 16-byte loads per tensor and batch
     static constexpr int TOTAL = NA * PER_ARRAY;
     static constexpr int NL = (TOTAL + kThreads - 1) / kThreads;   // loads per thread and batch
+    // What the i-th load of this thread reads is the same in every batch: found out once, kept in registers.  (Looked up in every
+    // batch, from arguments in memory, a walk of 256 tokens by the range exits took 87 us in the place of 72.)
+    const char *from[NL];              // the tensor at the load's channels, token 0
+    const char *from_lo[NL];           // ROLES: the tensor to be added
+    int todo[NL];                      // ROLES: the activation, bit 2: one minus, bit 3: the token before
     u4 raw[NL];
 
     // which tensor the i-th load of this thread reads, and where
     __device__ static void where(int i, int &arr, int &tok, int &c0)
     {
-        int idx = threadIdx.x + kThreads * i;
+        int idx = thread() + kThreads * i;
         idx = idx < TOTAL ? idx : TOTAL - 1;
         arr = idx / PER_ARRAY;
         const int w = idx - arr * PER_ARRAY;
@@ -127,32 +134,50 @@ struct Loader {
         c0 = (w - tok * (kD / VEC)) * VEC;
     }
 
-    __device__ const void *tensor(const ForwardArgs &a, int arr) const
-    {
-        if (ROLES) return roles->ptr[arr];
-        if (KIND == SCALAR) return arr == 0 ? a.q : arr == 1 ? a.k : a.v;
-        if (KIND == TIED) return arr == 0 ? a.q : arr == 1 ? a.lam : a.v;
-        return arr == 0 ? a.q : arr == 1 ? a.lam : arr == 2 ? a.k : a.v;
-    }
-
-    // issue the loads of the batch starting at token t0 (rows past the end re-read the last token;
-    // stage() replaces them by neutral tokens)
-    __device__ void fetch(const ForwardArgs &a, int64_t in_base, int t0)
+    __device__ void init(const ForwardArgs &a, int64_t in_base, const ScanRoles *roles)
     {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
             int arr, tok, c0;
             where(i, arr, tok, c0);
-            int t = min(t0 + tok, a.n_tokens - 1);
-            if (ROLES) t = max(t + roles->shift[arr], 0);
-            const int64_t idx = in_base + (int64_t)t * a.in.stride_n + c0;
-            const char *p = (const char *)tensor(a, arr) + idx * (IN_BF16 ? 2 : 4);
-            raw[i] = *(const u4 *)p;
+            const void *p, *lo = nullptr;
+            if (ROLES) {
+                p = roles->ptr[arr];
+                lo = roles->lo[arr];
+                todo[i] = roles->act[arr] | (roles->one_minus[arr] ? 4 : 0) | (roles->shift[arr] ? 8 : 0);
+            } else if (KIND == SCALAR) {
+                p = arr == 0 ? a.q : arr == 1 ? a.k : a.v;
+            } else if (KIND == TIED) {
+                p = arr == 0 ? a.q : arr == 1 ? a.lam : a.v;
+            } else {
+                p = arr == 0 ? a.q : arr == 1 ? a.lam : arr == 2 ? a.k : a.v;
+            }
+            from[i] = (const char *)p + (in_base + c0) * (IN_BF16 ? 2 : 4);
+            if (ROLES && IN_BF16) from_lo[i] = lo ? (const char *)lo + (in_base + c0) * 2 : nullptr;
+        }
+    }
+    // bytes from token 0 to the token of the i-th load, in the batch from t0 on (rows past the end re-read the last token;
+    // stage() replaces them by neutral tokens)
+    __device__ int64_t at(const ForwardArgs &a, int i, int tok, int t0) const
+    {
+        int t = min(t0 + tok, a.n_tokens - 1);
+        if (ROLES) t = max(t - (todo[i] >> 3), 0);
+        return (int64_t)t * a.in.stride_n * (IN_BF16 ? 2 : 4);
+    }
+
+    // issue the loads of the batch starting at token t0
+    __device__ void fetch(const ForwardArgs &a, int t0)
+    {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            int arr, tok, c0;
+            where(i, arr, tok, c0);
+            raw[i] = *(const u4 *)(from[i] + at(a, i, tok, t0));
         }
     }
 
     // convert the fetched batch to fp32 and write it to the LDS stage [plane][token][channel]
-    __device__ void stage(const ForwardArgs &a, int64_t in_base, int t0, float *st) const
+    __device__ void stage(const ForwardArgs &a, int t0, float *st) const
     {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
@@ -178,24 +203,24 @@ struct Loader {
             const bool past_end = t0 + tok >= a.n_tokens;
             if (ROLES) {
                 // plane = tensor index; rows past the end and a shifted read before the first token are neutral
-                if (IN_BF16 && roles->lo[arr]) {             // (rare route: loaded here, not ahead)
-                    const int t = max(min(t0 + tok, a.n_tokens - 1) + roles->shift[arr], 0);
-                    const u4 w = *(const u4 *)((const uint16_t *)roles->lo[arr] + in_base + (int64_t)t * a.in.stride_n + c0);
+                if (IN_BF16 && from_lo[i]) {                 // (rare route: loaded here, not ahead)
+                    const u4 w = *(const u4 *)(from_lo[i] + at(a, i, tok, t0));
 #pragma unroll
                     for (int e = 0; e < VEC / 2; ++e) {
                         f[2 * e] += __uint_as_float(w[e] << 16);
                         f[2 * e + 1] += __uint_as_float(w[e] & 0xffff0000u);
                     }
                 }
-                if (roles->act[arr]) {
+                const int act = todo[i] & 3;
+                if (act) {
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) f[e] = roles->act[arr] == ACT_SILU ? silu_f32(f[e]) : sigmoid_f32(f[e]);
+                    for (int e = 0; e < VEC; ++e) f[e] = act == ACT_SILU ? silu_f32(f[e]) : sigmoid_f32(f[e]);
                 }
-                if (roles->one_minus[arr]) {
+                if (todo[i] & 4) {
 #pragma unroll
                     for (int e = 0; e < VEC; ++e) f[e] = 1.0f - f[e];
                 }
-                const bool neutral = past_end || t0 + tok + roles->shift[arr] < 0;
+                const bool neutral = past_end || t0 + tok < todo[i] >> 3;
                 if (arr == PL && (neutral || is_boundary(a.start_pos + t0 + tok + 1, a.grid_w, a.mode))) {
 #pragma unroll
                     for (int e = 0; e < VEC; ++e) f[e] = 1.0f;
@@ -245,24 +270,31 @@ struct Loader {
     }
 };
 
-// LDS floats one workgroup needs (stage and partial-sum areas, both double-buffered)
-template <int KIND>
-constexpr int lds_floats() { return 2 * (KIND == SCALAR ? 3 : 4) * kT * kD + 2 * kT * kThreads; }
+// LDS floats of a walk: the stage, double-buffered, and RED partial-sum areas
+template <int KIND, int RED = 2>
+constexpr int lds_floats() { return 2 * (KIND == SCALAR ? 3 : 4) * kT * kD + RED * kT * kThreads; }
 
-// Walk sequence bh, value channels j0 .. j0+NJ-1, with the calling 256-thread workgroup.
-// lds: lds_floats<KIND>() floats, 16-byte aligned.
-template <int IN_BF16, int OUT_BF16, int KIND, int NJ>
+// The barriers of a walk of n tokens, for those of the workgroup's wavefronts that have no walk of their own beside others.
+template <int RED>
+__device__ __forceinline__ void barriers_only(int n)
+{
+    for (int i = 0; i < 1 + (RED == 1 ? 2 : 1) * ((n + kT - 1) / kT); ++i) __syncthreads();
+}
+
+// Walk sequence bh, value channels j0 .. j0+NJ-1, with 256 threads of the calling workgroup.
+// lds: lds_floats<KIND, RED>() floats, 16-byte aligned.  RED: 2, or 1 where LDS is short (one more barrier a batch).
+template <int IN_BF16, int OUT_BF16, int KIND, int NJ, int RED = 2>
 __device__ void scan_sequence(const ForwardArgs &a, int bh, int j0, float *lds, const ScanRoles *roles = nullptr)
 {
     constexpr int CG = kThreads / NJ;      // key-channel groups
     constexpr int R = kD / CG;             // key channels per thread (16 or 8)
     constexpr int NP = KIND == SCALAR ? 3 : 4;   // LDS planes per staged batch
     constexpr int STAGE = NP * kT * kD;
-    constexpr int RED = kT * CG * NJ;
-    float *const s_stage[2] = {lds, lds + STAGE};
-    float *const s_red[2] = {lds + 2 * STAGE, lds + 2 * STAGE + RED};
+    constexpr int SUMS = kT * CG * NJ;
+    // (offsets from one base: through an array of two pointers every LDS access is a flat one)
+    float *const s_red = lds + 2 * STAGE;
     const int b = bh / a.Hh, h = bh - b * a.Hh;
-    const int tid = threadIdx.x;
+    const int tid = thread();
     const int j = tid % NJ, cg = tid / NJ;
     const int cop = cg * R + (tid % 16) % R;      // key channel whose operands this lane carries
     const float gamma = KIND == SCALAR ? a.gamma[h] : 1.0f;
@@ -296,23 +328,23 @@ __device__ void scan_sequence(const ForwardArgs &a, int bh, int j0, float *lds, 
     const int nb = (a.n_tokens + kT - 1) / kT;
 
     Loader<IN_BF16, KIND> ld;
-    ld.roles = roles;
+    ld.init(a, in_base, roles);
     if (nb > 0) {
-        ld.fetch(a, in_base, 0);
-        ld.stage(a, in_base, 0, s_stage[0]);
+        ld.fetch(a, 0);
+        ld.stage(a, 0, lds);
     }
     __syncthreads();
 
     for (int bt = 0; bt < nb; ++bt) {
         const int t0 = bt * kT;
         const int nt = min(kT, a.n_tokens - t0);
-        const float *st = s_stage[bt & 1];
-        float *red = s_red[bt & 1];
+        const float *st = lds + (bt & 1) * STAGE;
+        float *red = s_red + (bt & (RED - 1)) * SUMS;
         // The next batch's loads are in flight while this one is computed.  They are issued and
         // consumed in the same iteration, unconditionally (after the last batch they re-read the
         // last token and stage neutral rows nobody uses), so that no register carries a pending
         // load around the loop and the compiler's wait counts stay exact.
-        ld.fetch(a, in_base, t0 + kT);
+        ld.fetch(a, t0 + kT);
         __builtin_amdgcn_sched_barrier(0);      // keep the loads ahead of the compute block
 
         // all 16 tokens of the batch, unrolled: rows past the end of the sequence were staged as
@@ -334,7 +366,7 @@ __device__ void scan_sequence(const ForwardArgs &a, int bh, int j0, float *lds, 
             red[(tt * CG + cg) * NJ + j] = (o[0] + o[1]) + (o[2] + o[3]);
         }
 
-        ld.stage(a, in_base, t0 + kT, s_stage[(bt + 1) & 1]);
+        ld.stage(a, t0 + kT, lds + ((bt + 1) & 1) * STAGE);
         __syncthreads();
 
         // add the groups' partial sums and store o for this batch, two channels per thread and pass
@@ -366,6 +398,7 @@ __device__ void scan_sequence(const ForwardArgs &a, int bh, int j0, float *lds, 
                     *(f2 *)((float *)a.o + oi) = acc;
             }
         }
+        if (RED == 1) __syncthreads();
     }
 
     if (a.state_out) {

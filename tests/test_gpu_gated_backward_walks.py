@@ -33,8 +33,9 @@ def _check(lasad, oracle, n, Hh, own, W, start=0, spike=None, carried=False):
     import torch
     rng, q, v, g, k, lam = _inputs(n, Hh, 7 * n + Hh)
     pick, c = [0, Hh // 2, Hh - 1], 5
-    if spike is not None:
-        lam[:, spike, Hh // 2, c] = 2.0 ** -120
+    spikes = [] if spike is None else list(np.atleast_1d(spike))
+    for t in spikes:                                         # (several: beyond the range together)
+        lam[:, t, Hh // 2, c] = 2.0 ** (-120 if len(spikes) == 1 else -60)
     if not own:
         k = None
     s0, ds = ((rng.standard_normal((1, Hh, D, D)) * 0.3).astype(np.float32) for _ in range(2))
@@ -54,8 +55,8 @@ def _check(lasad, oracle, n, Hh, own, W, start=0, spike=None, carried=False):
     for i, (a, r) in enumerate(zip(got, [x for x in ref if x is not None])):
         a = a.float().cpu().numpy()
         a, r = (a[:, pick] if i == state else a[:, :, pick]), np.array(r)
-        if i == 1 and spike is not None:                     # a quotient by the tiny gate, and what it hides of the steps before
-            a[:, :, 1, c] = r[:, :, 1, c] = 0
+        if i == 1 and spikes:                                # a quotient by the tiny gate, and what it hides of the steps before
+            a[:, :spikes[-1] + 1, 1, c] = r[:, :spikes[-1] + 1, 1, c] = 0
         assert rel_err(a, r) <= TOL["bf16"], (i, rel_err(a, r))
 
 
@@ -75,6 +76,38 @@ def test_carried(lasad, oracle, n, Hh, own):
 @pytest.mark.parametrize("carried", [False, True])
 def test_range_exit(lasad, oracle, n, Hh, spike, carried):
     _check(lasad, oracle, n, Hh, True, W=23, spike=spike, carried=carried)
+
+
+@pytest.mark.parametrize("n,Hh,spike", [(97, 81, [0]), (97, 81, [31, 32]), (520, 100, [0]), (520, 100, [287, 288]), (577, 129, [63, 64])],
+                         ids=["dq", "reversed", "dq_of_a_segment", "reversed_of_a_segment", "reversed_with_parts"])
+@pytest.mark.parametrize("carried", [False, True])
+def test_range_exit_of_one_walk(lasad, oracle, n, Hh, spike, carried):
+    """The first token's gate is in no product of the reversed order; two gates on both sides of a tile's bound are in one
+    product only there.  What the other walk made is then kept, or (dq) made again."""
+    _check(lasad, oracle, n, Hh, True, W=23, spike=spike, carried=carried)
+
+
+def test_range_exit_takes_no_longer_than_the_passes(lasad):
+    """Every gate leaves the range: 96 sequences, on the walks, against 80, whose three passes have a compute unit each (1.8
+    times their time; with the token-serial walks one after the other 3.1)."""
+    import torch
+
+    def time(Hh, n=256, W=16):
+        gen = torch.Generator(device="cuda").manual_seed(Hh)
+        x = [torch.randn((1, n, Hh, D), generator=gen, device="cuda").bfloat16() for _ in range(5)]
+        lam = torch.sigmoid(x[4].float() - 10).bfloat16()
+        best = 1e30
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                lasad.lasad_backward_gated(x[0], lam, x[1], x[2], n // W, W, k=x[3])
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    assert time(96) <= 2.3 * time(80)
 
 
 @pytest.mark.parametrize("n,Hh,mode", [(33, 81, 0), (100, 81, 1), (513, 96, 0), (580, 129, 2), (1000, 12, 1)])
