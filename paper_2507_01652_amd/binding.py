@@ -48,8 +48,8 @@ _steps = None                          # the extension with the decode steps' ma
 
 
 def load() -> ctypes.CDLL:
-    """Open liblasad.so and _steps.so (built in-tree by ``paper_2507_01652_amd.build``)."""
-    global _lib, _steps
+    """Open liblasad.so (built in-tree by ``paper_2507_01652_amd.build``)."""
+    global _lib
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -120,8 +120,6 @@ def load() -> ctypes.CDLL:
     lib.lasad_last_error.restype = ctypes.c_char_p
     lib.lasad_version.argtypes = []
     lib.lasad_version.restype = ctypes.c_char_p
-    from . import _steps as steps      # (links to the library opened above)
-    _steps = steps
     _lib = lib
     return lib
 
@@ -167,11 +165,23 @@ def _same(q: torch.Tensor, others, message: str):
             raise ValueError(message)
 
 
-def _step(name: str, *args):
-    """A decode step through the extension: its output, or None where the checks here have to see the call."""
+def extension():
+    """The extension of the decode steps (which links to the library that load() opens); no other call needs it."""
+    global _steps
     if _steps is None:
         load()
-    done = getattr(_steps, name)(*args)
+        try:
+            from . import _steps as steps
+        except ImportError as e:
+            raise ImportError(f"{e}: build the decode steps' extension (for the torch in use) with "
+                              "`python -m paper_2507_01652_amd.build`") from e
+        _steps = steps
+    return _steps
+
+
+def _step(name: str, *args):
+    """A decode step through the extension: its output, or None where the checks here have to see the call."""
+    done = getattr(_steps or extension(), name)(*args)
     if type(done) is int:
         _check(done)
     return done
