@@ -165,6 +165,19 @@ def _same(q: torch.Tensor, others, message: str):
             raise ValueError(message)
 
 
+def _reachable(*tensors):
+    """Every tensor lies where a kernel can reach it."""
+    for t in tensors:
+        if t is not None and not t.is_cuda and not t.is_pinned():
+            raise ValueError("tensors must be on the GPU")
+
+
+def _floats(t, n: int, message: str):
+    """None, or at least n fp32 values in a row."""
+    if t is not None and (t.dtype != torch.float32 or not t.is_contiguous() or t.numel() < n):
+        raise ValueError(message)
+
+
 def extension():
     """The extension of the decode steps (which links to the library that load() opens); no other call needs it."""
     global _steps
@@ -319,6 +332,7 @@ def lasad_decode_step(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, gamma: 
     elif out.shape != q.shape or not out.is_contiguous():
         raise ValueError("out must be contiguous [B, Hh, d]")
     assert gamma.dtype == torch.float32 and gamma.is_contiguous() and gamma.shape == (Hh,)
+    _reachable(q, k, v, gamma, state, out)
     _check(load().lasad_decode_step(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _dtype_code(q), _dtype_code(out),
                                     B, Hh, d, grid_h, grid_w, pos, _ptr(gamma), boundary_mode, q_scale,
                                     _ptr(state), _stream(stream)))
@@ -424,6 +438,7 @@ def lasad_decode_step_gated(q: torch.Tensor, lam: torch.Tensor, v: torch.Tensor,
         out = torch.empty_like(q, dtype=out_dtype or q.dtype)
     elif out.shape != q.shape or not out.is_contiguous():
         raise ValueError("out must be contiguous [B, Hh, d]")
+    _reachable(q, lam, k, v, state, out)
     _check(load().lasad_decode_step_gated(_ptr(q), _ptr(lam), _ptr(k), _ptr(v), _ptr(out),
                                           _dtype_code(q), _dtype_code(out), B, Hh, d, grid_h, grid_w, pos,
                                           boundary_mode, q_scale, _ptr(state), _stream(stream)))
@@ -475,6 +490,10 @@ def lasad_decode_step_layer(q_pre: torch.Tensor, z: torch.Tensor, v: torch.Tenso
         raise ValueError("state must be contiguous fp32 [B, Hh, d, d]")
     if out is None:
         out = torch.empty_like(q_pre, dtype=out_dtype or q_pre.dtype)
+    elif out.numel() < q_pre.numel() or not out.is_contiguous():
+        raise ValueError("out must be contiguous [B, Hh, d]")
+    _floats(norm_weight, Hh * d, "norm_weight must be contiguous fp32 [Hh, d]")
+    _reachable(q_pre, z, v, state, norm_weight, out)
     _check(load().lasad_decode_step_layer(_ptr(q_pre), _ptr(z), _ptr(v), _ptr(out), _dtype_code(q_pre), _dtype_code(out),
                                           B, Hh, d, grid_h, grid_w, pos, boundary_mode, q_scale,
                                           _ptr(norm_weight), norm_eps, _ptr(state), _stream(stream)))
@@ -504,6 +523,8 @@ def lasad_decode_step_rows(q: torch.Tensor, v: torch.Tensor, state: torch.Tensor
         out = torch.empty_like(q, dtype=out_dtype or q.dtype)
     elif out.shape != q.shape or not out.is_contiguous():
         raise ValueError("out must be contiguous [B, Hh, d]")
+    _floats(gamma, Hh, "gamma must be contiguous fp32 [Hh]")
+    _reachable(q, lam, k, v, state, pos_rows, gamma, out)
     _check(load().lasad_decode_step_rows(_ptr(q), _ptr(lam), _ptr(k), _ptr(v), _ptr(out),
                                          _dtype_code(q), _dtype_code(out), B, Hh, d, grid_h, grid_w,
                                          _ptr(pos_rows), _ptr(gamma), boundary_mode, q_scale, _ptr(state),
