@@ -110,6 +110,20 @@ def test_range_exit_takes_no_longer_than_the_passes(lasad):
     assert time(96) <= 2.3 * time(80)
 
 
+def test_the_decay_gradient_is_a_rounded_quotient(lasad):
+    """One token that adds nothing to the state: its decay gradient is (lambda s) / lambda, s a power of two, without an error."""
+    import torch
+    Hh = 200
+    zero = torch.zeros((1, 1, Hh, D), dtype=torch.bfloat16, device="cuda")
+    lam = (torch.arange(1, Hh * D + 1, device="cuda").reshape(1, 1, Hh, D) / (Hh * D + 1)).bfloat16()
+    s0, ds = (torch.zeros((1, Hh, D, D), device="cuda") for _ in range(2))
+    s0[..., 0] = 2.0 ** (torch.arange(D, device="cuda") % 7 - 3)
+    ds[..., 0] = 1
+    dlam = lasad.lasad_backward_gated_carried(zero, lam, zero, zero, 2, 8, k=zero.clone(), state_in=s0, d_state_out=ds,
+                                              grad_dtype=torch.float32)[1]
+    assert torch.equal(dlam[0, 0], s0[0, :, :, 0])
+
+
 @pytest.mark.parametrize("n,Hh,mode", [(33, 81, 0), (100, 81, 1), (513, 96, 0), (580, 129, 2), (1000, 12, 1)])
 def test_layer(lasad, oracle, n, Hh, mode):
     import torch
