@@ -10,7 +10,8 @@
 //      kernels read all their operands with one layout); the weight gradient is first summed over a
 //      workgroup's tokens, in a fixed order.  bf16: the epilogue of the forward's tiles
 //      (lasad_forward_gated_chunk.hip, NORM 2), o itself reaches no memory; else (fp32, strides the
-//      chunked forward refuses) o goes through the workspace to norm_backward_kernel of this file;
+//      chunked forward refuses, few sequences of middle length) o goes through the workspace to
+//      norm_backward_kernel of this file;
 //   3. the vector-decay backward (lasad_backward_gated.hip) with activations on load and the chain
 //      rule to q_pre and z where it stores the gradients;
 //   4. weight_grad_kernel adds the per-workgroup sums of step 2, again in a fixed order.
@@ -198,12 +199,13 @@ hipError_t launch_backward_layer(const LayerBackwardArgs &a, bool use_mfma, hipS
         f.state_in = nullptr; f.state_out = nullptr;
         f.seg_states = nullptr; f.n_segments = 1; f.seg_chunks = 0;
         f.fused_act = 1; f.norm = 0; f.norm_eps = -1.f; f.norm_w = nullptr;
-        if (in16 && use_mfma && forward_gated_chunk_fits(f)) {              // ... and 2. in one
+        const bool chunked = in16 && use_mfma;
+        if (chunked && forward_gated_chunk_fits(f) && forward_gated_norm_backward_pays(n_seq, n)) {     // ... and 2. in one
             const NormBackwardArgs nb{a.d_out, a.dout, a.norm_w, a.norm_eps, d_o, d_o_lo, a.d_o_f32, dl, wpart};
             e = launch_forward_gated_norm_backward(f, nb, &w_items, s);
             fused = true;
         } else {
-            e = launch_forward_generic(f, s);
+            e = chunked ? launch_forward_gated_chunk(f, s) : launch_forward_generic(f, s);
         }
         if (e != hipSuccess) return e;
     }

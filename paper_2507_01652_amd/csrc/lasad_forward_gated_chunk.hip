@@ -215,7 +215,8 @@ __device__ __noinline__ void redo_norm_backward(const ForwardArgs *a, const Norm
 // NORM: 1 the normalised output; 2 the output is not stored, but what the normalisation's backward makes of it, from the
 // gradient's row that the loaders hold one tile ahead.  In a pass of its own that was another fp32 tensor written and read, bound
 // by memory: 288 sequences of 16 x 16 tokens 23 + 16 us -> 29, a whole layer backward on rotating buffers 98 -> 90, 512 of 24 x 24
-// 256 -> 222, 96 of 64 x 64 436 -> 388, 300 of 8 x 8 42 -> 38, 12 of 16 x 16 41.7 -> 41.1.
+// 256 -> 222, 96 of 64 x 64 436 -> 388, 300 of 8 x 8 42 -> 38.  (Not for few sequences of middle length:
+// forward_gated_norm_backward_pays.)
 template <int OUT_BF16, int OWNKEY, int FUSED, int NORM, int NG>
 __global__ void __launch_bounds__((1 + NG) * kThreads, NG == 1 ? 4 : 3)
 forward_gated_chunk_kernel(ForwardArgs a, SegPlan plan, NormBackwardArgs nb)
@@ -702,6 +703,16 @@ SegPlan segment_plan(int64_t n_seq, int n_tokens)
 }  // namespace
 
 bool forward_gated_chunk_fits(const ForwardArgs &a) { return a.in.stride_n <= kMaxStride; }
+
+// The epilogue lengthens a tile's period of a workgroup that has a compute unit to itself by 0.4 us; a kernel of its own takes
+// 3.2 us and 0.085 us a sequence and 1000 tokens, spread over the idle units.  us (forward and epilogue | forward, then kernel):
+// 12 x 576 tokens 28.5 | 25.4, 33 x 400 22.2 | 21.5, 60 x 784 40.9 | 37.3, 80 x 1024 51.9 | 47.1, 96 x 784 41.8 | 39.8, but 12 x
+// 128 10.5 | 11.4, 48 x 256 16.0 | 16.5, 96 x 400 22.5 | 24.4, 128 x 784 41.7 | 42.3, 256 x 1024 55 | 66, 512 x 576 53 | 76; in
+// segments 12 x 4096 33.6 | 38.2, 96 x 4096 106 | 152.
+bool forward_gated_norm_backward_pays(int64_t n_seq, int n_tokens)
+{
+    return n_seq >= 147 || n_tokens * (147 - n_seq) <= 37600 || segment_plan(n_seq, n_tokens).n_seg > 1;
+}
 
 static hipError_t launch(const ForwardArgs &a, const NormBackwardArgs *nb, int *n_seg, hipStream_t s)
 {

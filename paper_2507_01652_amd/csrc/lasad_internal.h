@@ -206,6 +206,7 @@ hipError_t launch_forward_mfma(const ForwardArgs &a, hipStream_t s);
 hipError_t launch_forward_gated_chunk(const ForwardArgs &a, hipStream_t s);
 // with the normalisation's backward; n_seg: segments a sequence (of wpart)
 bool forward_gated_chunk_fits(const ForwardArgs &a);
+bool forward_gated_norm_backward_pays(int64_t n_seq, int n_tokens);
 hipError_t launch_forward_gated_norm_backward(const ForwardArgs &a, const NormBackwardArgs &nb, int *n_seg, hipStream_t s);
 // the same with eight wavefronts per sequence (whole sequences only, no segment plan)
 hipError_t launch_forward_mfma_ws(const ForwardArgs &a, hipStream_t s);
