@@ -329,7 +329,7 @@ void finish_segments(int64_t n_seq, int n, int *n_seg, int *seg_blocks)
 
 // How a call with bf16 inputs and head dim 64 runs.
 // PASSES: three independent passes side by side and a finishing kernel (lasad_backward_gated_mfma.hip), for calls whose
-//   passes all get a compute unit of their own (80 sequences) and that are too short to be cut.
+//   passes all get a compute unit of their own (80 sequences) and that are too short to be cut, and for short ones of some more.
 // WALKS: dq, then the reversed walk with everything else (lasad_backward_gated_chunk.hip).  Few long sequences are cut into
 //   segments, one workgroup a compute unit (two a unit: 96 sequences of 4096 tokens, own key, 259 -> 264 us, but 48 of 4096
 //   126 -> 143).  For the accuracy of dlam they keep the states at the bounds of as many parts as the passes had segments.
@@ -337,6 +337,31 @@ void finish_segments(int64_t n_seq, int n, int *n_seg, int *seg_blocks)
 // -> 38; 48 x 576 41 -> 57 -> 44; 48 x 784 49 -> 76 -> 47; 80 x 784 57 -> 81 -> 61; 80 x 1024 75 -> 107 -> 74; 96 x 256 33.3 -> 33.1 ->
 // 36.6; 96 x 400 48.4 -> 46.0 -> 46.0; 96 x 576 58 -> 59 -> 53; 128 x 576 63 -> 60 -> 56; 96 x 4096 410 -> 378 -> 264; uncut only: 160
 // x 1024 126 -> 109, 240 x 4096 752 -> 470, 512 x 576 234 -> 167.
+// The lines between them are the same for both types of the gradients (bf16 ones are the fp32 ones rounded).  Walks over passes,
+// time ratio (graph replays; own key / the same with fp32 gradients / carried states / fused layer):
+struct CallForm { bool fused, carried; };
+// Up to 80 sequences, most blocks of 64 tokens for the passes.  Their launch deals the sequences out by eights, one an XCD, and is
+// at its best with full groups.  24 x 704 tokens 1.03 / 1.10 / 1.07 / 0.98, x 768 0.95 / 0.99 / 1.00 / 0.93; 33 x 640 0.88 / 0.95 / 0.94 /
+// 0.95; 48 x 768 1.03 / 1.10 / 1.05 / 1.01, x 832 0.98 / 1.05 / 1.01 / 0.98; 49 x 900 0.81 / 0.85 / 0.87 / 0.91; 64 x 900 1.06 / 1.11 / 1.08 /
+// 1.02, 72 x 1088 1.09 / 1.17 / 1.10 / 1.05; 80 x 1024 0.98 / 1.07 / 1.00 / 0.98, x 1088 1.02 / 1.07 / 1.03 / 1.00, x 1200 0.97 / 1.04 / 0.99 /
+// 0.98, x 1444 0.95 / 1.01 / 0.98 / 0.96.
+int passes_blocks(int64_t n_seq)
+{
+    const bool full = n_seq % 8 == 0;
+    if (n_seq <= 48) return full ? (n_seq == 48 ? 12 : 11) : 10;
+    return full ? 17 : 14;
+}
+// More than that, calls for the passes all the same: with one loader group they go two chunks at a time, while the walks pay their
+// start twice.  88 sequences of 33 tokens 1.20 / 1.31 / 1.17 / 1.10, x 64 1.09 / 1.21 / 1.13 / 1.08; 96 x 33 1.09 / 1.16 / 1.12 / 1.02; 128
+// x 33 1.08 / 1.16 / 1.11 / 1.02, x 64 1.00 / 1.07 / 1.08 / 1.00, x 65 0.92 / 1.01 / 1.01 / 0.91; 144 x 48 1.02 / 1.10 / 1.08 / 0.99; 160 x 64
+// 0.97 / 1.06 / 1.07 / 0.96.  Carried states: 128 x 16 1.03, x 32 1.01, x 97 1.08, x 128 1.02, x 160 0.96; 160 x 16 1.02, x 128 1.02; 257
+// x 64 1.03, 352 x 64 0.98.
+bool short_passes(int64_t n_seq, int n, const CallForm &f)
+{
+    const int chunks = (n + 31) / 32;
+    if (chunks == 2) return n_seq <= (f.carried ? 160 : f.fused ? 88 : 128) || (f.carried && n_seq > 256 && n_seq <= 320);
+    return f.carried && (chunks == 1 || chunks == 4) && n_seq <= 128;
+}
 struct ChunkPlan { bool passes; int n_seg, n_part; };          // parts: of a segment
 // Floats of scratch for it: the states at the bounds, of the passes also a flag per sequence and side, of the walks what the
 // suffix sums start from.  0: none.
@@ -357,14 +382,15 @@ BoundsLayout bounds_layout(const ChunkPlan &p, int64_t n_seq)
 // call may have less); else fewer segments, and without room for those what is fastest without them: us, own key, three passes
 // against uncut walks: 12 x 1024 tokens 48 | 84, 48 x 4096 214 | 325, 80 x 1024 76 | 88, but 96 x 4096 410 | 378.  Three segments
 // are worth the walks there, and two where the passes have no compute unit to spare.
-ChunkPlan chunk_plan(int64_t n_seq, int n, size_t room)
+ChunkPlan chunk_plan(int64_t n_seq, int n, const CallForm &form, size_t room)
 {
     const int nblk = (n + kFinBlock - 1) / kFinBlock;
     auto fits = [&](const ChunkPlan &p) { return bounds_layout(p, n_seq).total <= room; };
     int parts, part_blocks;
     finish_segments(n_seq, n, &parts, &part_blocks);
     const bool few = n_seq <= 80;
-    if (!(few && nblk <= (n_seq <= 48 ? 10 : 14)) && n_seq <= 128 && nblk >= 8) {
+    if (!few && short_passes(n_seq, n, form)) return ChunkPlan{true, 1, 1};
+    if (!(few && nblk <= passes_blocks(n_seq)) && n_seq <= 128 && nblk >= 8) {
         int most = (int)(256 / n_seq);
         if (most > kMaxSegments) most = kMaxSegments;
         if (most > nblk / 2) most = nblk / 2;
@@ -395,7 +421,8 @@ size_t backward_gated_workspace_bytes(int64_t n_seq, int n_tokens, int d)
 
 size_t backward_gated_bounds_bytes(int64_t n_seq, int n_tokens, int d)
 {
-    return d == kD && n_tokens > 0 ? bounds_layout(chunk_plan(n_seq, n_tokens, SIZE_MAX), n_seq).total * sizeof(float) : 0;
+    // (long calls, which have bounds, run the same whatever their form)
+    return d == kD && n_tokens > 0 ? bounds_layout(chunk_plan(n_seq, n_tokens, CallForm{false, false}, SIZE_MAX), n_seq).total * sizeof(float) : 0;
 }
 
 hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
@@ -424,7 +451,8 @@ hipError_t launch_backward_gated(const GatedBackwardArgs &b, hipStream_t s)
     // step: the shifted decay of step 0 is neutral); the dv pass ends with g_1 / q_scale
     const bool carried = b.state_in || b.d_state_out || b.d_state_in;
     const size_t mat = (size_t)n_seq * b.d * b.d;
-    const ChunkPlan plan = chunk_plan(n_seq, n, b.bounds ? b.bounds_bytes / sizeof(float) : 0);
+    const CallForm form{b.fused_act != 0, carried};
+    const ChunkPlan plan = chunk_plan(n_seq, n, form, b.bounds ? b.bounds_bytes / sizeof(float) : 0);
     float *cw = dk32 + (size_t)n_seq * n * b.d + (size_t)n_seq * 8 * b.d;      // after the gradients and the segment totals
     float *hS = cw, *sn = cw + mat, *g1 = cw + 2 * mat, *sink_buf = cw + 3 * mat;
     const float *sink = (carried && b.d_state_out) ? sink_buf : nullptr;

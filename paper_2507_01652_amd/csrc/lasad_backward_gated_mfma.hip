@@ -1,4 +1,4 @@
-// Chunked matrix-core passes of the vector-decay backward for few short sequences (bf16 inputs, head dim 64; the rule is at
+// Chunked matrix-core passes of the vector-decay backward for few or short sequences (bf16 inputs, head dim 64; the rule is at
 // chunk_plan in lasad_backward_gated.hip): all three side by side, each with a compute unit of its own, on the building blocks of the
 // forward (lasad_gated_chunk.h: chunks of 32 tokens, loader wavefronts one chunk ahead, compute wavefronts that own 16
 // columns of the state).  lasad_backward_gated.hip has the derivation.  Two kinds of pass:
@@ -593,7 +593,7 @@ hipError_t launch_backward_gated_passes(const ForwardArgs *a, const scan::ScanRo
     PassSet ps;
     for (int i = 0; i < 3; ++i) { ps.a[i] = a[i]; ps.roles[i] = roles[i]; }
     // Two loader groups where every workgroup has a compute unit: an XCD gets three workgroups of every eighth sequence and has
-    // 32 units, so up to 80 sequences (more come here only with strides that the walks do not take).  One -> two groups, us a
+    // 32 units, so up to 80 sequences.  One -> two groups, us a
     // call: 80 of 576 44.1 -> 42.8, 88 -> 80 (fused layer); but 84 of 256 29.5 -> 32.7.  Two chunks
     // (one pair of one group) are bound by their first loads: 24 of 64 10.0 -> 10.4, of 96 13.4 -> 12.6.
     const bool pair = a[0].n_tokens > C && a[0].n_tokens <= 2 * C;

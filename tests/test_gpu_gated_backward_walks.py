@@ -110,6 +110,18 @@ def test_range_exit_takes_no_longer_than_the_passes(lasad):
     assert time(96) <= 2.3 * time(80)
 
 
+# The last call for the three passes and the first for the walks, and the other way round.
+@pytest.mark.parametrize("n,Hh", [(32, 128), (33, 128), (33, 129), (64, 128), (65, 128), (640, 33), (641, 33), (704, 24), (705, 24),
+                                  (768, 48), (769, 48), (896, 49), (897, 49), (1088, 72), (1089, 72)])
+def test_both_sides_of_the_lines(lasad, oracle, n, Hh):
+    _check(lasad, oracle, n, Hh, True, W=16, start=3)
+
+
+@pytest.mark.parametrize("n,Hh", [(32, 128), (32, 129), (64, 160), (64, 161), (40, 256), (40, 257), (33, 321), (97, 128), (97, 129)])
+def test_both_sides_of_the_lines_with_carried_states(lasad, oracle, n, Hh):
+    _check(lasad, oracle, n, Hh, False, W=16, start=3, carried=True)
+
+
 def test_the_decay_gradient_is_a_rounded_quotient(lasad):
     """One token that adds nothing to the state: its decay gradient is (lambda s) / lambda, s a power of two, without an error."""
     import torch
@@ -124,7 +136,7 @@ def test_the_decay_gradient_is_a_rounded_quotient(lasad):
     assert torch.equal(dlam[0, 0], s0[0, :, :, 0])
 
 
-@pytest.mark.parametrize("n,Hh,mode", [(33, 81, 0), (100, 81, 1), (513, 96, 0), (580, 129, 2), (1000, 12, 1)])
+@pytest.mark.parametrize("n,Hh,mode", [(33, 81, 0), (33, 89, 1), (100, 81, 1), (513, 96, 0), (580, 129, 2), (1000, 12, 1)])
 def test_layer(lasad, oracle, n, Hh, mode):
     import torch
     W = 16
