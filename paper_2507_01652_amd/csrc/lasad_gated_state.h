@@ -26,7 +26,8 @@ struct StatePass {
 
 constexpr int kStateRow = 3 * D + 16;          // K^ hi, lo, V
 constexpr int kStateSlot = SlotMap<kStateRow>::kHalfs;
-constexpr int kStateLdsBytes = 4 * kStateSlot * 2;
+constexpr int kStateLdsBytes = 4 * D * 4 + 4 * D * D * 4;      // at the end: the wavefronts' decays and states
+static_assert(kStateLdsBytes >= 4 * kStateSlot * 2, "a slot for each wavefront");
 
 // By a workgroup of four wavefronts; lds: kStateLdsBytes.  REV: the reversed order.  KEY: 0 the key is 1 - lambda, 1 given.
 // FUSED: lambda holds gate logits (sigmoid), and a given key is a pre-activation (SiLU).  The 64 x 64 state goes to
@@ -209,10 +210,10 @@ __device__ __forceinline__ void state_pass(const StatePass &a, int bh, int seg, 
     }
 
     // Together: S = U_3 + D_3 U_2 + D_3 D_2 U_1 + ... (REV: U_0 + D_0 U_1 + ...).  Every wavefront scales its state by the decays
-    // of the runs between it and the segment's end (start); then pairwise sums through LDS (fixed order).
+    // of the runs between it and the segment's end (start); then all 256 threads add the four up through LDS (in a fixed order; pair
+    // by pair, a wavefront at a time, the pass took 1 us more).
     float *const sD = (float *)lds;                // [wave][64]
-    float *const sAcc = sD + 4 * D;                // two states
-    static_assert(kStateLdsBytes >= (4 * D + 2 * D * D) * 4, "the states on their way");
+    float *const sAcc = sD + 4 * D;                // [wave][64][64]
     __syncthreads();
     if (pr == 0) {
 #pragma unroll
@@ -236,34 +237,18 @@ __device__ __forceinline__ void state_pass(const StatePass &a, int bh, int seg, 
 #pragma unroll
             for (int u = 0; u < 4; ++u) acc[t][u][r] *= f;
         }
-    auto put = [&](float *p) {
+    float *const mine = sAcc + wave * D * D;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) p[(state_channel(t, g) + r) * D + 16 * u + l16] = acc[t][u][r];
-    };
-    auto add = [&](const float *p) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[t][u][r] += p[(state_channel(t, g) + r) * D + 16 * u + l16];
-    };
-    if (wave & 1) put(sAcc + (wave >> 1) * D * D);
+            for (int r = 0; r < 4; ++r) mine[(state_channel(t, g) + r) * D + 16 * u + l16] = acc[t][u][r];
     __syncthreads();
-    if (!(wave & 1)) add(sAcc + (wave >> 1) * D * D);
-    __syncthreads();
-    if (wave == 2) put(sAcc);
-    __syncthreads();
-    if (wave == 0) {
-        add(sAcc);
-        put(sAcc + D * D);
+    for (int i = threadIdx.x * 4; i < D * D; i += 1024) {
+        const f32x4v *const p = (const f32x4v *)(sAcc + i);
+        *(f32x4v *)out.at(i) = (p[0] + p[D * D / 4]) + (p[2 * (D * D / 4)] + p[3 * (D * D / 4)]);
     }
-    __syncthreads();
-    for (int i = threadIdx.x * 4; i < D * D; i += 1024) *(float4 *)out.at(i) = *(const float4 *)(sAcc + D * D + i);
 }
 
 }  // namespace gchunk
