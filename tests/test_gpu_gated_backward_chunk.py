@@ -90,9 +90,10 @@ def test_segment_bounds_beside_a_range_exit(lasad, oracle, spike):
 
 
 @pytest.mark.parametrize("n", [1, 32, 33, 64, 96, 97, 129])
-@pytest.mark.parametrize("Hh", [80, 81], ids=["two_loader_groups", "one"])
+@pytest.mark.parametrize("Hh", [80, 81], ids=["80_sequences", "81"])
 def test_loader_groups(lasad, oracle, n, Hh):
-    """Both sides of the rule that gives a workgroup a second loader group (a compute unit for every workgroup)."""
+    """80 sequences take the three passes, whose workgroups have two loader groups here (33 to 64 tokens: one); 81 take the passes
+    with one loader group for 33 to 64 tokens, else the two walks."""
     import torch
     rng = np.random.default_rng(n)
     q, v, g = (wl.store_round(rng.standard_normal((1, n, Hh, D), dtype=np.float32) / np.float32(8), "bf16") for _ in range(3))
@@ -137,7 +138,7 @@ def test_workspace_of_a_longer_call(lasad, oracle, n, longer, carried):
 @pytest.mark.parametrize("n,Hh", [(33, 3), (63, 85), (77, 3), (513, 3)])
 def test_reversed_start(lasad, oracle, W, start, mode, n, Hh):
     """The reversed passes start with a chunk of n % 32 tokens: every row rule on grids narrower and wider than what is
-    missing from it, with two loader groups (few sequences) and with one."""
+    missing from it, with two loader groups (few sequences) and with one (33 to 64 tokens)."""
     import torch
     rng = np.random.default_rng(n + W)
     q, v, g = (wl.store_round(rng.standard_normal((1, n, Hh, D), dtype=np.float32) / np.float32(8), "bf16") for _ in range(3))

@@ -1,8 +1,9 @@
 """The two walks of the vector-decay backward (dq, then dv, dk and the decay gradient in reversed order) on both sides of
-the rules that choose them: 81 sequences and more (fewer take three passes when they are short), segments with a workgroup
-each up to 128 sequences of 449 tokens and more, parts of a sequence beyond that.  Lengths around the 32-token tiles, row ends
-on and off the bounds, carried states, all three key forms, bf16 and fp32 gradients, and a gate beyond the range of the
-factorised form (the token-serial walk of that part, and no states kept by it).  A few sequences of each call against the
+the rules that choose them: 81 sequences and more (fewer take three passes when they are short, and so do up to 160 of 33 to 64
+tokens), segments with a workgroup each up to 128 sequences of 449 tokens and more, parts of a sequence beyond that.  Lengths
+around the 32-token tiles, one and two loader groups of the dq walk, row ends on and off the bounds, carried states, all three
+key forms, bf16 and fp32 gradients, views and strides of all kinds, and a gate beyond the range of the factorised form (the
+token-serial walk of that part, and no states kept by it).  A few sequences of each call against the
 fp64 oracle at the storage type's tolerance (helpers.TOL)."""
 import numpy as np
 import pytest
@@ -108,6 +109,114 @@ def test_range_exit_takes_no_longer_than_the_passes(lasad):
         return best
 
     assert time(96) <= 2.3 * time(80)
+
+
+# dq's second loader group, up to 256 workgroups; with one, chunks go two at a time, and the second may be empty.
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 64, 65, 97])
+@pytest.mark.parametrize("Hh", [256, 257], ids=["two_loader_groups", "one"])
+@pytest.mark.parametrize("own", [False, True], ids=["tied", "own"])
+def test_loader_groups_of_dq(lasad, oracle, n, Hh, own):
+    _check(lasad, oracle, n, Hh, own, W=16, start=n % 16)
+
+
+@pytest.mark.parametrize("n,spike", [(33, 3), (65, 64), (97, 40), (97, 70), (128, 127)])
+@pytest.mark.parametrize("carried", [False, True])
+def test_range_exit_with_one_loader_group(lasad, oracle, n, spike, carried):
+    _check(lasad, oracle, n, 340, True, W=23, spike=spike, carried=carried)
+
+
+# two and three segments of two parts each, the states at their bounds and a range left in either segment
+@pytest.mark.parametrize("n,Hh,first,last", [(833, 100, 100, 700), (705, 128, 300, 704), (1444, 81, 5, 1300)])
+@pytest.mark.parametrize("how", ["whole", "carried", "first", "last", "carried_first", "carried_last"])
+def test_segments_with_parts(lasad, oracle, n, Hh, first, last, how):
+    spike = first if how.endswith("first") else last if how.endswith("last") else None
+    _check(lasad, oracle, n, Hh, True, W=23, start=2, spike=spike, carried=how.startswith("carried"))
+
+
+def _views(form, B, n, Hh, count, dtype):
+    """`count` tensors [B, n, Hh, D] with one set of strides"""
+    import torch
+    new = lambda *shape: torch.empty(shape, dtype=dtype, device="cuda")
+    if form == "projection":                                 # side by side in the rows of one tensor
+        return list(new(B, n, count, Hh, D).unbind(2))
+    if form == "padded_rows":                                # heads apart, a row longer than its heads
+        return [x[..., :Hh, 8:8 + D] for x in (new(B, n, Hh + 1, D + 16) for _ in range(count))]
+    return [x.transpose(1, 2) for x in (new(B, Hh, n, D) for _ in range(count))]       # head by head
+
+
+def _on_views(inputs, B, n, Hh, form, grad_form, n_grads, dtype):
+    """the inputs on views of one form, and gradient tensors of another"""
+    views = _views(form, B, n, Hh, len(inputs), inputs[0].dtype)
+    for x, y in zip(views, inputs):
+        x.copy_(y)
+    grads = _views(grad_form, B, n, Hh, n_grads, dtype)
+    assert grads[0].stride() != inputs[0].stride() and views[0].stride() != inputs[0].stride()
+    return views, grads
+
+
+@pytest.mark.parametrize("B,n,Hh", [(2, 97, 70), (1, 833, 100), (3, 64, 90)], ids=["whole", "segments", "one_loader_group"])
+@pytest.mark.parametrize("form,grad_form", [("projection", "heads"), ("heads", "projection"), ("padded_rows", "padded_rows")])
+@pytest.mark.parametrize("own", [False, True], ids=["tied", "own"])
+def test_views(lasad, B, n, Hh, form, grad_form, own):
+    """The same bits as for dense tensors (which the other tests hold to the oracle), in both types of the gradients."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    new = lambda: (torch.randn((B, n, Hh, D), generator=gen, device="cuda") / 8).bfloat16()
+    q, v, g, k = new(), new(), new(), new()
+    lam = torch.sigmoid(new().float() * 8 + 2).bfloat16()
+    W = 16
+    kw = dict(grid_h=(n + W) // W + 1, grid_w=W, start_pos=5, q_scale=0.7)
+    for dtype in (torch.bfloat16, torch.float32):
+        want = lasad.lasad_backward_gated(q, lam, v, g, k=k if own else None, grad_dtype=dtype, **kw)
+        ins, grads = _on_views([q, lam, v, g] + ([k] if own else []), B, n, Hh, form, grad_form, len(want), dtype)
+        got = lasad.lasad_backward_gated(*ins[:4], k=ins[4] if own else None, grads=tuple(grads), **kw)
+        for i, (a, b) in enumerate(zip(got, want)):
+            assert torch.equal(a, b), (dtype, i)
+
+
+@pytest.mark.parametrize("B,n,Hh", [(2, 97, 70), (1, 833, 100)], ids=["whole", "segments"])
+@pytest.mark.parametrize("form,grad_form", [("projection", "heads"), ("heads", "padded_rows")])
+def test_views_of_the_layer(lasad, B, n, Hh, form, grad_form):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    new = lambda: torch.randn((B, n, Hh, D), generator=gen, device="cuda").bfloat16()
+    q, z, v, g = new(), new() + 2, new(), new()
+    w = 1 + 0.1 * torch.randn((Hh, D), generator=gen, device="cuda")
+    W = 16
+    kw = dict(grid_h=(n + W) // W + 1, grid_w=W, start_pos=5, norm_weight=w)
+    want = lasad.lasad_backward_layer(q, z, v, g, **kw)
+    ins, grads = _on_views([q, z, v], B, n, Hh, form, grad_form, 3, torch.bfloat16)
+    d_out = _views(grad_form, B, n, Hh, 1, torch.bfloat16)[0].copy_(g)       # strides of its own
+    got = lasad.lasad_backward_layer(*ins, d_out, grads=tuple(grads), **kw)
+    for i, (a, b) in enumerate(zip(got, want)):
+        assert torch.equal(a, b), i
+
+
+@pytest.mark.parametrize("n", [65, 97, 129])
+@pytest.mark.parametrize("what", ["inputs", "gradients"])
+def test_token_strides_that_the_walks_refuse(lasad, oracle, n, what):
+    """A lane's offsets in a chunk of the walks are 32 bits; the three passes, with one loader group here, take a token stride of
+    2^25 elements, and any of the gradients."""
+    import torch
+    Hh, W, far = 161, 16, 1 << 25
+    rng, q, v, g, k, lam = _inputs(n, Hh, n)
+    pick = [0, Hh // 2, Hh - 1]
+    sub = lambda x: np.ascontiguousarray(x[:, :, pick])
+    ins = [lasad.to_device(x, "bf16") for x in (q, lam, v, g, k)]
+    grads = [torch.empty((1, n, Hh, D), device="cuda") for _ in range(4)]
+    side = ins if what == "inputs" else grads
+    base = torch.empty((n - 1) * far + len(side) * Hh * D, dtype=side[0].dtype, device="cuda")
+    apart = [base.as_strided((1, n, Hh, D), (Hh * D, far, D, 1), i * Hh * D) for i in range(len(side))]
+    for x, y in zip(apart, side):
+        x.copy_(y)
+    if what == "inputs":
+        ins = apart
+    else:
+        grads = apart
+    got = lasad.lasad_backward_gated(*ins[:4], (n + W - 1) // W, W, k=ins[4], grads=tuple(grads))
+    for i, (a, r) in enumerate(zip(got, oracle.gated_backward(sub(q), sub(lam), sub(v), sub(g), W, k=sub(k)))):
+        a = a[:, :, pick].cpu().numpy()
+        assert rel_err(a, r) <= TOL["bf16"], (i, rel_err(a, r))
 
 
 # The last call for the three passes and the first for the walks, and the other way round.
