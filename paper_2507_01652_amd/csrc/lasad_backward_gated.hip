@@ -331,8 +331,10 @@ void finish_segments(int64_t n_seq, int n, int *n_seg, int *seg_blocks)
 // PASSES: three independent passes side by side and a finishing kernel (lasad_backward_gated_mfma.hip), for calls whose
 //   passes all get a compute unit of their own (80 sequences) and that are too short to be cut, and for short ones of some more.
 // WALKS: dq, then the reversed walk with everything else (lasad_backward_gated_chunk.hip).  Few long sequences are cut into
-//   segments, one workgroup a compute unit (two a unit: 96 sequences of 4096 tokens, own key, 259 -> 264 us, but 48 of 4096
-//   126 -> 143).  For the accuracy of dlam they keep the states at the bounds of as many parts as the passes had segments.
+//   segments, one workgroup a compute unit.  (Two a unit, own key: 96 sequences of 4096 tokens 289 -> 266 us, but 96 x 2116 128 -> 132,
+//   96 x 1024 72 -> 87, 48 x 4096 120 -> 133, 128 x 4096 295 -> 340.  More than 128 sequences, whole -> two -> three segments: 129 x
+//   1024 90 -> 121 -> 104, 129 x 4096 367 -> 432 -> 347, 160 x 1024 95 -> 128 -> 110, 160 x 4096 448 -> 512 -> 417, 192 x 4096 492 ->
+//   593; fused layer 129 x 4096 545 -> 627 -> 533, 160 x 4096 578 -> 665 -> 595.)  For the accuracy of dlam they keep the states at the bounds of as many parts as the passes had segments.
 // us a call, passes -> walks uncut -> cut (own key): 12 x 400 tokens 31.5 -> 41 -> 35; 12 x 576 35 -> 54 -> 39; 12 x 784 44 -> 71
 // -> 38; 48 x 576 41 -> 57 -> 44; 48 x 784 49 -> 76 -> 47; 80 x 784 57 -> 81 -> 61; 80 x 1024 75 -> 107 -> 74; 96 x 256 33.3 -> 33.1 ->
 // 36.6; 96 x 400 48.4 -> 46.0 -> 46.0; 96 x 576 58 -> 59 -> 53; 128 x 576 63 -> 60 -> 56; 96 x 4096 410 -> 378 -> 264; uncut only: 160

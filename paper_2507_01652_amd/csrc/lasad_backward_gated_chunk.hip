@@ -14,13 +14,13 @@
 //       dk_j = q_scale A_j (.) [ G v_j + sum_i (v_j . g_i) Q~_i ],                  G <- diag(A_end) (G + Q~^T g).
 //   Four compute wavefronts take dv (16 value channels of G each), four dk (16 key channels of G^T each), from one set of
 //   prepared operands.  The running sum of r = q dq - k dk in walking order IS the suffix sum that the decay gradient
-//   needs, so the loaders finish a chunk as soon as its dk tile is there: dq, dk and dlam leave in the caller's type.
+//   needs, so four finishing wavefronts end a chunk as soon as its dk tile is there: dq, dk and dlam leave in the caller's type.
 //
 // Against three independent passes and a finishing kernel, which read q, the decay, d_o up to four times and dk back from the
 // workspace (us a call, graph replay, own key): 256 sequences of 256 tokens 56 -> 39, 512 of 24 x 24 234 -> 167, 96 of 64 x 64 in
-// segments 410 -> 259; fused layer 384 of 256 131 -> 109.  Bound: dq by what it moves (96 of 64 x 64: 306 MB in 72 us); the
-// reversed walk by the longest wavefront of a period (2600 vector instructions a chunk in 5200 cycles of four SIMDs; 556 MB in 150
-// us).  Its address unit is as busy as its vector units, which is why rows are read and written as whole lines wherever LDS can
+// segments 410 -> 287; fused layer 384 of 256 131 -> 109.  Bound: dq by what it moves (96 of 64 x 64, behind a forward: 306 MB in 85
+// us); the reversed walk by the longest wavefront of a period (2600 vector instructions a chunk in 5200 cycles of four SIMDs; 556 MB
+// in 176 us).  Its address unit is as busy as its vector units, which is why rows are read and written as whole lines wherever LDS can
 // turn them: finished rows stored straight from the lanes that make them took 400 us in the place of 314 (uncut).
 //
 // A chunk that leaves the range of the factorisation sends the sequence (segment) to the token-serial walks of the same passes

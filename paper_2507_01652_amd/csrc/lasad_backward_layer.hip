@@ -22,8 +22,8 @@
 // sequence the state is close to rank one with o along its dominant direction, so dq = S d_o and
 // dk are small differences of larger terms: d_o rounded to a single bf16 shows in dq_pre and dz up
 // to 0.15 of their RMS.  With bf16 inputs step 2 therefore leaves d_o as a bf16 PAIR hi + lo (two
-// tensors), and the two column passes of step 3 use both parts where d_o is their operand (the
-// row pass, dv, takes hi alone: no cancellation there).  fp32 inputs keep d_o in fp32.  Steps 1-2
+// tensors), and step 3 uses both parts wherever d_o is an operand, in dv too (no cancellation there,
+// but the last tokens' dv is a multiple of a single d_o row).  fp32 inputs keep d_o in fp32.  Steps 1-2
 // can be run alone (d_o_out: hi only), step 3 alone is the call without a normalisation.
 #include "lasad_scan.h"
 

@@ -17,7 +17,7 @@
 // Bound by the chain from chunk to chunk on the compute units that have a sequence: 52 matrix instructions of 32 cycles a
 // chunk and SIMD (0.8 us) and the LDS reads, decay and mask between them; 1.7 us a chunk in all, 0.5 of a chunk that is only
 // taken into the state.  So few sequences are dealt to several workgroups each (Parts).  96 sequences of 256
-// tokens: 22 us a call (27 with one workgroup each), 64 with the token-serial kernel (lasad_scan.h), which is left to the vector
+// tokens: 22 us a call (27 with one workgroup each), 56 with the token-serial kernel (lasad_scan.h), which is left to the vector
 // decay, to bf16 storage and to up to four tokens of few sequences; distance from fp64 results the same.  (The scores in
 // wavefronts of their own beside those with the state: 31 in the place of 27; a test in the loop for steps without output: 36.)
 #include "lasad_gated_chunk.h"

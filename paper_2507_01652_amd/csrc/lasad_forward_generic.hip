@@ -47,9 +47,9 @@ hipError_t launch_forward_generic(const ForwardArgs &a, hipStream_t s)
     // the fused activations and the norm exist in the scan kernel only: such calls go there whatever the switch says
     const bool fused = a.fused_act || a.norm;
     if (fused && a.d != 64) return hipErrorInvalidValue;
-    // scalar decay in fp32: in chunks on the fp32 matrix instruction, whatever gamma is (96 sequences of 256 tokens 27 us,
-    // 64 with the token-serial kernel).  Up to four tokens of few sequences stay with the latter, two workgroups a
-    // sequence: 12 x 1 4.0 us against 4.5, 96 x 4 4.5 against 4.6; but 96 x 5 4.7 against 4.6, 192 x 1 4.7 against 4.6
+    // scalar decay in fp32: in chunks on the fp32 matrix instruction, whatever gamma is (96 sequences of 256 tokens 22 us,
+    // 56 with the token-serial kernel).  Up to four tokens of few sequences stay with the latter, two workgroups a
+    // sequence: 12 x 4 4.7 us, x 5 4.9 against 5.1; 128 x 4 5.0, x 5 5.1 against 5.4, x 8 5.6 against 5.4; but 192 x 4 5.7 against 5.5
     const bool few = a.n_tokens <= 4 && (int64_t)a.B * a.Hh <= 128;
     if (a.d == 64 && scan && !a.lam && a.io_dtype == LASAD_F32 && !few && a.n_tokens > 0) return launch_forward_f32_chunk(a, s);
     if (a.d == 64 && (scan || fused)) return launch_forward_scan(a, s);

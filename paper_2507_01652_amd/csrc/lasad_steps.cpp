@@ -1,6 +1,6 @@
 // The decode steps' marshalling as a CPython extension (module _steps): what binding.py does for them in Python (shape, type
 // and layout checks, pointers, the current stream), for plain GPU tensors.  A decode step is one short kernel, so a loop of them is
-// bound by the host: one image through twelve layers 85 us a token with the checks in Python and ctypes, 47 with these.
+// bound by the host: one image through twelve layers 79 us a token with the checks in Python and ctypes, 48 with these.
 //
 // Every function returns the output tensor, a status of the library (an int other than 0), or None where an argument is not what
 // it expects: binding.py then goes through its own checks, so that a wrong call fails there as it always did.
