@@ -708,10 +708,13 @@ bool forward_gated_chunk_fits(const ForwardArgs &a) { return a.in.stride_n <= kM
 // 3.2 us and 0.085 us a sequence and 1000 tokens, spread over the idle units.  us (forward and epilogue | forward, then kernel):
 // 12 x 576 tokens 28.5 | 25.4, 33 x 400 22.2 | 21.5, 60 x 784 40.9 | 37.3, 80 x 1024 51.9 | 47.1, 96 x 784 41.8 | 39.8, but 12 x
 // 128 10.5 | 11.4, 48 x 256 16.0 | 16.5, 96 x 400 22.5 | 24.4, 128 x 784 41.7 | 42.3, 256 x 1024 55 | 66, 512 x 576 53 | 76; in
-// segments 12 x 4096 33.6 | 38.2, 96 x 4096 106 | 152.
+// segments 12 x 4096 33.6 | 38.2, 96 x 4096 106 | 152.  In the whole layer's backward the three passes come behind it, which want
+// full groups of eight sequences; without, the line lies lower (epilogue over kernel, the whole call: 33 x 320 1.02, 60 x 256
+// 1.01, x 400 1.04, 67 x 400 1.03; 48 x 400 0.96, 80 x 400 1.00).
 bool forward_gated_norm_backward_pays(int64_t n_seq, int n_tokens)
 {
-    return n_seq >= 147 || n_tokens * (147 - n_seq) <= 37600 || segment_plan(n_seq, n_tokens).n_seg > 1;
+    if (n_seq >= 147 || segment_plan(n_seq, n_tokens).n_seg > 1) return true;
+    return n_tokens <= (n_seq % 8 && n_seq < 80 ? 300 : 37600 / (147 - n_seq));
 }
 
 static hipError_t launch(const ForwardArgs &a, const NormBackwardArgs *nb, int *n_seg, hipStream_t s)

@@ -259,7 +259,7 @@ def test_backward_layer_head_major_inputs(lasad, oracle):
     (1, 2, 31, 67, None),                                              # segments, the last one short
     (1, 2, 31, 67, 1500),                                              # ... one of them left to the token-serial walk
     (130, 2, 5, 13, 40), (1, 2, 6, 11, 40),                            # a range left in a later chunk
-    (1, 2, 7, 37, None), (1, 2, 13, 23, None),                         # both sides of the rule that leaves it to a kernel of its own
+    (1, 2, 12, 25, None), (1, 2, 7, 43, None), (1, 8, 6, 45, None), (1, 8, 13, 21, None),     # both sides of the rule that leaves it to a kernel of its own
 ])
 def test_backward_layer_norm_in_the_recomputed_forward(lasad, oracle, B, Hh, H, W, gate):
     """The normalisation's backward is the recomputed forward's epilogue: every tile edge of both loader arrangements, a
