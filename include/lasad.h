@@ -362,7 +362,7 @@ int lasad_backward_chunked_carried(const void *q, const void *k, const void *v, 
  *                       segment bounds; some longer calls have fewer): a workspace that the query gave for a longer
  *                       call serves every shorter one, which may then be up to about 15 % slower and less accurate
  *                       in dlam.  The least that is accepted, 4 (2 n_tokens + 8) d bytes a sequence, holds no bounds:
- *                       few long sequences then take up to 2.4 times as long.
+ *                       few long sequences then take up to three times as long.
  * Asynchronous on hip_stream; no allocation, no synchronisation; deterministic.
  */
 size_t lasad_backward_gated_workspace_bytes(int B, int n_heads, int n_tokens, int d);
