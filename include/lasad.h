@@ -33,9 +33,9 @@
  *
  * Environment variables (test hooks, read once per process at the first call that needs them; none
  * changes a result beyond rounding, each forces a kernel the launcher would otherwise pick by size):
- *   LASAD_WS=0|8|12        scalar-decay forward, full pass: four-, eight- or twelve-wave workgroups
- *   LASAD_SPLIT=1|2        twelve-wave kernel: whole sequences | two workgroups per sequence
- *   LASAD_WS_MULTI=8|12    merged backward launch: eight- or twelve-wave workgroups
+ *   LASAD_WS=0|8|12        scalar-decay forward, full pass: four- or eight-wave workgroups, or those with a compute unit each
+ *   LASAD_SPLIT=1|2|4      workgroups per sequence of the latter
+ *   LASAD_WS_MULTI=8|12    merged backward launch: likewise
  *   LASAD_GATED_BWD=walk   vector-decay backward: fp32 token-serial walks instead of the chunked passes
  *   LASAD_SCAN=0           fp32 head dim 64: the generic recurrence kernel instead of the chunked (scalar decay) and scan kernels
  *   LASAD_FORCE_GENERIC=1  bf16 head dim 64: the fp32 kernels instead of the matrix-core kernels

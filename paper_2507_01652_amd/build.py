@@ -25,7 +25,7 @@ SOURCES = [
     "lasad_forward_f32_chunk.hip",
     "lasad_forward_mfma.hip",
     "lasad_forward_mfma_ws.hip",
-    "lasad_forward_mfma_ws12.hip",
+    "lasad_forward_scalar_chunk.hip",
     "lasad_forward_gated_chunk.hip",
     "lasad_decode.hip",
     "lasad_decode_cached.hip",

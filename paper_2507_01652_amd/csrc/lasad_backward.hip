@@ -24,14 +24,15 @@
 //
 //   dL/dgamma_h = (1 / gamma_h) sum_b sum_i E_i (q_i . dq_i - k_i . dk_i).
 //
-// bf16 inputs, head dim 64, enough sequences (or sequences too short to be cut into segments):
-// ONE launch of the wave-specialised forward kernel runs the three passes side by side.  Each
+// bf16 inputs, head dim 64: ONE launch of the forward kernels runs the three passes side by side.  Each
 // pass stores its gradient in the caller's type and layout, and the dq and dk passes add up
 // E_i (q_i . dq_i) and -E_i (k_i . dk_i) from their fp32 output tiles before those are rounded
 // (a per-wave partial sum per sequence, fixed order); a small kernel (one workgroup per head)
-// adds the partial sums in a fixed order (no atomics) and divides by gamma.
+// adds the partial sums in a fixed order (no atomics) and divides by gamma.  (Three passes in segments
+// for few long sequences, as the forward has them, and a finishing kernel: 12 sequences of 4096 tokens 104 us
+// in the place of 51, of 1300 36.5 and 19, 48 of 4096 135 and 95.)
 //
-// Otherwise (fp32 inputs, other head dims, few long sequences): three separate passes; dq and dk
+// Otherwise (fp32 inputs, other head dims): three separate passes; dq and dk
 // are produced in fp32 into the workspace, a finishing kernel (one workgroup per 64 tokens of a
 // sequence) forms its part of the sum above (fp32, fixed order) and stores dq, dk in the caller's
 // type and layout, and a last small kernel (one wave per head) adds the partial sums.
@@ -253,8 +254,7 @@ size_t backward_workspace_bytes(int64_t n_seq, int n_tokens, int d, int io_dtype
 {
     const size_t grads = 2 * (size_t)n_seq * n_tokens * d * sizeof(float);
     const size_t sums = sums_bytes(n_seq, n_tokens);
-    const size_t fwd = (io_dtype == LASAD_BF16 && d == 64) ? forward_mfma_workspace_bytes(n_seq, n_tokens) : 0;
-    return grads + sums + fwd;
+    return grads + sums;
 }
 
 hipError_t launch_backward(const BackwardArgs &b_in, bool use_mfma, hipStream_t s)
@@ -264,18 +264,16 @@ hipError_t launch_backward(const BackwardArgs &b_in, bool use_mfma, hipStream_t 
     const int n = b.n_tokens;
     const int elt = b.io_dtype == LASAD_BF16 ? 2 : 4;
     const int gelt = b.grad_dtype == LASAD_BF16 ? 2 : 4;
-    // workspace: dq32, dk32 ([B][n][Hh][d] fp32), partial sums, forward-kernel workspace
+    // workspace: dq32, dk32 ([B][n][Hh][d] fp32), partial sums
     char *ws = (char *)b.workspace;
     const size_t one = (size_t)n_seq * n * b.d * sizeof(float);
     b.dq32 = (float *)ws;
     b.dk32 = (float *)(ws + one);
     b.seq_sums = (float *)(ws + 2 * one);
-    float *fwd_ws = (float *)(ws + 2 * one + sums_bytes(n_seq, n));
-    const bool has_fwd_ws = use_mfma && forward_mfma_workspace_bytes(n_seq, n) > 0;
-    // carried states: transposed copies and the passes' final states follow the forward kernels' workspace
+    // carried states: transposed copies and the passes' final states follow
     const bool carried = b.state_in || b.d_state_out || b.d_state_in;
     const size_t mat = (size_t)n_seq * b.d * b.d;
-    float *cw = (float *)((char *)fwd_ws + (use_mfma ? forward_mfma_workspace_bytes(n_seq, n) : 0));
+    float *cw = (float *)(ws + 2 * one + sums_bytes(n_seq, n));
     float *s0T = cw, *hS = cw + mat, *hT = cw + 2 * mat, *snT = cw + 3 * mat, *g1 = cw + 4 * mat, *extra = cw + 5 * mat;
     const float *st_in[3] = {nullptr, nullptr, nullptr};      // per pass (dq, dv, dk)
     float *st_out[3] = {nullptr, nullptr, nullptr};
@@ -298,12 +296,6 @@ hipError_t launch_backward(const BackwardArgs &b_in, bool use_mfma, hipStream_t 
         hipLaunchKernelGGL(carried_finish_kernel, dim3((unsigned)n_seq), dim3(256), 0, s, b, g1, snT, (float *)extra_sum);
         return hipGetLastError();
     };
-    // The three passes are independent: one launch runs them side by side when that alone fills
-    // the chip or when a pass would not be cut into segments anyway.  The passes then store dq, dv
-    // and dk in the caller's type themselves and take the decay-gradient sums from their fp32
-    // output tiles, so nothing but those sums goes through the workspace.
-    const bool merged = use_mfma && (n_seq * 3 >= 192 || !has_fwd_ws);
-
     lasad_layout_t wl;                                   // layout of dq32 / dk32
     wl.stride_b = (int64_t)n * b.Hh * b.d; wl.stride_n = (int64_t)b.Hh * b.d; wl.stride_h = b.d;
     lasad_layout_t in_rev = b.in, grad_rev = b.grad, wl_rev = wl;
@@ -317,12 +309,14 @@ hipError_t launch_backward(const BackwardArgs &b_in, bool use_mfma, hipStream_t 
     f.grid_w = b.grid_w; f.n_tokens = n;
     f.gamma = b.gamma; f.mode = b.mode; f.q_scale = b.q_scale;
     f.state_in = nullptr; f.state_out = nullptr;
-    f.seg_states = has_fwd_ws ? fwd_ws : nullptr; f.n_segments = 1; f.seg_chunks = 0;
-    auto run = [&](const ForwardArgs &fa) { return use_mfma ? launch_forward_mfma(fa, s) : launch_forward_generic(fa, s); };
+    f.seg_states = nullptr; f.n_segments = 1; f.seg_chunks = 0;
+    auto run = [&](const ForwardArgs &fa) { return launch_forward_generic(fa, s); };
 
     const int rev_start = reversed_start(b.start_pos, n, b.grid_w, b.mode);
     hipError_t e;
-    if (merged) {
+    if (use_mfma) {
+        // (the passes store dq, dv and dk in the caller's type themselves and take the decay-gradient sums from their fp32 output
+        // tiles: nothing but those sums goes through the workspace)
         MultiPass m;
         m.n_pass = 3;
         // dq: forward order, (q, k, v) := (d_o, v, k); sum + E_t (q_t . dq_t)

@@ -42,9 +42,9 @@
 //
 // Few, long sequences.  When there are fewer sequences than the chip has room
 // for workgroups, each sequence is cut into segments of whole chunks and the work
-// is done in two launches: a state pass in which every segment but the last
-// builds, from a zero state, its own contribution U_g to the state (K, V only, no
-// scores, no output), written to a workspace; then the full pass, in which the
+// is done in two launches: a state pass (lasad_forward_scalar_chunk.hip) in which
+// every segment but the last builds, from a zero state, its own contribution U_g
+// to the state (K, V only, no scores, no output), written to a workspace; then the full pass, in which the
 // workgroup of segment g folds U_0..U_{g-1} (and the caller's initial state) into
 // its incoming state, S <- gamma^{E(end_g') - E(begin_g')} S + U_g', and walks its
 // own chunks.  The serial chain per sequence shrinks from all chunks to one
@@ -66,67 +66,6 @@ namespace {
 
 
 using namespace fwd;
-
-// ------------------------------------------------------------------------------------------
-// State pass: segment g < G-1 of every sequence builds U_g = sum_j gamma^{E(end) - E(j)} k_j v_j^T
-// from a zero state and writes it (fp32 [dk][dv]) to seg_states[(bh * (G-1) + g)].
-// ------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(kThreads, 2)
-segment_state_kernel(ForwardArgs a)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t sV[C * VS], sKh[C * VS], sKl[C * VS];
-    __shared__ __attribute__((aligned(16))) float tabC[C];
-
-    const int G1 = a.n_segments - 1;
-    const int bh = blockIdx.x / G1, seg = blockIdx.x - bh * G1;
-    const int b = bh / a.Hh, h = bh - b * a.Hh;
-    const float lg = log2f(a.gamma[h]);
-    if (!(lg * (float)C > -64.0f)) return;        // this head is walked by the fp32 recurrence
-
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int wa = wave >> 1, wc = wave & 1;
-    const int l32 = lane & 31, g = lane >> 5;
-
-    const int seg_t0 = seg * a.seg_chunks * C;                 // first token of the segment
-    const int n = min(a.seg_chunks * C, a.n_tokens - seg_t0);   // its length (a full segment here)
-    const int64_t base = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + (int64_t)seg_t0 * a.in.stride_n;
-    const uint16_t *gk = (const uint16_t *)a.k + base;
-    const uint16_t *gv = (const uint16_t *)a.v + base;
-
-    ChunkPos pos;
-    pos.init(a.start_pos + seg_t0, a.grid_w, a.mode);
-    SplitConst sc;
-    sc.init();
-
-    f32x16 accS;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) accS[r] = 0.f;
-
-    uint4 rk[2], rv[2];
-    load_kv(rk, rv, gk, gv, 0, n, a.in.stride_n, tid);
-    const int n_chunks = (n + C - 1) / C;
-    for (int chunk = 0; chunk < n_chunks; ++chunk) {
-        const int nt = min(C, n - chunk * C);
-        StagedKeys st;
-        prepare_keys(st, rk, rv, tid, nt, pos, lg, sc);
-        write_tiles<false>(nullptr, sV, sKh, sKl, tabC, rk, rv, st, tid);
-        pos.advance();
-        __syncthreads();
-        if (chunk + 1 < n_chunks) load_kv(rk, rv, gk, gv, (chunk + 1) * C, n, a.in.stride_n, tid);
-        Frag fv[4];
-        load_v_frags(fv, sV, wc, lane);
-        state_update(accS, sKh, sKl, fv, wa, lane);
-        const float r_end = __builtin_amdgcn_rcpf(tabC[nt - 1]);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) accS[r] *= r_end;
-        __syncthreads();                                   // tiles free for the next chunk
-    }
-    float *u = a.seg_states + ((int64_t)bh * G1 + seg) * D * D;
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-        u[(wa * 32 + 8 * (r / 4) + 4 * g + (r % 4)) * D + wc * 32 + l32] = accS[r];
-}
 
 // ------------------------------------------------------------------------------------------
 // Full pass: workgroup (bh, seg) walks the chunks of its segment.
@@ -401,30 +340,35 @@ forward_mfma_kernel(ForwardArgs a)
 
 }  // namespace
 
-// Segments per sequence for `n_seq` sequences of `n_chunks` chunks: enough workgroups to fill
-// the chip's resident slots (2 per compute unit) once.  Short sequences stay whole (two
-// launches cost more than their few chunks), and a workgroup folds at most kMaxSegments - 1
-// partial states.
+// Segments per sequence: as many as still get a compute unit each, at least five chunks long.  Most calls are best off whole: state
+// pass, second launch and fold cost about 5 us, and a chunk 0.5 (four workgroups a sequence) to 1.4 us.  us, whole | in segments:
+// 12 sequences of 1024 tokens 11.7 | 13.8, of 1300 14.3 | 14.0, of 2116 20.4 | 16.3, of 4096 35 | 21.6; 32 of 1300 14.9 | 17.2;
+// 40 of 1444 16.0 | 17.6, of 1800 23.5 | 21.8; 48 of 4096 57.6 | 37.2; 80 of 2116 34.9 | 30.5; 96 of 2116 37.5 | 40.9, of 2800 52.4 |
+// 50.0, of 4096 75.5 | 69.2; 128 of 4096 80.7 | 75.1.  (Two workgroups a compute unit and up to eight segments from eight chunks on, as
+// before: 48 of 1024 25.6, 96 of 576 21.5 in the place of 12.4, 192 of 2116 84 in the place of 52.)
 constexpr int kMaxSegments = 8;
-constexpr int kMinChunksToSplit = 8;
 void plan_segments(int64_t n_seq, int n_chunks, int *n_segments, int *seg_chunks)
 {
-    const int64_t slots = 512;
-    int G = (int)(slots / (n_seq > 0 ? n_seq : 1));
-    if (n_chunks < kMinChunksToSplit) G = 1;
+    int G = n_seq < 1 || n_seq > 128 || n_chunks < (n_seq <= 16 ? 20 : n_seq <= 85 ? 25 : 44) ? 1 : (int)(256 / n_seq);
     if (G > kMaxSegments) G = kMaxSegments;
-    if (G > n_chunks / 2) G = n_chunks / 2;          // at least two chunks per segment
+    if (G > n_chunks / 5) G = n_chunks / 5;
     if (G < 1) G = 1;
     const int L = (n_chunks + G - 1) / G;
     *seg_chunks = L > 0 ? L : 1;
     *n_segments = L > 0 ? (n_chunks + L - 1) / L : 1;
 }
 
+// Room for the most segments that a plan may ask for: two workgroups a compute unit, two chunks a segment, from eight chunks on.
+// (What callers are told to provide; the plan above never needs more.)
 size_t forward_mfma_workspace_bytes(int64_t n_seq, int n_tokens)
 {
-    int G, L;
-    plan_segments(n_seq, (n_tokens + C - 1) / C, &G, &L);
-    return G > 1 ? (size_t)n_seq * (G - 1) * D * D * sizeof(float) : 0;
+    const int n_chunks = (n_tokens + C - 1) / C;
+    int G = n_chunks < 8 || n_seq < 1 ? 1 : (int)(512 / n_seq);
+    if (G > kMaxSegments) G = kMaxSegments;
+    if (G > n_chunks / 2) G = n_chunks / 2;
+    if (G <= 1) return 0;
+    const int L = (n_chunks + G - 1) / G;
+    return (size_t)n_seq * ((n_chunks + L - 1) / L - 1) * D * D * sizeof(float);
 }
 
 hipError_t launch_forward_mfma(const ForwardArgs &a_in, hipStream_t s)
@@ -432,21 +376,21 @@ hipError_t launch_forward_mfma(const ForwardArgs &a_in, hipStream_t s)
     if (a_in.d != D || a_in.io_dtype != LASAD_BF16 || a_in.n_tokens < 1) return hipErrorInvalidValue;
     ForwardArgs a = a_in;
     const int64_t n_seq = (int64_t)a.B * a.Hh;
-    if (a.seg_states) plan_segments(n_seq, (a.n_tokens + C - 1) / C, &a.n_segments, &a.seg_chunks);
-    else { a.n_segments = 1; a.seg_chunks = (a.n_tokens + C - 1) / C; }
+    a.n_segments = 1;
+    a.seg_chunks = (a.n_tokens + C - 1) / C;
+    // (every segment reads the incoming state, the last one writes the final one: not where they are the same memory)
+    if (a.seg_states && !(a.state_in && a.state_in == a.state_out)) plan_segments(n_seq, (a.n_tokens + C - 1) / C, &a.n_segments, &a.seg_chunks);
     if (n_seq * a.n_segments > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 block(kThreads);
     if (a.n_segments > 1) {
-        hipLaunchKernelGGL(segment_state_kernel, dim3((unsigned)(n_seq * (a.n_segments - 1))), block, 0, s, a);
-        hipError_t e = hipGetLastError();
+        const hipError_t e = launch_scalar_segment_state(a, s);
         if (e != hipSuccess) return e;
     }
-    // The full pass: the twelve-wave kernel while every workgroup gets a compute unit of its own,
-    // else the eight-wave one (LASAD_WS = 12 / 8 / 0 forces one of them or the four-wave kernel).
+    // The full pass: the kernel for workgroups with a compute unit each while there are so few, else the eight-wave one
+    // (LASAD_WS = 12 / 8 / 0 forces one of them or the four-wave kernel).
     static const int ws = [] { const char *e = getenv("LASAD_WS"); return e ? atoi(e) : -1; }();
-    if (ws == 12 || (ws < 0 && n_seq * a.n_segments <= 256)) return launch_forward_mfma_ws12(a, s);
+    if ((ws == 12 || (ws < 0 && n_seq * a.n_segments <= 256)) && forward_scalar_chunk_fits(a)) return launch_forward_scalar_chunk(a, MultiPass(), s);
     if (ws != 0) return launch_forward_mfma_ws(a, s);
-    const dim3 grid((unsigned)(n_seq * a.n_segments));
+    const dim3 block(kThreads), grid((unsigned)(n_seq * a.n_segments));
     if (a.out_dtype == LASAD_BF16) hipLaunchKernelGGL(forward_mfma_kernel<1>, grid, block, 0, s, a);
     else hipLaunchKernelGGL(forward_mfma_kernel<0>, grid, block, 0, s, a);
     return hipGetLastError();

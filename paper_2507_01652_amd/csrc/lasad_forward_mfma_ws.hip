@@ -316,9 +316,7 @@ static hipError_t launch_ws8(const ForwardArgs &a, const MultiPass &m, hipStream
 
 hipError_t launch_forward_mfma_ws(const ForwardArgs &a, hipStream_t s)
 {
-    MultiPass one;
-    one.n_pass = 1;
-    return launch_ws8(a, one, s);
+    return launch_ws8(a, MultiPass(), s);
 }
 
 static hipError_t launch_ws8(const ForwardArgs &a, const MultiPass &m, hipStream_t s)
@@ -337,16 +335,14 @@ static hipError_t launch_ws8(const ForwardArgs &a, const MultiPass &m, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_ws12_passes(const ForwardArgs &a, const MultiPass &m, hipStream_t s);   // lasad_forward_mfma_ws12.hip
-
-// Several whole-sequence passes in one launch: twelve waves per workgroup while all workgroups of
-// all passes get a compute unit each, else eight waves (two workgroups per compute unit).
+// Several whole-sequence passes in one launch: the kernel for workgroups with a compute unit each while all passes together have so
+// few, else eight waves (two workgroups per compute unit).
 hipError_t launch_forward_mfma_multi(const ForwardArgs &common, const MultiPass &m, hipStream_t s)
 {
     if (common.n_segments != 1 || m.n_pass < 1 || m.n_pass > 3) return hipErrorInvalidValue;
     const int64_t n_wg = (int64_t)common.B * common.Hh * m.n_pass;
     static const int ws = [] { const char *e = getenv("LASAD_WS_MULTI"); return e ? atoi(e) : -1; }();
-    if (ws == 12 || (ws < 0 && n_wg <= 256)) return launch_ws12_passes(common, m, s);
+    if ((ws == 12 || (ws < 0 && n_wg <= 256)) && forward_scalar_chunk_fits(common)) return launch_forward_scalar_chunk(common, m, s);
     return launch_ws8(common, m, s);
 }
 

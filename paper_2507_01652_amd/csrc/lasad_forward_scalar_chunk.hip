@@ -1,0 +1,699 @@
+// Chunked forward for the per-head decay on the bf16 matrix cores (gfx950 MFMA), bf16 storage, head dim 64, for up to 256
+// workgroups: every one has a compute unit to itself.  Chunks of 64 tokens; with e_i = E(i) - E(chunk's start), r_i = gamma^e_i,
+// c_j = gamma^-e_j, f_j = gamma^(e_end - e_j):
+//
+//     o_i   = r_i ( q_i^T S + sum_{j<=i} c_j (q_i . k_j) v_j ),      S <- r_end S + sum_j k_j (f_j v_j)^T
+//
+// All computed operands (scores, S, f V) are bf16 hi + lo pairs against operands that are bf16 as they are: two MFMAs each.
+//
+// What bounds a lone workgroup is the longest wavefront between two barriers: a wavefront issues an instruction about every eight
+// cycles alone on its SIMD, and four on a SIMD one every four to five together.  So the work of a chunk is dealt to many wavefronts
+// with little each, and to few instructions in all (NV value tiles of 16 channels a workgroup, 4 / NV workgroups a sequence):
+//   - one wavefront copies Q and K of the chunk three (two) periods on to LDS without a register in between;
+//   - loader wavefronts turn V into V, f V hi and lo one chunk ahead, and store the output tile of the chunk before;
+//   - NV state wavefronts keep 16 columns of S each in accumulators and leave S^T, hi and lo, for the next chunk;
+//   - output wavefronts take one query tile of 16 tokens each (the later ones, with more keys, half of its value channels or keys).
+// One barrier a chunk; everything that one role leaves for another is doubled.
+//
+// Measured against the kernel this one replaced (10 or 12 wavefronts, 32 x 32 tiles, loaders that also moved Q and K), us a call,
+// graph replay: 16 sequences of 256 tokens 8.0 -> 5.5 (NV 1), of 576 13.4 -> 8.1, 64 of 576 14.0 -> 9.4, 96 of 256 8.6 -> 7.3 (NV 2),
+// 128 of 576 14.5 -> 11.5, 192 of 576 17.7 -> 15.1 (NV 4), 256 of 576 19.0 -> 18.2; three passes of a backward, 16 of 256 11.6 -> 8.8,
+// 24 of 311 14.1 -> 11.5, 80 of 311 16.9 -> 14.8.  Per chunk: 1.2 us -> 0.5 (NV 1), 0.8 (NV 2); 1.65 -> 1.4 (NV 4, from memory).
+// Dropped on the way: 32-token chunks (the latency of a period, about 1000 cycles, twice); compute wavefronts that own their state
+// columns and form all scores themselves, as in the vector-decay kernels (more instructions than the kernel replaced); loaders that
+// move Q and K through registers (16 wavefronts, 2000 cycles a chunk in the place of 1750).
+#include <stdlib.h>
+
+#include "lasad_gated_chunk.h"
+#include "lasad_forward_mfma_common.h"
+#include "lasad_recurrence.h"
+
+namespace lasad {
+
+namespace {
+
+using gchunk::SlotMap;
+using gchunk::SlotPtr;
+using gchunk::causal_mask;
+using gchunk::split_tiles;
+using gchunk::state_channel;
+
+constexpr int CT = 64;                 // tokens per chunk
+constexpr int D = 64;                  // head dim
+
+typedef __attribute__((address_space(3))) void LdsVoid;
+template <int I> struct Const { static constexpr int value = I; };
+
+// ---- Q and K of a chunk, copied from memory to LDS ----
+// Rows of 128 bytes one after the other, their 16-byte pieces permuted by the row (the copy leaves 64 pieces of 16 bytes in a
+// row, so a row cannot be moved, but which lane fetches what is free).  With this permutation sixteen lanes that are served
+// together meet no bank conflict in the operands' row reads, and two-way ones in the transposing reads of K.
+constexpr int kTile = CT * D;          // elements
+__device__ __forceinline__ int turned(int r)           // what the piece's index is XORed with
+{
+    const int x = r >> 1;
+    return (x & 1) | ((x & 2) << 1) | ((x & 4) >> 1);
+}
+
+// ---- V and f V of a chunk, in padded rows ----
+template <int NV>
+struct Slot {
+    static constexpr int V = 0, Fh = 16 * NV, Fl = 32 * NV;
+    static constexpr int ROW = 48 * NV + (NV == 1 ? 0 : 16);
+    using Map = SlotMap<ROW>;
+    static constexpr int kHalfs = CT / 16 * Map::kHalf;
+};
+
+// boundary tokens of a chunk (gchunk::RowBoundaries, for 64 of them)
+struct Boundaries {
+    uint64_t multiples;
+    int W, step, first;
+    __device__ __forceinline__ void init(int start, int grid_w, int mode)
+    {
+        W = grid_w;
+        multiples = 1;
+        for (int k = grid_w; k < 64; k += grid_w) multiples |= 1ull << k;
+        step = CT % grid_w;
+        const int col0 = start % grid_w;
+        first = mode == LASAD_RESET_LAST_COL ? grid_w - 1 - col0 : col0 ? grid_w - col0 : 0;
+        if (mode == LASAD_RESET_NONE) { multiples = 0; first = 0; }
+    }
+    __device__ __forceinline__ uint64_t mask() const { return first < CT ? multiples << first : 0ull; }
+    __device__ __forceinline__ void advance()
+    {
+        first -= step;
+        if (first < 0) first += W;
+    }
+};
+
+// A walk's rows of one tensor as a buffer: rows before the first and past the last are read as zero and not written, without a
+// branch (their offsets leave the range, below zero as unsigned numbers: forward_scalar_chunk_fits).
+struct WalkRows {
+    int step;                          // bytes from row to row (negative in a reversed pass)
+    int first;                         // offset of row 0
+    __device__ __forceinline__ WalkRows(int64_t stride, int n) : step((int)stride), first(stride < 0 ? -(n - 1) * (int)stride : 0) {}
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const char *row0, int n, int bytes) const      // bytes: of a row
+    {
+        const int span = (n - 1) * (step < 0 ? -step : step) + bytes;
+        return __builtin_amdgcn_make_buffer_rsrc((void *)(row0 - first), 0, span, 0x00020000);
+    }
+};
+
+template <bool NT>
+__device__ __forceinline__ u32x4 buf_load(__amdgpu_buffer_rsrc_t r, int off)
+{
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, NT ? 2 : 0));
+}
+template <bool NT>
+__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int off, u32x4 x)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(x, r, off, 0, NT ? 2 : 0);
+}
+
+// Wavefronts: output (NV 2: the two later query tiles by value tile, 96 sequences of 576 tokens 11.4 -> 11.0 us; NV 1: the last one
+// by half of the keys, 16 of 576 9.2 -> 8.1), loaders, all with the state's and the copy's.
+constexpr int out_waves(int nv) { return nv == 2 ? 6 : nv == 1 ? 5 : 4; }
+constexpr int loader_waves(int nv) { return nv == 1 ? 2 : 4; }
+constexpr int all_waves(int nv) { return nv + out_waves(nv) + loader_waves(nv) + 1; }
+
+template <int OUT_BF16, int NV, int DOT>
+struct Shape {
+    static constexpr int kOut = out_waves(NV), kLoaders = loader_waves(NV), kWaves = all_waves(NV);
+    static constexpr bool O16 = OUT_BF16 && !DOT && NV == 4;               // the output tile as bf16
+    static constexpr int R = NV == 4 ? (O16 ? 3 : 2) : 4;                  // Q and K slots (six for NV 1: no gain)
+    static constexpr int OS = O16 ? 16 * NV / 2 + 4 : 16 * NV + 4;         // output tile's row, floats
+    using SM = SlotMap<2 * D + 16>;                                        // S^T, hi and lo
+    static constexpr int kStateHalfs = NV * SM::kHalf;
+    static constexpr int kPart = NV == 1 ? 17 * OS : 0;                    // floats: the last query tile's first half of the keys, and a row of zeros
+    static constexpr int kBytes = 2 * kPart * 4 + R * 2 * kTile * 2 + 2 * Slot<NV>::kHalfs * 2 + 2 * kStateHalfs * 2 + 2 * CT * OS * 4;
+};
+
+// With m.n_pass > 1 one of several independent passes; DOT: the variant that also takes the decay-gradient sums (MultiPass::x).
+template <int OUT_BF16, int NV, int DOT>
+__global__ void __launch_bounds__(all_waves(NV) * 64)
+forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
+{
+    using SL = Slot<NV>;
+    using SH = Shape<OUT_BF16, NV, DOT>;
+    using SM = typename SH::SM;
+    constexpr int PARTS = 4 / NV, R = SH::R, OS = SH::OS, kCompute = NV + SH::kOut;
+    // Rows touched once: non-temporal.  The workgroups of a sequence and the passes of a backward launch share what they read through
+    // the L2.
+    constexpr bool NTL = !DOT && PARTS == 1, NTS = !DOT;
+    constexpr int kRecBytes = recurrence_lds_floats<D>() * 4;
+    constexpr int kTab = CT + 4;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[SH::kBytes > kRecBytes ? SH::kBytes : kRecBytes];
+    __shared__ __attribute__((aligned(16))) float tabs[2][kTab];   // gamma^-e_j of the chunk's tokens, gamma^e_end
+    uint16_t *const tiles = (uint16_t *)smem;                      // [slot][Q, K]
+    uint16_t *const slots = tiles + R * 2 * kTile;
+    uint16_t *const states = slots + 2 * SL::kHalfs;
+    float *const outs = (float *)(states + 2 * SH::kStateHalfs);
+    float *const parts = outs + 2 * CT * OS;
+
+    // the workgroups of a sequence, 8 ids apart: they start together on the same XCD (ids go round the 8 XCDs)
+    int blk = blockIdx.x, vp = 0, pass = 0;
+    const int P = PARTS * m.n_pass;
+    if (P > 1) {
+        const int grp = blockIdx.x / (8 * P), r = blockIdx.x - grp * (8 * P);
+        blk = grp * 8 + (r & 7);
+        vp = (r >> 3) % PARTS;
+        pass = (r >> 3) / PARTS;
+        if (blk >= a.B * a.Hh * a.n_segments) return;
+        if (m.n_pass > 1) {
+            a.q = m.q[pass]; a.k = m.k[pass]; a.v = m.v[pass]; a.o = m.o[pass];
+            a.in = m.in[pass]; a.out = m.out[pass]; a.start_pos = m.start_pos[pass];
+            a.state_in = m.state_in[pass]; a.state_out = m.state_out[pass]; a.first_decay_off = m.first_decay_off[pass];
+        }
+    }
+    const int G = a.n_segments;
+    const int bh = blk / G, seg = blk - bh * G;
+    const int b = bh / a.Hh, h = bh - b * a.Hh;
+    const int tid = threadIdx.x;
+    const int seg_t0 = seg * a.seg_chunks * CT;
+    const int n = min(a.seg_chunks * CT, a.n_tokens - seg_t0);
+    const int n_chunks = (n + CT - 1) / CT;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int64_t in_base = ((int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + (int64_t)seg_t0 * a.in.stride_n) * 2;
+    const WalkRows in(a.in.stride_n * 2, n);
+    const float gamma = a.gamma[h];
+    const float lg = log2f(gamma);
+    if (!(lg * (float)CT > -64.0f)) {  // gamma <= 0.5: c_j could overflow -> fp32 recurrence, the whole sequence by one workgroup
+        if (tid >= kRecThreads || seg != 0 || vp != 0) return;
+        if (DOT) fwd::recurrence_with_dot<OUT_BF16>(a, m, pass, bh, (float *)smem);
+        else recurrence_sequence<D, 1, OUT_BF16>(a, bh, (float *)smem);
+        return;
+    }
+
+    if (wave == SH::kWaves - 1) {
+        // ===================================== the copy of Q and K =====================================
+        const __amdgpu_buffer_rsrc_t rq = in.rsrc((const char *)a.q + in_base, n, 128), rk = in.rsrc((const char *)a.k + in_base, n, 128);
+        int off[2], slot = 0;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int r = 8 * e + (lane >> 3);
+            off[e] = in.first + r * in.step + ((lane & 7) ^ turned(r)) * 16;
+        }
+        auto copy = [&]() {                                    // the next chunk into the next slot
+            char __attribute__((address_space(3))) *const at = (char __attribute__((address_space(3))) *)(tiles + slot * 2 * kTile);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rq, (LdsVoid *)(at + i * 1024), 16, off[i & 1], 0, 0, NTL ? 2 : 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (LdsVoid *)(at + kTile * 2 + i * 1024), 16, off[i & 1], 0, 0, NTL ? 2 : 0);
+                off[i & 1] += 16 * in.step;
+            }
+            slot = slot + 1 == R ? 0 : slot + 1;
+        };
+        constexpr int kWait = 16 * (R - 2);                    // all but the last R - 2 chunks have arrived
+        for (int i = 0; i < R - 1; ++i) copy();                // (past the end: zeros)
+        __builtin_amdgcn_s_waitcnt(0x0f70 | (kWait & 15) | (kWait >> 4 << 14));
+        __builtin_amdgcn_s_barrier();
+        for (int chunk = 0; chunk < n_chunks; ++chunk) {
+            if (chunk + R - 1 < n_chunks) {
+                copy();
+                __builtin_amdgcn_s_waitcnt(0x0f70 | (kWait & 15) | (kWait >> 4 << 14));
+            } else {
+                __builtin_amdgcn_s_waitcnt(0x0f70);
+            }
+            __builtin_amdgcn_s_barrier();
+        }
+        return;
+    }
+    SplitConst sc;
+    sc.init();
+
+    if (wave >= kCompute) {
+        // ===================================== loader wavefronts =====================================
+        constexpr int PC = 2 * NV, ROWS = SH::kLoaders * 64 / PC, IT = CT / ROWS;
+        const int st = tid - 64 * kCompute, row = st / PC, pc = st % PC;
+        constexpr int E = OUT_BF16 ? 2 : 4;
+        const WalkRows out(a.out.stride_n * E, n);
+        const __amdgpu_buffer_rsrc_t rv = in.rsrc((const char *)a.v + in_base, n, 128);
+        const __amdgpu_buffer_rsrc_t ro = out.rsrc((char *)a.o + ((int64_t)b * a.out.stride_b + (int64_t)h * a.out.stride_h + (int64_t)seg_t0 * a.out.stride_n) * E, n, D * E);
+        int v_off = in.first + row * in.step + vp * (32 * NV) + pc * 16, x_off = v_off;
+        int o_off = out.first + (row - CT) * out.step + (vp * 16 * NV + pc * 8) * E;       // (of the chunk before the first)
+        constexpr int PF = 2;              // (four: 1 to 3 % slower, for the periods past the end)
+        struct Regs { u32x4 v[IT]; } r[PF];
+        auto fetch = [&](Regs &x) {
+#pragma unroll
+            for (int i = 0; i < IT; ++i) x.v[i] = buf_load<NTL>(rv, v_off + i * ROWS * in.step);
+            v_off += CT * in.step;
+        };
+#pragma unroll
+        for (int i = 0; i < PF; ++i) fetch(r[i]);
+        __builtin_amdgcn_sched_barrier(0);
+        Boundaries bounds;
+        bounds.init(a.start_pos + seg_t0, a.grid_w, a.mode);
+        const uint64_t upto = ~0ull >> (63 - row);
+        const int put = SL::Map::at(row, pc * 8);
+        float *const tab_at = &tabs[0][pc == 0 ? row : CT];
+        int p_left = n;                                        // tokens from the next chunk to be prepared on
+        // decay-gradient sums: weights of the rows of the chunks under way, and the fourth tensor's rows one period ahead
+        float wq[3][IT], acc = 0.f;
+        int e_before = 0;
+        float e_sign = 0.f, e_add = 0.f;
+        u32x4 x4[IT];
+        const bool dots = DOT && m.x[pass];
+        const __amdgpu_buffer_rsrc_t rx = in.rsrc((const char *)(dots ? m.x[pass] : a.v) + in_base, n, 128);
+        if (DOT) {
+            if (dots) {
+                const int e_all = cum_exp(m.x_start_pos + a.n_tokens, a.grid_w, a.mode) - cum_exp(m.x_start_pos, a.grid_w, a.mode);
+                // in a reversed pass step i applies the decay of the token walked before it, the first step somebody else's
+                const int first = is_boundary(a.start_pos + 1, a.grid_w, a.mode) ? 0 : 1;
+                e_sign = m.x_rev[pass] ? -m.x_sign[pass] : m.x_sign[pass];
+                e_add = m.x_rev[pass] ? m.x_sign[pass] * (float)(e_all + first) : 0.f;
+            }
+        }
+        auto prepare = [&](const Regs &x, int p) {
+            const uint64_t bmask = bounds.mask();
+            bounds.advance();
+            const int nt = min(p_left, CT);
+            p_left -= CT;
+            const int e_end = nt - __builtin_popcountll(bmask & (~0ull >> (CT - nt)));
+            const float end = __builtin_amdgcn_exp2f((float)e_end * lg);
+#pragma unroll
+            for (int i = 0; i < IT; ++i) {
+                const int e = row + i * ROWS + 1 - __builtin_popcountll(bmask & (IT == 1 || i == 0 ? upto : ((1ull << ROWS) - 1) | upto << ROWS));
+                if (DOT) wq[2][i] = e_sign * (float)(e_before + e) + e_add;
+                const float cj = __builtin_amdgcn_exp2f(-(float)e * lg), fj = cj * end;
+                uint16_t *const s = slots + p * SL::kHalfs + put + i * (ROWS / 16) * SL::Map::kHalf;
+                if (pc < 2) tab_at[p * kTab + (pc == 0 ? i * ROWS : 0)] = pc == 0 ? cj : end;
+                *(u32x4 *)(s + SL::V) = x.v[i];
+                u32x4 hi, lo;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    uint32_t hw, lw;
+                    split2(__uint_as_float(x.v[i][w] << 16) * fj, __uint_as_float(x.v[i][w] & 0xffff0000u) * fj, hw, lw, sc);
+                    hi[w] = hw;
+                    lo[w] = lw;
+                }
+                *(u32x4 *)(s + SL::Fh) = hi;
+                *(u32x4 *)(s + SL::Fl) = lo;
+            }
+            if (DOT) e_before += e_end;
+        };
+        struct Tile { f32x4v u[IT], w[IT]; };
+        auto read_tile = [&](Tile &t, int p) {
+#pragma unroll
+            for (int i = 0; i < IT; ++i) {
+                if (SH::O16) {
+                    t.u[i] = *(const f32x4v *)(outs + p * CT * OS + (row + i * ROWS) * OS + pc * 4);
+                } else {
+                    const float *tile = outs + p * CT * OS + (row + i * ROWS) * OS + pc * 8;
+                    t.u[i] = *(const f32x4v *)tile;
+                    t.w[i] = *(const f32x4v *)(tile + 4);
+                    if (NV == 1) {
+                        const float *const more = parts + p * SH::kPart + (row < CT - 16 ? 16 : row - (CT - 16)) * OS + pc * 8;
+                        t.u[i] += *(const f32x4v *)more;
+                        t.w[i] += *(const f32x4v *)(more + 4);
+                    }
+                }
+            }
+        };
+        int t_row = row - CT;                                  // token of this thread's first row in the tile to be stored
+        auto store_tile = [&](const Tile &t) {
+#pragma unroll
+            for (int i = 0; i < IT; ++i) {
+                const int at = o_off + i * ROWS * out.step;
+                const f32x4v &u = t.u[i], &w = t.w[i];
+                if (SH::O16) {
+                    buf_store<NTS>(ro, at, __builtin_bit_cast(u32x4, u));
+                } else if (OUT_BF16) {
+                    buf_store<NTS>(ro, at, u32x4{pack2(u[0], u[1]), pack2(u[2], u[3]), pack2(w[0], w[1]), pack2(w[2], w[3])});
+                } else {
+                    buf_store<NTS>(ro, at, __builtin_bit_cast(u32x4, u));
+                    buf_store<NTS>(ro, at + 16, __builtin_bit_cast(u32x4, w));
+                }
+                if (DOT) {
+                    float d = 0.f;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const f32x4v &y = j < 2 ? u : w;
+                        d = fmaf(__uint_as_float(x4[i][j] << 16), y[2 * (j & 1)], d);
+                        d = fmaf(__uint_as_float(x4[i][j] & 0xffff0000u), y[2 * (j & 1) + 1], d);
+                    }
+                    acc = (uint32_t)(t_row + i * ROWS) < (uint32_t)n ? fmaf(wq[0][i], d, acc) : acc;
+                    wq[0][i] = wq[1][i];
+                    wq[1][i] = wq[2][i];
+                    x4[i] = buf_load<false>(rx, x_off + i * ROWS * in.step);       // (of the tile stored next)
+                }
+            }
+            o_off += CT * out.step;
+            if (DOT) { x_off += CT * in.step; t_row += CT; }
+        };
+        if (NV == 1 && st < 2 * OS) parts[(st / OS) * SH::kPart + 16 * OS + st % OS] = 0.f;
+        prepare(r[0], 0);
+        if (DOT)
+            for (int i = 0; i < IT; ++i) { wq[0][i] = 0.f; wq[1][i] = wq[2][i]; }
+        fetch(r[0]);
+        __syncthreads();
+        // Pairs of periods: with a way out between them the compiler waits for all loads at the loop's top.  (What is past the
+        // end does nothing.)
+        for (int c0 = 0; c0 <= n_chunks; c0 += PF) {
+#pragma unroll
+            for (int u = 0; u < PF; ++u) {
+                const int chunk = c0 + u;
+                Tile t;
+                read_tile(t, (u + 1) & 1);
+                if (chunk + 1 < n_chunks) prepare(r[(u + 1) % PF], (u + 1) & 1);
+                store_tile(t);
+                fetch(r[(u + 1) % PF]);
+                if (chunk < n_chunks) __syncthreads();
+            }
+        }
+        if (dots) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+            if (lane == 0) {
+                float *dst = m.x_sums + ((int64_t)pass * a.B * a.Hh + bh) * kDotSlots;
+                dst[vp * SH::kLoaders + (st >> 6)] = acc;
+                if (NV == 4) dst[4 + (st >> 6)] = 0.f;
+            }
+        }
+        return;
+    }
+
+    const int l16 = lane & 15, g = lane >> 4;
+    const SlotPtr<SL::ROW> sp0(slots, lane);
+    if (wave < NV) {
+        // ===================================== state wavefronts =====================================
+        const int col = 16 * wave;                             // value channels of this wavefront in the slot
+        const int64_t s_off = (int64_t)bh * D * D + vp * 16 * NV + col + l16;
+        f32x4v accS[4];                                        // S[state_channel(t, g) + r][.. + l16]
+#pragma unroll
+        for (int t = 0; t < 4; ++t) accS[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
+        if (a.state_in) {
+            const float s_in = incoming_state_scale(a, gamma);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) accS[t][r] = s_in * a.state_in[s_off + (state_channel(t, g) + r) * D];
+        }
+        for (int sp = 0; sp < seg; ++sp) {
+            const int begin = a.start_pos + sp * a.seg_chunks * CT;
+            const int de = fwd::range_exponent(begin, begin + a.seg_chunks * CT, a.grid_w, a.mode);
+            const float dec = de == 0 ? 1.0f : __builtin_amdgcn_exp2f((float)de * lg);
+            const float *u = a.seg_states + ((int64_t)bh * (G - 1) + sp) * D * D + vp * 16 * NV + col + l16;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) accS[t][r] = fmaf(dec, accS[t][r], u[(state_channel(t, g) + r) * D]);
+        }
+        uint16_t *const st_put = states + SM::row(col + l16) + SM::piece(col + l16, g);
+        auto publish = [&](int p) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                uint2 hi, lo;
+                split2(accS[t][0], accS[t][1], hi.x, lo.x, sc);
+                split2(accS[t][2], accS[t][3], hi.y, lo.y, sc);
+                uint16_t *const d = st_put + p * SH::kStateHalfs + 32 * (t >> 1) + 4 * (t & 1);
+                *(uint2 *)d = hi;
+                *(uint2 *)(d + D) = lo;
+            }
+        };
+        // K: rows 4 g + l16 / 4 (and 16, 32, 48 on), the tiles' channels
+        const int kr = 4 * g + (l16 >> 2);
+        const uint16_t *const k0 = tiles + kTile + kr * D + ((lane & 3) ^ turned(kr)) * 8;
+        const uint16_t *const k1 = tiles + kTile + kr * D + (((lane & 3) + 4) ^ turned(kr)) * 8;
+        publish(0);
+        __syncthreads();
+        int slot = 0;
+        auto step = [&](auto parity, bool last) {
+            constexpr int p = decltype(parity)::value;
+            const float end = tabs[p][CT];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) accS[t] *= end;
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                const SlotPtr<SL::ROW> sp(sp0, p * SL::kHalfs + kk * 2 * SL::Map::kHalf);
+                const Frag fh = sp.tokens(SL::Fh + col), fl = sp.tokens(SL::Fl + col);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const uint16_t *const kp = (t >> 1 ? k1 : k0) + slot + kk * 32 * D + 4 * (t & 1);
+                    Frag k;
+                    k.h[0] = tr_read(kp);
+                    k.h[1] = tr_read(kp + 16 * D);
+                    accS[t] = mfma16(k, fh, accS[t]);
+                    accS[t] = mfma16(k, fl, accS[t]);
+                }
+            }
+            if (!last) publish(p ^ 1);
+            slot = slot == (R - 1) * 2 * kTile ? 0 : slot + 2 * kTile;
+            __syncthreads();
+        };
+        for (int chunk = 0; chunk < n_chunks; chunk += 2) {
+            step(Const<0>(), chunk + 1 == n_chunks);
+            if (chunk + 1 < n_chunks) step(Const<1>(), chunk + 2 == n_chunks);
+        }
+        if (a.state_out && seg == G - 1) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) a.state_out[s_off + (state_channel(t, g) + r) * D] = accS[t][r];
+        }
+        return;
+    }
+
+    // ===================================== output wavefronts =====================================
+    const f32x4v zero4 = {0.f, 0.f, 0.f, 0.f};
+    const uint16_t *const st_get = states + SM::row(l16) + SM::piece(l16, g);
+    const uint16_t *const row0 = tiles + l16 * D + (g ^ turned(l16)) * 8, *const row1 = tiles + l16 * D + ((g + 4) ^ turned(l16)) * 8;
+    __syncthreads();
+    // query tile QT, value tiles C0 .. C0 + CN - 1; KEYS: 3 all keys of the chunk, 1 the first half of them alone, 2 the others
+    auto walk = [&](auto tile, auto first, auto count, auto keys) {
+        constexpr int KEYS = decltype(keys)::value;
+        constexpr int QT = decltype(tile)::value, C0 = decltype(first)::value, CN = decltype(count)::value;
+        int slot = 0;
+        auto step = [&](auto parity) {
+            constexpr int p = decltype(parity)::value;
+            f32x4v pt[4] = {zero4, zero4, zero4, zero4}, o[CN];        // P^T[j][i] of the key tiles, O^T[n][i]
+#pragma unroll
+            for (int c = 0; c < CN; ++c) o[c] = zero4;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const uint16_t *const rows = (s ? row1 : row0) + slot;
+                Frag q;
+                q.u = *(const uint4 *)(rows + QT * 16 * D);
+#pragma unroll
+                for (int kt = 0; kt <= QT; ++kt) {
+                    if (!(KEYS >> kt / 2 & 1)) continue;
+                    Frag k;
+                    k.u = *(const uint4 *)(rows + kTile + kt * 16 * D);
+                    pt[kt] = mfma16(k, q, pt[kt]);
+                }
+#pragma unroll
+                for (int c = 0; c < CN; ++c) {
+                    if (!(KEYS & 2)) continue;
+                    Frag sh, sl;
+                    sh.u = *(const uint4 *)(st_get + p * SH::kStateHalfs + (C0 + c) * SM::kHalf + 32 * s);
+                    sl.u = *(const uint4 *)(st_get + p * SH::kStateHalfs + (C0 + c) * SM::kHalf + D + 32 * s);
+                    o[c] = mfma16(sh, q, o[c]);
+                    o[c] = mfma16(sl, q, o[c]);
+                }
+            }
+            const float osc = a.q_scale * __builtin_amdgcn_rcpf(tabs[p][16 * QT + l16]);
+#pragma unroll
+            for (int kt = 0; kt <= QT; ++kt)
+                if (KEYS >> kt / 2 & 1) pt[kt] *= *(const f32x4v *)&tabs[p][16 * kt + 4 * g];
+            if (KEYS >> QT / 2 & 1) causal_mask(pt[QT], lane);
+#pragma unroll
+            for (int kk = 0; kk <= QT / 2; ++kk) {
+                if (!(KEYS >> kk & 1)) continue;
+                const SlotPtr<SL::ROW> sk(sp0, p * SL::kHalfs + kk * 2 * SL::Map::kHalf);
+                Frag ph, pl;
+                split_tiles(pt[2 * kk], pt[2 * kk + 1], ph, pl, sc);   // (keys past the query tile: zero)
+#pragma unroll
+                for (int c = 0; c < CN; ++c) {
+                    const Frag v = sk.tokens(SL::V + 16 * (C0 + c));
+                    o[c] = mfma16(v, ph, o[c]);
+                    o[c] = mfma16(v, pl, o[c]);
+                }
+            }
+            if (SH::O16) {
+                uint16_t *tile_at = (uint16_t *)outs + (p * CT + 16 * QT + l16) * 2 * OS + 4 * g;
+#pragma unroll
+                for (int c = 0; c < CN; ++c) {
+                    o[c] *= osc;
+                    *(uint2 *)(tile_at + 16 * (C0 + c)) = make_uint2(pack2(o[c][0], o[c][1]), pack2(o[c][2], o[c][3]));
+                }
+            } else {
+                float *tile_at = (KEYS == 1 ? parts + p * SH::kPart : outs + p * CT * OS + 16 * QT * OS) + l16 * OS + 4 * g;
+#pragma unroll
+                for (int c = 0; c < CN; ++c) *(f32x4v *)(tile_at + 16 * (C0 + c)) = o[c] * osc;
+            }
+            slot = slot == (R - 1) * 2 * kTile ? 0 : slot + 2 * kTile;
+            __syncthreads();
+        };
+        for (int chunk = 0; chunk < n_chunks; chunk += 2) {
+            step(Const<0>());
+            if (chunk + 1 < n_chunks) step(Const<1>());
+        }
+    };
+    const int w = wave - NV;
+    const Const<3> all;
+    if constexpr (NV == 1) {
+        if (w == 0) walk(Const<0>(), Const<0>(), Const<1>(), all);
+        else if (w == 1) walk(Const<1>(), Const<0>(), Const<1>(), all);
+        else if (w == 2) walk(Const<2>(), Const<0>(), Const<1>(), all);
+        else if (w == 3) walk(Const<3>(), Const<0>(), Const<1>(), Const<1>());
+        else walk(Const<3>(), Const<0>(), Const<1>(), Const<2>());
+    } else if constexpr (NV == 2) {
+        if (w == 0) walk(Const<0>(), Const<0>(), Const<2>(), all);
+        else if (w == 1) walk(Const<1>(), Const<0>(), Const<2>(), all);
+        else if (w == 2) walk(Const<2>(), Const<0>(), Const<1>(), all);
+        else if (w == 3) walk(Const<2>(), Const<1>(), Const<1>(), all);
+        else if (w == 4) walk(Const<3>(), Const<0>(), Const<1>(), all);
+        else walk(Const<3>(), Const<1>(), Const<1>(), all);
+    } else {
+        if (w == 0) walk(Const<0>(), Const<0>(), Const<NV>(), all);
+        else if (w == 1) walk(Const<1>(), Const<0>(), Const<NV>(), all);
+        else if (w == 2) walk(Const<2>(), Const<0>(), Const<NV>(), all);
+        else walk(Const<3>(), Const<0>(), Const<NV>(), all);
+    }
+}
+
+// State pass of the segment plan: what a segment (all but the last) adds to the state, gamma^(E(end) - E(j)) k_j v_j^T summed over
+// its tokens (bound by memory; a workgroup of four wavefronts that met at two barriers a chunk took 54 us a call where this one
+// takes 36, 12 sequences of 4096 tokens in two segments; 96 of 4096 87 -> 69).  Weights from the segment's end on are at most 1, so nothing is ever rescaled, and a wavefront needs no other: it walks
+// a quarter of the segment's chunks of 32 tokens in a slot of its own, all 64 x 64 of the state in its accumulators, without a
+// barrier; the four states are added up at the end.
+constexpr int kStateRow = 3 * D + 16;          // K, f V hi, lo
+constexpr int kStateSlot = SlotMap<kStateRow>::kHalfs;
+__global__ void __launch_bounds__(256, 2)
+scalar_segment_state_kernel(ForwardArgs a)
+{
+    using Map = SlotMap<kStateRow>;
+    constexpr int C = 32, kK = 0, kFh = D, kFl = 2 * D;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[4 * D * D * 4 > 4 * kStateSlot * 2 ? 4 * D * D * 4 : 4 * kStateSlot * 2];
+    const int G1 = a.n_segments - 1;
+    const int bh = blockIdx.x / G1, seg = blockIdx.x - bh * G1;
+    const int b = bh / a.Hh, h = bh - b * a.Hh;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    // chunks of 32 tokens of this wavefront (the segment has an even number of them, all full)
+    const int n_chunks = 2 * a.seg_chunks, c_lo = n_chunks * wave / 4, c_hi = n_chunks * (wave + 1) / 4;
+    const int seg_t0 = seg * a.seg_chunks * CT;
+    const int64_t base = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + (int64_t)(seg_t0 + c_lo * C) * a.in.stride_n;
+    const int lr = lane >> 3, lc = lane & 7;       // rows r0 .. of a chunk: eight lanes a row, eight rows an instruction
+    const int64_t step = 8 * a.in.stride_n, lane_off = lr * a.in.stride_n + lc * 8;
+    const uint16_t *gk = (const uint16_t *)a.k + base + lane_off, *gv = (const uint16_t *)a.v + base + lane_off;
+    u32x4 rk[4], rv[4];
+    auto fetch = [&]() {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            rk[i] = *(const u32x4 *)(gk + i * step);
+            rv[i] = *(const u32x4 *)(gv + i * step);
+        }
+        gk += 4 * step; gv += 4 * step;
+    };
+    if (c_lo < c_hi) fetch();
+    __builtin_amdgcn_sched_barrier(0);
+    const float lg = log2f(a.gamma[h]);
+    SplitConst sc;
+    sc.init();
+    const int start = a.start_pos + seg_t0 + c_lo * C;
+    gchunk::RowBoundaries bounds;
+    bounds.init(start, a.grid_w, a.mode, C);
+    int to_end = fwd::range_exponent(start, a.start_pos + seg_t0 + a.seg_chunks * CT, a.grid_w, a.mode);     // exponent of the chunk's start
+    uint16_t *const slot = (uint16_t *)lds + wave * kStateSlot;
+    const SlotPtr<kStateRow> sp(slot, lane);
+    f32x4v acc[4][4];                              // [key tile][value tile]
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[t][u] = f32x4v{0.f, 0.f, 0.f, 0.f};
+    for (int c = c_lo; c < c_hi; ++c) {
+        const uint32_t bmask = bounds.mask();
+        bounds.advance();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 8 * i + lr;
+            const int e = r + 1 - __builtin_popcount(bmask & (0xffffffffu >> (31 - r)));
+            const float f = __builtin_amdgcn_exp2f((float)(to_end - e) * lg);
+            uint16_t *const p = slot + Map::row(r) + Map::piece(r, lc);
+            *(u32x4 *)(p + kK) = rk[i];
+            u32x4 hi, lo;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                uint32_t hw, lw;
+                split2(__uint_as_float(rv[i][w] << 16) * f, __uint_as_float(rv[i][w] & 0xffff0000u) * f, hw, lw, sc);
+                hi[w] = hw;
+                lo[w] = lw;
+            }
+            *(u32x4 *)(p + kFh) = hi;
+            *(u32x4 *)(p + kFl) = lo;
+        }
+        to_end -= C - __builtin_popcount(bmask);
+        if (c + 1 < c_hi) fetch();
+        Frag fh[4], fl[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { fh[u] = sp.tokens(kFh + 16 * u); fl[u] = sp.tokens(kFl + 16 * u); }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const Frag k = sp.state_rows(kK, t);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc[t][u] = mfma16(k, fh[u], acc[t][u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc[t][u] = mfma16(k, fl[u], acc[t][u]);
+        }
+    }
+    float *const sAcc = (float *)lds;              // [wave][64][64]
+    __syncthreads();
+    float *const mine = sAcc + wave * D * D;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mine[(state_channel(t, g) + r) * D + 16 * u + l16] = acc[t][u][r];
+    __syncthreads();
+    float *const out = a.seg_states + ((int64_t)bh * G1 + seg) * D * D;
+    for (int i = threadIdx.x * 4; i < D * D; i += 1024) {
+        const f32x4v *const p = (const f32x4v *)(sAcc + i);
+        *(f32x4v *)(out + i) = (p[0] + p[D * D / 4]) + (p[2 * (D * D / 4)] + p[3 * (D * D / 4)]);
+    }
+}
+
+}  // namespace
+
+// The rows of a walk, and four chunks beyond them, within 2^31 bytes.
+bool forward_scalar_chunk_fits(const ForwardArgs &a)
+{
+    auto ok = [&](const lasad_layout_t &l, int elt) {
+        return (l.stride_n < 0 ? -l.stride_n : l.stride_n) * elt < ((int64_t)1 << 31) / (a.n_tokens + 4 * CT) - 4;
+    };
+    return ok(a.in, 2) && ok(a.out, a.out_dtype == LASAD_BF16 ? 2 : 4);
+}
+
+hipError_t launch_scalar_segment_state(const ForwardArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL(scalar_segment_state_kernel, dim3((unsigned)((int64_t)a.B * a.Hh * (a.n_segments - 1))), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+// As many workgroups a sequence (or segment) as still get a compute unit each.  (64 sequences of 576 tokens, NV 4, 2, 1: 14.1, 10.8,
+// 9.4 us; 96 of 576: 14.4, 11.0, 16.4; 192 of 576: 15.0, 20.1.)
+hipError_t launch_forward_scalar_chunk(const ForwardArgs &a, const MultiPass &m, hipStream_t s)
+{
+    if (a.d != D || a.io_dtype != LASAD_BF16 || a.n_tokens < 1 || (m.n_pass > 1 && a.n_segments != 1)) return hipErrorInvalidValue;
+    const int64_t n_blk = (int64_t)a.B * a.Hh * a.n_segments;
+    static const int split_env = [] { const char *e = getenv("LASAD_SPLIT"); return e ? atoi(e) : 0; }();
+    const int split = split_env == 1 || split_env == 2 || split_env == 4 ? split_env
+                      : n_blk * m.n_pass <= 64 ? 4 : n_blk * m.n_pass <= 128 ? 2 : 1;
+    const int P = split * m.n_pass;
+    const int64_t n_wg = P > 1 ? (n_blk + 7) / 8 * 8 * P : n_blk;
+    if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
+    const bool dot = m.n_pass > 1 && (m.x[0] || m.x[1] || m.x[2]);
+    const bool out16 = a.out_dtype == LASAD_BF16;
+#define LASAD_LAUNCH(O, V, X) hipLaunchKernelGGL((forward_scalar_chunk_kernel<O, V, X>), dim3((unsigned)n_wg), dim3(all_waves(V) * 64), 0, s, a, m)
+#define LASAD_LAUNCH1(V) do { \
+        if (dot) { if (out16) LASAD_LAUNCH(1, V, 1); else LASAD_LAUNCH(0, V, 1); } \
+        else { if (out16) LASAD_LAUNCH(1, V, 0); else LASAD_LAUNCH(0, V, 0); } } while (0)
+    if (split == 4) LASAD_LAUNCH1(1);
+    else if (split == 2) LASAD_LAUNCH1(2);
+    else LASAD_LAUNCH1(4);
+#undef LASAD_LAUNCH1
+#undef LASAD_LAUNCH
+    return hipGetLastError();
+}
+
+}  // namespace lasad

@@ -55,7 +55,7 @@ struct ForwardArgs {
 // slots it does not use are written as zero.
 constexpr int kDotSlots = 8;
 struct MultiPass {
-    int n_pass;                  // 1: the ForwardArgs as they are (no other member is read)
+    int n_pass = 1;              // 1: the ForwardArgs as they are (no other member is read)
     int start_pos[3];
     const void *q[3], *k[3], *v[3];
     void *o[3];
@@ -210,8 +210,11 @@ bool forward_gated_norm_backward_pays(int64_t n_seq, int n_tokens);
 hipError_t launch_forward_gated_norm_backward(const ForwardArgs &a, const NormBackwardArgs &nb, int *n_seg, hipStream_t s);
 // the same with eight wavefronts per sequence (whole sequences only, no segment plan)
 hipError_t launch_forward_mfma_ws(const ForwardArgs &a, hipStream_t s);
-// twelve wavefronts, doubled LDS buffers, one barrier per chunk: for workgroups that own a compute unit
-hipError_t launch_forward_mfma_ws12(const ForwardArgs &a, hipStream_t s);
+// many wavefronts with one role each, one barrier per chunk: for workgroups that own a compute unit (m.n_pass 1: the ForwardArgs as
+// they are), if the layouts fit its 32-bit offsets; and the state pass of the segment plan
+bool forward_scalar_chunk_fits(const ForwardArgs &a);
+hipError_t launch_forward_scalar_chunk(const ForwardArgs &a, const MultiPass &m, hipStream_t s);
+hipError_t launch_scalar_segment_state(const ForwardArgs &a, hipStream_t s);
 // n_pass whole-sequence passes (same shapes, types, gamma; fp32 or bf16 output alike) in ONE launch
 hipError_t launch_forward_mfma_multi(const ForwardArgs &common, const MultiPass &m, hipStream_t s);
 // device workspace the MFMA kernel wants for n_seq sequences of n_tokens tokens (0 = none)
