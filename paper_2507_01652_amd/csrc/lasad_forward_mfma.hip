@@ -341,15 +341,15 @@ forward_mfma_kernel(ForwardArgs a)
 }  // namespace
 
 // Segments per sequence: as many as still get a compute unit each, at least five chunks long.  Most calls are best off whole: state
-// pass, second launch and fold cost about 5 us, and a chunk 0.5 (four workgroups a sequence) to 1.4 us.  us, whole | in segments:
-// 12 sequences of 1024 tokens 11.7 | 13.8, of 1300 14.3 | 14.0, of 2116 20.4 | 16.3, of 4096 35 | 21.6; 32 of 1300 14.9 | 17.2;
-// 40 of 1444 16.0 | 17.6, of 1800 23.5 | 21.8; 48 of 4096 57.6 | 37.2; 80 of 2116 34.9 | 30.5; 96 of 2116 37.5 | 40.9, of 2800 52.4 |
-// 50.0, of 4096 75.5 | 69.2; 128 of 4096 80.7 | 75.1.  (Two workgroups a compute unit and up to eight segments from eight chunks on, as
+// pass, second launch and fold cost 5 to 10 us, and a chunk 0.5 (four workgroups a sequence) to 1.4 us.  us, whole | in segments:
+// 12 sequences of 1024 tokens 11.7 | 13.8, 6 of 1280 13.7 | 14.5, 12 of 2116 20.4 | 16.3, of 4096 35 | 21.6; 40 of 1700 20.3 | 22.2;
+// 48 of 4096 57.6 | 38.3; 72 of 1800 34.2 | 28.2, 85 of 1600 25.3 | 27.3; 96 of 2000 37.4 | 34.8, of 4096 75.5 | 64.5; 112 of 1800 34.5 |
+// 34.7; 128 of 1600 30.9 | 32.2, of 4096 80.7 | 69.3.  (Two workgroups a compute unit and up to eight segments from eight chunks on, as
 // before: 48 of 1024 25.6, 96 of 576 21.5 in the place of 12.4, 192 of 2116 84 in the place of 52.)
 constexpr int kMaxSegments = 8;
 void plan_segments(int64_t n_seq, int n_chunks, int *n_segments, int *seg_chunks)
 {
-    int G = n_seq < 1 || n_seq > 128 || n_chunks < (n_seq <= 16 ? 20 : n_seq <= 85 ? 25 : 44) ? 1 : (int)(256 / n_seq);
+    int G = n_seq < 1 || n_seq > 128 || n_chunks < (n_seq <= 16 ? 22 : 29) ? 1 : (int)(256 / n_seq);
     if (G > kMaxSegments) G = kMaxSegments;
     if (G > n_chunks / 5) G = n_chunks / 5;
     if (G < 1) G = 1;
@@ -360,15 +360,19 @@ void plan_segments(int64_t n_seq, int n_chunks, int *n_segments, int *seg_chunks
 
 // Room for the most segments that a plan may ask for: two workgroups a compute unit, two chunks a segment, from eight chunks on.
 // (What callers are told to provide; the plan above never needs more.)
-size_t forward_mfma_workspace_bytes(int64_t n_seq, int n_tokens)
+static int most_states(int64_t n_seq, int n_chunks)
 {
-    const int n_chunks = (n_tokens + C - 1) / C;
     int G = n_chunks < 8 || n_seq < 1 ? 1 : (int)(512 / n_seq);
     if (G > kMaxSegments) G = kMaxSegments;
     if (G > n_chunks / 2) G = n_chunks / 2;
     if (G <= 1) return 0;
     const int L = (n_chunks + G - 1) / G;
-    return (size_t)n_seq * ((n_chunks + L - 1) / L - 1) * D * D * sizeof(float);
+    return (n_chunks + L - 1) / L - 1;
+}
+
+size_t forward_mfma_workspace_bytes(int64_t n_seq, int n_tokens)
+{
+    return (size_t)n_seq * most_states(n_seq, (n_tokens + C - 1) / C) * D * D * sizeof(float);
 }
 
 hipError_t launch_forward_mfma(const ForwardArgs &a_in, hipStream_t s)
@@ -381,14 +385,22 @@ hipError_t launch_forward_mfma(const ForwardArgs &a_in, hipStream_t s)
     // (every segment reads the incoming state, the last one writes the final one: not where they are the same memory)
     if (a.seg_states && !(a.state_in && a.state_in == a.state_out)) plan_segments(n_seq, (a.n_tokens + C - 1) / C, &a.n_segments, &a.seg_chunks);
     if (n_seq * a.n_segments > 0x7fffffff) return hipErrorInvalidValue;
-    if (a.n_segments > 1) {
-        const hipError_t e = launch_scalar_segment_state(a, s);
-        if (e != hipSuccess) return e;
-    }
     // The full pass: the kernel for workgroups with a compute unit each while there are so few, else the eight-wave one
     // (LASAD_WS = 12 / 8 / 0 forces one of them or the four-wave kernel).
     static const int ws = [] { const char *e = getenv("LASAD_WS"); return e ? atoi(e) : -1; }();
-    if ((ws == 12 || (ws < 0 && n_seq * a.n_segments <= 256)) && forward_scalar_chunk_fits(a)) return launch_forward_scalar_chunk(a, MultiPass(), s);
+    const bool own_unit = (ws == 12 || (ws < 0 && n_seq * a.n_segments <= 256)) && forward_scalar_chunk_fits(a);
+    if (a.n_segments > 1) {
+        // The state pass gets the chip's units too, as far as there is room for its states.  (128 sequences of 4096 tokens in two
+        // segments, one, two, three workgroups a segment: 75.5, 69.3, 72.1 us a call.)
+        const int64_t n_first = n_seq * (a.n_segments - 1);
+        if (own_unit) a.seg_parts = (int)(256 / n_first);
+        const int room = most_states(n_seq, (a.n_tokens + C - 1) / C) / (a.n_segments - 1);
+        if (a.seg_parts > room) a.seg_parts = room;
+        if (a.seg_parts < 1) a.seg_parts = 1;
+        const hipError_t e = launch_scalar_segment_state(a, s);
+        if (e != hipSuccess) return e;
+    }
+    if (own_unit) return launch_forward_scalar_chunk(a, MultiPass(), s);
     if (ws != 0) return launch_forward_mfma_ws(a, s);
     const dim3 block(kThreads), grid((unsigned)(n_seq * a.n_segments));
     if (a.out_dtype == LASAD_BF16) hipLaunchKernelGGL(forward_mfma_kernel<1>, grid, block, 0, s, a);

@@ -128,6 +128,17 @@ struct Shape {
     static constexpr int kBytes = 2 * kPart * 4 + R * 2 * kTile * 2 + 2 * Slot<NV>::kHalfs * 2 + 2 * kStateHalfs * 2 + 2 * CT * OS * 4;
 };
 
+// The state pass of a segment plan is dealt out finer than the segments: part i of a sequence, tokens t0 .. t1 - 1.
+struct StatePart {
+    int t0, t1;
+    __device__ __forceinline__ StatePart(const ForwardArgs &a, int i)
+    {
+        const int seg = i / a.seg_parts, j = i - seg * a.seg_parts, len = (a.seg_chunks + a.seg_parts - 1) / a.seg_parts;
+        t0 = (seg * a.seg_chunks + min(j * len, a.seg_chunks)) * CT;
+        t1 = (seg * a.seg_chunks + min((j + 1) * len, a.seg_chunks)) * CT;
+    }
+};
+
 // With m.n_pass > 1 one of several independent passes; DOT: the variant that also takes the decay-gradient sums (MultiPass::x).
 template <int OUT_BF16, int NV, int DOT>
 __global__ void __launch_bounds__(all_waves(NV) * 64)
@@ -388,11 +399,11 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) accS[t][r] = s_in * a.state_in[s_off + (state_channel(t, g) + r) * D];
         }
-        for (int sp = 0; sp < seg; ++sp) {
-            const int begin = a.start_pos + sp * a.seg_chunks * CT;
-            const int de = fwd::range_exponent(begin, begin + a.seg_chunks * CT, a.grid_w, a.mode);
+        for (int sp = 0; sp < seg * a.seg_parts; ++sp) {
+            const StatePart part(a, sp);
+            const int de = fwd::range_exponent(a.start_pos + part.t0, a.start_pos + part.t1, a.grid_w, a.mode);
             const float dec = de == 0 ? 1.0f : __builtin_amdgcn_exp2f((float)de * lg);
-            const float *u = a.seg_states + ((int64_t)bh * (G - 1) + sp) * D * D + vp * 16 * NV + col + l16;
+            const float *u = a.seg_states + ((int64_t)bh * (G - 1) * a.seg_parts + sp) * D * D + vp * 16 * NV + col + l16;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -553,7 +564,7 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
 
 // State pass of the segment plan: what a segment (all but the last) adds to the state, gamma^(E(end) - E(j)) k_j v_j^T summed over
 // its tokens (bound by memory; a workgroup of four wavefronts that met at two barriers a chunk took 54 us a call where this one
-// takes 36, 12 sequences of 4096 tokens in two segments; 96 of 4096 87 -> 69).  Weights from the segment's end on are at most 1, so nothing is ever rescaled, and a wavefront needs no other: it walks
+// takes 36, 12 sequences of 4096 tokens in two segments; 96 of 4096 87 -> 69, and 64 with two workgroups a segment).  Weights from the segment's end on are at most 1, so nothing is ever rescaled, and a wavefront needs no other: it walks
 // a quarter of the segment's chunks of 32 tokens in a slot of its own, all 64 x 64 of the state in its accumulators, without a
 // barrier; the four states are added up at the end.
 constexpr int kStateRow = 3 * D + 16;          // K, f V hi, lo
@@ -564,15 +575,15 @@ scalar_segment_state_kernel(ForwardArgs a)
     using Map = SlotMap<kStateRow>;
     constexpr int C = 32, kK = 0, kFh = D, kFl = 2 * D;
     __shared__ __attribute__((aligned(16))) unsigned char lds[4 * D * D * 4 > 4 * kStateSlot * 2 ? 4 * D * D * 4 : 4 * kStateSlot * 2];
-    const int G1 = a.n_segments - 1;
-    const int bh = blockIdx.x / G1, seg = blockIdx.x - bh * G1;
+    const int n_parts = (a.n_segments - 1) * a.seg_parts;
+    const int bh = blockIdx.x / n_parts, part_i = blockIdx.x - bh * n_parts;
     const int b = bh / a.Hh, h = bh - b * a.Hh;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, g = lane >> 4;
-    // chunks of 32 tokens of this wavefront (the segment has an even number of them, all full)
-    const int n_chunks = 2 * a.seg_chunks, c_lo = n_chunks * wave / 4, c_hi = n_chunks * (wave + 1) / 4;
-    const int seg_t0 = seg * a.seg_chunks * CT;
-    const int64_t base = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + (int64_t)(seg_t0 + c_lo * C) * a.in.stride_n;
+    const StatePart part(a, part_i);
+    // chunks of 32 tokens of this wavefront (all full)
+    const int n_chunks = (part.t1 - part.t0) / C, c_lo = n_chunks * wave / 4, c_hi = n_chunks * (wave + 1) / 4;
+    const int64_t base = (int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + (int64_t)(part.t0 + c_lo * C) * a.in.stride_n;
     const int lr = lane >> 3, lc = lane & 7;       // rows r0 .. of a chunk: eight lanes a row, eight rows an instruction
     const int64_t step = 8 * a.in.stride_n, lane_off = lr * a.in.stride_n + lc * 8;
     const uint16_t *gk = (const uint16_t *)a.k + base + lane_off, *gv = (const uint16_t *)a.v + base + lane_off;
@@ -590,10 +601,10 @@ scalar_segment_state_kernel(ForwardArgs a)
     const float lg = log2f(a.gamma[h]);
     SplitConst sc;
     sc.init();
-    const int start = a.start_pos + seg_t0 + c_lo * C;
+    const int start = a.start_pos + part.t0 + c_lo * C;
     gchunk::RowBoundaries bounds;
     bounds.init(start, a.grid_w, a.mode, C);
-    int to_end = fwd::range_exponent(start, a.start_pos + seg_t0 + a.seg_chunks * CT, a.grid_w, a.mode);     // exponent of the chunk's start
+    int to_end = fwd::range_exponent(start, a.start_pos + part.t1, a.grid_w, a.mode);     // exponent of the chunk's start
     uint16_t *const slot = (uint16_t *)lds + wave * kStateSlot;
     const SlotPtr<kStateRow> sp(slot, lane);
     f32x4v acc[4][4];                              // [key tile][value tile]
@@ -646,7 +657,7 @@ scalar_segment_state_kernel(ForwardArgs a)
 #pragma unroll
             for (int r = 0; r < 4; ++r) mine[(state_channel(t, g) + r) * D + 16 * u + l16] = acc[t][u][r];
     __syncthreads();
-    float *const out = a.seg_states + ((int64_t)bh * G1 + seg) * D * D;
+    float *const out = a.seg_states + ((int64_t)bh * n_parts + part_i) * D * D;
     for (int i = threadIdx.x * 4; i < D * D; i += 1024) {
         const f32x4v *const p = (const f32x4v *)(sAcc + i);
         *(f32x4v *)(out + i) = (p[0] + p[D * D / 4]) + (p[2 * (D * D / 4)] + p[3 * (D * D / 4)]);
@@ -666,7 +677,7 @@ bool forward_scalar_chunk_fits(const ForwardArgs &a)
 
 hipError_t launch_scalar_segment_state(const ForwardArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(scalar_segment_state_kernel, dim3((unsigned)((int64_t)a.B * a.Hh * (a.n_segments - 1))), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(scalar_segment_state_kernel, dim3((unsigned)((int64_t)a.B * a.Hh * (a.n_segments - 1) * a.seg_parts)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -32,8 +32,9 @@ struct ForwardArgs {
     float norm_eps;
     const float *norm_w;         // [Hh][d] fp32, or NULL for ones
     // segment-parallel plan of the MFMA kernel (filled by its launcher)
-    float *seg_states;           // workspace: [B*Hh][n_segments-1][d][d] fp32, or NULL
+    float *seg_states;           // workspace: [B*Hh][(n_segments-1) * seg_parts][d][d] fp32, or NULL
     int n_segments, seg_chunks;
+    int seg_parts = 1;           // states kept per segment (the state pass is dealt out finer than the segments)
     // column passes of the layer backward only: low-order bf16 parts of the tensors in the q and v fields
     // (the operand is hi + lo; same layout), or NULL
     const void *q_lo = nullptr, *v_lo = nullptr;

@@ -63,7 +63,7 @@ def test_split_by_value_channels(lasad, oracle, B, Hh, n):
     _forward(lasad, oracle, B, Hh, n, 19, 3, 0, seed=Hh + n)
 
 
-@pytest.mark.parametrize("B,Hh,n", [(1, 2, 1217), (4, 4, 1280), (1, 17, 1599), (1, 17, 1601), (5, 17, 1650), (2, 64, 2817), (3, 43, 2900)])
+@pytest.mark.parametrize("B,Hh,n", [(1, 2, 1344), (1, 2, 1345), (4, 4, 1400), (1, 17, 1792), (1, 17, 1793), (5, 17, 1850), (1, 86, 1900), (2, 64, 2817), (3, 43, 1900)])
 @pytest.mark.parametrize("carry", [False, True])
 def test_segments(lasad, oracle, B, Hh, n, carry):
     """Calls with and without segments, next to the line between them, with a ragged last segment."""
