@@ -3,9 +3,9 @@
 // 0.5 flop per byte: the kernel is a stream over the fp32 states (read once,
 // written once, in place), so the design goal is HBM bandwidth.
 //
-// One 64-lane wavefront owns one d x d state.  A lane reads 16-byte pieces
-// (4 value channels) so that every wave-wide load covers whole contiguous rows of
-// S; up to 16 loads per lane (the whole state at d = 64) are issued back to back
+// One 64-lane wavefront owns one d x d state, or a quarter of its rows (see launch_decode).  A lane
+// reads 16-byte pieces (4 value channels) so that every wave-wide load covers whole contiguous
+// rows of S; up to 16 loads per lane (the whole state at d = 64) are issued back to back
 // before any arithmetic to keep many bytes in flight.  Each lane keeps the partial q-weighted column sums of
 // the rows it touched; lanes that share a column group are then combined with
 // cross-lane shuffles (no LDS round trip for the reduction).
@@ -13,14 +13,12 @@
 // The states are touched exactly once per step, so their loads and stores carry
 // the non-temporal hint (measured: 28.6 us instead of 33.6 us per step on 5120
 // states, the same as a plain read-modify-write stream over the same bytes), and
-// a workgroup is a single wavefront so that every wave starts as early as possible.
+// a workgroup is one state's wavefronts so that every wave starts as early as possible.
 #include "lasad_internal.h"
 
 namespace lasad {
 
 namespace {
-
-constexpr int kWaves = 1;   // wavefronts (= states) per workgroup
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -46,27 +44,28 @@ __device__ inline float ld_in(const void *p, int64_t idx)
 // GATED = 1: the decay is a vector over the key channels (row i of S is scaled by lambda[i],
 // or by 1 at a row-boundary position) and the key is 1 - lambda unless a key is given
 // (Section 3.4, Algorithm 1 as written).
-template <int D, int IN_BF16, int OUT_BF16, int GATED>
-__global__ void __launch_bounds__(kWaves * 64)
-decode_kernel(DecodeArgs a, int n_states)
+// WV: wavefronts per state, each with D / WV of its rows; their sums meet in LDS.
+template <int D, int IN_BF16, int OUT_BF16, int GATED, int WV>
+__global__ void __launch_bounds__(WV * 64)
+decode_kernel(DecodeArgs a)
 {
     constexpr int CG = D / 4;        // column groups (float4) per row
     constexpr int RPP = 64 / CG;     // rows covered by one wave-wide load
-    constexpr int P = D / RPP;       // loads per lane for the whole state
+    constexpr int P = D / RPP / WV;  // loads per lane for the wavefront's rows
     constexpr int PB = P < 16 ? P : 16;   // loads in flight per lane at a time
-    __shared__ float sqk[kWaves][2 + GATED][D];
+    __shared__ float sqk[WV][2 + GATED][D];
+    __shared__ __attribute__((aligned(16))) float sSum[WV == 1 ? 1 : WV][WV == 1 ? 4 : D];
 
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int bh = blockIdx.x * kWaves + wave;
-    if (bh >= n_states) return;      // whole wave leaves together; no barrier below
+    const int wave = WV == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int bh = blockIdx.x;
     const int h = bh % a.Hh;
-    const int cg = lane % CG, r0 = lane / CG;
+    const int cg = lane % CG, r0 = wave * (D / WV) + lane / CG;      // column group, first row
     const int64_t vec = (int64_t)bh * D;
     int pos = a.pos;
     if (a.pos_rows) {                // continuous batching: every batch row at its own raster position
         pos = a.pos_rows[bh / a.Hh];
         if (pos < 0 || pos >= a.grid_n) {      // inactive row: state untouched, output row zero (whole wave)
-            if (r0 == 0) {
+            if (threadIdx.x < CG) {
                 if (OUT_BF16) *(ushort4 *)((uint16_t *)a.o + vec + cg * 4) = make_ushort4(0, 0, 0, 0);
                 else *(float4 *)((float *)a.o + vec + cg * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
             }
@@ -154,6 +153,17 @@ decode_kernel(DecodeArgs a, int n_states)
         acc.z += __shfl_xor(acc.z, off, 64);
         acc.w += __shfl_xor(acc.w, off, 64);
     }
+    if (WV > 1) {                    // ... and the wavefronts, in the first one
+        if (lane < CG) *(float4 *)&sSum[wave][cg * 4] = acc;
+        __syncthreads();
+        if (wave != 0) return;
+        acc = *(const float4 *)&sSum[0][cg * 4];
+#pragma unroll
+        for (int w = 1; w < WV; ++w) {
+            const float4 x = *(const float4 *)&sSum[w][cg * 4];
+            acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
+        }
+    }
     float qs = a.q_scale;
     if (GATED && a.norm) {           // Norm(o): root mean square over the D channels (lanes 0 .. CG-1 hold them)
         float ss = (acc.x * acc.x + acc.y * acc.y) + (acc.z * acc.z + acc.w * acc.w);
@@ -166,7 +176,7 @@ decode_kernel(DecodeArgs a, int n_states)
             acc.x *= w4.x; acc.y *= w4.y; acc.z *= w4.z; acc.w *= w4.w;
         }
     }
-    if (r0 == 0) {
+    if (lane < CG) {
         if (OUT_BF16) {
             uint16_t *o = (uint16_t *)a.o + vec + cg * 4;
             ushort4 pk;
@@ -182,32 +192,37 @@ decode_kernel(DecodeArgs a, int n_states)
     }
 }
 
-template <int D>
+template <int D, int WV>
 hipError_t launch_d(const DecodeArgs &a, hipStream_t s)
 {
-    const int n_states = a.B * a.Hh;
-    const dim3 grid((unsigned)((n_states + kWaves - 1) / kWaves)), block(kWaves * 64);
+    const dim3 grid((unsigned)(a.B * a.Hh)), block(WV * 64);
     const bool in16 = a.io_dtype == LASAD_BF16, out16 = a.out_dtype == LASAD_BF16;
     if (a.lam) {
-        if (in16 && out16) hipLaunchKernelGGL((decode_kernel<D, 1, 1, 1>), grid, block, 0, s, a, n_states);
-        else if (in16) hipLaunchKernelGGL((decode_kernel<D, 1, 0, 1>), grid, block, 0, s, a, n_states);
-        else hipLaunchKernelGGL((decode_kernel<D, 0, 0, 1>), grid, block, 0, s, a, n_states);
+        if (in16 && out16) hipLaunchKernelGGL((decode_kernel<D, 1, 1, 1, WV>), grid, block, 0, s, a);
+        else if (in16) hipLaunchKernelGGL((decode_kernel<D, 1, 0, 1, WV>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((decode_kernel<D, 0, 0, 1, WV>), grid, block, 0, s, a);
     } else {
-        if (in16 && out16) hipLaunchKernelGGL((decode_kernel<D, 1, 1, 0>), grid, block, 0, s, a, n_states);
-        else if (in16) hipLaunchKernelGGL((decode_kernel<D, 1, 0, 0>), grid, block, 0, s, a, n_states);
-        else hipLaunchKernelGGL((decode_kernel<D, 0, 0, 0>), grid, block, 0, s, a, n_states);
+        if (in16 && out16) hipLaunchKernelGGL((decode_kernel<D, 1, 1, 0, WV>), grid, block, 0, s, a);
+        else if (in16) hipLaunchKernelGGL((decode_kernel<D, 1, 0, 0, WV>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((decode_kernel<D, 0, 0, 0, WV>), grid, block, 0, s, a);
     }
     return hipGetLastError();
 }
 
 }  // namespace
 
+// Four wavefronts a state (d = 64) where the chip has a unit for each state, and the chain load, update, store of a lone wavefront is
+// what a step waits for, and for so many states that their number of loads in flight counts again.  In between a fourth of
+// the loads a wavefront with four times the wavefronts to start is slower.  us a step (graph replay), one | four wavefronts: 12
+// states 3.06 | 2.86, 128 3.26 | 3.12, 256 3.91 | 3.81, fused layer 12 3.48 | 3.18, 256 3.95 | 3.84; 320 4.10 | 4.25, 512 4.60 | 4.70,
+// 1024 6.9 | 7.8, 2048 13.0 | 13.1; 3072 18.9 | 18.6, 5120 30.1 | 29.1, 8192 46.8 | 44.7.
 hipError_t launch_decode(const DecodeArgs &a, hipStream_t s)
 {
+    const int64_t n_states = (int64_t)a.B * a.Hh;
     switch (a.d) {
-        case 32: return launch_d<32>(a, s);
-        case 64: return launch_d<64>(a, s);
-        case 128: return launch_d<128>(a, s);
+        case 32: return launch_d<32, 1>(a, s);
+        case 64: return n_states <= 256 || n_states >= 3000 ? launch_d<64, 4>(a, s) : launch_d<64, 1>(a, s);
+        case 128: return launch_d<128, 1>(a, s);
         default: return hipErrorInvalidValue;
     }
 }
