@@ -335,14 +335,17 @@ static hipError_t launch_ws8(const ForwardArgs &a, const MultiPass &m, hipStream
     return hipGetLastError();
 }
 
-// Several whole-sequence passes in one launch: the kernel for workgroups with a compute unit each while all passes together have so
-// few, else eight waves (two workgroups per compute unit).
+// Several whole-sequence passes in one launch: workgroups with a compute unit each while all passes together have so few, or from 512
+// tokens on; else eight waves, two workgroups a unit: there the starts and ends of short walks overlap, which counts for more than the
+// shorter period.  Eight waves against this, us of a backward (three passes with the decay gradient): 512 sequences of 100 tokens 30.2
+// and 33.7, of 256 49.5 and 51.2, of 400 77.3 and 74.3, of 576 102 and 89, of 1024 200 and 159; 300 of 256 34.5 and 36.7; 260 of 400
+// 49.7 and 51.4; 1536 of 576 336 and 330; 96 of 4096 216 and 178, 200 of them 332 and 293.
 hipError_t launch_forward_mfma_multi(const ForwardArgs &common, const MultiPass &m, hipStream_t s)
 {
     if (common.n_segments != 1 || m.n_pass < 1 || m.n_pass > 3) return hipErrorInvalidValue;
     const int64_t n_wg = (int64_t)common.B * common.Hh * m.n_pass;
     static const int ws = [] { const char *e = getenv("LASAD_WS_MULTI"); return e ? atoi(e) : -1; }();
-    if ((ws == 12 || (ws < 0 && n_wg <= 256)) && forward_scalar_chunk_fits(common)) return launch_forward_scalar_chunk(common, m, s);
+    if ((ws == 12 || (ws < 0 && (n_wg <= 256 || common.n_tokens >= 512))) && forward_scalar_chunk_fits(common)) return launch_forward_scalar_chunk(common, m, s);
     return launch_ws8(common, m, s);
 }
 

@@ -1,5 +1,5 @@
-// Chunked forward for the per-head decay on the bf16 matrix cores (gfx950 MFMA), bf16 storage, head dim 64, for up to 256
-// workgroups: every one has a compute unit to itself.  Chunks of 64 tokens; with e_i = E(i) - E(chunk's start), r_i = gamma^e_i,
+// Chunked forward for the per-head decay on the bf16 matrix cores (gfx950 MFMA), bf16 storage, head dim 64: workgroups that have a
+// compute unit to themselves, and with more sequences than units walk several, one after the other.  Chunks of 64 tokens; with e_i = E(i) - E(chunk's start), r_i = gamma^e_i,
 // c_j = gamma^-e_j, f_j = gamma^(e_end - e_j):
 //
 //     o_i   = r_i ( q_i^T S + sum_{j<=i} c_j (q_i . k_j) v_j ),      S <- r_end S + sum_j k_j (f_j v_j)^T
@@ -10,7 +10,9 @@
 // cycles alone on its SIMD, and four on a SIMD one every four to five together.  So the work of a chunk is dealt to many wavefronts
 // with little each, and to few instructions in all (NV value tiles of 16 channels a workgroup, 4 / NV workgroups a sequence):
 //   - one wavefront copies Q and K of the chunk three (two) periods on to LDS without a register in between;
-//   - loader wavefronts turn V into V, f V hi and lo one chunk ahead, and store the output tile of the chunk before;
+//   - loader wavefronts turn V into V, f V hi and lo one chunk ahead;
+//   - store wavefronts take the output tile of the chunk before to memory (and multiply it into the decay-gradient sums): apart from
+//     the loads, as a load issued after a store is waited for with it;
 //   - NV state wavefronts keep 16 columns of S each in accumulators and leave S^T, hi and lo, for the next chunk;
 //   - output wavefronts take one query tile of 16 tokens each (the later ones, with more keys, half of its value channels or keys).
 // One barrier a chunk; everything that one role leaves for another is doubled.
@@ -19,6 +21,10 @@
 // graph replay: 16 sequences of 256 tokens 8.0 -> 5.5 (NV 1), of 576 13.4 -> 8.1, 64 of 576 14.0 -> 9.4, 96 of 256 8.6 -> 7.3 (NV 2),
 // 128 of 576 14.5 -> 11.5, 192 of 576 17.7 -> 15.1 (NV 4), 256 of 576 19.0 -> 18.2; three passes of a backward, 16 of 256 11.6 -> 8.8,
 // 24 of 311 14.1 -> 11.5, 80 of 311 16.9 -> 14.8.  Per chunk: 1.2 us -> 0.5 (NV 1), 0.8 (NV 2); 1.65 -> 1.4 (NV 4, from memory).
+// Stores apart from the loaders, NV 4 (and non-temporal ones in a backward too): three passes of 80 sequences of 576 tokens 23.7 ->
+// 19.9 us, of 512 102 -> 89, a period 3340 -> 2870 cycles; NV 2, NV 1: 40 of 576 16.0 -> 15.0, 16 of 400 11.0 -> 10.7.
+// Several sequences a workgroup without a pause, against the kernel of eight wavefronts with two workgroups a unit: 512 of 576 41.1 ->
+// 37.6 us, 1000 of 576 81 -> 67; three passes, 512 of 576 102 -> 89, of 1024 200 -> 159, 96 of 4096 216 -> 178.
 // Dropped on the way: 32-token chunks (the latency of a period, about 1000 cycles, twice); compute wavefronts that own their state
 // columns and form all scores themselves, as in the vector-decay kernels (more instructions than the kernel replaced); loaders that
 // move Q and K through registers (16 wavefronts, 2000 cycles a chunk in the place of 1750).
@@ -68,14 +74,17 @@ struct Slot {
 struct Boundaries {
     uint64_t multiples;
     int W, step, first;
-    __device__ __forceinline__ void init(int start, int grid_w, int mode)
+    __device__ __forceinline__ void init(int grid_w)
     {
         W = grid_w;
         multiples = 1;
         for (int k = grid_w; k < 64; k += grid_w) multiples |= 1ull << k;
         step = CT % grid_w;
-        const int col0 = start % grid_w;
-        first = mode == LASAD_RESET_LAST_COL ? grid_w - 1 - col0 : col0 ? grid_w - col0 : 0;
+    }
+    __device__ __forceinline__ void begin(int start, int mode)
+    {
+        const int col0 = start % W;
+        first = mode == LASAD_RESET_LAST_COL ? W - 1 - col0 : col0 ? W - col0 : 0;
         if (mode == LASAD_RESET_NONE) { multiples = 0; first = 0; }
     }
     __device__ __forceinline__ uint64_t mask() const { return first < CT ? multiples << first : 0ull; }
@@ -110,15 +119,16 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int off, u32
     __builtin_amdgcn_raw_buffer_store_b128(x, r, off, 0, NT ? 2 : 0);
 }
 
-// Wavefronts: output (NV 2: the two later query tiles by value tile, 96 sequences of 576 tokens 11.4 -> 11.0 us; NV 1: the last one
-// by half of the keys, 16 of 576 9.2 -> 8.1), loaders, all with the state's and the copy's.
+// Wavefronts, in this order, number modulo 4 being the SIMD: the state's, output (NV 2: the two later query tiles by value tile, 96 sequences of 576 tokens 11.4 -> 11.0 us; NV 1: the last one
+// by half of the keys, 16 of 576 9.2 -> 8.1), loaders, stores, copy.  (NV 4: the SIMDs with the two short query tiles have the stores.)
 constexpr int out_waves(int nv) { return nv == 2 ? 6 : nv == 1 ? 5 : 4; }
 constexpr int loader_waves(int nv) { return nv == 1 ? 2 : 4; }
-constexpr int all_waves(int nv) { return nv + out_waves(nv) + loader_waves(nv) + 1; }
+constexpr int store_waves(int nv) { return nv == 1 ? 1 : 2; }
+constexpr int all_waves(int nv) { return nv + out_waves(nv) + loader_waves(nv) + store_waves(nv) + 1; }
 
 template <int OUT_BF16, int NV, int DOT>
 struct Shape {
-    static constexpr int kOut = out_waves(NV), kLoaders = loader_waves(NV), kWaves = all_waves(NV);
+    static constexpr int kOut = out_waves(NV), kLoaders = loader_waves(NV), kStore = store_waves(NV), kWaves = all_waves(NV);
     static constexpr bool O16 = OUT_BF16 && !DOT && NV == 4;               // the output tile as bf16
     static constexpr int R = NV == 4 ? (O16 ? 3 : 2) : 4;                  // Q and K slots (six for NV 1: no gain)
     static constexpr int OS = O16 ? 16 * NV / 2 + 4 : 16 * NV + 4;         // output tile's row, floats
@@ -139,6 +149,10 @@ struct StatePart {
     }
 };
 
+// Whether the P items of a sequence stay on one XCD: not where some XCD would then have an item more than it has compute units, while
+// the chip has enough (82 sequences, three passes: 33 items on two of the XCDs, 22.6 -> 17.0 us).
+__host__ __device__ __forceinline__ bool by_xcd(int64_t n_blk, int P) { return (n_blk + 7) / 8 * P <= 32 || n_blk * P > 256; }
+
 // With m.n_pass > 1 one of several independent passes; DOT: the variant that also takes the decay-gradient sums (MultiPass::x).
 template <int OUT_BF16, int NV, int DOT>
 __global__ void __launch_bounds__(all_waves(NV) * 64)
@@ -148,9 +162,10 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
     using SH = Shape<OUT_BF16, NV, DOT>;
     using SM = typename SH::SM;
     constexpr int PARTS = 4 / NV, R = SH::R, OS = SH::OS, kCompute = NV + SH::kOut;
+    constexpr bool MANY = NV == 4;
     // Rows touched once: non-temporal.  The workgroups of a sequence and the passes of a backward launch share what they read through
     // the L2.
-    constexpr bool NTL = !DOT && PARTS == 1, NTS = !DOT;
+    constexpr bool NTL = !DOT && PARTS == 1;
     constexpr int kRecBytes = recurrence_lds_floats<D>() * 4;
     constexpr int kTab = CT + 4;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[SH::kBytes > kRecBytes ? SH::kBytes : kRecBytes];
@@ -161,65 +176,85 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
     float *const outs = (float *)(states + 2 * SH::kStateHalfs);
     float *const parts = outs + 2 * CT * OS;
 
-    // the workgroups of a sequence, 8 ids apart: they start together on the same XCD (ids go round the 8 XCDs)
-    int blk = blockIdx.x, vp = 0, pass = 0;
-    const int P = PARTS * m.n_pass;
-    if (P > 1) {
-        const int grp = blockIdx.x / (8 * P), r = blockIdx.x - grp * (8 * P);
-        blk = grp * 8 + (r & 7);
-        vp = (r >> 3) % PARTS;
-        pass = (r >> 3) / PARTS;
-        if (blk >= a.B * a.Hh * a.n_segments) return;
-        if (m.n_pass > 1) {
-            a.q = m.q[pass]; a.k = m.k[pass]; a.v = m.v[pass]; a.o = m.o[pass];
-            a.in = m.in[pass]; a.out = m.out[pass]; a.start_pos = m.start_pos[pass];
-            a.state_in = m.state_in[pass]; a.state_out = m.state_out[pass]; a.first_decay_off = m.first_decay_off[pass];
-        }
-    }
-    const int G = a.n_segments;
-    const int bh = blk / G, seg = blk - bh * G;
-    const int b = bh / a.Hh, h = bh - b * a.Hh;
+    // A workgroup's items are whole sequences of a pass, segments, or some value channels of one; MANY: it walks several, one after
+    // the other (ids gridDim.x apart) without a pause, so that only the first one's loads are waited for.  The ids of a sequence's
+    // items are 8 apart: they are walked at the same time on the same XCD (ids go round the 8 XCDs).
+    const int G = a.n_segments, n_blk = a.B * a.Hh * G, P = PARTS * m.n_pass;
+    struct Item { int blk, vp, pass; };
+    auto item = [&](int i) {
+        const uint32_t id = blockIdx.x + (uint32_t)i * gridDim.x;
+        if (P == 1) return Item{(int)id, 0, 0};
+        if (!by_xcd(n_blk, P)) return Item{(int)(id / P), (int)(id % P % PARTS), (int)(id % P / PARTS)};
+        const uint32_t grp = id / (8 * P), r = id - grp * (8 * P);
+        return Item{(int)(grp * 8 + (r & 7)), (int)((r >> 3) % PARTS), (int)((r >> 3) / PARTS)};
+    };
     const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    uint64_t todo, rest;               // items walked in chunks; those with gamma <= 0.5, where c_j could overflow
+    float lg_lane = 0.f;               // log2 gamma of item `lane`
+    {
+        const Item it = item(MANY ? lane : 0);
+        const bool mine = it.blk < n_blk && (MANY || lane == 0);
+        if (mine) lg_lane = log2f(a.gamma[it.blk / G % a.Hh]);
+        todo = __ballot(mine && lg_lane * (float)CT > -64.0f);
+        rest = __ballot(mine) & ~todo;
+    }
+    auto take = [](uint64_t &left) {
+        const int i = __builtin_ctzll(left);
+        left &= left - 1;
+        return i;
+    };
+    auto log_gamma = [&](int i) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lg_lane), i)); };
+    const bool multi = m.n_pass > 1;
+    const int seg = G > 1 ? item(0).blk % G : 0;
     const int seg_t0 = seg * a.seg_chunks * CT;
     const int n = min(a.seg_chunks * CT, a.n_tokens - seg_t0);
-    const int n_chunks = (n + CT - 1) / CT;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int64_t in_base = ((int64_t)b * a.in.stride_b + (int64_t)h * a.in.stride_h + (int64_t)seg_t0 * a.in.stride_n) * 2;
-    const WalkRows in(a.in.stride_n * 2, n);
-    const float gamma = a.gamma[h];
-    const float lg = log2f(gamma);
-    if (!(lg * (float)CT > -64.0f)) {  // gamma <= 0.5: c_j could overflow -> fp32 recurrence, the whole sequence by one workgroup
-        if (tid >= kRecThreads || seg != 0 || vp != 0) return;
-        if (DOT) fwd::recurrence_with_dot<OUT_BF16>(a, m, pass, bh, (float *)smem);
-        else recurrence_sequence<D, 1, OUT_BF16>(a, bh, (float *)smem);
-        return;
-    }
-
+    const int n_chunks = (n + CT - 1) / CT;                                        // of an item
+    const int n_all = MANY ? (int)__builtin_popcountll(todo) * n_chunks : n_chunks;
+    // element offset of an item's first row in a layout
+    auto first_row = [&](const lasad_layout_t &l, int bh) {
+        const int b = bh / a.Hh, h = bh - b * a.Hh;
+        return (int64_t)b * l.stride_b + (int64_t)h * l.stride_h + (int64_t)seg_t0 * l.stride_n;
+    };
+    auto walk_items = [&]() {
     if (wave == SH::kWaves - 1) {
         // ===================================== the copy of Q and K =====================================
-        const __amdgpu_buffer_rsrc_t rq = in.rsrc((const char *)a.q + in_base, n, 128), rk = in.rsrc((const char *)a.k + in_base, n, 128);
-        int off[2], slot = 0;
+        uint64_t items = todo;
+        __amdgpu_buffer_rsrc_t rq, rk;
+        int off[2], step, slot = 0, left;
+        auto begin = [&]() {
+            const Item it = item(take(items));
+            const lasad_layout_t l = multi ? m.in[it.pass] : a.in;
+            const WalkRows in(l.stride_n * 2, n);
+            const int64_t base = first_row(l, it.blk / G) * 2;
+            rq = in.rsrc((const char *)(multi ? m.q[it.pass] : a.q) + base, n, 128);
+            rk = in.rsrc((const char *)(multi ? m.k[it.pass] : a.k) + base, n, 128);
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int r = 8 * e + (lane >> 3);
-            off[e] = in.first + r * in.step + ((lane & 7) ^ turned(r)) * 16;
-        }
+            for (int e = 0; e < 2; ++e) {
+                const int r = 8 * e + (lane >> 3);
+                off[e] = in.first + r * in.step + ((lane & 7) ^ turned(r)) * 16;
+            }
+            step = in.step;
+            left = n_chunks;
+        };
+        begin();
         auto copy = [&]() {                                    // the next chunk into the next slot
             char __attribute__((address_space(3))) *const at = (char __attribute__((address_space(3))) *)(tiles + slot * 2 * kTile);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rq, (LdsVoid *)(at + i * 1024), 16, off[i & 1], 0, 0, NTL ? 2 : 0);
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (LdsVoid *)(at + kTile * 2 + i * 1024), 16, off[i & 1], 0, 0, NTL ? 2 : 0);
-                off[i & 1] += 16 * in.step;
+                off[i & 1] += 16 * step;
             }
             slot = slot + 1 == R ? 0 : slot + 1;
+            if (MANY && --left == 0 && items) begin();
         };
         constexpr int kWait = 16 * (R - 2);                    // all but the last R - 2 chunks have arrived
         for (int i = 0; i < R - 1; ++i) copy();                // (past the end: zeros)
         __builtin_amdgcn_s_waitcnt(0x0f70 | (kWait & 15) | (kWait >> 4 << 14));
         __builtin_amdgcn_s_barrier();
-        for (int chunk = 0; chunk < n_chunks; ++chunk) {
-            if (chunk + R - 1 < n_chunks) {
+        for (int chunk = 0; chunk < n_all; ++chunk) {
+            if (chunk + R - 1 < n_all) {
                 copy();
                 __builtin_amdgcn_s_waitcnt(0x0f70 | (kWait & 15) | (kWait >> 4 << 14));
             } else {
@@ -232,48 +267,206 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
     SplitConst sc;
     sc.init();
 
+    // ---- the output tiles' way out, by the loaders or by wavefronts of their own ----
+    constexpr int SGROUPS = SH::kStore ? SH::kStore : SH::kLoaders, PC = 2 * NV, SROWS = SGROUPS * 64 / PC, SIT = CT / SROWS, E = OUT_BF16 ? 2 : 4;
+    const int st = tid - 64 * (kCompute + (SH::kStore ? SH::kLoaders : 0)), srow = st / PC, pc = tid % PC;
+    struct Tile { f32x4v u[SIT], w[SIT]; };
+    auto read_tile = [&](Tile &t, int p) {
+#pragma unroll
+        for (int i = 0; i < SIT; ++i) {
+            if (SH::O16) {
+                t.u[i] = *(const f32x4v *)(outs + p * CT * OS + (srow + i * SROWS) * OS + pc * 4);
+            } else {
+                const float *tile = outs + p * CT * OS + (srow + i * SROWS) * OS + pc * 8;
+                t.u[i] = *(const f32x4v *)tile;
+                t.w[i] = *(const f32x4v *)(tile + 4);
+                if (NV == 1) {
+                    const int r = srow + i * SROWS;
+                    const float *const more = parts + p * SH::kPart + (r < CT - 16 ? 16 : r - (CT - 16)) * OS + pc * 8;
+                    t.u[i] += *(const f32x4v *)more;
+                    t.w[i] += *(const f32x4v *)(more + 4);
+                }
+            }
+        }
+    };
+    // One period behind the output: before the first tile there is one that leaves the range.  Decay-gradient sums: the fourth
+    // tensor's rows, two periods ahead of their tile (one: the stores before them have to be through by then).
+    uint64_t s_items = todo, x_items = todo;
+    __amdgpu_buffer_rsrc_t ro, rx;
+    int o_off = 0, o_step = 0, s_left = n_chunks + 1, x_off = 0, x_step = 0, x_left = 0;
+    int t0 = -CT;                                              // token of the tile's first row
+    float *sums = nullptr;
+    float acc = 0.f, e_sign = 0.f, e_add = 0.f;
+    int e_before = 0;
+    Boundaries s_bounds;
+    u32x4 x4[2][SIT];
+    auto store_begin = [&]() {
+        const Item it = item(take(s_items));
+        const int bh = it.blk / G;
+        const lasad_layout_t l = multi ? m.out[it.pass] : a.out;
+        const WalkRows out(l.stride_n * E, n);
+        ro = out.rsrc((char *)(multi ? m.o[it.pass] : a.o) + first_row(l, bh) * E, n, D * E);
+        o_off = out.first + srow * out.step + (it.vp * 16 * NV + pc * 8) * E;
+        o_step = out.step;
+        if (DOT) {
+            t0 = 0;
+            e_before = 0;
+            e_sign = e_add = 0.f;
+            sums = nullptr;
+            s_bounds.begin(m.start_pos[it.pass], a.mode);
+            if (m.x[it.pass]) {
+                const int e_all = cum_exp(m.x_start_pos + a.n_tokens, a.grid_w, a.mode) - cum_exp(m.x_start_pos, a.grid_w, a.mode);
+                // in a reversed pass step i applies the decay of the token walked before it, the first step somebody else's
+                const int before = is_boundary(m.start_pos[it.pass] + 1, a.grid_w, a.mode) ? 0 : 1;
+                e_sign = m.x_rev[it.pass] ? -m.x_sign[it.pass] : m.x_sign[it.pass];
+                e_add = m.x_rev[it.pass] ? m.x_sign[it.pass] * (float)(e_all + before) : 0.f;
+                sums = m.x_sums + ((int64_t)it.pass * a.B * a.Hh + bh) * kDotSlots + it.vp * SGROUPS + (st >> 6);
+            }
+        }
+    };
+    auto x_begin = [&]() {
+        const Item it = item(take(x_items));
+        const lasad_layout_t l = m.in[it.pass];
+        const WalkRows in(l.stride_n * 2, n);
+        rx = in.rsrc((const char *)(m.x[it.pass] ? m.x[it.pass] : m.v[it.pass]) + first_row(l, it.blk / G) * 2, n, 128);
+        x_off = in.first + srow * in.step + it.vp * (32 * NV) + pc * 16;
+        x_step = in.step;
+        x_left = n_chunks;
+    };
+    auto x_fetch = [&](u32x4 (&x)[SIT]) {
+#pragma unroll
+        for (int i = 0; i < SIT; ++i) x[i] = buf_load<false>(rx, x_off + i * SROWS * x_step);
+        x_off += CT * x_step;
+        if (MANY && --x_left == 0 && x_items) x_begin();
+    };
+    auto leave_sum = [&]() {
+        if (!sums) return;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+        if (lane == 0) {
+            sums[0] = acc;
+            for (int i = PARTS * SGROUPS; i < kDotSlots; i += PARTS * SGROUPS) sums[i] = 0.f;
+        }
+        acc = 0.f;
+    };
+    auto stores_begin = [&]() {
+        if (DOT) s_bounds.init(a.grid_w);
+        store_begin();
+        o_off -= CT * o_step;
+        if (DOT) {
+            t0 = -CT;
+            x_begin();
+            x_fetch(x4[1]);
+        }
+    };
+    auto store_tile = [&](const Tile &t, int p) {              // (tile p - 1 in the order of the walk)
+        uint64_t bmask = 0;
+        if (DOT) bmask = s_bounds.mask();
+#pragma unroll
+        for (int i = 0; i < SIT; ++i) {
+            const int at = o_off + i * SROWS * o_step;
+            const f32x4v &u = t.u[i], &w = t.w[i];
+            if (SH::O16) {
+                buf_store<true>(ro, at, __builtin_bit_cast(u32x4, u));
+            } else if (OUT_BF16) {
+                buf_store<true>(ro, at, u32x4{pack2(u[0], u[1]), pack2(u[2], u[3]), pack2(w[0], w[1]), pack2(w[2], w[3])});
+            } else {
+                buf_store<true>(ro, at, __builtin_bit_cast(u32x4, u));
+                buf_store<true>(ro, at + 16, __builtin_bit_cast(u32x4, w));
+            }
+            if (DOT) {
+                float d = 0.f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const f32x4v &y = j < 2 ? u : w;
+                    d = fmaf(__uint_as_float(x4[p][i][j] << 16), y[2 * (j & 1)], d);
+                    d = fmaf(__uint_as_float(x4[p][i][j] & 0xffff0000u), y[2 * (j & 1) + 1], d);
+                }
+                const int r = srow + i * SROWS, e = r + 1 - __builtin_popcountll(bmask & (~0ull >> (63 - r)));
+                const float weight = e_sign * (float)(e_before + e) + e_add;
+                acc = (uint32_t)(t0 + r) < (uint32_t)n ? fmaf(weight, d, acc) : acc;
+            }
+        }
+        o_off += CT * o_step;
+        if (DOT) {
+            if (t0 >= 0) {                                     // (the tile before the first has no rows)
+                e_before += CT - __builtin_popcountll(bmask);
+                s_bounds.advance();
+            }
+            t0 += CT;
+        }
+        if (--s_left == 0 && s_items) {
+            if (DOT) leave_sum();
+            store_begin();
+            s_left = n_chunks;
+        }
+        if (DOT) x_fetch(x4[p]);
+    };
+
+    if (SH::kStore && wave >= kCompute + SH::kLoaders) {
+        // ===================================== store wavefronts =====================================
+        stores_begin();
+        __syncthreads();
+        for (int c0 = 0; c0 <= n_all; c0 += 2) {               // (pairs of periods, as the loaders)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                Tile t;
+                read_tile(t, (u + 1) & 1);
+                store_tile(t, u);
+                if (c0 + u < n_all) __syncthreads();
+            }
+        }
+        if (DOT) leave_sum();
+        return;
+    }
+
     if (wave >= kCompute) {
         // ===================================== loader wavefronts =====================================
-        constexpr int PC = 2 * NV, ROWS = SH::kLoaders * 64 / PC, IT = CT / ROWS;
-        const int st = tid - 64 * kCompute, row = st / PC, pc = st % PC;
-        constexpr int E = OUT_BF16 ? 2 : 4;
-        const WalkRows out(a.out.stride_n * E, n);
-        const __amdgpu_buffer_rsrc_t rv = in.rsrc((const char *)a.v + in_base, n, 128);
-        const __amdgpu_buffer_rsrc_t ro = out.rsrc((char *)a.o + ((int64_t)b * a.out.stride_b + (int64_t)h * a.out.stride_h + (int64_t)seg_t0 * a.out.stride_n) * E, n, D * E);
-        int v_off = in.first + row * in.step + vp * (32 * NV) + pc * 16, x_off = v_off;
-        int o_off = out.first + (row - CT) * out.step + (vp * 16 * NV + pc * 8) * E;       // (of the chunk before the first)
+        constexpr int ROWS = SH::kLoaders * 64 / PC, IT = CT / ROWS;
+        const int ld = tid - 64 * kCompute, row = ld / PC;
         constexpr int PF = 2;              // (four: 1 to 3 % slower, for the periods past the end)
         struct Regs { u32x4 v[IT]; } r[PF];
+        // the loads' own way through the items
+        uint64_t f_items = todo;
+        __amdgpu_buffer_rsrc_t rv;
+        int v_off, v_step, f_left;
+        auto fetch_begin = [&]() {
+            const Item it = item(take(f_items));
+            const lasad_layout_t l = multi ? m.in[it.pass] : a.in;
+            const WalkRows in(l.stride_n * 2, n);
+            rv = in.rsrc((const char *)(multi ? m.v[it.pass] : a.v) + first_row(l, it.blk / G) * 2, n, 128);
+            v_off = in.first + row * in.step + it.vp * (32 * NV) + pc * 16;
+            v_step = in.step;
+            f_left = n_chunks;
+        };
+        fetch_begin();
         auto fetch = [&](Regs &x) {
 #pragma unroll
-            for (int i = 0; i < IT; ++i) x.v[i] = buf_load<NTL>(rv, v_off + i * ROWS * in.step);
-            v_off += CT * in.step;
+            for (int i = 0; i < IT; ++i) x.v[i] = buf_load<NTL>(rv, v_off + i * ROWS * v_step);
+            v_off += CT * v_step;
+            if (MANY && --f_left == 0 && f_items) fetch_begin();
         };
 #pragma unroll
         for (int i = 0; i < PF; ++i) fetch(r[i]);
         __builtin_amdgcn_sched_barrier(0);
-        Boundaries bounds;
-        bounds.init(a.start_pos + seg_t0, a.grid_w, a.mode);
         const uint64_t upto = ~0ull >> (63 - row);
         const int put = SL::Map::at(row, pc * 8);
         float *const tab_at = &tabs[0][pc == 0 ? row : CT];
-        int p_left = n;                                        // tokens from the next chunk to be prepared on
-        // decay-gradient sums: weights of the rows of the chunks under way, and the fourth tensor's rows one period ahead
-        float wq[3][IT], acc = 0.f;
-        int e_before = 0;
-        float e_sign = 0.f, e_add = 0.f;
-        u32x4 x4[IT];
-        const bool dots = DOT && m.x[pass];
-        const __amdgpu_buffer_rsrc_t rx = in.rsrc((const char *)(dots ? m.x[pass] : a.v) + in_base, n, 128);
-        if (DOT) {
-            if (dots) {
-                const int e_all = cum_exp(m.x_start_pos + a.n_tokens, a.grid_w, a.mode) - cum_exp(m.x_start_pos, a.grid_w, a.mode);
-                // in a reversed pass step i applies the decay of the token walked before it, the first step somebody else's
-                const int first = is_boundary(a.start_pos + 1, a.grid_w, a.mode) ? 0 : 1;
-                e_sign = m.x_rev[pass] ? -m.x_sign[pass] : m.x_sign[pass];
-                e_add = m.x_rev[pass] ? m.x_sign[pass] * (float)(e_all + first) : 0.f;
-            }
-        }
+        // the preparation's
+        Boundaries bounds;
+        bounds.init(a.grid_w);
+        uint64_t p_items = todo;
+        int p_left;                                            // tokens from the next chunk to be prepared on
+        float lg;
+        auto prepare_begin = [&]() {
+            const int i = take(p_items), pass = item(i).pass;
+            lg = log_gamma(i);
+            const int start = multi ? m.start_pos[pass] : a.start_pos;
+            bounds.begin(start + seg_t0, a.mode);
+            p_left = n;
+        };
+        prepare_begin();
+        if (SH::kStore == 0) stores_begin();
         auto prepare = [&](const Regs &x, int p) {
             const uint64_t bmask = bounds.mask();
             bounds.advance();
@@ -284,7 +477,6 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
 #pragma unroll
             for (int i = 0; i < IT; ++i) {
                 const int e = row + i * ROWS + 1 - __builtin_popcountll(bmask & (IT == 1 || i == 0 ? upto : ((1ull << ROWS) - 1) | upto << ROWS));
-                if (DOT) wq[2][i] = e_sign * (float)(e_before + e) + e_add;
                 const float cj = __builtin_amdgcn_exp2f(-(float)e * lg), fj = cj * end;
                 uint16_t *const s = slots + p * SL::kHalfs + put + i * (ROWS / 16) * SL::Map::kHalf;
                 if (pc < 2) tab_at[p * kTab + (pc == 0 ? i * ROWS : 0)] = pc == 0 ? cj : end;
@@ -300,86 +492,27 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
                 *(u32x4 *)(s + SL::Fh) = hi;
                 *(u32x4 *)(s + SL::Fl) = lo;
             }
-            if (DOT) e_before += e_end;
+            if (MANY && p_left <= 0 && p_items) prepare_begin();
         };
-        struct Tile { f32x4v u[IT], w[IT]; };
-        auto read_tile = [&](Tile &t, int p) {
-#pragma unroll
-            for (int i = 0; i < IT; ++i) {
-                if (SH::O16) {
-                    t.u[i] = *(const f32x4v *)(outs + p * CT * OS + (row + i * ROWS) * OS + pc * 4);
-                } else {
-                    const float *tile = outs + p * CT * OS + (row + i * ROWS) * OS + pc * 8;
-                    t.u[i] = *(const f32x4v *)tile;
-                    t.w[i] = *(const f32x4v *)(tile + 4);
-                    if (NV == 1) {
-                        const float *const more = parts + p * SH::kPart + (row < CT - 16 ? 16 : row - (CT - 16)) * OS + pc * 8;
-                        t.u[i] += *(const f32x4v *)more;
-                        t.w[i] += *(const f32x4v *)(more + 4);
-                    }
-                }
-            }
-        };
-        int t_row = row - CT;                                  // token of this thread's first row in the tile to be stored
-        auto store_tile = [&](const Tile &t) {
-#pragma unroll
-            for (int i = 0; i < IT; ++i) {
-                const int at = o_off + i * ROWS * out.step;
-                const f32x4v &u = t.u[i], &w = t.w[i];
-                if (SH::O16) {
-                    buf_store<NTS>(ro, at, __builtin_bit_cast(u32x4, u));
-                } else if (OUT_BF16) {
-                    buf_store<NTS>(ro, at, u32x4{pack2(u[0], u[1]), pack2(u[2], u[3]), pack2(w[0], w[1]), pack2(w[2], w[3])});
-                } else {
-                    buf_store<NTS>(ro, at, __builtin_bit_cast(u32x4, u));
-                    buf_store<NTS>(ro, at + 16, __builtin_bit_cast(u32x4, w));
-                }
-                if (DOT) {
-                    float d = 0.f;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const f32x4v &y = j < 2 ? u : w;
-                        d = fmaf(__uint_as_float(x4[i][j] << 16), y[2 * (j & 1)], d);
-                        d = fmaf(__uint_as_float(x4[i][j] & 0xffff0000u), y[2 * (j & 1) + 1], d);
-                    }
-                    acc = (uint32_t)(t_row + i * ROWS) < (uint32_t)n ? fmaf(wq[0][i], d, acc) : acc;
-                    wq[0][i] = wq[1][i];
-                    wq[1][i] = wq[2][i];
-                    x4[i] = buf_load<false>(rx, x_off + i * ROWS * in.step);       // (of the tile stored next)
-                }
-            }
-            o_off += CT * out.step;
-            if (DOT) { x_off += CT * in.step; t_row += CT; }
-        };
-        if (NV == 1 && st < 2 * OS) parts[(st / OS) * SH::kPart + 16 * OS + st % OS] = 0.f;
+        if (NV == 1 && ld < 2 * OS) parts[(ld / OS) * SH::kPart + 16 * OS + ld % OS] = 0.f;
         prepare(r[0], 0);
-        if (DOT)
-            for (int i = 0; i < IT; ++i) { wq[0][i] = 0.f; wq[1][i] = wq[2][i]; }
         fetch(r[0]);
         __syncthreads();
         // Pairs of periods: with a way out between them the compiler waits for all loads at the loop's top.  (What is past the
         // end does nothing.)
-        for (int c0 = 0; c0 <= n_chunks; c0 += PF) {
+        for (int c0 = 0; c0 <= n_all; c0 += PF) {
 #pragma unroll
             for (int u = 0; u < PF; ++u) {
                 const int chunk = c0 + u;
                 Tile t;
-                read_tile(t, (u + 1) & 1);
-                if (chunk + 1 < n_chunks) prepare(r[(u + 1) % PF], (u + 1) & 1);
-                store_tile(t);
+                if (SH::kStore == 0) read_tile(t, (u + 1) & 1);
+                if (chunk + 1 < n_all) prepare(r[(u + 1) % PF], (u + 1) & 1);
+                if (SH::kStore == 0) store_tile(t, u);
                 fetch(r[(u + 1) % PF]);
-                if (chunk < n_chunks) __syncthreads();
+                if (chunk < n_all) __syncthreads();
             }
         }
-        if (dots) {
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-            if (lane == 0) {
-                float *dst = m.x_sums + ((int64_t)pass * a.B * a.Hh + bh) * kDotSlots;
-                dst[vp * SH::kLoaders + (st >> 6)] = acc;
-                if (NV == 4) dst[4 + (st >> 6)] = 0.f;
-            }
-        }
+        if (DOT && SH::kStore == 0) leave_sum();
         return;
     }
 
@@ -388,27 +521,50 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
     if (wave < NV) {
         // ===================================== state wavefronts =====================================
         const int col = 16 * wave;                             // value channels of this wavefront in the slot
-        const int64_t s_off = (int64_t)bh * D * D + vp * 16 * NV + col + l16;
         f32x4v accS[4];                                        // S[state_channel(t, g) + r][.. + l16]
+        uint64_t items = todo;
+        int left;
+        int64_t s_off;
+        float *state_out;
+        auto begin = [&]() {
+            const int i = take(items);
+            const Item it = item(i);
+            const int bh = it.blk / G;
+            s_off = (int64_t)bh * D * D + it.vp * 16 * NV + col + l16;
+            left = n_chunks;
+            const float *const state_in = multi ? m.state_in[it.pass] : a.state_in;
+            state_out = multi ? m.state_out[it.pass] : a.state_out;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) accS[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
-        if (a.state_in) {
-            const float s_in = incoming_state_scale(a, gamma);
+            for (int t = 0; t < 4; ++t) accS[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
+            if (state_in) {
+                const bool undo = multi ? m.first_decay_off[it.pass] : a.first_decay_off;
+                const bool at_boundary = is_boundary((multi ? m.start_pos[it.pass] : a.start_pos) + 1, a.grid_w, a.mode);
+                const float s_in = undo && !at_boundary ? 1.0f / a.gamma[bh % a.Hh] : 1.0f;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) accS[t][r] = s_in * state_in[s_off + (state_channel(t, g) + r) * D];
+            }
+            const float lg = log_gamma(i);
+            for (int sp = 0; sp < seg * a.seg_parts; ++sp) {
+                const StatePart part(a, sp);
+                const int de = fwd::range_exponent(a.start_pos + part.t0, a.start_pos + part.t1, a.grid_w, a.mode);
+                const float dec = de == 0 ? 1.0f : __builtin_amdgcn_exp2f((float)de * lg);
+                const float *u = a.seg_states + ((int64_t)bh * (G - 1) * a.seg_parts + sp) * D * D + it.vp * 16 * NV + col + l16;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) accS[t][r] = fmaf(dec, accS[t][r], u[(state_channel(t, g) + r) * D]);
+            }
+        };
+        auto finish = [&]() {
+            if (!state_out || seg != G - 1) return;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) accS[t][r] = s_in * a.state_in[s_off + (state_channel(t, g) + r) * D];
-        }
-        for (int sp = 0; sp < seg * a.seg_parts; ++sp) {
-            const StatePart part(a, sp);
-            const int de = fwd::range_exponent(a.start_pos + part.t0, a.start_pos + part.t1, a.grid_w, a.mode);
-            const float dec = de == 0 ? 1.0f : __builtin_amdgcn_exp2f((float)de * lg);
-            const float *u = a.seg_states + ((int64_t)bh * (G - 1) * a.seg_parts + sp) * D * D + vp * 16 * NV + col + l16;
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) accS[t][r] = fmaf(dec, accS[t][r], u[(state_channel(t, g) + r) * D]);
-        }
+                for (int r = 0; r < 4; ++r) state_out[s_off + (state_channel(t, g) + r) * D] = accS[t][r];
+        };
+        begin();
         uint16_t *const st_put = states + SM::row(col + l16) + SM::piece(col + l16, g);
         auto publish = [&](int p) {
 #pragma unroll
@@ -447,20 +603,19 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
                     accS[t] = mfma16(k, fl, accS[t]);
                 }
             }
+            if (MANY && --left == 0 && !last) {
+                finish();
+                begin();
+            }
             if (!last) publish(p ^ 1);
             slot = slot == (R - 1) * 2 * kTile ? 0 : slot + 2 * kTile;
             __syncthreads();
         };
-        for (int chunk = 0; chunk < n_chunks; chunk += 2) {
-            step(Const<0>(), chunk + 1 == n_chunks);
-            if (chunk + 1 < n_chunks) step(Const<1>(), chunk + 2 == n_chunks);
+        for (int chunk = 0; chunk < n_all; chunk += 2) {
+            step(Const<0>(), chunk + 1 == n_all);
+            if (chunk + 1 < n_all) step(Const<1>(), chunk + 2 == n_all);
         }
-        if (a.state_out && seg == G - 1) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) a.state_out[s_off + (state_channel(t, g) + r) * D] = accS[t][r];
-        }
+        finish();
         return;
     }
 
@@ -534,9 +689,9 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
             slot = slot == (R - 1) * 2 * kTile ? 0 : slot + 2 * kTile;
             __syncthreads();
         };
-        for (int chunk = 0; chunk < n_chunks; chunk += 2) {
+        for (int chunk = 0; chunk < n_all; chunk += 2) {
             step(Const<0>());
-            if (chunk + 1 < n_chunks) step(Const<1>());
+            if (chunk + 1 < n_all) step(Const<1>());
         }
     };
     const int w = wave - NV;
@@ -559,6 +714,25 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
         else if (w == 1) walk(Const<1>(), Const<0>(), Const<NV>(), all);
         else if (w == 2) walk(Const<2>(), Const<0>(), Const<NV>(), all);
         else walk(Const<3>(), Const<0>(), Const<NV>(), all);
+    }
+    };
+    if (todo) walk_items();
+    if (!rest) return;
+    // the fp32 recurrence, a whole sequence by one workgroup
+    __syncthreads();
+    if (tid >= kRecThreads || seg != 0) return;
+    while (rest) {
+        const Item it = item(take(rest));
+        if (it.vp != 0) continue;
+        ForwardArgs s = a;
+        if (multi) {
+            s.q = m.q[it.pass]; s.k = m.k[it.pass]; s.v = m.v[it.pass]; s.o = m.o[it.pass];
+            s.in = m.in[it.pass]; s.out = m.out[it.pass]; s.start_pos = m.start_pos[it.pass];
+            s.state_in = m.state_in[it.pass]; s.state_out = m.state_out[it.pass]; s.first_decay_off = m.first_decay_off[it.pass];
+        }
+        if (DOT) fwd::recurrence_with_dot<OUT_BF16>(s, m, it.pass, it.blk / G, (float *)smem);
+        else recurrence_sequence<D, 1, OUT_BF16>(s, it.blk / G, (float *)smem);
+        __syncthreads();
     }
 }
 
@@ -681,7 +855,7 @@ hipError_t launch_scalar_segment_state(const ForwardArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// As many workgroups a sequence (or segment) as still get a compute unit each.  (64 sequences of 576 tokens, NV 4, 2, 1: 14.1, 10.8,
+// As many workgroups a sequence (or segment) as still get a compute unit each (all of a sequence are on one XCD, of 32 units).  (64 sequences of 576 tokens, NV 4, 2, 1: 14.1, 10.8,
 // 9.4 us; 96 of 576: 14.4, 11.0, 16.4; 192 of 576: 15.0, 20.1.)
 hipError_t launch_forward_scalar_chunk(const ForwardArgs &a, const MultiPass &m, hipStream_t s)
 {
@@ -689,9 +863,11 @@ hipError_t launch_forward_scalar_chunk(const ForwardArgs &a, const MultiPass &m,
     const int64_t n_blk = (int64_t)a.B * a.Hh * a.n_segments;
     static const int split_env = [] { const char *e = getenv("LASAD_SPLIT"); return e ? atoi(e) : 0; }();
     const int split = split_env == 1 || split_env == 2 || split_env == 4 ? split_env
-                      : n_blk * m.n_pass <= 64 ? 4 : n_blk * m.n_pass <= 128 ? 2 : 1;
+                      : (n_blk + 7) / 8 * m.n_pass <= 8 ? 4 : (n_blk + 7) / 8 * m.n_pass <= 16 ? 2 : 1;
     const int P = split * m.n_pass;
-    const int64_t n_wg = P > 1 ? (n_blk + 7) / 8 * 8 * P : n_blk;
+    int64_t n_wg = P > 1 && by_xcd(n_blk, P) ? (n_blk + 7) / 8 * 8 * P : n_blk * P;
+    // A workgroup for each compute unit walks its sequences one after the other (at most 64: a lane each).
+    if (split == 1 && a.n_segments == 1 && n_wg > 256) n_wg = n_wg <= 256 * 64 ? 256 : (n_wg + 511) / 512 * 8;
     if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
     const bool dot = m.n_pass > 1 && (m.x[0] || m.x[1] || m.x[2]);
     const bool out16 = a.out_dtype == LASAD_BF16;

@@ -83,10 +83,12 @@ def test_state_in_place_over_segments(lasad):
     assert rel_err(o2.cpu().numpy(), o.cpu().numpy()) <= TOL["bf16"] and rel_err(s.cpu().numpy(), s1.cpu().numpy()) <= TOL["bf16"]
 
 
-@pytest.mark.parametrize("B,Hh", [(1, 3), (1, 21), (1, 22), (2, 21), (1, 43), (5, 17), (2, 43)])
-@pytest.mark.parametrize("n,W,start,mode", [(1, 5, 2, 0), (65, 9, 4, 1), (130, 17, 0, 0), (257, 33, 12, 2)])
+@pytest.mark.parametrize("B,Hh", [(1, 3), (1, 16), (1, 17), (2, 20), (1, 41), (5, 16), (3, 27), (5, 17), (2, 43), (9, 23)])
+@pytest.mark.parametrize("n,W,start,mode", [(1, 5, 2, 0), (65, 9, 4, 1), (130, 17, 0, 0), (257, 33, 12, 2), (511, 33, 0, 0), (513, 30, 7, 1)])
 def test_backward_passes(lasad, oracle, B, Hh, n, W, start, mode):
-    """Three passes in one launch at 9 to 258 workgroups (63 | 66, 126 | 129, 255 | 258), with the decay gradient."""
+    """Three passes in one launch: 3 to 207 sequences, of four, two, one workgroup a pass (16 | 17, 40 | 41), those of a sequence on
+    one XCD or not (80 | 81, 85 | 86), a workgroup walking several (with 512 tokens and more), another kernel; with the decay
+    gradient."""
     import torch
     rng = np.random.default_rng(n + Hh)
     q, k, v, g = (_draw(rng, B, n, Hh, D) for _ in range(4))
@@ -105,3 +107,23 @@ def test_backward_passes(lasad, oracle, B, Hh, n, W, start, mode):
     E = (cum[1:] - cum[0]).astype(np.float64)
     terms = ((np.abs(q * rq).sum(axis=3) + np.abs(k * rk).sum(axis=3)) * E[None, :, None]).sum(axis=(0, 1)).max()
     assert np.abs(dgam.cpu().numpy() - rgam).max() <= TOL["bf16"] * np.abs(rgam).max() + 1e-6 * terms / float(gamma.min())
+
+
+@pytest.mark.parametrize("B,Hh,n,W", [(3, 87, 768, 31), (5, 103, 800, 25), (9, 64, 769, 40)])
+@pytest.mark.parametrize("lo", [0.3, 0.6])
+def test_several_sequences_a_workgroup(lasad, oracle, B, Hh, n, W, lo):
+    """More sequences than workgroups, one after the other with carried states; lo 0.3: among them some for the fp32 recurrence
+    (gamma <= 0.5)."""
+    _forward(lasad, oracle, B, Hh, n, W, 5, 0, seed=n, lo=lo)
+
+
+def test_many_sequences_a_workgroup(lasad):
+    """More than 64 for each of 256 workgroups: the same results as part by part."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    q, k, v = (torch.randn((1, 768, 16400, D), generator=gen, device="cuda", dtype=torch.bfloat16).div_(8) for _ in range(3))
+    gamma = torch.rand((16400,), generator=gen, device="cuda") * 0.3 + 0.7
+    o = lasad.lasad_forward_chunked(q, k, v, gamma, 32, 24)
+    for i in (0, 8, 16390):
+        part = lasad.lasad_forward_chunked(q[:, :, i:i + 10], k[:, :, i:i + 10], v[:, :, i:i + 10], gamma[i:i + 10].contiguous(), 32, 24)
+        assert rel_err(o[:, :, i:i + 10].float().cpu().numpy(), part.float().cpu().numpy()) <= TOL["bf16"]
