@@ -385,12 +385,13 @@ hipError_t launch_forward_mfma(const ForwardArgs &a_in, hipStream_t s)
     // (every segment reads the incoming state, the last one writes the final one: not where they are the same memory)
     if (a.seg_states && !(a.state_in && a.state_in == a.state_out)) plan_segments(n_seq, (a.n_tokens + C - 1) / C, &a.n_segments, &a.seg_chunks);
     if (n_seq * a.n_segments > 0x7fffffff) return hipErrorInvalidValue;
-    // The full pass: workgroups with a compute unit each while there are so few, or walks long enough; else eight waves, two workgroups
-    // a unit.  (Eight waves against this, us: 512 sequences of 64 tokens 8.7 and 9.4, of 128 11.9 and 12.6, of 256 19.9 and 19.3; 300 of
-    // 256 17.0 and 17.5, of 400 24.6 and 24.0; 1000 of 400 53 and 48; 512 of 576 41.1 and 37.6, one set of buffers 35.3 and 34.9; 260 of
-    // 4096 191 and 172.)  LASAD_WS = 12 / 8 / 0 forces one of them or the four-wave kernel.
+    // The full pass: workgroups with a compute unit each while there are so few, or from four chunks on; else eight waves, two
+    // workgroups a unit, whose starts and ends overlap.  (Eight waves against this, us: 512 sequences of 64 tokens 8.6 and 9.1, of 128
+    // 11.9 and 12.4, of 192 16.9 and 16.3, of 256 21.4 and 19.5, of 576 39.6 and 36.2, one set of buffers 35.3 and 34.9; 300 of 192 13.9
+    // and 14.3, of 256 17.0 and 17.0, of 400 25.3 and 24.1; 2000 of 128 37.9 and 33.4; 1000 of 400 57 and 52; 260 of 4096 193 and 174.)
+    // LASAD_WS = 12 / 8 / 0 forces one of them or the four-wave kernel.
     static const int ws = [] { const char *e = getenv("LASAD_WS"); return e ? atoi(e) : -1; }();
-    const bool own_unit = (ws == 12 || (ws < 0 && (n_seq * a.n_segments <= 256 || a.n_tokens >= 384))) && forward_scalar_chunk_fits(a);
+    const bool own_unit = (ws == 12 || (ws < 0 && (n_seq * a.n_segments <= 256 || a.n_tokens > 192))) && forward_scalar_chunk_fits(a);
     if (a.n_segments > 1) {
         // The state pass gets the chip's units too, as far as there is room for its states.  (128 sequences of 4096 tokens in two
         // segments, one, two, three workgroups a segment: 75.5, 69.3, 72.1 us a call.)

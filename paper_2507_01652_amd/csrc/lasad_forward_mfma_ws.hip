@@ -335,17 +335,17 @@ static hipError_t launch_ws8(const ForwardArgs &a, const MultiPass &m, hipStream
     return hipGetLastError();
 }
 
-// Several whole-sequence passes in one launch: workgroups with a compute unit each while all passes together have so few, or from 512
-// tokens on; else eight waves, two workgroups a unit: there the starts and ends of short walks overlap, which counts for more than the
-// shorter period.  Eight waves against this, us of a backward (three passes with the decay gradient): 512 sequences of 100 tokens 30.2
-// and 33.7, of 256 49.5 and 51.2, of 400 77.3 and 74.3, of 576 102 and 89, of 1024 200 and 159; 300 of 256 34.5 and 36.7; 260 of 400
-// 49.7 and 51.4; 1536 of 576 336 and 330; 96 of 4096 216 and 178, 200 of them 332 and 293.
+// Several whole-sequence passes in one launch: workgroups with a compute unit each while all passes together have so few, or from four
+// chunks on; else eight waves, two workgroups a unit, whose starts and ends overlap.  Eight waves against this, us of a backward (three
+// passes with the decay gradient): 512 sequences of 16 tokens 21.1 and 22.9, of 64 22.5 and 24.0, of 100 31.1 and 30.2, of 256 53 and
+// 48, of 576 105 and 93, of 1024 181 and 156; 90 of 100 13.6 and 14.9, of 256 19.9 and 20.0; 300 of 130 28.5 and 27.6, of 256 37 and 33;
+// 2000 of 64 67.5 and 68.5, of 256 200 and 179; 96 of 4096 221 and 180, 200 of them 345 and 282.
 hipError_t launch_forward_mfma_multi(const ForwardArgs &common, const MultiPass &m, hipStream_t s)
 {
     if (common.n_segments != 1 || m.n_pass < 1 || m.n_pass > 3) return hipErrorInvalidValue;
     const int64_t n_wg = (int64_t)common.B * common.Hh * m.n_pass;
     static const int ws = [] { const char *e = getenv("LASAD_WS_MULTI"); return e ? atoi(e) : -1; }();
-    if ((ws == 12 || (ws < 0 && (n_wg <= 256 || common.n_tokens >= 512))) && forward_scalar_chunk_fits(common)) return launch_forward_scalar_chunk(common, m, s);
+    if ((ws == 12 || (ws < 0 && (n_wg <= 256 || common.n_tokens > 192))) && forward_scalar_chunk_fits(common)) return launch_forward_scalar_chunk(common, m, s);
     return launch_ws8(common, m, s);
 }
 
