@@ -273,10 +273,10 @@ struct RecDotHook {
 };
 
 template <int OUT_BF16>
-__device__ inline void recurrence_with_dot(const ForwardArgs &a, const MultiPass &m, int y, int bh, float *smem)
+__device__ inline void recurrence_with_dot(const ForwardArgs &a, const MultiPass &m, int y, int bh, float *smem, const int tid = threadIdx.x)
 {
     if (!(m.n_pass > 1 && m.x[y])) {
-        recurrence_sequence<D, 1, OUT_BF16>(a, bh, smem);
+        recurrence_sequence<D, 1, OUT_BF16>(a, bh, smem, RecNoHook(), tid);
         return;
     }
     const int b = bh / a.Hh, h = bh - b * a.Hh;
@@ -288,19 +288,19 @@ __device__ inline void recurrence_with_dot(const ForwardArgs &a, const MultiPass
     hook.grid_w = a.grid_w; hook.mode = a.mode;
     hook.e0 = cum_exp(m.x_start_pos, a.grid_w, a.mode);
     hook.acc = &acc;
-    recurrence_sequence<D, 1, OUT_BF16>(a, bh, smem, hook);
+    recurrence_sequence<D, 1, OUT_BF16>(a, bh, smem, hook, tid);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
     __syncthreads();                   // the recurrence's last reads of its LDS block
-    if ((threadIdx.x & 63) == 0) smem[threadIdx.x >> 6] = acc;
+    if ((tid & 63) == 0) smem[tid >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x < kDotSlots) {     // the total in slot 0, the other slots zero
+    if (tid < kDotSlots) {     // the total in slot 0, the other slots zero
         float v = 0.f;
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             for (int w = 0; w < kRecThreads / 64; ++w) v += smem[w];
             v *= m.x_sign[y];
         }
-        m.x_sums[((int64_t)y * a.B * a.Hh + bh) * kDotSlots + threadIdx.x] = v;
+        m.x_sums[((int64_t)y * a.B * a.Hh + bh) * kDotSlots + tid] = v;
     }
 }
 

@@ -718,21 +718,38 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
     };
     if (todo) walk_items();
     if (!rest) return;
-    // the fp32 recurrence, a whole sequence by one workgroup
+    // The fp32 recurrence, a whole sequence by four wavefronts, as many at a time as there are wavefronts for.  (One after the other:
+    // 512 sequences of 576 tokens 462 us, two workgroups a unit in the eight-wave kernel 261, up to three at a time 255; three passes of them 845 and 681.)
+    constexpr int kSide = MANY ? SH::kWaves / (kRecThreads / 64) : 1;
+    static_assert(kSide * kRecBytes <= (int)sizeof(smem), "a block of LDS for each");
     __syncthreads();
-    if (tid >= kRecThreads || seg != 0) return;
-    while (rest) {
-        const Item it = item(take(rest));
-        if (it.vp != 0) continue;
+    const int side = wave / (kRecThreads / 64);
+    if (side >= kSide || seg != 0) return;
+    for (;;) {
+        uint64_t mine = rest;
+        for (int i = 0; i < side; ++i) mine &= mine - 1;       // (of none: none)
+        if (!mine) return;
+        const Item it = item(take(mine));
+        if (it.vp != 0) return;                                // (a single item)
         ForwardArgs s = a;
         if (multi) {
             s.q = m.q[it.pass]; s.k = m.k[it.pass]; s.v = m.v[it.pass]; s.o = m.o[it.pass];
             s.in = m.in[it.pass]; s.out = m.out[it.pass]; s.start_pos = m.start_pos[it.pass];
             s.state_in = m.state_in[it.pass]; s.state_out = m.state_out[it.pass]; s.first_decay_off = m.first_decay_off[it.pass];
         }
-        if (DOT) fwd::recurrence_with_dot<OUT_BF16>(s, m, it.pass, it.blk / G, (float *)smem);
-        else recurrence_sequence<D, 1, OUT_BF16>(s, it.blk / G, (float *)smem);
+        float *const lds = (float *)(smem + side * kRecBytes);
+        const int rt = tid & (kRecThreads - 1);
+        if (DOT) {
+            fwd::recurrence_with_dot<OUT_BF16>(s, m, it.pass, it.blk / G, lds, rt);
+            if (!m.x[it.pass]) {                               // (as many barriers as the passes with a sum)
+                __syncthreads();
+                __syncthreads();
+            }
+        } else {
+            recurrence_sequence<D, 1, OUT_BF16>(s, it.blk / G, lds, RecNoHook(), rt);
+        }
         __syncthreads();
+        for (int i = 0; i < kSide; ++i) rest &= rest - 1;
     }
 }
 

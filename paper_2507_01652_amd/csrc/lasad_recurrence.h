@@ -41,13 +41,14 @@ __device__ inline void rec_store(void *p, int64_t idx, float x)
     else ((float *)p)[idx] = x;
 }
 
+// (tid: the thread among the sequence's kRecThreads; a workgroup may walk several sequences of one length side by side.)
 // hook(token, channel, value) sees every output element (fp32, before it is stored) in the thread that stores it
 struct RecNoHook {
     __device__ void operator()(int, int, float) const {}
 };
 
 template <int D, int IN_BF16, int OUT_BF16, int GATED = 0, class Hook = RecNoHook>
-__device__ void recurrence_sequence(const ForwardArgs &a, int bh, float *smem, Hook hook = Hook())
+__device__ void recurrence_sequence(const ForwardArgs &a, int bh, float *smem, Hook hook = Hook(), const int tid = threadIdx.x)
 {
     constexpr int G = kRecThreads / D;   // row groups
     constexpr int R = D / G;             // rows of S per thread
@@ -58,7 +59,6 @@ __device__ void recurrence_sequence(const ForwardArgs &a, int bh, float *smem, H
     float (*red)[G][D] = (float (*)[G][D])(smem + (3 + GATED) * kRecT * D);
 
     const int b = bh / a.Hh, h = bh - b * a.Hh;
-    const int tid = threadIdx.x;
     const int j = tid % D, g = tid / D;
     const float gamma = GATED ? 1.0f : a.gamma[h];
 

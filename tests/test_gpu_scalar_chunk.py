@@ -83,16 +83,11 @@ def test_state_in_place_over_segments(lasad):
     assert rel_err(o2.cpu().numpy(), o.cpu().numpy()) <= TOL["bf16"] and rel_err(s.cpu().numpy(), s1.cpu().numpy()) <= TOL["bf16"]
 
 
-@pytest.mark.parametrize("B,Hh", [(1, 3), (1, 16), (1, 17), (2, 20), (1, 41), (5, 16), (3, 27), (5, 17), (2, 43), (9, 23)])
-@pytest.mark.parametrize("n,W,start,mode", [(1, 5, 2, 0), (65, 9, 4, 1), (130, 17, 0, 0), (257, 33, 12, 2), (192, 33, 0, 0), (193, 30, 7, 1)])
-def test_backward_passes(lasad, oracle, B, Hh, n, W, start, mode):
-    """Three passes in one launch: 3 to 207 sequences, of four, two, one workgroup a pass (16 | 17, 40 | 41), those of a sequence on
-    one XCD or not (80 | 81, 85 | 86), a workgroup walking several (with more than 192 tokens), another kernel; with the decay
-    gradient."""
+def _backward(lasad, oracle, B, Hh, n, W, start, mode, lo=0.55):
     import torch
     rng = np.random.default_rng(n + Hh)
     q, k, v, g = (_draw(rng, B, n, Hh, D) for _ in range(4))
-    gamma = rng.uniform(0.55, 1.0, Hh).astype(np.float32)
+    gamma = rng.uniform(lo, 1.0, Hh).astype(np.float32)
     up = lambda x: torch.from_numpy(x).cuda().bfloat16()
     H = (start + n + W - 1) // W
     dq, dk, dv, dgam = both_outputs(lasad.lasad_backward_chunked, True, dtype_kw="grad_dtype", q=up(q), k=up(k), v=up(v), d_o=up(g),
@@ -107,6 +102,21 @@ def test_backward_passes(lasad, oracle, B, Hh, n, W, start, mode):
     E = (cum[1:] - cum[0]).astype(np.float64)
     terms = ((np.abs(q * rq).sum(axis=3) + np.abs(k * rk).sum(axis=3)) * E[None, :, None]).sum(axis=(0, 1)).max()
     assert np.abs(dgam.cpu().numpy() - rgam).max() <= TOL["bf16"] * np.abs(rgam).max() + 1e-6 * terms / float(gamma.min())
+
+
+@pytest.mark.parametrize("B,Hh", [(1, 3), (1, 16), (1, 17), (2, 20), (1, 41), (5, 16), (3, 27), (5, 17), (2, 43), (9, 23)])
+@pytest.mark.parametrize("n,W,start,mode", [(1, 5, 2, 0), (65, 9, 4, 1), (130, 17, 0, 0), (257, 33, 12, 2), (192, 33, 0, 0), (193, 30, 7, 1)])
+def test_backward_passes(lasad, oracle, B, Hh, n, W, start, mode):
+    """Three passes in one launch: 3 to 207 sequences, of four, two, one workgroup a pass (16 | 17, 40 | 41), those of a sequence on
+    one XCD or not (80 | 81, 85 | 86), a workgroup walking several (with more than 192 tokens), another kernel; with the decay
+    gradient."""
+    _backward(lasad, oracle, B, Hh, n, W, start, mode)
+
+
+@pytest.mark.parametrize("B,Hh", [(5, 16), (9, 23)])
+def test_backward_small_gamma(lasad, oracle, B, Hh):
+    """Heads for the fp32 recurrence among the others, one and up to three at a time in a workgroup, passes with and without a sum."""
+    _backward(lasad, oracle, B, Hh, 200, 23, 3, 0, lo=0.2)
 
 
 @pytest.mark.parametrize("B,Hh,n,W", [(3, 87, 192, 31), (3, 87, 193, 31), (5, 103, 320, 25), (9, 64, 769, 40)])
