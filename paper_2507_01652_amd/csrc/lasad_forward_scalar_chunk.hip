@@ -340,14 +340,15 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
         if (MANY && --x_left == 0 && x_items) x_begin();
     };
     auto leave_sum = [&]() {
-        if (!sums) return;
+        if (sums) {
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-        if (lane == 0) {
-            sums[0] = acc;
-            for (int i = PARTS * SGROUPS; i < kDotSlots; i += PARTS * SGROUPS) sums[i] = 0.f;
+            for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+            if (lane == 0) {
+                sums[0] = acc;
+                for (int i = PARTS * SGROUPS; i < kDotSlots; i += PARTS * SGROUPS) sums[i] = 0.f;
+            }
         }
-        acc = 0.f;
+        acc = 0.f;                                             // (also of an item without a sum: 0 * Inf there is not the next item's)
     };
     auto stores_begin = [&]() {
         if (DOT) s_bounds.init(a.grid_w);

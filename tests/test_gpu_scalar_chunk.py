@@ -137,3 +137,22 @@ def test_many_sequences_a_workgroup(lasad):
     for i in (0, 8, 16390):
         part = lasad.lasad_forward_chunked(q[:, :, i:i + 10], k[:, :, i:i + 10], v[:, :, i:i + 10], gamma[i:i + 10].contiguous(), 10, 20)
         assert rel_err(o[:, :, i:i + 10].float().cpu().numpy(), part.float().cpu().numpy()) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("B,Hh", [(11, 9), (32, 16)])
+def test_non_finite_values_stay_in_their_sequence(lasad, B, Hh, value):
+    """A value of d_o that is not finite, in one sequence: every other sequence's gradients, and every other head's decay gradient, have
+    the bits of the call without it (a workgroup walks several sequences and passes, with one accumulator for their sums)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v, d_o = (torch.randn((B, 200, Hh, D), generator=gen, device="cuda").div_(8).bfloat16() for _ in range(4))
+    gamma = torch.rand((Hh,), generator=gen, device="cuda") * 0.2 + 0.79
+    clean = lasad.lasad_backward_chunked(q, k, v, d_o, gamma, 10, 20)
+    d_o[0, 70, 0, 5] = value
+    got = lasad.lasad_backward_chunked(q, k, v, d_o, gamma, 10, 20)
+    assert not torch.isfinite(got[3][0]) and torch.equal(got[3][1:], clean[3][1:])
+    for x, y in zip(got[:3], clean[:3]):
+        x, y = (t.view(torch.int16).clone() for t in (x, y))
+        x[0, :, 0] = y[0, :, 0] = 0
+        assert torch.equal(x, y)
