@@ -116,9 +116,9 @@ size_t lasad_forward_workspace_bytes(int B, int n_heads, int n_tokens, int d, in
  *   state_out [B, n_heads, d, d] fp32 or NULL; may equal state_in.
  *   workspace device scratch of at least lasad_forward_workspace_bytes(...) bytes, 16-byte
  *             aligned, contents irrelevant on entry and undefined on return; a smaller
- *             non-NULL workspace is LASAD_ERR_WORKSPACE.  NULL is allowed: the call then
- *             walks every sequence with one workgroup (same results up to rounding,
- *             slower when there are fewer sequences than the GPU has compute units).
+ *             non-NULL workspace is LASAD_ERR_WORKSPACE.  NULL is allowed: no sequence is then
+ *             cut into segments (same results up to rounding, slower for few, long sequences);
+ *             nor is any where state_out equals state_in.
  * Pointers must be aligned to 16 bytes and strides multiples of 8 elements for the
  * bf16 kernels (4 for fp32).  n_tokens may be 0 (then state_out = state_in).
  */

@@ -358,14 +358,16 @@ void plan_segments(int64_t n_seq, int n_chunks, int *n_segments, int *seg_chunks
     *n_segments = L > 0 ? (n_chunks + L - 1) / L : 1;
 }
 
-// Room for the most segments that a plan may ask for: two workgroups a compute unit, two chunks a segment, from eight chunks on.
-// (What callers are told to provide; the plan above never needs more.)
+// Room for a sequence's partial states in a call that is cut (0: in one that is not).  Two workgroups a compute unit and two chunks a
+// share: the plan's segments never need more, and what is left over lets the state pass be dealt out finer than they are.
 static int most_states(int64_t n_seq, int n_chunks)
 {
-    int G = n_chunks < 8 || n_seq < 1 ? 1 : (int)(512 / n_seq);
+    int n_segments, seg_chunks;
+    plan_segments(n_seq, n_chunks, &n_segments, &seg_chunks);
+    if (n_segments == 1) return 0;
+    int G = (int)(512 / n_seq);
     if (G > kMaxSegments) G = kMaxSegments;
     if (G > n_chunks / 2) G = n_chunks / 2;
-    if (G <= 1) return 0;
     const int L = (n_chunks + G - 1) / G;
     return (n_chunks + L - 1) / L - 1;
 }

@@ -45,12 +45,22 @@ def test_binding_names_match_header():
 
 def test_version_and_workspace(lib):
     assert b"gfx950" in lib.lasad_version()
-    # high-res stress: 96 sequences of 64 chunks -> 5 segments, 4 partial 64x64 fp32 states each
+    # high-res stress: 96 sequences of 64 chunks, room for 4 partial 64x64 fp32 states each
     assert lib.lasad_forward_workspace_bytes(4, 24, 4096, 64, 1) == 96 * 4 * 64 * 64 * 4
     assert lib.lasad_forward_workspace_bytes(8, 12, 256, 64, 1) == 0       # 4 chunks: not worth two launches
     assert lib.lasad_forward_workspace_bytes(32, 16, 576, 64, 1) == 0      # 512 sequences fill the chip
     assert lib.lasad_forward_workspace_bytes(4, 24, 4096, 64, 0) == 0      # fp32 kernel needs none
     assert lib.lasad_forward_workspace_bytes(4, 24, 4096, 32, 1) == 0
+
+
+def test_only_calls_that_are_cut_ask_for_a_workspace(lib):
+    """Both sides of the segment plan's lines: 22 chunks up to 16 sequences, 29 up to 128, none beyond."""
+    size = lambda n_seq, n: lib.lasad_forward_workspace_bytes(1, n_seq, n, 64, 1)
+    for n_seq, chunks in ((1, 22), (16, 22), (17, 29), (128, 29)):
+        assert size(n_seq, 64 * (chunks - 1)) == 0
+        assert size(n_seq, 64 * (chunks - 1) + 1) >= n_seq * 64 * 64 * 4
+    for n_seq, n in ((4, 512), (16, 1024), (128, 1024), (129, 4096), (200, 1 << 16), (256, 4096), (257, 4096)):
+        assert size(n_seq, n) == 0
 
 
 class Layout(ctypes.Structure):
