@@ -155,11 +155,11 @@ def test_backward_dgamma_full_batch(lasad, oracle):
 
 
 @pytest.mark.parametrize("B,Hh,H,W", [(4, 12, 16, 16), (8, 12, 16, 16), (11, 8, 9, 15), (1, 2, 40, 16)],
-                         ids=["48seq_twelve_wave", "96seq_eight_wave", "88seq_tail", "2seq_segmented"])
+                         ids=["48seq_own_unit", "96seq_several_a_workgroup", "88seq_eight_wave_tail", "2seq_four_workgroups"])
 def test_backward_launch_shapes(lasad, oracle, B, Hh, H, W):
-    """Every launch shape of the three passes, all gradients against the oracle on the full batch: one merged
-    launch of the twelve-wave kernel (whole and split sequences: the smaller cases above), of the eight-wave
-    kernel (more than 85 sequences), and three separate segmented passes (few long sequences)."""
+    """Every launch shape of the three passes, all gradients against the oracle on the full batch: workgroups with a compute unit
+    each (one a pass of a sequence; four, as in the smaller cases above; walking several), and the eight-wave kernel (more than 85
+    sequences of at most 192 tokens)."""
     w = wl.Workload("bwd_launch", B, Hh, 64, H, W, "bf16", 0.85, 0.999, seed=31 * B + Hh)
     _check(lasad, oracle, w, grad_bf16=True)
     _check(lasad, oracle, w, grad_bf16=False, mode=1, q_scale=0.25)

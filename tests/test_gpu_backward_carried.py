@@ -131,9 +131,10 @@ def test_backward_carried_small_gamma_heads(lasad, oracle):
 
 
 @pytest.mark.parametrize("B,Hh,H,W", [(4, 12, 16, 16), (8, 12, 16, 16), (11, 8, 9, 15), (1, 2, 40, 16)],
-                         ids=["48seq_twelve_wave", "96seq_eight_wave", "88seq_tail", "2seq_segmented"])
+                         ids=["48seq_own_unit", "96seq_several_a_workgroup", "88seq_eight_wave_tail", "2seq_four_workgroups"])
 def test_backward_carried_launch_shapes(lasad, oracle, B, Hh, H, W):
-    """Every launch shape of the three passes (merged twelve-wave and eight-wave launches, separate segmented passes)."""
+    """Every launch shape of the three passes (workgroups with a compute unit each: one a pass of a sequence, walking several, four;
+    the eight-wave kernel)."""
     w = wl.Workload("carried_launch", B, Hh, 64, H, W, "bf16", 0.85, 0.999, seed=31 * B + Hh)
     _check(lasad, oracle, w, grad_bf16=True)
     _check(lasad, oracle, w, mode=1, q_scale=0.25)

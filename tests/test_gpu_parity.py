@@ -128,7 +128,7 @@ CASES = [
     ("d64_f32", 2, 2, 64, 10, 10, "f32"),
     ("d128_f32", 1, 1, 128, 5, 5, "f32"),
     ("d64_f32_many_seqs", 6, 50, 64, 3, 13, "f32"),
-    ("bf16_160_seqs", 10, 16, 64, 9, 16, "bf16"),      # between 128 and 256 sequences: one twelve-wave workgroup each    # > 256 sequences: one workgroup per head in the fp32 kernel
+    ("bf16_160_seqs", 10, 16, 64, 9, 16, "bf16"),      # between 128 and 256 sequences: one workgroup each    # > 256 sequences: one workgroup per head in the fp32 kernel
 ]
 
 
@@ -163,11 +163,12 @@ def test_forward_carried_state_mid_row(lasad, oracle, dtype, start, n):
     assert rel_err(s_got, s_ref) <= TOL[dtype]
 
 
-@pytest.mark.parametrize("name,B,Hh,H,W", [("seg_ragged", 1, 3, 33, 19), ("seg_two", 2, 2, 32, 16), ("seg_long", 1, 1, 40, 33), ("seg_many", 70, 1, 24, 24)])
+@pytest.mark.parametrize("name,B,Hh,H,W", [("seg_ragged", 1, 3, 41, 37), ("seg_even", 2, 2, 88, 16), ("seg_long", 1, 1, 64, 61), ("seg_many", 70, 1, 59, 32)])
 @pytest.mark.parametrize("mode", [0, 1, 2])
 def test_forward_segmented_vs_oracle(lasad, oracle, name, B, Hh, H, W, mode):
-    """Few sequences of several chunks: the segment-parallel plan (state pass + full pass), with a
-    carried-in state, a ragged last chunk, and one head whose small gamma takes the fp32 recurrence."""
+    """Few, long sequences (24, 22, 61 and 30 chunks): the segment-parallel plan (state pass + full pass), with a
+    carried-in state, a ragged last chunk, and one head whose small gamma takes the fp32 recurrence.  (The query is of the plan:
+    without segments it asks for nothing.)"""
     torch = _torch()
     w = wl.Workload(name, B, Hh, 64, H, W, "bf16", 0.6, 0.999, seed=zlib.crc32(name.encode()) % 1000 + mode)
     q, k, v, g = wl.prefill_inputs(w)
@@ -175,13 +176,16 @@ def test_forward_segmented_vs_oracle(lasad, oracle, name, B, Hh, H, W, mode):
         g[1] = 0.3
     assert lasad.lasad_forward_workspace_bytes(B, Hh, w.N, 64, lasad.BF16) > 0
     s0 = wl.random_state(w, seed=11)
-    lam, _ = oracle.decay_factors(g, H, W, 0, w.N, mode)
-    ref, s_ref = oracle.forward_fullmask(q, k, v, lam, s0=s0.astype(np.float64), want_state=True)
-    for segmented in (True, False):
-        got, s_got = _gpu_forward(lasad, w, q, k, v, g, mode=mode, s0=s0, want_state=True,
-                                  out_dtype=torch.float32, use_workspace=segmented)
-        assert rel_err(got, ref) <= TOL["bf16"], segmented
-        assert rel_err(s_got, s_ref) <= TOL["bf16"], segmented
+    pairs = sample_pairs(B, Hh, 4, seed=mode)
+    lam, _ = oracle.decay_factors(g[[h for _, h in pairs]], H, W, 0, w.N, mode)
+    states = lambda s: np.stack([s[b, h] for b, h in pairs])[None]
+    ref, s_ref = oracle.forward_fullmask(*(gather_pairs(x, pairs) for x in (q, k, v)), lam, s0=states(s0).astype(np.float64), want_state=True)
+    both = [_gpu_forward(lasad, w, q, k, v, g, mode=mode, s0=s0, want_state=True, out_dtype=torch.float32, use_workspace=segmented)
+            for segmented in (True, False)]
+    for got, s_got in both:
+        assert rel_err(gather_pairs(got, pairs), ref) <= TOL["bf16"]
+        assert rel_err(states(s_got), s_ref) <= TOL["bf16"]
+    assert both[0][0].tobytes() != both[1][0].tobytes()            # (other sums: two launches and one)
 
 
 def test_forward_split_equals_single_call_on_gpu(lasad, oracle):
@@ -324,14 +328,16 @@ from paper_2507_01652_amd import binding as lasad, workloads as wl
 from oracle import lasad_oracle as oracle
 from helpers import rel_err
 worst = 0.0
-for B, Hh, H, W in ((2, 3, 13, 17), (1, 2, 40, 33)):
+for B, Hh, H, W, mode in ((2, 3, 13, 17, 0), (1, 3, 44, 33, 0), (1, 3, 44, 33, 1)):
     w = wl.Workload('variant', B, Hh, 64, H, W, 'bf16', 0.6, 0.999, seed=11 + B)
     q, k, v, g = wl.prefill_inputs(w)
-    lam, _ = oracle.decay_factors(g, H, W, 0, w.N)
+    g[1] = 0.3                                    # (a head for the fp32 recurrence)
+    assert (lasad.lasad_forward_workspace_bytes(B, Hh, w.N, 64, lasad.BF16) > 0) == (w.N > 1344)
+    lam, _ = oracle.decay_factors(g, H, W, 0, w.N, mode)
     s0 = wl.random_state(w, 3)
     ref, s_ref = oracle.forward_fullmask(q, k, v, lam, s0=s0.astype(np.float64), want_state=True)
     s1 = torch.empty((B, Hh, 64, 64), dtype=torch.float32, device='cuda')
-    o = lasad.lasad_forward_chunked(*(lasad.to_device(x, 'bf16') for x in (q, k, v)), torch.from_numpy(g).cuda(), H, W,
+    o = lasad.lasad_forward_chunked(*(lasad.to_device(x, 'bf16') for x in (q, k, v)), torch.from_numpy(g).cuda(), H, W, boundary_mode=mode,
                                     state_in=torch.from_numpy(s0).cuda(), state_out=s1, out_dtype=torch.float32)
     torch.cuda.synchronize()
     worst = max(worst, rel_err(o.cpu().numpy(), ref), rel_err(s1.cpu().numpy(), s_ref))
@@ -341,12 +347,12 @@ assert worst <= 2e-2
 
 
 @pytest.mark.parametrize("env", [{"LASAD_WS": "0"}, {"LASAD_WS": "8"}, {"LASAD_WS": "12", "LASAD_SPLIT": "1"},
-                                 {"LASAD_WS": "12", "LASAD_SPLIT": "2"}],
-                         ids=["four_wave", "eight_wave", "twelve_wave_whole", "twelve_wave_split"])
+                                 {"LASAD_WS": "12", "LASAD_SPLIT": "2"}, {"LASAD_WS": "12", "LASAD_SPLIT": "4"}],
+                         ids=["four_wave", "eight_wave", "own_unit_whole", "own_unit_two", "own_unit_four"])
 def test_forward_kernel_variants(env):
     """Every full-pass kernel variant (the launcher picks one by the number of workgroups; the choice is read
     from the environment once per process, hence the child process) against the oracle, with and without the
-    segment plan (the second shape is long enough to be cut into segments)."""
+    segment plan (the longer shapes are cut into segments)."""
     import os
     import subprocess
     import sys

@@ -24,8 +24,10 @@ def _case(torch, lasad, B, Hh, H, W, seed, start_pos=0, with_state=False):
     ws = torch.empty((need,), dtype=torch.uint8, device="cuda")
     o_ref = torch.empty_like(tq)
     s_ref = torch.empty((B, Hh, 64, 64), dtype=torch.float32, device="cuda")
+    ws.fill_(255)
     lasad.lasad_forward_chunked(tq, tk, tv, tg, H, W, start_pos=start_pos, state_in=s0, state_out=s_ref,
                                 out=o_ref, workspace=ws)
+    assert (ws[:B * Hh * 64 * 64 * 4] != 255).any(), "no partial state was written: the call was not cut"
     o = torch.full_like(tq, float("nan"))
     s1 = torch.full_like(s_ref, float("nan"))
     lasad.lasad_forward_chunked_static(tq, tk, tv, tg, H, W, o, start_pos=start_pos, state_in=s0, state_out=s1)
@@ -47,12 +49,12 @@ def test_static_entry_matches_workspace_entry(oracle):
     from paper_2507_01652_amd import binding as lasad
     lasad.load()
     assert lasad.lasad_forward_static_scratch_bytes() == 8 << 20
-    # 4 sequences of 16 chunks -> 8 segments; then 6 sequences of 9 chunks (ragged tail) -> 4 segments,
-    # started mid-row from a carried state
-    _case(torch, lasad, 1, 4, 32, 32, 4101)
-    o, (q, k, v, gam, s0) = _case(torch, lasad, 2, 3, 24, 24, 4102, start_pos=31, with_state=True)
+    # 4 sequences of 36 chunks -> 6 segments and more of the array than the next call takes; then 6 sequences of 24 chunks (ragged
+    # tail) -> 4 segments, started mid-row from a carried state
+    _case(torch, lasad, 1, 4, 48, 48, 4101)
+    o, (q, k, v, gam, s0) = _case(torch, lasad, 2, 3, 40, 38, 4102, start_pos=31, with_state=True)
     # and the second call's fp32 output against the oracle (fp64, full mask), tolerance of bf16 inputs
     from helpers import rel_err
-    lam, _ = oracle.decay_factors(gam, 24, 24, 31, q.shape[1])
+    lam, _ = oracle.decay_factors(gam, 40, 38, 31, q.shape[1])
     ref = oracle.forward_fullmask(q, k, v, lam, s0=s0.cpu().numpy().astype(np.float64))
     assert rel_err(o.cpu().numpy(), ref) <= 2e-2
