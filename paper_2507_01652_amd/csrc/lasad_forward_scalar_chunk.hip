@@ -95,6 +95,11 @@ struct Boundaries {
     }
 };
 
+constexpr int kPeriods = 2;            // chunks whose V the loaders hold in registers, and periods they are written out in (four: 1 to 3 % slower, for the periods past the end)
+// Tokens from the walk's last one on, at the most, that a load may be asked for (and gets zeros): the loaders fetch kPeriods chunks, one
+// more, and then one a period for all periods, rounded up to whole turns of kPeriods; a chunk's own rows past the end add to that.
+constexpr int kPast = (2 * kPeriods + 2) * CT;
+
 // A walk's rows of one tensor as a buffer: rows before the first and past the last are read as zero and not written, without a
 // branch (their offsets leave the range, below zero as unsigned numbers: forward_scalar_chunk_fits).
 struct WalkRows {
@@ -425,7 +430,7 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
         // ===================================== loader wavefronts =====================================
         constexpr int ROWS = SH::kLoaders * 64 / PC, IT = CT / ROWS;
         const int ld = tid - 64 * kCompute, row = ld / PC;
-        constexpr int PF = 2;              // (four: 1 to 3 % slower, for the periods past the end)
+        constexpr int PF = kPeriods;
         struct Regs { u32x4 v[IT]; } r[PF];
         // the loads' own way through the items
         uint64_t f_items = todo;
@@ -858,11 +863,11 @@ scalar_segment_state_kernel(ForwardArgs a)
 
 }  // namespace
 
-// The rows of a walk, and four chunks beyond them, within 2^31 bytes.
+// The rows of a walk, and those past its end that loads are asked for (kPast), within 2^31 bytes.
 bool forward_scalar_chunk_fits(const ForwardArgs &a)
 {
     auto ok = [&](const lasad_layout_t &l, int elt) {
-        return (l.stride_n < 0 ? -l.stride_n : l.stride_n) * elt < ((int64_t)1 << 31) / (a.n_tokens + 4 * CT) - 4;
+        return (l.stride_n < 0 ? -l.stride_n : l.stride_n) * elt < ((int64_t)1 << 31) / (a.n_tokens + kPast) - 4;
     };
     return ok(a.in, 2) && ok(a.out, a.out_dtype == LASAD_BF16 ? 2 : 4);
 }

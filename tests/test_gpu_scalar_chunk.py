@@ -156,3 +156,24 @@ def test_non_finite_values_stay_in_their_sequence(lasad, B, Hh, value):
         x, y = (t.view(torch.int16).clone() for t in (x, y))
         x[0, :, 0] = y[0, :, 0] = 0
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("n", [1, 65, 128])
+@pytest.mark.parametrize("beyond", [-8, 8])
+def test_widest_token_stride(lasad, n, beyond):
+    """Token strides on both sides of the widest one whose rows, and the 384 past them that loads are asked for, lie within 2^31 bytes
+    (beyond it another kernel takes the call): as with dense tensors."""
+    import torch
+    Hh = 2
+    stride = ((1 << 31) // (n + 384) - 4) // 2 // 8 * 8 + beyond
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn((3, 1, n, Hh, D), generator=gen, device="cuda").div_(8).bfloat16()
+    gamma = torch.tensor([0.9, 0.97], device="cuda")
+    rows = torch.full(((n - 1) * stride + 4 * Hh * D,), float("nan"), dtype=torch.bfloat16, device="cuda")    # q, k, v, o: one row
+    q, k, v, o = (rows.as_strided((1, n, Hh, D), (n * stride, stride, D, 1), i * Hh * D) for i in range(4))
+    for t, y in zip((q, k, v), x):
+        t.copy_(y)
+    want = lasad.lasad_forward_chunked(*x, gamma, 16, 16)
+    lasad.lasad_forward_chunked(q, k, v, gamma, 16, 16, out=o)
+    assert rel_err(o.float().cpu().numpy(), want.float().cpu().numpy()) <= TOL["bf16"]
+    assert all(torch.equal(t, y) for t, y in zip((q, k, v), x))
