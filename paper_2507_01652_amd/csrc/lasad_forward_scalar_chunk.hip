@@ -1,6 +1,6 @@
 // Chunked forward for the per-head decay on the bf16 matrix cores (gfx950 MFMA), bf16 storage, head dim 64: workgroups that have a
-// compute unit to themselves, and with more sequences than units walk several, one after the other.  Chunks of 64 tokens; with e_i = E(i) - E(chunk's start), r_i = gamma^e_i,
-// c_j = gamma^-e_j, f_j = gamma^(e_end - e_j):
+// compute unit to themselves, and with more sequences than units walk several, one after the other.  Chunks of 64 tokens; with
+// e_i = E(i) - E(chunk's start), r_i = gamma^e_i, c_j = gamma^-e_j, f_j = gamma^(e_end - e_j):
 //
 //     o_i   = r_i ( q_i^T S + sum_{j<=i} c_j (q_i . k_j) v_j ),      S <- r_end S + sum_j k_j (f_j v_j)^T
 //
@@ -95,7 +95,8 @@ struct Boundaries {
     }
 };
 
-constexpr int kPeriods = 2;            // chunks whose V the loaders hold in registers, and periods they are written out in (four: 1 to 3 % slower, for the periods past the end)
+// Chunks whose V the loaders hold in registers, and periods that a turn of their loop has (four: 1 to 3 % slower, for those past the end).
+constexpr int kPeriods = 2;
 // Tokens from the walk's last one on, at the most, that a load may be asked for (and gets zeros): the loaders fetch kPeriods chunks, one
 // more, and then one a period for all periods, rounded up to whole turns of kPeriods; a chunk's own rows past the end add to that.
 constexpr int kPast = (2 * kPeriods + 2) * CT;
@@ -124,8 +125,9 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int off, u32
     __builtin_amdgcn_raw_buffer_store_b128(x, r, off, 0, NT ? 2 : 0);
 }
 
-// Wavefronts, in this order, number modulo 4 being the SIMD: the state's, output (NV 2: the two later query tiles by value tile, 96 sequences of 576 tokens 11.4 -> 11.0 us; NV 1: the last one
-// by half of the keys, 16 of 576 9.2 -> 8.1), loaders, stores, copy.  (NV 4: the SIMDs with the two short query tiles have the stores.)
+// Wavefronts, in this order, number modulo 4 being the SIMD: the state's, output (NV 2: the two later query tiles by value tile, 96
+// sequences of 576 tokens 11.4 -> 11.0 us; NV 1: the last one by half of the keys, 16 of 576 9.2 -> 8.1), loaders, stores, copy.
+// (NV 4: the SIMDs with the two short query tiles have the stores.)
 constexpr int out_waves(int nv) { return nv == 2 ? 6 : nv == 1 ? 5 : 4; }
 constexpr int loader_waves(int nv) { return nv == 1 ? 2 : 4; }
 constexpr int store_waves(int nv) { return nv == 1 ? 1 : 2; }
@@ -272,145 +274,145 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
     SplitConst sc;
     sc.init();
 
-    // ---- the output tiles' way out, by the loaders or by wavefronts of their own ----
-    constexpr int SGROUPS = SH::kStore ? SH::kStore : SH::kLoaders, PC = 2 * NV, SROWS = SGROUPS * 64 / PC, SIT = CT / SROWS, E = OUT_BF16 ? 2 : 4;
-    const int st = tid - 64 * (kCompute + (SH::kStore ? SH::kLoaders : 0)), srow = st / PC, pc = tid % PC;
-    struct Tile { f32x4v u[SIT], w[SIT]; };
-    auto read_tile = [&](Tile &t, int p) {
-#pragma unroll
-        for (int i = 0; i < SIT; ++i) {
-            if (SH::O16) {
-                t.u[i] = *(const f32x4v *)(outs + p * CT * OS + (srow + i * SROWS) * OS + pc * 4);
-            } else {
-                const float *tile = outs + p * CT * OS + (srow + i * SROWS) * OS + pc * 8;
-                t.u[i] = *(const f32x4v *)tile;
-                t.w[i] = *(const f32x4v *)(tile + 4);
-                if (NV == 1) {
-                    const int r = srow + i * SROWS;
-                    const float *const more = parts + p * SH::kPart + (r < CT - 16 ? 16 : r - (CT - 16)) * OS + pc * 8;
-                    t.u[i] += *(const f32x4v *)more;
-                    t.w[i] += *(const f32x4v *)(more + 4);
-                }
-            }
-        }
-    };
-    // One period behind the output: before the first tile there is one that leaves the range.  Decay-gradient sums: the fourth
-    // tensor's rows, two periods ahead of their tile (one: the stores before them have to be through by then).
-    uint64_t s_items = todo, x_items = todo;
-    __amdgpu_buffer_rsrc_t ro, rx;
-    int o_off = 0, o_step = 0, s_left = n_chunks + 1, x_off = 0, x_step = 0, x_left = 0;
-    int t0 = -CT;                                              // token of the tile's first row
-    float *sums = nullptr;
-    float acc = 0.f, e_sign = 0.f, e_add = 0.f;
-    int e_before = 0;
-    Boundaries s_bounds;
-    u32x4 x4[2][SIT];
-    auto store_begin = [&]() {
-        const Item it = item(take(s_items));
-        const int bh = it.blk / G;
-        const lasad_layout_t l = multi ? m.out[it.pass] : a.out;
-        const WalkRows out(l.stride_n * E, n);
-        ro = out.rsrc((char *)(multi ? m.o[it.pass] : a.o) + first_row(l, bh) * E, n, D * E);
-        o_off = out.first + srow * out.step + (it.vp * 16 * NV + pc * 8) * E;
-        o_step = out.step;
-        if (DOT) {
-            t0 = 0;
-            e_before = 0;
-            e_sign = e_add = 0.f;
-            sums = nullptr;
-            s_bounds.begin(m.start_pos[it.pass], a.mode);
-            if (m.x[it.pass]) {
-                const int e_all = cum_exp(m.x_start_pos + a.n_tokens, a.grid_w, a.mode) - cum_exp(m.x_start_pos, a.grid_w, a.mode);
-                // in a reversed pass step i applies the decay of the token walked before it, the first step somebody else's
-                const int before = is_boundary(m.start_pos[it.pass] + 1, a.grid_w, a.mode) ? 0 : 1;
-                e_sign = m.x_rev[it.pass] ? -m.x_sign[it.pass] : m.x_sign[it.pass];
-                e_add = m.x_rev[it.pass] ? m.x_sign[it.pass] * (float)(e_all + before) : 0.f;
-                sums = m.x_sums + ((int64_t)it.pass * a.B * a.Hh + bh) * kDotSlots + it.vp * SGROUPS + (st >> 6);
-            }
-        }
-    };
-    auto x_begin = [&]() {
-        const Item it = item(take(x_items));
-        const lasad_layout_t l = m.in[it.pass];
-        const WalkRows in(l.stride_n * 2, n);
-        rx = in.rsrc((const char *)(m.x[it.pass] ? m.x[it.pass] : m.v[it.pass]) + first_row(l, it.blk / G) * 2, n, 128);
-        x_off = in.first + srow * in.step + it.vp * (32 * NV) + pc * 16;
-        x_step = in.step;
-        x_left = n_chunks;
-    };
-    auto x_fetch = [&](u32x4 (&x)[SIT]) {
-#pragma unroll
-        for (int i = 0; i < SIT; ++i) x[i] = buf_load<false>(rx, x_off + i * SROWS * x_step);
-        x_off += CT * x_step;
-        if (MANY && --x_left == 0 && x_items) x_begin();
-    };
-    auto leave_sum = [&]() {
-        if (sums) {
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-            if (lane == 0) {
-                sums[0] = acc;
-                for (int i = PARTS * SGROUPS; i < kDotSlots; i += PARTS * SGROUPS) sums[i] = 0.f;
-            }
-        }
-        acc = 0.f;                                             // (also of an item without a sum: 0 * Inf there is not the next item's)
-    };
-    auto stores_begin = [&]() {
-        if (DOT) s_bounds.init(a.grid_w);
-        store_begin();
-        o_off -= CT * o_step;
-        if (DOT) {
-            t0 = -CT;
-            x_begin();
-            x_fetch(x4[1]);
-        }
-    };
-    auto store_tile = [&](const Tile &t, int p) {              // (tile p - 1 in the order of the walk)
-        uint64_t bmask = 0;
-        if (DOT) bmask = s_bounds.mask();
-#pragma unroll
-        for (int i = 0; i < SIT; ++i) {
-            const int at = o_off + i * SROWS * o_step;
-            const f32x4v &u = t.u[i], &w = t.w[i];
-            if (SH::O16) {
-                buf_store<true>(ro, at, __builtin_bit_cast(u32x4, u));
-            } else if (OUT_BF16) {
-                buf_store<true>(ro, at, u32x4{pack2(u[0], u[1]), pack2(u[2], u[3]), pack2(w[0], w[1]), pack2(w[2], w[3])});
-            } else {
-                buf_store<true>(ro, at, __builtin_bit_cast(u32x4, u));
-                buf_store<true>(ro, at + 16, __builtin_bit_cast(u32x4, w));
-            }
-            if (DOT) {
-                float d = 0.f;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const f32x4v &y = j < 2 ? u : w;
-                    d = fmaf(__uint_as_float(x4[p][i][j] << 16), y[2 * (j & 1)], d);
-                    d = fmaf(__uint_as_float(x4[p][i][j] & 0xffff0000u), y[2 * (j & 1) + 1], d);
-                }
-                const int r = srow + i * SROWS, e = r + 1 - __builtin_popcountll(bmask & (~0ull >> (63 - r)));
-                const float weight = e_sign * (float)(e_before + e) + e_add;
-                acc = (uint32_t)(t0 + r) < (uint32_t)n ? fmaf(weight, d, acc) : acc;
-            }
-        }
-        o_off += CT * o_step;
-        if (DOT) {
-            if (t0 >= 0) {                                     // (the tile before the first has no rows)
-                e_before += CT - __builtin_popcountll(bmask);
-                s_bounds.advance();
-            }
-            t0 += CT;
-        }
-        if (--s_left == 0 && s_items) {
-            if (DOT) leave_sum();
-            store_begin();
-            s_left = n_chunks;
-        }
-        if (DOT) x_fetch(x4[p]);
-    };
-
-    if (SH::kStore && wave >= kCompute + SH::kLoaders) {
+    constexpr int PC = 2 * NV;                                 // pieces of eight channels a row
+    const int pc = tid % PC;
+    if (wave >= kCompute + SH::kLoaders) {
         // ===================================== store wavefronts =====================================
+        constexpr int SROWS = SH::kStore * 64 / PC, SIT = CT / SROWS, E = OUT_BF16 ? 2 : 4;
+        const int st = tid - 64 * (kCompute + SH::kLoaders), srow = st / PC;
+        struct Tile { f32x4v u[SIT], w[SIT]; };
+        auto read_tile = [&](Tile &t, int p) {
+#pragma unroll
+            for (int i = 0; i < SIT; ++i) {
+                if (SH::O16) {
+                    t.u[i] = *(const f32x4v *)(outs + p * CT * OS + (srow + i * SROWS) * OS + pc * 4);
+                } else {
+                    const float *tile = outs + p * CT * OS + (srow + i * SROWS) * OS + pc * 8;
+                    t.u[i] = *(const f32x4v *)tile;
+                    t.w[i] = *(const f32x4v *)(tile + 4);
+                    if (NV == 1) {
+                        const int r = srow + i * SROWS;
+                        const float *const more = parts + p * SH::kPart + (r < CT - 16 ? 16 : r - (CT - 16)) * OS + pc * 8;
+                        t.u[i] += *(const f32x4v *)more;
+                        t.w[i] += *(const f32x4v *)(more + 4);
+                    }
+                }
+            }
+        };
+        // One period behind the output: before the first tile there is one that leaves the range.  Decay-gradient sums: the fourth
+        // tensor's rows, two periods ahead of their tile (one: the stores before them have to be through by then).
+        uint64_t s_items = todo, x_items = todo;
+        __amdgpu_buffer_rsrc_t ro, rx;
+        int o_off = 0, o_step = 0, s_left = n_chunks + 1, x_off = 0, x_step = 0, x_left = 0;
+        int t0 = -CT;                                              // token of the tile's first row
+        float *sums = nullptr;
+        float acc = 0.f, e_sign = 0.f, e_add = 0.f;
+        int e_before = 0;
+        Boundaries s_bounds;
+        u32x4 x4[2][SIT];
+        auto store_begin = [&]() {
+            const Item it = item(take(s_items));
+            const int bh = it.blk / G;
+            const lasad_layout_t l = multi ? m.out[it.pass] : a.out;
+            const WalkRows out(l.stride_n * E, n);
+            ro = out.rsrc((char *)(multi ? m.o[it.pass] : a.o) + first_row(l, bh) * E, n, D * E);
+            o_off = out.first + srow * out.step + (it.vp * 16 * NV + pc * 8) * E;
+            o_step = out.step;
+            if (DOT) {
+                t0 = 0;
+                e_before = 0;
+                e_sign = e_add = 0.f;
+                sums = nullptr;
+                s_bounds.begin(m.start_pos[it.pass], a.mode);
+                if (m.x[it.pass]) {
+                    const int e_all = cum_exp(m.x_start_pos + a.n_tokens, a.grid_w, a.mode) - cum_exp(m.x_start_pos, a.grid_w, a.mode);
+                    // in a reversed pass step i applies the decay of the token walked before it, the first step somebody else's
+                    const int before = is_boundary(m.start_pos[it.pass] + 1, a.grid_w, a.mode) ? 0 : 1;
+                    e_sign = m.x_rev[it.pass] ? -m.x_sign[it.pass] : m.x_sign[it.pass];
+                    e_add = m.x_rev[it.pass] ? m.x_sign[it.pass] * (float)(e_all + before) : 0.f;
+                    sums = m.x_sums + ((int64_t)it.pass * a.B * a.Hh + bh) * kDotSlots + it.vp * SH::kStore + (st >> 6);
+                }
+            }
+        };
+        auto x_begin = [&]() {
+            const Item it = item(take(x_items));
+            const lasad_layout_t l = m.in[it.pass];
+            const WalkRows in(l.stride_n * 2, n);
+            rx = in.rsrc((const char *)(m.x[it.pass] ? m.x[it.pass] : m.v[it.pass]) + first_row(l, it.blk / G) * 2, n, 128);
+            x_off = in.first + srow * in.step + it.vp * (32 * NV) + pc * 16;
+            x_step = in.step;
+            x_left = n_chunks;
+        };
+        auto x_fetch = [&](u32x4 (&x)[SIT]) {
+#pragma unroll
+            for (int i = 0; i < SIT; ++i) x[i] = buf_load<false>(rx, x_off + i * SROWS * x_step);
+            x_off += CT * x_step;
+            if (MANY && --x_left == 0 && x_items) x_begin();
+        };
+        auto leave_sum = [&]() {
+            if (sums) {
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+                if (lane == 0) {
+                    sums[0] = acc;
+                    for (int i = PARTS * SH::kStore; i < kDotSlots; i += PARTS * SH::kStore) sums[i] = 0.f;
+                }
+            }
+            acc = 0.f;                                             // (also of an item without a sum: 0 * Inf there is not the next item's)
+        };
+        auto stores_begin = [&]() {
+            if (DOT) s_bounds.init(a.grid_w);
+            store_begin();
+            o_off -= CT * o_step;
+            if (DOT) {
+                t0 = -CT;
+                x_begin();
+                x_fetch(x4[1]);
+            }
+        };
+        auto store_tile = [&](const Tile &t, int p) {              // (tile p - 1 in the order of the walk)
+            uint64_t bmask = 0;
+            if (DOT) bmask = s_bounds.mask();
+#pragma unroll
+            for (int i = 0; i < SIT; ++i) {
+                const int at = o_off + i * SROWS * o_step;
+                const f32x4v &u = t.u[i], &w = t.w[i];
+                if (SH::O16) {
+                    buf_store<true>(ro, at, __builtin_bit_cast(u32x4, u));
+                } else if (OUT_BF16) {
+                    buf_store<true>(ro, at, u32x4{pack2(u[0], u[1]), pack2(u[2], u[3]), pack2(w[0], w[1]), pack2(w[2], w[3])});
+                } else {
+                    buf_store<true>(ro, at, __builtin_bit_cast(u32x4, u));
+                    buf_store<true>(ro, at + 16, __builtin_bit_cast(u32x4, w));
+                }
+                if (DOT) {
+                    float d = 0.f;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const f32x4v &y = j < 2 ? u : w;
+                        d = fmaf(__uint_as_float(x4[p][i][j] << 16), y[2 * (j & 1)], d);
+                        d = fmaf(__uint_as_float(x4[p][i][j] & 0xffff0000u), y[2 * (j & 1) + 1], d);
+                    }
+                    const int r = srow + i * SROWS, e = r + 1 - __builtin_popcountll(bmask & (~0ull >> (63 - r)));
+                    const float weight = e_sign * (float)(e_before + e) + e_add;
+                    acc = (uint32_t)(t0 + r) < (uint32_t)n ? fmaf(weight, d, acc) : acc;
+                }
+            }
+            o_off += CT * o_step;
+            if (DOT) {
+                if (t0 >= 0) {                                     // (the tile before the first has no rows)
+                    e_before += CT - __builtin_popcountll(bmask);
+                    s_bounds.advance();
+                }
+                t0 += CT;
+            }
+            if (--s_left == 0 && s_items) {
+                if (DOT) leave_sum();
+                store_begin();
+                s_left = n_chunks;
+            }
+            if (DOT) x_fetch(x4[p]);
+        };
         stores_begin();
         __syncthreads();
         for (int c0 = 0; c0 <= n_all; c0 += 2) {               // (pairs of periods, as the loaders)
@@ -472,7 +474,6 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
             p_left = n;
         };
         prepare_begin();
-        if (SH::kStore == 0) stores_begin();
         auto prepare = [&](const Regs &x, int p) {
             const uint64_t bmask = bounds.mask();
             bounds.advance();
@@ -482,7 +483,8 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
             const float end = __builtin_amdgcn_exp2f((float)e_end * lg);
 #pragma unroll
             for (int i = 0; i < IT; ++i) {
-                const int e = row + i * ROWS + 1 - __builtin_popcountll(bmask & (IT == 1 || i == 0 ? upto : ((1ull << ROWS) - 1) | upto << ROWS));
+                const uint64_t first = i == 0 ? upto : ((1ull << (ROWS & 63)) - 1) | upto << (ROWS & 63);      // (at most two rows a thread)
+                const int e = row + i * ROWS + 1 - __builtin_popcountll(bmask & first);
                 const float cj = __builtin_amdgcn_exp2f(-(float)e * lg), fj = cj * end;
                 uint16_t *const s = slots + p * SL::kHalfs + put + i * (ROWS / 16) * SL::Map::kHalf;
                 if (pc < 2) tab_at[p * kTab + (pc == 0 ? i * ROWS : 0)] = pc == 0 ? cj : end;
@@ -510,15 +512,11 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
 #pragma unroll
             for (int u = 0; u < PF; ++u) {
                 const int chunk = c0 + u;
-                Tile t;
-                if (SH::kStore == 0) read_tile(t, (u + 1) & 1);
                 if (chunk + 1 < n_all) prepare(r[(u + 1) % PF], (u + 1) & 1);
-                if (SH::kStore == 0) store_tile(t, u);
                 fetch(r[(u + 1) % PF]);
                 if (chunk < n_all) __syncthreads();
             }
         }
-        if (DOT && SH::kStore == 0) leave_sum();
         return;
     }
 
@@ -761,9 +759,10 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
 
 // State pass of the segment plan: what a segment (all but the last) adds to the state, gamma^(E(end) - E(j)) k_j v_j^T summed over
 // its tokens (bound by memory; a workgroup of four wavefronts that met at two barriers a chunk took 54 us a call where this one
-// takes 36, 12 sequences of 4096 tokens in two segments; 96 of 4096 87 -> 69, and 64 with two workgroups a segment).  Weights from the segment's end on are at most 1, so nothing is ever rescaled, and a wavefront needs no other: it walks
-// a quarter of the segment's chunks of 32 tokens in a slot of its own, all 64 x 64 of the state in its accumulators, without a
-// barrier; the four states are added up at the end.
+// takes 36, 12 sequences of 4096 tokens in two segments; 96 of 4096 87 -> 69, and 64 with two workgroups a segment).  Weights from
+// the segment's end on are at most 1, so nothing is ever rescaled, and a wavefront needs no other: it walks a quarter of the
+// segment's chunks of 32 tokens in a slot of its own, all 64 x 64 of the state in its accumulators, without a barrier; the four
+// states are added up at the end.
 constexpr int kStateRow = 3 * D + 16;          // K, f V hi, lo
 constexpr int kStateSlot = SlotMap<kStateRow>::kHalfs;
 __global__ void __launch_bounds__(256, 2)
@@ -878,8 +877,8 @@ hipError_t launch_scalar_segment_state(const ForwardArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// As many workgroups a sequence (or segment) as still get a compute unit each (all of a sequence are on one XCD, of 32 units).  (64 sequences of 576 tokens, NV 4, 2, 1: 14.1, 10.8,
-// 9.4 us; 96 of 576: 14.4, 11.0, 16.4; 192 of 576: 15.0, 20.1.)
+// As many workgroups a sequence (or segment) as still get a compute unit each (all of a sequence are on one XCD, of 32 units).  (64
+// sequences of 576 tokens, NV 4, 2, 1: 14.1, 10.8, 9.4 us; 96 of 576: 14.4, 11.0, 16.4; 192 of 576: 15.0, 20.1.)
 hipError_t launch_forward_scalar_chunk(const ForwardArgs &a, const MultiPass &m, hipStream_t s)
 {
     if (a.d != D || a.io_dtype != LASAD_BF16 || a.n_tokens < 1 || (m.n_pass > 1 && a.n_segments != 1)) return hipErrorInvalidValue;

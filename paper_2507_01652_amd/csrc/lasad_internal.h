@@ -44,10 +44,8 @@ struct ForwardArgs {
     int first_decay_off = 0;
 };
 
-// Up to three independent forward passes in one launch of the wave-specialised kernels
-// (blockIdx.y = pass): the fields below replace those of the common ForwardArgs.
-// Several independent passes of the scalar-decay forward kernels in one launch (blockIdx.y = pass):
-// per-pass operands, layouts and start column; everything else is shared (ForwardArgs).
+// Up to three independent passes of the scalar-decay forward kernels in one launch: the fields below replace those of the common
+// ForwardArgs (operands, layouts, start column, states); everything else is shared.
 // A pass may also accumulate the decay-gradient term of the backward pass,
 //   sign * sum_t E_t (x_t . o_t),   E_t = non-boundary tokens among the first t + 1 of the call,
 // from its fp32 output tiles: x is a fourth bf16 tensor laid out like the pass's inputs, and with
