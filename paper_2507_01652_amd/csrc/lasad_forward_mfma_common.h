@@ -272,11 +272,11 @@ struct RecDotHook {
     }
 };
 
-template <int OUT_BF16>
+template <int OUT_BF16, bool FIRST = false>
 __device__ inline void recurrence_with_dot(const ForwardArgs &a, const MultiPass &m, int y, int bh, float *smem, const int tid = threadIdx.x)
 {
     if (!(m.n_pass > 1 && m.x[y])) {
-        recurrence_sequence<D, 1, OUT_BF16>(a, bh, smem, RecNoHook(), tid);
+        recurrence_sequence<D, 1, OUT_BF16, 0, FIRST>(a, bh, smem, RecNoHook(), tid);
         return;
     }
     const int b = bh / a.Hh, h = bh - b * a.Hh;
@@ -288,7 +288,7 @@ __device__ inline void recurrence_with_dot(const ForwardArgs &a, const MultiPass
     hook.grid_w = a.grid_w; hook.mode = a.mode;
     hook.e0 = cum_exp(m.x_start_pos, a.grid_w, a.mode);
     hook.acc = &acc;
-    recurrence_sequence<D, 1, OUT_BF16>(a, bh, smem, hook, tid);
+    recurrence_sequence<D, 1, OUT_BF16, 0, FIRST>(a, bh, smem, hook, tid);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
     __syncthreads();                   // the recurrence's last reads of its LDS block

@@ -722,8 +722,11 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
     };
     if (todo) walk_items();
     if (!rest) return;
-    // The fp32 recurrence, a whole sequence by four wavefronts, as many at a time as there are wavefronts for.  (One after the other:
-    // 512 sequences of 576 tokens 462 us, two workgroups a unit in the eight-wave kernel 261, up to three at a time 255; three passes of them 845 and 681.)
+    // The fp32 recurrence, a whole sequence by four wavefronts, as many at a time as there are wavefronts for.  (One after the other: 512
+    // sequences of 576 tokens 462 us, up to three at a time 221.  Against the kernels of eight and twelve wavefronts that had these
+    // calls before, all heads such: forward 16 of 256 98 -> 85, 200 of 256 105 -> 92, 512 of 576 240 -> 221; three passes 16 of 256
+    // 104 -> 97, 96 of 576 246 -> 235, 200 of 256 210 -> 129, 512 of 576 780 -> 589; 300 of 256 227 -> 232, one head in eight such 217 ->
+    // 230: there a workgroup of four items has one for a second round.)
     constexpr int kSide = MANY ? SH::kWaves / (kRecThreads / 64) : 1;
     static_assert(kSide * kRecBytes <= (int)sizeof(smem), "a block of LDS for each");
     __syncthreads();
@@ -744,13 +747,13 @@ forward_scalar_chunk_kernel(ForwardArgs a, MultiPass m)
         float *const lds = (float *)(smem + side * kRecBytes);
         const int rt = tid & (kRecThreads - 1);
         if (DOT) {
-            fwd::recurrence_with_dot<OUT_BF16>(s, m, it.pass, it.blk / G, lds, rt);
+            fwd::recurrence_with_dot<OUT_BF16, true>(s, m, it.pass, it.blk / G, lds, rt);
             if (!m.x[it.pass]) {                               // (as many barriers as the passes with a sum)
                 __syncthreads();
                 __syncthreads();
             }
         } else {
-            recurrence_sequence<D, 1, OUT_BF16>(s, it.blk / G, lds, RecNoHook(), rt);
+            recurrence_sequence<D, 1, OUT_BF16, 0, true>(s, it.blk / G, lds, RecNoHook(), rt);
         }
         __syncthreads();
         for (int i = 0; i < kSide; ++i) rest &= rest - 1;

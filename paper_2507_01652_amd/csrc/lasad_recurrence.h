@@ -47,7 +47,11 @@ struct RecNoHook {
     __device__ void operator()(int, int, float) const {}
 };
 
-template <int D, int IN_BF16, int OUT_BF16, int GATED = 0, class Hook = RecNoHook>
+// FIRST: a token's reads from LDS before its arithmetic.  In a kernel with many registers in use elsewhere the compiler gives the reads
+// one set of registers and waits for them four times a token (scalar-decay kernel with the decay gradient, heads of gamma <= 0.5 only,
+// three passes of 16 sequences of 256 tokens 109.8 -> 96.7 us, 96 of 576 274 -> 234; its forward 90.0 -> 85.4); where it does not, they
+// are better left to it (bf16, d 32 54.3 and 56.8 us, eight-wave kernel 88.7 and 92.1).
+template <int D, int IN_BF16, int OUT_BF16, int GATED = 0, bool FIRST = false, class Hook = RecNoHook>
 __device__ void recurrence_sequence(const ForwardArgs &a, int bh, float *smem, Hook hook = Hook(), const int tid = threadIdx.x)
 {
     constexpr int G = kRecThreads / D;   // row groups
@@ -101,6 +105,20 @@ __device__ void recurrence_sequence(const ForwardArgs &a, int bh, float *smem, H
             const float lam = (is_boundary(t, a.grid_w, a.mode) || (a.first_decay_off && t0 + tt == 0)) ? 1.0f : gamma;
             const float vj = sv[tt][j];
             float part = 0.f;
+            if constexpr (FIRST) {
+                static_assert(!GATED, "a third vector a token");
+                float kr[R], qr[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) { kr[r] = sk[tt][g * R + r]; qr[r] = sq[tt][g * R + r]; }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    S[r] = fmaf(lam, S[r], kr[r] * vj);
+                    part = fmaf(qr[r], S[r], part);
+                }
+                red[tt][g][j] = part;
+                continue;
+            }
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const float lr = GATED ? sl[tt][g * R + r] : lam;
@@ -113,8 +131,17 @@ __device__ void recurrence_sequence(const ForwardArgs &a, int bh, float *smem, H
         for (int e = tid; e < nt * D; e += kRecThreads) {
             const int tt = e / D, c = e - tt * D;
             float acc = 0.f;
+            if constexpr (FIRST) {
+                float x[G];
 #pragma unroll
-            for (int gg = 0; gg < G; ++gg) acc += red[tt][gg][c];
+                for (int gg = 0; gg < G; ++gg) x[gg] = red[tt][gg][c];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int gg = 0; gg < G; ++gg) acc += x[gg];
+            } else {
+#pragma unroll
+                for (int gg = 0; gg < G; ++gg) acc += red[tt][gg][c];
+            }
             rec_store<OUT_BF16>(a.o, out_base + (int64_t)(t0 + tt) * a.out.stride_n + c, a.q_scale * acc);
             hook(t0 + tt, c, a.q_scale * acc);
         }
