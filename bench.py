@@ -361,7 +361,7 @@ def bench_backward(args, timer, torch, lasad, wl):
     res = {"workload": w.name, "value": w.B * w.N / dur_s, "unit": "tokens/s", "ms_per_step": ms_per_step,
            "steps_timed": steps, "eager_ms_per_step": eager_ms, "workspace_bytes": ws_bytes,
            "launches_per_step": "one launch of the forward kernel over the 3 passes (dq, dv, dk; decay-gradient sums in its "
-                                "epilogue) + 1 reduction kernel; few long sequences: 3 segmented passes + 2 finishing kernels",
+                                "epilogue) + 1 reduction kernel",
            "roofline": hbm_roofline("lasad_backward_chunked (all launches of one call)", bytes_bwd, dur_s,
                                     measured_traffic("backward", w.name))}
     del bufs, ws

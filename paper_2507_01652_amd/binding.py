@@ -188,7 +188,7 @@ def extension():
         try:
             from . import _steps as steps
         except ImportError as e:
-            raise ImportError(f"{e}: build the decode steps' extension (for the torch in use) with "
+            raise ImportError(f"{e}: build the extension (for the torch in use) with "
                               "`python -m paper_2507_01652_amd.build`") from e
         _steps = steps
     return _steps

@@ -1,4 +1,4 @@
-"""Build liblasad.so (hand-written HIP, gfx950 only) in-tree with hipcc, and _steps.so, the decode steps' marshalling
+"""Build liblasad.so (hand-written HIP, gfx950 only) in-tree with hipcc, and _steps.so, the marshalling of the calls
 (host code against torch's C++ interface), with g++.
 
 Usage: ``python -m paper_2507_01652_amd.build``.  Both land next to this

@@ -389,8 +389,10 @@ hipError_t launch_forward_mfma(const ForwardArgs &a_in, hipStream_t s)
     if (n_seq * a.n_segments > 0x7fffffff) return hipErrorInvalidValue;
     // The full pass: workgroups with a compute unit each while there are so few, or from four chunks on; else eight waves, two
     // workgroups a unit, whose starts and ends overlap.  (Eight waves against this, us: 512 sequences of 64 tokens 8.6 and 9.1, of 128
-    // 11.9 and 12.4, of 192 16.9 and 16.3, of 256 21.4 and 19.5, of 576 39.6 and 36.2, one set of buffers 35.3 and 34.9; 300 of 192 13.9
-    // and 14.3, of 256 17.0 and 17.0, of 400 25.3 and 24.1; 2000 of 128 37.9 and 33.4; 1000 of 400 57 and 52; 260 of 4096 193 and 174.)
+    // 11.9 and 12.4, of 192 16.9 and 16.3, of 256 21.4 and 19.5, of 576 39.6 and 36.2; 300 of 192 13.9 and 14.3, of 256 17.0 and 17.0, of
+    // 400 25.3 and 24.1; 2000 of 128 37.9 and 33.4; 1000 of 400 57 and 52; 260 of 4096 193 and 174.  These are inputs that are not in
+    // the caches.  On few sets of buffers in turn 512 of 576 is a draw that the card's clock decides, 35.1 to 36.0 and 33.5 to 36.4,
+    // and 300 of 256 15.2 and 15.4; the other sizes gain there too: 512 of 256 18.6 and 17.6, of 1024 59 and 54, 768 of 256 27.5 and 24.2.)
     // LASAD_WS = 12 / 8 / 0 forces one of them or the four-wave kernel.
     static const int ws = [] { const char *e = getenv("LASAD_WS"); return e ? atoi(e) : -1; }();
     const bool own_unit = (ws == 12 || (ws < 0 && (n_seq * a.n_segments <= 256 || a.n_tokens > 192))) && forward_scalar_chunk_fits(a);

@@ -25,6 +25,9 @@
 // 19.9 us, of 512 102 -> 89, a period 3340 -> 2870 cycles; NV 2, NV 1: 40 of 576 16.0 -> 15.0, 16 of 400 11.0 -> 10.7.
 // Several sequences a workgroup without a pause, against the kernel of eight wavefronts with two workgroups a unit: 512 of 576 41.1 ->
 // 37.6 us, 1000 of 576 81 -> 67; three passes, 512 of 576 102 -> 89, of 1024 200 -> 159, 96 of 4096 216 -> 178.
+// Counters at 512 of 576: matrix cores busy 23 % of the SIMD cycles, vector ALU 40 %, LDS 44 %, wavefronts waiting 53 % of theirs.
+// Scalar registers: the variants with the decay gradient spill 40 to 54 (18 in NV 4 without it), as five roles of one function share
+// both argument structures; the state and output wavefronts' loops read none of them back.
 // Dropped on the way: 32-token chunks (the latency of a period, about 1000 cycles, twice); compute wavefronts that own their state
 // columns and form all scores themselves, as in the vector-decay kernels (more instructions than the kernel replaced); loaders that
 // move Q and K through registers (16 wavefronts, 2000 cycles a chunk in the place of 1750).
