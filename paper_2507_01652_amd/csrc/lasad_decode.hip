@@ -215,13 +215,14 @@ hipError_t launch_d(const DecodeArgs &a, hipStream_t s)
 // what a step waits for, and for so many states that their number of loads in flight counts again.  In between a fourth of
 // the loads a wavefront with four times the wavefronts to start is slower.  us a step (graph replay), one | four wavefronts: 12
 // states 3.06 | 2.86, 128 3.26 | 3.12, 256 3.91 | 3.81, fused layer 12 3.48 | 3.18, 256 3.95 | 3.84; 320 4.10 | 4.25, 512 4.60 | 4.70,
-// 1024 6.9 | 7.8, 2048 13.0 | 13.1; 3072 18.9 | 18.6, 5120 30.1 | 29.1, 8192 46.8 | 44.7.
+// 1024 6.9 | 7.8, 2048 13.0 | 13.1; 3072 18.9 | 18.6, 5120 30.1 | 29.1, 8192 46.8 | 44.7.  (A launch has room for 2^32 threads: states
+// that fill the memory, 2^24 and more, keep one wavefront.)
 hipError_t launch_decode(const DecodeArgs &a, hipStream_t s)
 {
     const int64_t n_states = (int64_t)a.B * a.Hh;
     switch (a.d) {
         case 32: return launch_d<32, 1>(a, s);
-        case 64: return n_states <= 256 || n_states >= 3000 ? launch_d<64, 4>(a, s) : launch_d<64, 1>(a, s);
+        case 64: return n_states <= 256 || (n_states >= 3000 && n_states < 1 << 24) ? launch_d<64, 4>(a, s) : launch_d<64, 1>(a, s);
         case 128: return launch_d<128, 1>(a, s);
         default: return hipErrorInvalidValue;
     }
