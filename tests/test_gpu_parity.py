@@ -81,15 +81,15 @@ def test_forward_tiny_fp32(lasad, oracle):
     assert rel_err(s_got, s_ref) <= TOL["f32"]
 
 
-@pytest.mark.parametrize("segmented", [True, False], ids=["segments", "single_pass"])
+@pytest.mark.parametrize("use_workspace", [True, False], ids=["workspace", "no_workspace"])
 @pytest.mark.parametrize("out", ["bf16", "f32"])
-def test_forward_base_prefill_full(lasad, oracle, out, segmented):
+def test_forward_base_prefill_full(lasad, oracle, out, use_workspace):
     w = wl.BASE_PREFILL
     q, k, v, g = wl.prefill_inputs(w)
     lam, _ = oracle.decay_factors(g, w.grid_h, w.grid_w, 0, w.N)
     ref, s_ref = oracle.forward_fullmask(q, k, v, lam, want_state=True)
     got, s_got = _gpu_forward(lasad, w, q, k, v, g, want_state=True, out_dtype=_odt(out),
-                              use_workspace=segmented)
+                              use_workspace=use_workspace)
     assert rel_err(got, ref) <= TOL["bf16"]
     assert rel_err(s_got, s_ref) <= TOL["bf16"]
 
